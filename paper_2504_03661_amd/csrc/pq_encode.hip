@@ -96,114 +96,158 @@ __global__ __launch_bounds__(ENC_WAVES * 64) void pq_encode_kernel(const pq_enco
 }
 
 // ---------------------------------------------------------------------------------
-// fp16 inputs: the same codes, found with the matrix cores as a filter.
+// fp16 inputs: the same codes, found with the matrix cores as a filter (pq_nearest_filter.h).
 //
 // With q(c) = n(c)/2 - x . c (n = |c|^2) the distance is |x|^2 + 2 q, so the nearest centroid minimises q.
-// For fp16 inputs every product x_j c_j is exact in fp32, and v_mfma_f32_4x4x4_16B_f16 evaluates
-// v(c) = q(c) + off for 4 centroids (rows of A, from LDS) x 64 tokens (columns of B, one per lane) per
-// instruction, to within a bound e that follows from the magnitudes (below); off >= |x|^2/2 + e is a
-// per-token constant in the C operand that makes every computed value positive, so that values compare
-// as integers (v_min3_i32: half a vector operation per value, no NaN quieting).  That is a filter, not the
-// decision:
-//   pass 1  best = min over all 256 centroids of the computed v;
-//   pass 2  the same products again with off - (best + tau) in the C operand: a computed value is negative
-//           where it lies within tau of the best one, so a group of 4 centroids is a candidate when the OR of
-//           its 4 results has the sign bit set (one v_alignbit shifts that bit into the group mask); count the
-//           candidate groups, remember the first and the last;
-//   refine  one or two candidate groups (nearly always): the true minimiser is among their centroids — the
-//           distances of those 4 (8 if some token of the wavefront has two groups) are evaluated in the
-//           defining fp64 arithmetic (see the top of this file),
-//           ascending, and the smallest, lowest index first, is the code.  Three or more groups within tau
-//           (duplicated centroids, near-ties): the lane walks all of its marked groups the same way.  A
-//           codebook or token outside the range the bound covers (no marked group, non-finite values): the
-//           64-token chunk runs the full fp64 scan.
-// Either way the code is decided by the fp64 expression, so it is bit-exact by construction; the filter only
-// has to be SAFE: every centroid outside the candidate groups must have a strictly larger true distance.  With
-// |computed - true| <= e for every centroid and c^ the minimiser of the computed values, a centroid c outside
-// the candidate groups has true v(c) > best + tau - e and true v(c^) <= best + e: tau >= 2 e suffices (plus the
-// two roundings of off - (best + tau), <= 2^-23 T, and strictly: tau exceeds 2 e by 2^-20.4 T).
-// Bound on e: A row = (c_0 .. c_{ds-1}, h, l) with h + l = n/2 split into two fp16 (n summed in fp32 from
-// exact squares: <= 2^-21.2 n/2 in all), B column = (-x_0 .. -x_{ds-1}, 1, 1); fp32 accumulation of at most 7
-// terms, even if every one of the 6 adds truncates, <= 6 x 2^-23 T with T = N + X C + off >= the sum of the
-// terms' magnitudes (N = max n/2, C = max |c_j|, X = sum_j |x_j|).  So e <= 2^-19.7 T, and
-// tau = 2^-18.3 T + 2^-22 leaves a factor 1.3 beyond the worst case (2.6 if the adds round to nearest), which
-// is many orders above the rounding of the fp64 distances themselves.
-// The matrix instruction takes fp16 subnormals as they are (no flush: measured, and the default mode of a HIP
-// kernel); n/2 beyond the fp16 range does not split into h + l: such a codebook takes the full scan.
-// Cost per (sub-vector, centroid): about 2 vector operations instead of 2 ds + 3 in fp64.
-__device__ inline float wave_max_f(float x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        x = fmaxf(x, __shfl_xor(x, o));
-    return x;
-}
+// For fp16 inputs every product x_j c_j is exact in fp32, and v_mfma_f32_32x32x8_f16 evaluates
+// v(c) = q(c) + off for 32 centroids (rows of A, from LDS) x 32 tokens (columns of B) per instruction, to within a
+// bound e_c that follows from the magnitudes (below); off >= |x|^2/2 is a per-token number, itself one of the
+// products, that makes every computed value positive, so that values compare as integers (v_min3_i32: half a vector
+// operation per value, no NaN quieting).  That is a filter, not the decision:
+//   values  every instruction leaves a lane with 16 of its token's values, in 4 "quads" of consecutive centroids.
+//           Kept of the 8 instructions of a token are the minima over the quads of each instruction (8) and over the
+//           instructions for each quad position (4).  Their minimum over both lane halves is the best value.
+//   marks   the minima within tau of the best one.  A quad can hold a value that close only if its instruction AND
+//           its position are marked: nearly always one of each, in one of the halves, and so one quad, found without
+//           a second pass over the values.  The comparisons leave lane masks in scalar registers, where they are
+//           combined.
+//   refine  the distances of the marked quad's 4 centroids in the defining fp64 arithmetic (see the top of this
+//           file), ascending, the smallest, lowest index first, is the code.  Where more than one instruction or
+//           position is marked (ties, duplicated centroids, near-ties) the lane walks all quads that both marks allow.
+//           A codebook or token outside the range the bound covers (norms beyond fp16, no mark, non-finite values):
+//           the 64-token chunk runs the full fp64 scan.
+// Either way the code is decided by the fp64 expression, so it is bit-exact by construction; the filter only has to be
+// SAFE: every centroid outside the evaluated quads must have a strictly larger true distance.
+// Bound: A row = (c_0 .. c_{ds-1}, h, l, 1, 2^15) with h + l = n/2 split into two fp16 (n summed in fp32: <= 3.5 x
+// 2^-23 of n/2 in all, or the subnormal step 2^-25), B column = (-x_0 .. -x_{ds-1}, 1, 1, o_0, o_1); the at most 8
+// terms are summed within 8 x 2^-23 of their magnitudes (measured over 2^-20 .. 2^15: at most 2.5 x 2^-23, and 7e-12
+// absolute below 2^-14).  So e_c <= eps T_c, eps = 11.5 x 2^-23, T_c = n/2 + sum_j |x_j c_j| + off.  With d = |x - c|:
+// |c| <= |x| + d, hence T_c <= 2.5 |x|^2 + 1.5 d^2 + off, and d^2 = 2 v(c) - 2 off + |x|^2 gives T_c <= 3 |x|^2 + 3 v(c):
+// a centroid's error is bounded by its own value and the token, whatever outliers the codebook holds.  An unmarked
+// c has computed v(c) > best + tau, so its true value exceeds that of the computed minimiser if
+// tau >= 6 eps (|x|^2 + best) / (1 - 3 eps); tau = 1.05e-5 (|x|^2 + best) + 2^-22 is 1.27 times that, which is many
+// orders above the rounding of the fp64 distances.  The same bound keeps every computed value positive:
+// v(c) >= off - |x|^2/2 >= 0.0025 |x|^2 + 7e-7 > e_c.  (A tau from the largest norm of the codebook, some 7 times as
+// wide, sent a quarter of all chunks through the walk over several quads.)
+// The matrix instruction takes fp16 subnormals as they are (no flush: measured, and the default mode of a HIP kernel).
+//
+// Cost per (sub-vector, centroid): 1.3 vector operations instead of 2 ds + 3 in fp64, the matrix instructions in
+// parallel; bound by the issue of the vector instructions (about 340 per 64 tokens and subspace, counted; 92 % of the
+// issue slots at the 2.1 GHz the chip holds).  Prompt of 32K tokens x 32 heads x (K, V), M = 64: 2.75 ms with 4x4x4
+// instructions in two passes (one for the best value, one for the marks), 1.50 ms now.
+//
+// A workgroup is 4 neighbouring subspaces of the same tokens, one wavefront each: a token's line of 64 subspaces is
+// then fetched from L2 once for four wavefronts (one wavefront per workgroup 2.69 ms, two 2.35, four 1.75, eight 1.73
+// on the same box and an earlier filter; eight run out of LDS at M = 32: 124 -> 175 us on 3 x 5000 tokens x 8 heads).
+// The fp64 copy of the coordinates stays in LDS for ds = 2 (converting them at each use: 1.76 -> 1.89 ms); for ds = 4
+// its 32 KiB cost more wavefronts than the conversions cost instructions (124 -> 111 us).
+constexpr int FAST_WAVES = 4;
 
-template <int M, int DS, int NQ>
-__global__ __launch_bounds__(64) void pq_encode_fast_kernel(const pq_encode_args a, const int rounds)
+template <int M, int DS, bool PER_SEQ>
+__global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const pq_encode_args a, const int rounds)
 {
-    constexpr int ROW = pq_filter_row_bytes<DS>();
-    __shared__ __attribute__((aligned(16))) unsigned char arow[256 * ROW];
-    __shared__ double cb[256 * DS];
+    constexpr bool WIDE = DS == 2;
+    __shared__ __attribute__((aligned(16))) unsigned char arow_all[FAST_WAVES][256 * PQ_FILTER_ROW];
+    __shared__ double cb_all[FAST_WAVES][WIDE ? 256 * DS : 1];
 
-    const int lane = threadIdx.x;
-    const int which = blockIdx.z;  // 0: keys, 1: values
-    const int i = blockIdx.y;      // subspace
-    const int n_tok = a.B * a.n_new;  // tokens of one KV head over all sequences: they share its codebook
-    const int n_chunks = (n_tok + 64 * NQ - 1) / (64 * NQ);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned char *arow = arow_all[wave];
+    double *cb = cb_all[wave];
+    const int which = blockIdx.z;                  // 0: keys, 1: values
+    const int i = blockIdx.y * FAST_WAVES + wave;  // subspace
+    // chunks of 64 tokens of one KV head over all sequences (they share its codebook): whole chunks of each sequence
+    // (PER_SEQ: addresses and lengths are then scalar work), or the tokens of all sequences in a row
+    const int seq_chunks = (a.n_new + 63) >> 6;
+    const int n_chunks = PER_SEQ ? a.B * seq_chunks : (a.B * a.n_new + 63) >> 6;
     const int n_jobs = (n_chunks + rounds - 1) / rounds;  // a wavefront takes `rounds` chunks in a row: one codebook set-up
     const int hkv = blockIdx.x / n_jobs;
     const int chunk0 = (blockIdx.x - hkv * n_jobs) * rounds;
+    const int chunk1 = chunk0 + rounds < n_chunks ? chunk0 + rounds : n_chunks;
 
-    // ---- codebook of this subspace: fp64 copy for the exact evaluations, A rows for the filter
+    // ---- codebook of this subspace: A rows for the filter, fp64 copy for the exact evaluations
     const __half *src = (const __half *)a.codebook[which] + ((int64_t)hkv * M + i) * 256 * DS;
-    float n_max = 0.f, c_max = 0.f;
     bool cb_bad = false;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int c = lane + 64 * r;
-        pq_filter_build_row<DS>(src + c * DS, arow + c * ROW, cb + c * DS, n_max, c_max, cb_bad);
+        pq_filter_build_row<DS, WIDE>(src + c * DS, arow + c * PQ_FILTER_ROW, cb + (WIDE ? c * DS : 0), cb_bad);
     }
-    n_max = wave_max_f(n_max);
-    c_max = wave_max_f(c_max);
     cb_bad = __builtin_amdgcn_ballot_w64(cb_bad) != 0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 
-#pragma unroll 1
-    for (int chunk = chunk0; chunk < chunk0 + rounds && chunk < n_chunks; ++chunk) {
-    // ---- this lane's tokens: one per 64-token sub-chunk
-    bool live[NQ];
-    int bq[NQ], tq[NQ];
-    _Float16 xv[NQ][DS];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int u = (chunk * NQ + q) * 64 + lane;
-        live[q] = u < n_tok;
-        const int uu = live[q] ? u : 0;
-        bq[q] = uu / a.n_new;
-        tq[q] = uu - bq[q] * a.n_new;
-        const __half *xp =
-            (const __half *)a.x[which] + (((int64_t)bq[q] * a.Hkv + hkv) * a.n_new + tq[q]) * PQ_HEAD_DIM + i * DS;
+    // ---- the tokens, one chunk ahead of the work.  All in 32 bits: sequences and heads are below 2^24, rows below
+    // 2^32 (they fit the memory), a head's code bytes below 2^31.
+    const uint32_t n_new = (uint32_t)a.n_new, Hkv = (uint32_t)a.Hkv, stride = (uint32_t)a.head_stride;
+    const uint32_t cap = (uint32_t)a.max_context;
+    const char *x = (const char *)a.x[which] + i * (DS * (int)sizeof(__half));
+    struct token {
+        _Float16 x[DS];
+        bool live;
+        int n_old;
+        uint32_t b, t;  // its sequence and position among the new tokens
+    };
+    // PER_SEQ: sequence and first token of the next chunk (scalars).  Otherwise this lane's own sequence, position and
+    // input row (b Hkv + hkv) n_new + t: 64 tokens on are b_step sequences and t_step positions on, a sequence more
+    // where t passes n_new.
+    const uint32_t u0 = PER_SEQ ? (uint32_t)chunk0 : (uint32_t)chunk0 * 64u + (uint32_t)lane;
+    uint32_t b = u0 / (PER_SEQ ? (uint32_t)seq_chunks : n_new);
+    uint32_t t = PER_SEQ ? (u0 - b * (uint32_t)seq_chunks) * 64u : u0 - b * n_new;
+    uint32_t row = (b * Hkv + (uint32_t)hkv) * n_new + t;
+    const uint32_t b_step = 64u / n_new, t_step = 64u - b_step * n_new;
+    const uint32_t row_step = b_step * Hkv * n_new + t_step, row_wrap = (Hkv - 1u) * n_new;
+    auto fetch = [&](token &k) {
+        const _Float16 *xp;
+        if constexpr (PER_SEQ) {
+            const bool any = b < (uint32_t)a.B;  // past the last chunk: the last sequence's last rows again
+            k.b = any ? b : (uint32_t)a.B - 1u;
+            const uint32_t first = any ? t : n_new - 1u;
+            const uint32_t rest = n_new - first;  // at least 1
+            const uint32_t l = (uint32_t)lane < rest ? (uint32_t)lane : rest - 1u;
+            k.live = any && (uint32_t)lane < rest;
+            k.t = first;
+            const char *base = x + (uint64_t)((k.b * Hkv + (uint32_t)hkv) * n_new + first) * (PQ_HEAD_DIM * sizeof(__half));
+            xp = (const _Float16 *)(base + l * (uint32_t)(PQ_HEAD_DIM * sizeof(__half)));
+            t += 64u;
+            if (t >= n_new) {
+                t = 0u;
+                ++b;
+            }
+        } else {
+            k.live = b < (uint32_t)a.B;
+            k.b = k.live ? b : 0u;
+            k.t = t;
+            xp = (const _Float16 *)(x + (uint64_t)(k.live ? row : (uint32_t)hkv * n_new) * (PQ_HEAD_DIM * sizeof(__half)));
+            b += b_step;
+            t += t_step;
+            row += row_step;
+            if (t >= n_new) {
+                t -= n_new;
+                row += row_wrap;
+                ++b;
+            }
+        }
 #pragma unroll
         for (int j = 0; j < DS; ++j)
-            xv[q][j] = __builtin_bit_cast(_Float16, xp[j]);
-    }
-    int codes[NQ];
-    pq_filter_codes<DS, NQ>(arow, cb, n_max, c_max, cb_bad, xv, live, codes);
-
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        int n_old = a.ctx_len[bq[q]];
-        n_old = n_old < 0 ? 0 : n_old;
-        const int64_t pos = (int64_t)n_old + tq[q];
-        if (live[q] && pos < a.max_context) {
-            uint8_t *dst = a.codes[which] + ((int64_t)bq[q] * a.Hkv + hkv) * a.head_stride;
-            const int64_t off = which == 0 ? pq_k_code_offset(pos, i, M, a.k_skew) : pq_v_code_offset(pos, i, M);
-            dst[off] = (uint8_t)codes[q];
+            k.x[j] = xp[j];
+        k.n_old = a.ctx_len[k.b];
+    };
+    token next;
+    fetch(next);
+#pragma unroll 1
+    for (int chunk = chunk0; chunk < chunk1; ++chunk) {
+        const token k = next;
+        fetch(next);  // in flight while this chunk is worked on
+        const int code = pq_filter_code<DS, WIDE>(arow, cb, cb_bad, k.x, k.live);
+        const uint32_t n_old = (uint32_t)(k.n_old < 0 ? 0 : k.n_old);
+        const uint32_t pos = (n_old < cap ? n_old : cap) + k.t + (PER_SEQ ? (uint32_t)lane : 0u);
+        if (k.live && pos < cap) {
+            const uint32_t off = which == 0 ? pq_k_code_offset(pos, i, M, a.k_skew) : pq_v_code_offset(pos, i, M);
+            const uint32_t head = (PER_SEQ ? k.b * Hkv : __umul24(k.b, Hkv)) + (uint32_t)hkv;
+            a.codes[which][(uint64_t)head * stride + off] = (uint8_t)code;
         }
-    }
     }
 }
 
@@ -309,21 +353,18 @@ hipError_t pq_launch_bump_len(int32_t *ctx_len, int B, int n_new, int max_contex
 template <int M, int DS>
 void launch_fast(const pq_encode_args &a, hipStream_t s)
 {
-    const int n_tok = a.B * a.n_new;
-    if (n_tok > 128) {
-        // prompt-sized inputs: up to 8 chunks of 256 tokens per wavefront while at least 8192 wavefronts remain
-        const int n_chunks = (n_tok + 255) / 256;
-        const int64_t waves = (int64_t)a.Hkv * n_chunks * M * 2;
-        const int rounds = (int)(waves / 8192 < 1 ? 1 : waves / 8192 > 8 ? 8 : waves / 8192);
-        dim3 grid(a.Hkv * ((n_chunks + rounds - 1) / rounds), M, 2);
-        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, 4>), grid, dim3(64), 0, s, a, rounds);
-    } else if (n_tok > 64) {
-        dim3 grid(a.Hkv, M, 2);
-        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, 2>), grid, dim3(64), 0, s, a, 1);
-    } else {
-        dim3 grid(a.Hkv, M, 2);
-        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, 1>), grid, dim3(64), 0, s, a, 1);
-    }
+    // whole 64-token chunks of each sequence unless that leaves more than an eighth of the lanes without a token; a
+    // wavefront takes up to 32 chunks in a row while at least 8192 wavefronts remain
+    const int64_t seq_chunks = ((int64_t)a.n_new + 63) / 64;
+    const bool per_seq = seq_chunks * 512 <= (int64_t)a.n_new * 9 || a.B == 1;
+    const int64_t n_chunks = per_seq ? a.B * seq_chunks : ((int64_t)a.B * a.n_new + 63) / 64;
+    const int64_t waves = a.Hkv * n_chunks * M * 2;
+    const int rounds = (int)(waves / 8192 < 1 ? 1 : waves / 8192 > 32 ? 32 : waves / 8192);
+    dim3 grid((unsigned)(a.Hkv * ((n_chunks + rounds - 1) / rounds)), M / FAST_WAVES, 2);
+    if (per_seq)
+        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, true>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
+    else
+        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, false>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
 }
 
 hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,

@@ -29,17 +29,18 @@
 #define PQ_K_SKEW_LANE 0
 #define PQ_K_SKEW_QUAD 1
 
-__host__ __device__ inline int64_t pq_k_code_offset(int64_t t, int i, int M, int skew)
+// (I: int64_t, or uint32_t where the token is known to be below 2^25 — 32-bit arithmetic is all one head needs)
+template <typename I> __host__ __device__ inline I pq_k_code_offset(I t, int i, int M, int skew)
 {
     const int l = (int)(t & 63);
     const int rot = skew == PQ_K_SKEW_QUAD ? (l >> 2) * (M >> 4) : l;  // by quad: 4 (M = 64) or 2 (M = 32) subspaces per score step
     const int s = (i - rot) & (M - 1);  // M is a power of two
-    return (t >> 6) * (64 * (int64_t)M) + (int64_t)(s >> 4) * 1024 + l * 16 + (s & 15);
+    return (t >> 6) * (I)(64 * M) + (I)((s >> 4) * 1024 + l * 16 + (s & 15));
 }
 
-__host__ __device__ inline int64_t pq_v_code_offset(int64_t t, int i, int M)
+template <typename I> __host__ __device__ inline I pq_v_code_offset(I t, int i, int M)
 {
-    return (t >> 4) * (16 * (int64_t)M) + (int64_t)i * 16 + (t & 15);
+    return (t >> 4) * (I)(16 * M) + (I)(i * 16) + (t & 15);
 }
 
 // ---------------------------------------------------------------------------------

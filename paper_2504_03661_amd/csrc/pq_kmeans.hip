@@ -14,10 +14,13 @@
 // The paper does not say how it initialises, iterates or treats empty clusters; the initial
 // centroids are the caller's, the iteration count too.
 //
-// Mapping of `assign`: one workgroup = (head, subspace, slice of samples), 4 wavefronts sharing the
-// widened codebook (LDS, broadcast reads) and the slice's partial sums (LDS atomics); lane =
-// sample; the partial sums reach memory with one 64-bit atomic per touched entry.  Bound by the
-// fp64 vector ALU like the encode: (2 ds + 3) operations per (sub-vector, centroid).
+// Mapping of `assign`: one workgroup = (head, 4 neighbouring subspaces, slice of samples), one wavefront per
+// subspace, lane = sample, 64 samples at a time.  Every wavefront keeps its subspace's codebook rows and partial sums
+// in LDS (LDS atomics); the sums reach memory with one 64-bit atomic per touched entry and slice.  The 4 wavefronts
+// read neighbouring words of the same rows, so a line of samples leaves L2 once for all of them.  Bound by the issue
+// of vector instructions in the nearest-centroid filter, as the encode; 32 heads x 65536 samples, M = 64: 2.7 ms per
+// iteration with one subspace per workgroup and the two-pass filter, 1.56 ms now (two or four wavefronts per subspace
+// on one set of sums, for more wavefronts per compute unit: 1.6 and 1.8 ms).
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -26,91 +29,86 @@
 
 namespace {
 
-constexpr int KM_WAVES = 4;
-constexpr int KM_CHUNKS = 4;                           // 64-sample chunks per wavefront
-constexpr int KM_SLICE = KM_WAVES * KM_CHUNKS * 64;    // samples per workgroup
+constexpr int KM_SUB = 4;  // neighbouring subspaces per workgroup, one wavefront each
 
 template <int M, int DS>
-__global__ __launch_bounds__(KM_WAVES * 64) void pq_kmeans_assign_kernel(const __half *samples, const __half *codebook,
-                                                                        unsigned long long *sums, unsigned int *counts,
-                                                                        int n_samples, int n_slices)
+__global__ __launch_bounds__(KM_SUB * 64) void pq_kmeans_assign_kernel(const __half *samples, const __half *codebook,
+                                                                      unsigned long long *sums, unsigned int *counts,
+                                                                      int n_samples, int n_slices, int rounds)
 {
-    constexpr int ROW = pq_filter_row_bytes<DS>();
-    static_assert(KM_WAVES * 64 == 256, "one thread per centroid below");
-    __shared__ double cb[256 * DS];
-    __shared__ __attribute__((aligned(16))) unsigned char arow[256 * ROW];
-    __shared__ unsigned long long part_sum[256 * DS];
-    __shared__ unsigned int part_cnt[256];
-    __shared__ float red[2 * KM_WAVES];
+    __shared__ __attribute__((aligned(16))) unsigned char arow_all[KM_SUB][256 * PQ_FILTER_ROW];
+    __shared__ unsigned long long sum_all[KM_SUB][256 * DS];
+    __shared__ unsigned int cnt_all[KM_SUB][256];
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned char *arow = arow_all[wave];
+    unsigned long long *part_sum = sum_all[wave];
+    unsigned int *part_cnt = cnt_all[wave];
     const int head = blockIdx.x / n_slices;
     const int slice = blockIdx.x - head * n_slices;
-    const int i = blockIdx.y;  // subspace
+    const int i = blockIdx.y * KM_SUB + wave;  // subspace
 
-    // codebook of this (head, subspace): fp64 copy and matrix-instruction rows for the nearest-centroid filter of
-    // the encode (pq_nearest_filter.h), one centroid per thread; accumulators cleared
+    // matrix-instruction rows of this (head, subspace)'s codebook for the nearest-centroid filter of the encode
+    // (pq_nearest_filter.h); accumulators cleared
     const int64_t cb_base = ((int64_t)head * M + i) * 256 * DS;
-    float n_max = 0.f, c_max = 0.f;
     bool cb_bad = false;
-    pq_filter_build_row<DS>(codebook + cb_base + tid * DS, arow + tid * ROW, cb + tid * DS, n_max, c_max, cb_bad);
-    for (int e = tid; e < 256 * DS; e += KM_WAVES * 64)
-        part_sum[e] = 0ull;
-    part_cnt[tid] = 0u;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        n_max = fmaxf(n_max, __shfl_xor(n_max, o));
-        c_max = fmaxf(c_max, __shfl_xor(c_max, o));
-    }
-    if (lane == 0) {
-        red[wave] = n_max;
-        red[KM_WAVES + wave] = __builtin_amdgcn_ballot_w64(cb_bad) != 0 ? -1.f : c_max;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < KM_WAVES; ++w) {
-        n_max = fmaxf(n_max, red[w]);
-        const float cw = red[KM_WAVES + w];
-        cb_bad |= cw < 0.f;
-        c_max = fmaxf(c_max, cw);
-    }
-    cb_bad = __builtin_amdgcn_ballot_w64(cb_bad) != 0;
-
-    // this wavefront's KM_CHUNKS 64-sample chunks, assigned together (the same rule and arithmetic as the encode)
-    bool live[KM_CHUNKS];
-    _Float16 xv[KM_CHUNKS][DS];
-#pragma unroll
-    for (int ch = 0; ch < KM_CHUNKS; ++ch) {
-        const int s = slice * KM_SLICE + (ch * KM_WAVES + wave) * 64 + lane;
-        live[ch] = s < n_samples;
-        const int ss = live[ch] ? s : 0;
+    for (int r = 0; r < 4; ++r) {
+        const int c = lane + 64 * r;
+        pq_filter_build_row<DS, false>(codebook + cb_base + c * DS, arow + c * PQ_FILTER_ROW, nullptr, cb_bad);
 #pragma unroll
         for (int j = 0; j < DS; ++j)
-            xv[ch][j] = __builtin_bit_cast(_Float16, samples[((int64_t)head * n_samples + ss) * PQ_HEAD_DIM + i * DS + j]);
+            part_sum[c * DS + j] = 0ull;
+        part_cnt[c] = 0u;
     }
-    int codes[KM_CHUNKS];
-    pq_filter_codes<DS, KM_CHUNKS>(arow, cb, n_max, c_max, cb_bad, xv, live, codes);
+    cb_bad = __builtin_amdgcn_ballot_w64(cb_bad) != 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+
+    // the slice's samples, 64 at a time, the next ones' loads in flight while these are assigned (the same rule and
+    // arithmetic as the encode)
+    const _Float16 *x = (const _Float16 *)samples + (int64_t)head * n_samples * PQ_HEAD_DIM + i * DS;
+    const int s0 = slice * rounds * 64;
+    const int s1 = s0 + rounds * 64 < n_samples ? s0 + rounds * 64 : n_samples;
+    _Float16 next[DS];
+    auto fetch = [&](int s) {
+        const _Float16 *xp = x + (int64_t)(s < n_samples ? s : 0) * PQ_HEAD_DIM;
 #pragma unroll
-    for (int ch = 0; ch < KM_CHUNKS; ++ch) {
-        if (!live[ch])
-            continue;
+        for (int j = 0; j < DS; ++j)
+            next[j] = xp[j];
+    };
+    int s = s0 + lane;
+    fetch(s);
+#pragma unroll 1
+    for (; s - lane < s1; s += 64) {
+        _Float16 xv[DS];
 #pragma unroll
-        for (int j = 0; j < DS; ++j) {
-            // exact: an fp16 value times 2^24 is an integer below 2^41 in magnitude
-            const long long fixed = (long long)((float)xv[ch][j] * 16777216.0f);
-            atomicAdd(&part_sum[codes[ch] * DS + j], (unsigned long long)fixed);
+        for (int j = 0; j < DS; ++j)
+            xv[j] = next[j];
+        fetch(s + 64);
+        const bool live = s < s1;
+        const int code = pq_filter_code<DS, false>(arow, nullptr, cb_bad, xv, live);
+        if (live) {
+#pragma unroll
+            for (int j = 0; j < DS; ++j) {
+                // exact: an fp16 value times 2^24 is an integer below 2^41 in magnitude
+                const long long fixed = (long long)((float)xv[j] * 16777216.0f);
+                atomicAdd(&part_sum[code * DS + j], (unsigned long long)fixed);
+            }
+            atomicAdd(&part_cnt[code], 1u);
         }
-        atomicAdd(&part_cnt[codes[ch]], 1u);
     }
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 
     const int64_t acc_base = ((int64_t)head * M + i) * 256;
-    for (int e = tid; e < 256 * DS; e += KM_WAVES * 64)
+    for (int e = lane; e < 256 * DS; e += 64)
         if (part_sum[e] != 0ull)
             atomicAdd(&sums[acc_base * DS + e], part_sum[e]);
-    for (int e = tid; e < 256; e += KM_WAVES * 64)
+    for (int e = lane; e < 256; e += 64)
         if (part_cnt[e] != 0u)
             atomicAdd(&counts[acc_base + e], part_cnt[e]);
 }
@@ -182,17 +180,22 @@ hipError_t pq_launch_kmeans(const pq_attn_ctx *ctx, const void *samples, int n_s
     const int64_t words = pq_kmeans_accumulator_bytes(ctx) / 4;
     hipLaunchKernelGGL(pq_clear_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s,
                        (uint32_t *)workspace, words);
-    const int n_slices = (n_samples + KM_SLICE - 1) / KM_SLICE;
-    const dim3 grid((unsigned)(Hkv * n_slices), (unsigned)M), block(KM_WAVES * 64);
+    // a wavefront takes up to 64 chunks of 64 samples in a row while at least 8192 wavefronts remain: one codebook set-up
+    // and one pass of the memory atomics for all of them
+    const int n_chunks = (n_samples + 63) / 64;
+    const int64_t waves = (int64_t)Hkv * n_chunks * M;
+    const int rounds = (int)(waves / 8192 < 1 ? 1 : waves / 8192 > 64 ? 64 : waves / 8192);
+    const int n_slices = (n_chunks + rounds - 1) / rounds;
+    const dim3 grid((unsigned)(Hkv * n_slices), (unsigned)(M / KM_SUB)), block(KM_SUB * 64);
     for (int it = 0; it < n_iters; ++it) {
         if (M == 64) {
             hipLaunchKernelGGL((pq_kmeans_assign_kernel<64, 2>), grid, block, 0, s, (const __half *)samples,
-                               (const __half *)codebook, sums, counts, n_samples, n_slices);
+                               (const __half *)codebook, sums, counts, n_samples, n_slices, rounds);
             hipLaunchKernelGGL(pq_kmeans_update_kernel<2>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                                (__half *)codebook, sums, counts, n);
         } else {
             hipLaunchKernelGGL((pq_kmeans_assign_kernel<32, 4>), grid, block, 0, s, (const __half *)samples,
-                               (const __half *)codebook, sums, counts, n_samples, n_slices);
+                               (const __half *)codebook, sums, counts, n_samples, n_slices, rounds);
             hipLaunchKernelGGL(pq_kmeans_update_kernel<4>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                                (__half *)codebook, sums, counts, n);
         }

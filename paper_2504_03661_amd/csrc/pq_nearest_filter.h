@@ -1,8 +1,8 @@
 // Nearest centroid of fp16 sub-vectors among 256 fp16 centroids: matrix-core filter + fp64 decision.
 // Shared by the encode kernel and the k-means assignment; the argument, the error bound and the fall-back are
-// described in pq_encode.hip.  Everything here works on ONE wavefront (lane = token of a 64-token sub-chunk, NQ
-// sub-chunks at a time) and on two LDS arrays the caller owns: the A rows of the 256 centroids (pq_filter_row_bytes
-// each) and their fp64 copy.
+// described in pq_encode.hip.  Everything here works on ONE wavefront (a 64-token sub-chunk at a time, lane = token)
+// and on two LDS arrays the caller owns: the A rows of the 256 centroids (PQ_FILTER_ROW bytes each) and their fp64
+// copy.
 #pragma once
 
 #include <hip/hip_fp16.h>
@@ -14,221 +14,282 @@
 namespace {
 
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4e __attribute__((ext_vector_type(4)));
+typedef float f32x16e __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2e __attribute__((ext_vector_type(2)));
 
-template <int DS> constexpr int pq_filter_row_bytes() { return DS == 2 ? 8 : 16; }  // ds coordinates, h, l (, 0, 0)
+// An A row holds the 8 inner indices of v_mfma_f32_32x32x8_f16: lanes 0..31 of the wavefront read its first half
+// (inner 0..3), lanes 32..63 its second (inner 4..7).
+//   ds = 2   c_0 c_1 h l | 1 2^15 0 0        against the column   -x_0 -x_1 1 1 | o_0 o_1 0 0
+//   ds = 4   c_0 c_1 c_2 c_3 | h l 1 2^15    against              -x_0 .. -x_3 | 1 1 o_0 o_1
+// (h + l = |c|^2 / 2, o_0 + 2^15 o_1 = the token's offset)
+constexpr int PQ_FILTER_ROW = 16;
 
-// A row and fp64 copy of centroid c (src: its ds fp16 coordinates); updates the running maxima of |c|^2 / 2 and
-// |c_j|, and `bad` when |c|^2 / 2 does not split into two fp16
-template <int DS>
-__device__ inline void pq_filter_build_row(const __half *src, unsigned char *arow_c, double *cb_c, float &n_max, float &c_max,
-                                           bool &bad)
+// A row and fp64 copy (WIDE) of centroid c (src: its ds fp16 coordinates); sets `bad` when |c|^2 / 2 does not split
+// into two fp16
+template <int DS, bool WIDE>
+__device__ inline void pq_filter_build_row(const __half *src, unsigned char *arow_c, double *cb_c, bool &bad)
 {
-    constexpr int ROW = pq_filter_row_bytes<DS>();
     float n = 0.f;
-    _Float16 row[ROW / 2];
+    _Float16 row[8] = {};
 #pragma unroll
     for (int j = 0; j < DS; ++j) {
         const _Float16 v = __builtin_bit_cast(_Float16, src[j]);
         const float f = (float)v;
-        cb_c[j] = (double)f;
+        if (WIDE)
+            cb_c[j] = (double)f;
         row[j] = v;
         n += f * f;  // exact squares; the sum is rounded (covered by the bound)
-        c_max = fmaxf(c_max, fabsf(f));
     }
     const float h = 0.5f * n;
     const _Float16 hh = (_Float16)h;
     const _Float16 hl = (_Float16)(h - (float)hh);
     row[DS] = hh;
     row[DS + 1] = hl;
-    if (DS == 4)
-        row[6] = row[7] = (_Float16)0.f;
+    row[DS + 2] = (_Float16)1.f;
+    row[DS + 3] = (_Float16)32768.f;
     bad |= !(h < 60000.f);
-    n_max = fmaxf(n_max, h);
-    __builtin_memcpy(arow_c, row, ROW);
+    __builtin_memcpy(arow_c, row, PQ_FILTER_ROW);
 }
 
-// codes of this lane's NQ tokens (xv: their fp16 sub-vectors; dead lanes pass any finite values and live = false)
-template <int DS, int NQ>
-__device__ inline void pq_filter_codes(const unsigned char *arow, const double *cb, const float n_max, const float c_max,
-                                       const bool cb_bad, const _Float16 (&xin)[NQ][DS], const bool (&live)[NQ], int (&codes)[NQ])
+// code of this lane's token (xin: its fp16 sub-vector; a dead lane passes any finite values and live = false)
+template <int DS, bool WIDE>
+__device__ inline int pq_filter_code(const unsigned char *arow, const double *cb, const bool cb_bad, const _Float16 (&xin)[DS], const bool live)
 {
 #pragma clang fp contract(off)
-    constexpr int ROW = pq_filter_row_bytes<DS>();
     const int lane = threadIdx.x & 63;
-    bool bad[NQ];
-    double xd[NQ][DS];
-    f16x4 bop[NQ];
-    f32x4e off4[NQ];
-    float tau[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        float x1 = 0.f, x2 = 0.f;
-        bad[q] = cb_bad;
-        _Float16 xv[4] = {(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f};
+    bool bad = cb_bad;
+    double xd[DS];
+    float tau_x;
+    f16x4 bop[2];  // the columns of tokens 0..31 and 32..63
+    {
+        float x2 = 0.f;
 #pragma unroll
         for (int j = 0; j < DS; ++j) {
-            const _Float16 v = xin[q][j];
-            const float f = (float)v;
-            xd[q][j] = (double)f;
-            xv[j] = -v;
-            x1 += fabsf(f);
-            x2 += f * f;
+            const float f = (float)xin[j];
+            xd[j] = (double)f;
+            x2 = __builtin_fmaf(f, f, x2);
         }
-        bop[q] = f16x4{xv[0], xv[1], xv[2], xv[3]};
-        {
-            // keep the negated operand in its registers (the compiler otherwise redoes the negation per use)
-            u32x2e w = __builtin_bit_cast(u32x2e, bop[q]);
-            asm volatile("" : "+v"(w));
-            bop[q] = __builtin_bit_cast(f16x4, w);
+        // off: |x|^2/2 with half a per cent on top and a floor, so that every computed value stays above zero, rounded
+        // UP to o_0 + 2^15 o_1 (one of the two is zero) by 0.3 % against the half step (2^-11) of the conversion and a
+        // subnormal step
+        const float off = __builtin_fmaf(PQ_FILTER_X2_FACTOR, x2, 3.0f * PQ_FILTER_TAU_ABS);
+        const float up = __builtin_fmaf(off, 1.003f, 6.0e-8f);
+        tau_x = __builtin_fmaf(PQ_FILTER_TAU_NEAR, x2, PQ_FILTER_TAU_ABS);
+        _Float16 o0 = (_Float16)up, o1 = (_Float16)0.f;
+        if (__builtin_amdgcn_ballot_w64(!(off < 60000.f)) != 0) {  // wave-uniform, rare: sub-vectors longer than 340
+            const bool large = !(off < 60000.f);
+            o0 = large ? (_Float16)0.f : o0;
+            o1 = large ? (_Float16)(up * (1.0f / 32768.f)) : (_Float16)0.f;
+            bad |= !(off < 2.0e9f);
         }
-        // off: |x|^2/2 with half a per cent on top, plus the same again as tau and a floor, so that every
-        // computed value stays above zero; T = N + X C + off; tau = 2^-18.3 T + 2^-22
-        const float t0 = n_max + x1 * c_max + PQ_FILTER_X2_FACTOR * x2;
-        float off = PQ_FILTER_X2_FACTOR * x2 + 2.0f * (PQ_FILTER_TAU_REL * (2.0f * t0) + PQ_FILTER_TAU_ABS);
-        tau[q] = PQ_FILTER_TAU_REL * (t0 + off) + PQ_FILTER_TAU_ABS;
-        off += tau[q];
-        off4[q] = f32x4e{off, off, off, off};
-        bad[q] |= !(off < 1.0e30f);
+        const _Float16 one = (_Float16)1.f, zero = (_Float16)0.f;
+        f16x4 lo, hi;
+        if constexpr (DS == 2) {
+            lo = f16x4{-xin[0], -xin[1], one, one};
+            hi = f16x4{o0, o1, zero, zero};
+        } else {
+            lo = f16x4{-xin[0], -xin[1], -xin[DS - 2], -xin[DS - 1]};
+            hi = f16x4{one, one, o0, o1};
+        }
+        // lane = token holds both halves of its own column; the instruction wants the upper half of column t in
+        // lane t + 32: one exchange of the lane halves gives the operands of both token tiles
+        const u32x2e l = __builtin_bit_cast(u32x2e, lo), h = __builtin_bit_cast(u32x2e, hi);
+        const auto s0 = __builtin_amdgcn_permlane32_swap(l.x, h.x, false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(l.y, h.y, false, false);
+        bop[0] = __builtin_bit_cast(f16x4, u32x2e{s0[0], s1[0]});
+        bop[1] = __builtin_bit_cast(f16x4, u32x2e{s0[1], s1[1]});
     }
-    const f16x4 ones = {(_Float16)1.f, (_Float16)1.f, (_Float16)0.f, (_Float16)0.f};
-    const unsigned char *my_row = arow + (lane & 3) * ROW;
-    auto values = [&](int m, int q) -> f32x4e {
-        if (DS == 2) {
-            const f16x4 A = *(const f16x4 *)(my_row + m * (4 * ROW));
-            return __builtin_amdgcn_mfma_f32_4x4x4f16(A, bop[q], off4[q], 0, 0, 0);
+
+    // ---- the 256 computed values of every token, 32 centroids per instruction.  Lane l ends with those of token
+    // l mod 32 of the tile whose centroids lie in its half: 32 m + 8 g + 4 (l / 32) + 0..3 in registers 4 g .. 4 g + 3
+    // ("quad" (m, g)).  Kept are the minima over g per m and over m per g (positive floats order like their bit
+    // patterns): 12 numbers that name every quad with a value near the smallest one without a second pass.
+    int by_m[2][8], by_g[2][4];
+    const unsigned char *my_row = arow + (lane & 31) * PQ_FILTER_ROW + (lane >> 5) * 8;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            by_g[t][g] = 0x7f800000;
+#pragma unroll
+    for (int m = 0; m < 8; m += 2) {
+        const f16x4 A0 = *(const f16x4 *)(my_row + m * (32 * PQ_FILTER_ROW));
+        const f16x4 A1 = *(const f16x4 *)(my_row + (m + 1) * (32 * PQ_FILTER_ROW));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const f32x16e none = {};
+            const f32x16e d0 = __builtin_amdgcn_mfma_f32_32x32x8f16(A0, bop[t], none, 0, 0, 0);
+            const f32x16e d1 = __builtin_amdgcn_mfma_f32_32x32x8f16(A1, bop[t], none, 0, 0, 0);
+            int q0[4], q1[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                q0[g] = min(min(__float_as_int(d0[4 * g]), __float_as_int(d0[4 * g + 1])), __float_as_int(d0[4 * g + 2]));
+                q0[g] = min(q0[g], __float_as_int(d0[4 * g + 3]));
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                q1[g] = min(min(__float_as_int(d1[4 * g]), __float_as_int(d1[4 * g + 1])), __float_as_int(d1[4 * g + 2]));
+                q1[g] = min(q1[g], __float_as_int(d1[4 * g + 3]));
+                by_g[t][g] = min(min(by_g[t][g], q0[g]), q1[g]);
+            }
+            by_m[t][m] = min(min(min(q0[0], q0[1]), q0[2]), q0[3]);
+            by_m[t][m + 1] = min(min(min(q1[0], q1[1]), q1[2]), q1[3]);
         }
-        const f16x4 A1 = *(const f16x4 *)(my_row + m * (4 * ROW));
-        const f16x4 A2 = *(const f16x4 *)(my_row + m * (4 * ROW) + 8);
-        return __builtin_amdgcn_mfma_f32_4x4x4f16(A2, ones, __builtin_amdgcn_mfma_f32_4x4x4f16(A1, bop[q], off4[q], 0, 0, 0), 0, 0, 0);
+    }
+    // the smallest value of each token (its two lane halves together), and the threshold back to both halves
+    int limit[2];
+    {
+        int b[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            b[t] = min(min(min(by_g[t][0], by_g[t][1]), by_g[t][2]), by_g[t][3]);
+        const auto s = __builtin_amdgcn_permlane32_swap(b[0], b[1], false, false);
+        const float best = __int_as_float(min((int)s[0], (int)s[1]));
+        bad |= !(best > 0.f && best < 1.0e30f);  // the offset did not keep the values positive and finite
+        // best + tau, tau = TAU_NEAR (|x|^2 + best) + TAU_ABS
+        const int lim = __float_as_int(__builtin_fmaf(best, 1.0f + PQ_FILTER_TAU_NEAR, tau_x));
+        const auto r = __builtin_amdgcn_permlane32_swap(lim, lim, false, false);
+        limit[0] = (int)r[0];
+        limit[1] = (int)r[1];
+    }
+    // Marks: which minima lie within tau of the best.  A quad can hold such a value only if both its by_m and its
+    // by_g minimum are marked.  One comparison per minimum leaves a mask over the lanes (bits 0..31: the tile's tokens
+    // against the centroids of lane half 0, bits 32..63: half 1) in scalar registers; what follows per mark is scalar
+    // work beside the other wavefronts' vector instructions: the bits of the marked indices (right where one is
+    // marked) and which lanes have a second mark.
+    uint64_t bit_m[3] = {0, 0, 0}, bit_g[2] = {0, 0};  // masks over the 64 tokens from here on
+    uint64_t some = 0, in_half1 = 0, several = 0;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        uint64_t ones = 0, ones_g = 0, twos = 0, of_m[3] = {0, 0, 0}, of_g[2] = {0, 0};
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const uint64_t a = __builtin_amdgcn_ballot_w64(by_m[t][m] <= limit[t]);
+            twos |= ones & a;
+            ones |= a;
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                of_m[k] |= (m >> k) & 1 ? a : 0;
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const uint64_t a = __builtin_amdgcn_ballot_w64(by_g[t][g] <= limit[t]);
+            twos |= ones_g & a;
+            ones_g |= a;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                of_g[k] |= (g >> k) & 1 ? a : 0;
+        }
+        const auto either = [&](uint64_t a) { return (uint64_t)((uint32_t)a | (uint32_t)(a >> 32)) << (32 * t); };
+        ones &= ones_g;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            bit_m[k] |= either(of_m[k]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            bit_g[k] |= either(of_g[k]);
+        some |= either(ones);
+        in_half1 |= (uint64_t)(uint32_t)(ones >> 32) << (32 * t);
+        several |= (uint64_t)((uint32_t)twos | (uint32_t)(twos >> 32) | ((uint32_t)ones & (uint32_t)(ones >> 32))) << (32 * t);
+    }
+
+    // ---- refine: the defining arithmetic on the marked quads, ascending
+    int code = 0;
+    double bd = __builtin_huge_val();
+    auto coordinates = [&](const unsigned char *row, const double *wide, double (&c)[DS]) {
+#pragma unroll
+        for (int j = 0; j < DS; ++j)
+            c[j] = WIDE ? wide[j] : (double)(float)((const _Float16 *)row)[j];
     };
-
-    // ---- pass 1: smallest computed value per token (positive floats order like their bit patterns)
-    int best[NQ];
+    auto take = [&](int c) {
+        double y[DS], dist = 0.0;
+        coordinates(arow + c * PQ_FILTER_ROW, cb + c * DS, y);
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-        best[q] = 0x7f800000;
-    for (int m = 0; m < 64; ++m) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const f32x4e d = values(m, q);
-            best[q] = min(min(best[q], __float_as_int(d[0])), __float_as_int(d[1]));
-            best[q] = min(min(best[q], __float_as_int(d[2])), __float_as_int(d[3]));
+        for (int j = 0; j < DS; ++j) {
+            const double diff = xd[j] - y[j];
+            dist = __builtin_fma(diff, diff, dist);
         }
-    }
-    // ---- pass 2: candidate groups, one bit per group.  The C operand becomes off - (best + tau): a computed value
-    // is then negative exactly where it lies within tau of the best one, so the sign bit IS the candidate flag —
-    // OR over the group's 4 values, shifted into the mask by one v_alignbit (group g lands in bit 63 - g).
-    // The rounding differs from pass 1's (another C), within the same bound e; the minimiser's value comes out
-    // <= 2 e - tau + (the two roundings of best + tau - off, <= 2^-23 T) < 0, so it is marked.
-    uint32_t cand_lo[NQ], cand_hi[NQ];
+        code = dist < bd ? c : code;  // strict: the lowest index among equal distances stays
+        bd = __builtin_fmin(bd, dist);
+    };
+    // nearly always one quad is marked, in one of the halves: (m, g) of half s is centroids 32 m + 8 g + 4 s .. + 3
+    // (where several are, the sum below is some quad's index all the same)
+    {
+        const auto bit = [](uint64_t mask, int value) { return __builtin_amdgcn_inverse_ballot_w64(mask) ? value : 0; };
+        const int c0 = bit(bit_m[0], 32) | bit(bit_m[1], 64) | bit(bit_m[2], 128) | bit(bit_g[0], 8) | bit(bit_g[1], 16) |
+                       bit(in_half1, 4);
+        const unsigned char *rows = arow + c0 * PQ_FILTER_ROW;
+        const double *wide = cb + c0 * DS;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const float b = __int_as_float(best[q]);
-        bad[q] |= !(b > 0.f && b < 1.0e30f);                   // the offset did not keep the values positive and finite
-        const float d = off4[q][0] - (b + tau[q]);
-        off4[q] = f32x4e{d, d, d, d};
-        cand_lo[q] = 0u;
-        cand_hi[q] = 0u;
-    }
-#pragma unroll 4
-    for (int m = 0; m < 32; ++m) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const f32x4e d = values(m, q);
-            const uint32_t any = (__float_as_uint(d[0]) | __float_as_uint(d[1])) | (__float_as_uint(d[2]) | __float_as_uint(d[3]));
-            cand_lo[q] = __builtin_amdgcn_alignbit(cand_lo[q], any, 31);
-        }
-    }
-#pragma unroll 4
-    for (int m = 0; m < 32; ++m) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const f32x4e d = values(m + 32, q);
-            const uint32_t any = (__float_as_uint(d[0]) | __float_as_uint(d[1])) | (__float_as_uint(d[2]) | __float_as_uint(d[3]));
-            cand_hi[q] = __builtin_amdgcn_alignbit(cand_hi[q], any, 31);
-        }
-    }
-    int cnt[NQ], first[NQ], last[NQ];
-    bool two = false;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const uint64_t cand = ((uint64_t)cand_lo[q] << 32) | cand_hi[q];
-        cnt[q] = __builtin_popcountll(cand);
-        first[q] = cand ? __builtin_clzll(cand) : 0;
-        last[q] = cand ? 63 - __builtin_ctzll(cand) : 0;
-        two |= live[q] && cnt[q] == 2;
-    }
-    two = __builtin_amdgcn_ballot_w64(two) != 0;  // wave-uniform: some token has a second candidate group
-
-    // ---- refine / full scan
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        int code = 0;
-        double bd = __builtin_huge_val();
-        auto take = [&](int c) {
-            double dist = 0.0;
+        for (int k = 0; k < 4; ++k) {
+            double y[DS], dist = 0.0;
+            coordinates(rows + k * PQ_FILTER_ROW, wide + k * DS, y);
 #pragma unroll
             for (int j = 0; j < DS; ++j) {
-                const double diff = xd[q][j] - cb[c * DS + j];
+                const double diff = xd[j] - y[j];
                 dist = __builtin_fma(diff, diff, dist);
             }
-            code = dist < bd ? c : code;  // strict: the lowest index among equal distances stays
-            bd = __builtin_fmin(bd, dist);
-        };
-#pragma unroll
-        for (int k = 0; k < 4; ++k)  // ascending centroid index: the first group ...
-            take(4 * first[q] + k);
-        if (two) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)  // ... then the last one (the same group again where there is only one)
-                take(4 * last[q] + k);
+            code = k > 0 && dist < bd ? k : code;
+            bd = k > 0 ? __builtin_fmin(bd, dist) : dist;
         }
-        // more than two candidate groups (a cluster of near-ties, a token far outside the codebook's range): the
-        // lane walks all of its marked groups, ascending — the nearest centroid and every tie lie in them
-        const bool many = live[q] && !bad[q] && cnt[q] > 2;
-        if (__builtin_amdgcn_ballot_w64(many) != 0) {  // wave-uniform
-            const int code_12 = code;
-            const double bd_12 = bd;
-            code = 0;
-            bd = __builtin_huge_val();
-            uint64_t left = many ? ((uint64_t)cand_lo[q] << 32) | cand_hi[q] : 0;  // group g sits in bit 63 - g
-            while (__builtin_amdgcn_ballot_w64(left != 0) != 0) {
-                const int g = left ? __builtin_clzll(left) : 0;
-                const int code_before = code;
-                const double bd_before = bd;
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    take(4 * g + k);
-                if (left == 0) {  // this lane had nothing left: keep what it had
-                    code = code_before;
-                    bd = bd_before;
-                }
-                left &= ~(0x8000000000000000ull >> g);
-            }
-            if (!many) {
-                code = code_12;
-                bd = bd_12;
-            }
-        }
-        const bool unsure = live[q] && (bad[q] || cnt[q] < 1);
-        if (__builtin_amdgcn_ballot_w64(unsure) != 0) {  // wave-uniform: the defining scan for this sub-chunk
-            code = 0;
-            bd = __builtin_huge_val();
-            for (int c = 0; c < 256; ++c) {
-                double dist = 0.0;
-#pragma unroll
-                for (int j = 0; j < DS; ++j) {
-                    const double diff = xd[q][j] - cb[c * DS + j];
-                    dist = __builtin_fma(diff, diff, dist);
-                }
-                code = dist < bd ? c : code;
-                bd = __builtin_fmin(bd, dist);
-            }
-        }
-        codes[q] = code;
+        code += c0;
     }
+    // several (ties, near-ties, a token far outside the codebook's range): the lane walks every quad whose two bits
+    // are set — quad (m, g) of half s is centroids 4 (8 m + 2 g + s) .. + 3
+    several &= __builtin_amdgcn_ballot_w64(live && !bad);
+    if (several != 0) {  // wave-uniform
+        const bool mine = __builtin_amdgcn_inverse_ballot_w64(several);
+        uint32_t w[2];  // per tile: bit g a mark of by_g, bit 4 + m one of by_m
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            int lim = limit[t];
+            asm volatile("" : "+v"(lim));  // (keeps these selects inside the branch)
+            w[t] = 0;
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+                w[t] |= by_m[t][m] <= lim ? 16u << m : 0u;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                w[t] |= by_g[t][g] <= lim ? 1u << g : 0u;
+        }
+        const auto halves = __builtin_amdgcn_permlane32_swap(w[0], w[1], false, false);  // of this lane's token
+        uint64_t left = 0;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const uint32_t h = halves[s];
+            const uint32_t of_g = ((h & 1u) | (h & 2u) << 1 | (h & 4u) << 2 | (h & 8u) << 3) << s;  // bits 2 g + s
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+                left |= (uint64_t)((h >> (4 + m)) & 1u ? of_g : 0u) << (8 * m);
+        }
+        left = mine ? left : 0;
+        const int code_one = code;
+        code = 0;
+        bd = __builtin_huge_val();
+        while (__builtin_amdgcn_ballot_w64(left != 0) != 0) {
+            const int quad = left ? __builtin_ctzll(left) : 0;
+            const int code_before = code;
+            const double bd_before = bd;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                take(4 * quad + k);
+            if (left == 0) {  // this lane had nothing left: keep what it had
+                code = code_before;
+                bd = bd_before;
+            }
+            left &= left - 1;
+        }
+        if (!mine)
+            code = code_one;
+    }
+    const uint64_t unsure = __builtin_amdgcn_ballot_w64(live && bad) | (__builtin_amdgcn_ballot_w64(live) & ~some);
+    if (unsure != 0) {  // wave-uniform: the defining scan for this sub-chunk
+        code = 0;
+        bd = __builtin_huge_val();
+        for (int c = 0; c < 256; ++c)
+            take(c);
+    }
+    return code;
 }
 
 }  // namespace
