@@ -7,30 +7,21 @@
 // each fused multiply-add rounded once, nothing else contracted (this file is compiled
 // with -ffp-contract=off and the loop below also pins it with a pragma).  fp64 vector
 // arithmetic runs at the same rate as unpacked fp32 on gfx950, so exactness costs
-// nothing here; the scan costs 2 ds + 3 vector operations per (sub-vector, centroid).
+// nothing here; a scan of all centroids costs 2 ds + 3 vector operations per (sub-vector, centroid).
 //
-// Mapping.  One wavefront = one (K or V, sequence, KV head, subspace, 64-token
-// chunk).  Lane = token: all 64 lanes walk the 256 centroids in lock step, the
-// centroid (widened to double) comes out of LDS as a broadcast read, the running
-// best is a compare + two selects, and no cross-lane reduction is needed.  The
-// strict "<" on an ascending scan keeps the lowest index among equal distances.
-// The code byte is stored straight into the device layout of its tensor.
-// This scan (pq_encode_kernel) serves fp32 contexts; fp16 contexts reach the same codes through
-// pq_encode_fast_kernel further down, where the matrix cores find the few centroids that can be
-// the nearest and the expression above decides among them.
+// Appends of more than a few tokens reach the codes through pq_encode_fast_kernel, where the matrix cores find the
+// few centroids that can be the nearest and the expression above decides among them; a handful of tokens per head
+// through pq_encode_few_kernel, which evaluates the expression for all 256.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "pq_internal.h"
 #include "pq_device_utils.h"
 #include "pq_nearest_filter.h"
 
 namespace {
-
-// One wavefront per workgroup: its LDS footprint (the widened codebook of one subspace, 4-8 KiB)
-// fits beside a resident decode workgroup, so an encode issued on another stream can share the
-// compute units with a running decode (asynchronous quantization, Section III-B).
-constexpr int ENC_WAVES = 1;
 
 template <typename T> __device__ inline double widen(const void *p, int64_t i);
 template <> __device__ inline double widen<__half>(const void *p, int64_t i)
@@ -42,61 +33,8 @@ template <> __device__ inline double widen<float>(const void *p, int64_t i)
     return (double)((const float *)p)[i];
 }
 
-template <int M, int DS, typename T>
-__global__ __launch_bounds__(ENC_WAVES * 64) void pq_encode_kernel(const pq_encode_args a)
-{
-#pragma clang fp contract(off)
-    __shared__ double cb[ENC_WAVES][256 * DS];
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int which = blockIdx.z;                     // 0: keys, 1: values
-    const int i = blockIdx.y * ENC_WAVES + wave;      // subspace
-    const int n_chunks = (a.n_new + 63) >> 6;
-    const int chunk = blockIdx.x % n_chunks;
-    const int head = blockIdx.x / n_chunks;           // b * Hkv + hkv
-    const int b = head / a.Hkv;
-    const int hkv = head - b * a.Hkv;
-
-    // this wavefront's codebook C^i, widened
-    const int64_t cb_base = ((int64_t)hkv * M + i) * 256 * DS;
-    for (int e = lane; e < 256 * DS; e += 64)
-        cb[wave][e] = widen<T>(a.codebook[which], cb_base + e);
-    __builtin_amdgcn_wave_barrier();
-
-    const int tok = chunk * 64 + lane;
-    const bool live = tok < a.n_new;
-    double x[DS];
-#pragma unroll
-    for (int j = 0; j < DS; ++j)
-        x[j] = live ? widen<T>(a.x[which], ((int64_t)head * a.n_new + tok) * PQ_HEAD_DIM + i * DS + j) : 0.0;
-
-    int best = 0;
-    double best_dist = __builtin_huge_val();  // finite inputs: centroid 0 always beats it
-    for (int c = 0; c < 256; ++c) {
-        double dist = 0.0;
-#pragma unroll
-        for (int j = 0; j < DS; ++j) {
-            const double diff = x[j] - cb[wave][c * DS + j];
-            dist = __builtin_fma(diff, diff, dist);
-        }
-        // strict "<" on an ascending scan: the lowest index among equal distances stays
-        best = dist < best_dist ? c : best;
-        best_dist = __builtin_fmin(best_dist, dist);
-    }
-
-    int n_old = a.ctx_len[b];
-    n_old = n_old < 0 ? 0 : n_old;
-    const int64_t pos = (int64_t)n_old + tok;
-    if (live && pos < a.max_context) {
-        uint8_t *dst = a.codes[which] + (int64_t)head * a.head_stride;
-        const int64_t off = which == 0 ? pq_k_code_offset(pos, i, M, a.k_skew) : pq_v_code_offset(pos, i, M);
-        dst[off] = (uint8_t)best;
-    }
-}
-
 // ---------------------------------------------------------------------------------
-// fp16 inputs: the same codes, found with the matrix cores as a filter (pq_nearest_filter.h).
+// The codes of many tokens, found with the matrix cores as a filter (pq_nearest_filter.h); fp16 inputs first.
 //
 // With q(c) = n(c)/2 - x . c (n = |c|^2) the distance is |x|^2 + 2 q, so the nearest centroid minimises q.
 // For fp16 inputs every product x_j c_j is exact in fp32, and v_mfma_f32_32x32x8_f16 evaluates
@@ -131,6 +69,16 @@ __global__ __launch_bounds__(ENC_WAVES * 64) void pq_encode_kernel(const pq_enco
 // wide, sent a quarter of all chunks through the walk over several quads.)
 // The matrix instruction takes fp16 subnormals as they are (no flush: measured, and the default mode of a HIP kernel).
 //
+// fp32 inputs run the same filter on split operands: coordinates are scaled by a power of two that brings the
+// codebook's largest into [32, 64) and split into two fp16, v = v' + v'' (to 2^-22 of v, or 2^-25), and
+// v_mfma_f32_32x32x16_f16 sums x'c' + x'c'' + x''c' and the same last four terms.  Against the fp16 bound: twice the
+// terms of the sum (16 x 2^-23), 3 x 2^-22 of |x_j c_j| for what the split drops, 4 x 2^-23 for n/2 — eps = 26 x 2^-23 —
+// and absolute terms 2^-25 (|x_j| + |c_j|), which with |c| <= |x| + d stay below 2^-24 (1.5 + |x|^2 + v): tau =
+// 2.5e-5 (|x|^2 + best) + 2^-22 is 1.33 x 6 eps.  The refinement reads the unscaled fp32 coordinates.  A token longer
+// than some 1000 times the codebook's largest coordinate leaves the range and sends its chunk through the full scan.
+// (8192 tokens x 32 heads x (K, V), fp32: the full scan for every token 1.79 ms at M = 64 and 1.50 ms at M = 32, now
+// 0.46 and 0.26 ms.)
+//
 // Cost per (sub-vector, centroid): 1.3 vector operations instead of 2 ds + 3 in fp64, the matrix instructions in
 // parallel; bound by the issue of the vector instructions (about 340 per 64 tokens and subspace, counted; 92 % of the
 // issue slots at the 2.1 GHz the chip holds).  Prompt of 32K tokens x 32 heads x (K, V), M = 64: 2.75 ms with 4x4x4
@@ -139,21 +87,23 @@ __global__ __launch_bounds__(ENC_WAVES * 64) void pq_encode_kernel(const pq_enco
 // A workgroup is 4 neighbouring subspaces of the same tokens, one wavefront each: a token's line of 64 subspaces is
 // then fetched from L2 once for four wavefronts (one wavefront per workgroup 2.69 ms, two 2.35, four 1.75, eight 1.73
 // on the same box and an earlier filter; eight run out of LDS at M = 32: 124 -> 175 us on 3 x 5000 tokens x 8 heads).
-// The fp64 copy of the coordinates stays in LDS for ds = 2 (converting them at each use: 1.76 -> 1.89 ms); for ds = 4
+// fp16: a fp64 copy of the coordinates stays in LDS for ds = 2 (converting them at each use: 1.76 -> 1.89 ms); for ds = 4
 // its 32 KiB cost more wavefronts than the conversions cost instructions (124 -> 111 us).
 constexpr int FAST_WAVES = 4;
 
-template <int M, int DS, bool PER_SEQ>
+template <int M, int DS, typename T, bool PER_SEQ>
 __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const pq_encode_args a, const int rounds)
 {
-    constexpr bool WIDE = DS == 2;
-    __shared__ __attribute__((aligned(16))) unsigned char arow_all[FAST_WAVES][256 * PQ_FILTER_ROW];
-    __shared__ double cb_all[FAST_WAVES][WIDE ? 256 * DS : 1];
+    // T: _Float16 or float; W: what the centroids' coordinates are kept as for the refinement
+    typedef typename std::conditional<sizeof(T) == 4, float, typename std::conditional<DS == 2, double, _Float16>::type>::type W;
+    constexpr int ROW = pq_filter_row_bytes<T>();
+    __shared__ __attribute__((aligned(16))) unsigned char arow_all[FAST_WAVES][256 * ROW];
+    __shared__ __attribute__((aligned(16))) W coord_all[FAST_WAVES][sizeof(W) == 2 ? 1 : 256 * DS];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned char *arow = arow_all[wave];
-    double *cb = cb_all[wave];
+    W *coord = coord_all[wave];
     const int which = blockIdx.z;                  // 0: keys, 1: values
     const int i = blockIdx.y * FAST_WAVES + wave;  // subspace
     // chunks of 64 tokens of one KV head over all sequences (they share its codebook): whole chunks of each sequence
@@ -165,13 +115,37 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
     const int chunk0 = (blockIdx.x - hkv * n_jobs) * rounds;
     const int chunk1 = chunk0 + rounds < n_chunks ? chunk0 + rounds : n_chunks;
 
-    // ---- codebook of this subspace: A rows for the filter, fp64 copy for the exact evaluations
-    const __half *src = (const __half *)a.codebook[which] + ((int64_t)hkv * M + i) * 256 * DS;
+    // ---- codebook of this subspace: A rows for the filter, coordinates for the exact evaluations
+    const T *src = (const T *)a.codebook[which] + ((int64_t)hkv * M + i) * 256 * DS;
+    T y[4][DS];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < DS; ++j)
+            y[r][j] = src[(lane + 64 * r) * DS + j];
+    float scale = 1.f;
+    if constexpr (sizeof(T) == 4) {
+        float c_max = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < DS; ++j)
+                c_max = fmaxf(c_max, fabsf(y[r][j]));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+            c_max = fmaxf(c_max, __shfl_xor(c_max, o));
+        scale = pq_filter_scale(c_max);
+    }
     bool cb_bad = false;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int c = lane + 64 * r;
-        pq_filter_build_row<DS, WIDE>(src + c * DS, arow + c * PQ_FILTER_ROW, cb + (WIDE ? c * DS : 0), cb_bad);
+        pq_filter_build_row<DS>(y[r], scale, arow + c * ROW, cb_bad);
+        if constexpr (sizeof(W) > 2) {
+#pragma unroll
+            for (int j = 0; j < DS; ++j)
+                coord[c * DS + j] = (W)(float)y[r][j];
+        }
     }
     cb_bad = __builtin_amdgcn_ballot_w64(cb_bad) != 0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -182,9 +156,9 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
     // 2^32 (they fit the memory), a head's code bytes below 2^31.
     const uint32_t n_new = (uint32_t)a.n_new, Hkv = (uint32_t)a.Hkv, stride = (uint32_t)a.head_stride;
     const uint32_t cap = (uint32_t)a.max_context;
-    const char *x = (const char *)a.x[which] + i * (DS * (int)sizeof(__half));
+    const char *x = (const char *)a.x[which] + i * (DS * (int)sizeof(T));
     struct token {
-        _Float16 x[DS];
+        T x[DS];
         bool live;
         int n_old;
         uint32_t b, t;  // its sequence and position among the new tokens
@@ -199,7 +173,7 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
     const uint32_t b_step = 64u / n_new, t_step = 64u - b_step * n_new;
     const uint32_t row_step = b_step * Hkv * n_new + t_step, row_wrap = (Hkv - 1u) * n_new;
     auto fetch = [&](token &k) {
-        const _Float16 *xp;
+        const T *xp;
         if constexpr (PER_SEQ) {
             const bool any = b < (uint32_t)a.B;  // past the last chunk: the last sequence's last rows again
             k.b = any ? b : (uint32_t)a.B - 1u;
@@ -208,8 +182,8 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
             const uint32_t l = (uint32_t)lane < rest ? (uint32_t)lane : rest - 1u;
             k.live = any && (uint32_t)lane < rest;
             k.t = first;
-            const char *base = x + (uint64_t)((k.b * Hkv + (uint32_t)hkv) * n_new + first) * (PQ_HEAD_DIM * sizeof(__half));
-            xp = (const _Float16 *)(base + l * (uint32_t)(PQ_HEAD_DIM * sizeof(__half)));
+            const char *base = x + (uint64_t)((k.b * Hkv + (uint32_t)hkv) * n_new + first) * (PQ_HEAD_DIM * sizeof(T));
+            xp = (const T *)(base + l * (uint32_t)(PQ_HEAD_DIM * sizeof(T)));
             t += 64u;
             if (t >= n_new) {
                 t = 0u;
@@ -219,7 +193,7 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
             k.live = b < (uint32_t)a.B;
             k.b = k.live ? b : 0u;
             k.t = t;
-            xp = (const _Float16 *)(x + (uint64_t)(k.live ? row : (uint32_t)hkv * n_new) * (PQ_HEAD_DIM * sizeof(__half)));
+            xp = (const T *)(x + (uint64_t)(k.live ? row : (uint32_t)hkv * n_new) * (PQ_HEAD_DIM * sizeof(T)));
             b += b_step;
             t += t_step;
             row += row_step;
@@ -240,7 +214,7 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
     for (int chunk = chunk0; chunk < chunk1; ++chunk) {
         const token k = next;
         fetch(next);  // in flight while this chunk is worked on
-        const int code = pq_filter_code<DS, WIDE>(arow, cb, cb_bad, k.x, k.live);
+        const int code = pq_filter_code<DS, T, W>(arow, sizeof(W) == 2 ? arow : (const unsigned char *)coord, scale, cb_bad, k.x, k.live);
         const uint32_t n_old = (uint32_t)(k.n_old < 0 ? 0 : k.n_old);
         const uint32_t pos = (n_old < cap ? n_old : cap) + k.t + (PER_SEQ ? (uint32_t)lane : 0u);
         if (k.live && pos < cap) {
@@ -257,7 +231,7 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
 // registers, evaluates the defining fp64 distances of the token at hand to its 4 (ascending, strict "<") and
 // the wavefront takes the lexicographic minimum of (distance, index) — the lowest index among equal distances,
 // as in the scan.  One wavefront per (K or V, KV head, subspace) loops over the head's tokens of all sequences.
-constexpr int FEW_TOKENS = 16;
+constexpr int FEW_TOKENS = 6;
 
 template <int M, int DS, typename T>
 __global__ __launch_bounds__(64) void pq_encode_few_kernel(const pq_encode_args a)
@@ -334,14 +308,6 @@ __global__ void pq_bump_len_kernel(int32_t *ctx_len, int B, int n_new, int max_c
     ctx_len[b] = (int32_t)m;
 }
 
-template <int M, int DS, typename T>
-void launch(const pq_encode_args &a, hipStream_t s)
-{
-    const int n_chunks = (a.n_new + 63) >> 6;
-    dim3 grid(a.B * a.Hkv * n_chunks, M / ENC_WAVES, 2);
-    hipLaunchKernelGGL((pq_encode_kernel<M, DS, T>), grid, dim3(ENC_WAVES * 64), 0, s, a);
-}
-
 }  // namespace
 
 hipError_t pq_launch_bump_len(int32_t *ctx_len, int B, int n_new, int max_context, unsigned int *dev_err, hipStream_t s)
@@ -350,7 +316,7 @@ hipError_t pq_launch_bump_len(int32_t *ctx_len, int B, int n_new, int max_contex
     return hipGetLastError();
 }
 
-template <int M, int DS>
+template <int M, int DS, typename T>
 void launch_fast(const pq_encode_args &a, hipStream_t s)
 {
     // whole 64-token chunks of each sequence unless that leaves more than an eighth of the lanes without a token; a
@@ -362,18 +328,19 @@ void launch_fast(const pq_encode_args &a, hipStream_t s)
     const int rounds = (int)(waves / 8192 < 1 ? 1 : waves / 8192 > 32 ? 32 : waves / 8192);
     dim3 grid((unsigned)(a.Hkv * ((n_chunks + rounds - 1) / rounds)), M / FAST_WAVES, 2);
     if (per_seq)
-        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, true>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
+        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, true>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
     else
-        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, false>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
+        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, false>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
 }
 
 hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,
                             hipStream_t s)
 {
     const bool f16 = ctx->cfg.dtype == PQ_F16;
-    // fp16: from 7 tokens per head the filter kernel is the faster one (32 heads, one new token per sequence: 4
-    // sequences 7.4 us, 8 sequences 10.7 us, 16 sequences 17.9 us here against 10.1 us there)
-    if ((int64_t)a.B * a.n_new <= (f16 ? 6 : FEW_TOKENS)) {
+    // from 7 tokens per head the filter kernel is the faster one (fp16, 32 heads, one new token per sequence: 4
+    // sequences 7.4 us, 8 sequences 10.7 us, 16 sequences 17.9 us here against 10.1 us there; fp32, 16 sequences, with
+    // the length reset and the launches: 19.8 against 13.1 us)
+    if ((int64_t)a.B * a.n_new <= FEW_TOKENS) {
         const dim3 grid(a.Hkv, ctx->cfg.n_subspaces, 2);
         if (ctx->cfg.n_subspaces == 64) {
             if (f16) hipLaunchKernelGGL((pq_encode_few_kernel<64, 2, __half>), grid, dim3(64), 0, s, a);
@@ -387,12 +354,10 @@ hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int
             return e;
         return pq_launch_bump_len(ctx_len, a.B, a.n_new, a.max_context, dev_err, s);
     }
-    // the filter kernel indexes the tokens of a head over all sequences with 32 bits
-    const bool fast = f16 && (int64_t)a.B * a.n_new < ((int64_t)1 << 30);
     if (ctx->cfg.n_subspaces == 64) {
-        if (fast) launch_fast<64, 2>(a, s); else if (f16) launch<64, 2, __half>(a, s); else launch<64, 2, float>(a, s);
+        if (f16) launch_fast<64, 2, _Float16>(a, s); else launch_fast<64, 2, float>(a, s);
     } else {
-        if (fast) launch_fast<32, 4>(a, s); else if (f16) launch<32, 4, __half>(a, s); else launch<32, 4, float>(a, s);
+        if (f16) launch_fast<32, 4, _Float16>(a, s); else launch_fast<32, 4, float>(a, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)

@@ -9,10 +9,11 @@
 // magnitudes even if every addition truncated); PQ_FILTER_TAU_ABS = 2^-22 is a floor for tiny magnitudes.
 // 8-bit kernels (the argument is in pq_encode.hip), with `best` the token's smallest computed value:
 //   off = PQ_FILTER_X2_FACTOR X2 + 3 PQ_FILTER_TAU_ABS, rounded up
-//   tau = PQ_FILTER_TAU_NEAR (X2 + best) + PQ_FILTER_TAU_ABS
+//   tau = PQ_FILTER_TAU_NEAR (X2 + best) + PQ_FILTER_TAU_ABS     (fp32 inputs: PQ_FILTER_TAU_NEAR_F32)
 #pragma once
 
 #define PQ_FILTER_X2_FACTOR 0.5025f
 #define PQ_FILTER_TAU_REL 3.1e-06f
 #define PQ_FILTER_TAU_ABS 2.4e-07f
 #define PQ_FILTER_TAU_NEAR 1.05e-05f
+#define PQ_FILTER_TAU_NEAR_F32 2.5e-05f

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(KM_SUB * 64) void pq_kmeans_assign_kernel(const __h
                                                                       unsigned long long *sums, unsigned int *counts,
                                                                       int n_samples, int n_slices, int rounds)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char arow_all[KM_SUB][256 * PQ_FILTER_ROW];
+    __shared__ __attribute__((aligned(16))) unsigned char arow_all[KM_SUB][256 * pq_filter_row_bytes<_Float16>()];
     __shared__ unsigned long long sum_all[KM_SUB][256 * DS];
     __shared__ unsigned int cnt_all[KM_SUB][256];
 
@@ -56,10 +56,13 @@ __global__ __launch_bounds__(KM_SUB * 64) void pq_kmeans_assign_kernel(const __h
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int c = lane + 64 * r;
-        pq_filter_build_row<DS, false>(codebook + cb_base + c * DS, arow + c * PQ_FILTER_ROW, nullptr, cb_bad);
+        _Float16 y[DS];
 #pragma unroll
-        for (int j = 0; j < DS; ++j)
+        for (int j = 0; j < DS; ++j) {
+            y[j] = ((const _Float16 *)codebook)[cb_base + c * DS + j];
             part_sum[c * DS + j] = 0ull;
+        }
+        pq_filter_build_row<DS>(y, 1.f, arow + c * pq_filter_row_bytes<_Float16>(), cb_bad);
         part_cnt[c] = 0u;
     }
     cb_bad = __builtin_amdgcn_ballot_w64(cb_bad) != 0;
@@ -89,7 +92,7 @@ __global__ __launch_bounds__(KM_SUB * 64) void pq_kmeans_assign_kernel(const __h
             xv[j] = next[j];
         fetch(s + 64);
         const bool live = s < s1;
-        const int code = pq_filter_code<DS, false>(arow, nullptr, cb_bad, xv, live);
+        const int code = pq_filter_code<DS, _Float16, _Float16>(arow, arow, 1.f, cb_bad, xv, live);
         if (live) {
 #pragma unroll
             for (int j = 0; j < DS; ++j) {

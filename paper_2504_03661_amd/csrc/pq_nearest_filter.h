@@ -1,111 +1,168 @@
-// Nearest centroid of fp16 sub-vectors among 256 fp16 centroids: matrix-core filter + fp64 decision.
-// Shared by the encode kernel and the k-means assignment; the argument, the error bound and the fall-back are
-// described in pq_encode.hip.  Everything here works on ONE wavefront (a 64-token sub-chunk at a time, lane = token)
-// and on two LDS arrays the caller owns: the A rows of the 256 centroids (PQ_FILTER_ROW bytes each) and their fp64
-// copy.
+// Nearest centroid of fp16 or fp32 sub-vectors among 256 centroids of the same type: matrix-core filter + fp64
+// decision.  Shared by the encode kernel and the k-means assignment; the argument, the error bound and the fall-back
+// are described in pq_encode.hip.  Everything here works on ONE wavefront (a 64-token sub-chunk at a time, lane =
+// token) and on LDS arrays the caller owns: the A rows of the 256 centroids (pq_filter_row_bytes each) and, where the
+// coordinates are not read from the rows, a copy of them.
 #pragma once
 
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "pq_filter_constants.h"
 
 namespace {
 
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16e __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2e __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4e __attribute__((ext_vector_type(4)));
 
-// An A row holds the 8 inner indices of v_mfma_f32_32x32x8_f16: lanes 0..31 of the wavefront read its first half
-// (inner 0..3), lanes 32..63 its second (inner 4..7).
-//   ds = 2   c_0 c_1 h l | 1 2^15 0 0        against the column   -x_0 -x_1 1 1 | o_0 o_1 0 0
-//   ds = 4   c_0 c_1 c_2 c_3 | h l 1 2^15    against              -x_0 .. -x_3 | 1 1 o_0 o_1
-// (h + l = |c|^2 / 2, o_0 + 2^15 o_1 = the token's offset)
-constexpr int PQ_FILTER_ROW = 16;
+// An A row holds the inner indices of one matrix instruction: lanes 0..31 of the wavefront read its first half, lanes
+// 32..63 its second.  h + l = |c|^2 / 2, o_0 + 2^15 o_1 = the token's offset.
+//   fp16 (v_mfma_f32_32x32x8_f16, 16 bytes)
+//     ds = 2   c_0 c_1 h l | 1 2^15 0 0        against the column   -x_0 -x_1 1 1 | o_0 o_1 0 0
+//     ds = 4   c_0 c_1 c_2 c_3 | h l 1 2^15    against              -x_0 .. -x_3 | 1 1 o_0 o_1
+//   fp32 (v_mfma_f32_32x32x16_f16, 32 bytes), coordinates scaled by a power of two per codebook and split into two
+//   fp16, c = c' + c'', x = x' + x''
+//     ds = 2   c'_0 c'_1 c''_0 c''_1 c'_0 c'_1 h l | 1 2^15 0 0 0 0 0 0
+//                                    against -x'_0 -x'_1 -x'_0 -x'_1 -x''_0 -x''_1 1 1 | o_0 o_1 0 0 0 0 0 0
+//     ds = 4   c'_0 .. c'_3 c''_0 .. c''_3 | c'_0 .. c'_3 h l 1 2^15
+//                                    against -x'_0 .. -x'_3 -x'_0 .. -x'_3 | -x''_0 .. -x''_3 1 1 o_0 o_1
+template <typename T> constexpr int pq_filter_row_bytes() { return sizeof(T) == 2 ? 16 : 32; }
 
-// A row and fp64 copy (WIDE) of centroid c (src: its ds fp16 coordinates); sets `bad` when |c|^2 / 2 does not split
-// into two fp16
-template <int DS, bool WIDE>
-__device__ inline void pq_filter_build_row(const __half *src, unsigned char *arow_c, double *cb_c, bool &bad)
+// the power of two that brings the largest coordinate of an fp32 codebook into [32, 64)
+__device__ inline float pq_filter_scale(float c_max)
 {
+    int e = 0;
+    (void)__builtin_frexpf(c_max, &e);
+    e = e < -100 ? -100 : e;  // (a codebook this small is one cluster of near-ties to the filter)
+    return c_max > 0.f ? __builtin_ldexpf(1.0f, 6 - e) : 1.0f;
+}
+
+// A row of a centroid (c: its ds coordinates; fp32: scaled by `scale`); sets `bad` when |c|^2 / 2 does not split into
+// two fp16
+template <int DS, typename T>
+__device__ inline void pq_filter_build_row(const T (&c)[DS], const float scale, unsigned char *arow_c, bool &bad)
+{
+    constexpr int SLOTS = pq_filter_row_bytes<T>() / 2;
     float n = 0.f;
-    _Float16 row[8] = {};
+    _Float16 row[SLOTS] = {};
+    constexpr int N_AT = sizeof(T) == 2 ? DS : 3 * DS;  // h, l, 1, 2^15 stand behind the coordinates
 #pragma unroll
     for (int j = 0; j < DS; ++j) {
-        const _Float16 v = __builtin_bit_cast(_Float16, src[j]);
-        const float f = (float)v;
-        if (WIDE)
-            cb_c[j] = (double)f;
-        row[j] = v;
-        n += f * f;  // exact squares; the sum is rounded (covered by the bound)
+        const float f = sizeof(T) == 2 ? (float)c[j] : (float)c[j] * scale;
+        n += f * f;  // (the roundings are covered by the bound)
+        row[j] = (_Float16)f;
+        if constexpr (sizeof(T) == 4) {
+            row[DS + j] = (_Float16)(f - (float)row[j]);
+            row[2 * DS + j] = row[j];
+        }
     }
     const float h = 0.5f * n;
     const _Float16 hh = (_Float16)h;
     const _Float16 hl = (_Float16)(h - (float)hh);
-    row[DS] = hh;
-    row[DS + 1] = hl;
-    row[DS + 2] = (_Float16)1.f;
-    row[DS + 3] = (_Float16)32768.f;
+    row[N_AT] = hh;
+    row[N_AT + 1] = hl;
+    row[N_AT + 2] = (_Float16)1.f;
+    row[N_AT + 3] = (_Float16)32768.f;
     bad |= !(h < 60000.f);
-    __builtin_memcpy(arow_c, row, PQ_FILTER_ROW);
+    __builtin_memcpy(arow_c, row, pq_filter_row_bytes<T>());
 }
 
-// code of this lane's token (xin: its fp16 sub-vector; a dead lane passes any finite values and live = false)
-template <int DS, bool WIDE>
-__device__ inline int pq_filter_code(const unsigned char *arow, const double *cb, const bool cb_bad, const _Float16 (&xin)[DS], const bool live)
+// code of this lane's token (xin: its sub-vector; a dead lane passes any finite values and live = false).
+// `coord`: the centroids' coordinates as W (double, float, or _Float16 = inside the fp16 A rows)
+template <int DS, typename T, typename W>
+__device__ inline int pq_filter_code(const unsigned char *arow, const unsigned char *coord, const float scale, const bool cb_bad,
+                                     const T (&xin)[DS], const bool live)
 {
 #pragma clang fp contract(off)
+    constexpr bool F16 = sizeof(T) == 2;
+    constexpr int ROW = pq_filter_row_bytes<T>();
+    constexpr int STRIDE = sizeof(W) == 2 ? ROW : DS * (int)sizeof(W);  // of a centroid's coordinates
+    constexpr float TAU_NEAR = F16 ? PQ_FILTER_TAU_NEAR : PQ_FILTER_TAU_NEAR_F32;
+    typedef typename std::conditional<F16, f16x4, f16x8>::type operand;
     const int lane = threadIdx.x & 63;
     bool bad = cb_bad;
     double xd[DS];
     float tau_x;
-    f16x4 bop[2];  // the columns of tokens 0..31 and 32..63
+    operand bop[2];  // the columns of tokens 0..31 and 32..63
     {
-        float x2 = 0.f;
+        float x2 = 0.f, xs[DS];
 #pragma unroll
         for (int j = 0; j < DS; ++j) {
-            const float f = (float)xin[j];
-            xd[j] = (double)f;
-            x2 = __builtin_fmaf(f, f, x2);
+            xd[j] = (double)(float)xin[j];
+            xs[j] = F16 ? (float)xin[j] : (float)xin[j] * scale;
+            x2 = __builtin_fmaf(xs[j], xs[j], x2);
         }
         // off: |x|^2/2 with half a per cent on top and a floor, so that every computed value stays above zero, rounded
         // UP to o_0 + 2^15 o_1 (one of the two is zero) by 0.3 % against the half step (2^-11) of the conversion and a
         // subnormal step
         const float off = __builtin_fmaf(PQ_FILTER_X2_FACTOR, x2, 3.0f * PQ_FILTER_TAU_ABS);
         const float up = __builtin_fmaf(off, 1.003f, 6.0e-8f);
-        tau_x = __builtin_fmaf(PQ_FILTER_TAU_NEAR, x2, PQ_FILTER_TAU_ABS);
+        tau_x = __builtin_fmaf(TAU_NEAR, x2, PQ_FILTER_TAU_ABS);
         _Float16 o0 = (_Float16)up, o1 = (_Float16)0.f;
-        if (__builtin_amdgcn_ballot_w64(!(off < 60000.f)) != 0) {  // wave-uniform, rare: sub-vectors longer than 340
+        if (__builtin_amdgcn_ballot_w64(!(off < 60000.f)) != 0) {  // wave-uniform, rare: (scaled) length beyond 340
             const bool large = !(off < 60000.f);
             o0 = large ? (_Float16)0.f : o0;
             o1 = large ? (_Float16)(up * (1.0f / 32768.f)) : (_Float16)0.f;
             bad |= !(off < 2.0e9f);
         }
         const _Float16 one = (_Float16)1.f, zero = (_Float16)0.f;
-        f16x4 lo, hi;
-        if constexpr (DS == 2) {
+        operand lo, hi;
+        if constexpr (F16 && DS == 2) {
             lo = f16x4{-xin[0], -xin[1], one, one};
             hi = f16x4{o0, o1, zero, zero};
-        } else {
+        } else if constexpr (F16) {
             lo = f16x4{-xin[0], -xin[1], -xin[DS - 2], -xin[DS - 1]};
             hi = f16x4{one, one, o0, o1};
+        } else {
+            _Float16 p[DS], r[DS];
+#pragma unroll
+            for (int j = 0; j < DS; ++j) {
+                p[j] = (_Float16)(-xs[j]);
+                r[j] = (_Float16)(-xs[j] - (float)p[j]);
+            }
+            if constexpr (DS == 2) {
+                lo = f16x8{p[0], p[1], p[0], p[1], r[0], r[1], one, one};
+                hi = f16x8{o0, o1, zero, zero, zero, zero, zero, zero};
+            } else {
+                lo = f16x8{p[0], p[1], p[DS - 2], p[DS - 1], p[0], p[1], p[DS - 2], p[DS - 1]};
+                hi = f16x8{r[0], r[1], r[DS - 2], r[DS - 1], one, one, o0, o1};
+            }
         }
         // lane = token holds both halves of its own column; the instruction wants the upper half of column t in
         // lane t + 32: one exchange of the lane halves gives the operands of both token tiles
-        const u32x2e l = __builtin_bit_cast(u32x2e, lo), h = __builtin_bit_cast(u32x2e, hi);
-        const auto s0 = __builtin_amdgcn_permlane32_swap(l.x, h.x, false, false);
-        const auto s1 = __builtin_amdgcn_permlane32_swap(l.y, h.y, false, false);
-        bop[0] = __builtin_bit_cast(f16x4, u32x2e{s0[0], s1[0]});
-        bop[1] = __builtin_bit_cast(f16x4, u32x2e{s0[1], s1[1]});
+        constexpr int WORDS = (int)sizeof(operand) / 4;
+        typedef typename std::conditional<F16, u32x2e, u32x4e>::type words;
+        const words l = __builtin_bit_cast(words, lo), h = __builtin_bit_cast(words, hi);
+        words b0, b1;
+#pragma unroll
+        for (int k = 0; k < WORDS; ++k) {
+            const auto s = __builtin_amdgcn_permlane32_swap(l[k], h[k], false, false);
+            b0[k] = s[0];
+            b1[k] = s[1];
+        }
+        bop[0] = __builtin_bit_cast(operand, b0);
+        bop[1] = __builtin_bit_cast(operand, b1);
     }
+    auto values = [&](const operand &A, const operand &B) -> f32x16e {
+        const f32x16e none = {};
+        if constexpr (F16)
+            return __builtin_amdgcn_mfma_f32_32x32x8f16(A, B, none, 0, 0, 0);
+        else
+            return __builtin_amdgcn_mfma_f32_32x32x16_f16(A, B, none, 0, 0, 0);
+    };
 
     // ---- the 256 computed values of every token, 32 centroids per instruction.  Lane l ends with those of token
     // l mod 32 of the tile whose centroids lie in its half: 32 m + 8 g + 4 (l / 32) + 0..3 in registers 4 g .. 4 g + 3
     // ("quad" (m, g)).  Kept are the minima over g per m and over m per g (positive floats order like their bit
     // patterns): 12 numbers that name every quad with a value near the smallest one without a second pass.
     int by_m[2][8], by_g[2][4];
-    const unsigned char *my_row = arow + (lane & 31) * PQ_FILTER_ROW + (lane >> 5) * 8;
+    const unsigned char *my_row = arow + (lane & 31) * ROW + (lane >> 5) * (ROW / 2);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -113,13 +170,12 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const double *cb
             by_g[t][g] = 0x7f800000;
 #pragma unroll
     for (int m = 0; m < 8; m += 2) {
-        const f16x4 A0 = *(const f16x4 *)(my_row + m * (32 * PQ_FILTER_ROW));
-        const f16x4 A1 = *(const f16x4 *)(my_row + (m + 1) * (32 * PQ_FILTER_ROW));
+        const operand A0 = *(const operand *)(my_row + m * (32 * ROW));
+        const operand A1 = *(const operand *)(my_row + (m + 1) * (32 * ROW));
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const f32x16e none = {};
-            const f32x16e d0 = __builtin_amdgcn_mfma_f32_32x32x8f16(A0, bop[t], none, 0, 0, 0);
-            const f32x16e d1 = __builtin_amdgcn_mfma_f32_32x32x8f16(A1, bop[t], none, 0, 0, 0);
+            const f32x16e d0 = values(A0, bop[t]);
+            const f32x16e d1 = values(A1, bop[t]);
             int q0[4], q1[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -147,7 +203,7 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const double *cb
         const float best = __int_as_float(min((int)s[0], (int)s[1]));
         bad |= !(best > 0.f && best < 1.0e30f);  // the offset did not keep the values positive and finite
         // best + tau, tau = TAU_NEAR (|x|^2 + best) + TAU_ABS
-        const int lim = __float_as_int(__builtin_fmaf(best, 1.0f + PQ_FILTER_TAU_NEAR, tau_x));
+        const int lim = __float_as_int(__builtin_fmaf(best, 1.0f + TAU_NEAR, tau_x));
         const auto r = __builtin_amdgcn_permlane32_swap(lim, lim, false, false);
         limit[0] = (int)r[0];
         limit[1] = (int)r[1];
@@ -196,14 +252,18 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const double *cb
     // ---- refine: the defining arithmetic on the marked quads, ascending
     int code = 0;
     double bd = __builtin_huge_val();
-    auto coordinates = [&](const unsigned char *row, const double *wide, double (&c)[DS]) {
+    auto coordinates = [&](const unsigned char *at, double (&c)[DS]) {
 #pragma unroll
-        for (int j = 0; j < DS; ++j)
-            c[j] = WIDE ? wide[j] : (double)(float)((const _Float16 *)row)[j];
+        for (int j = 0; j < DS; ++j) {
+            if constexpr (sizeof(W) == 2)
+                c[j] = (double)(float)((const W *)at)[j];
+            else
+                c[j] = (double)((const W *)at)[j];
+        }
     };
     auto take = [&](int c) {
         double y[DS], dist = 0.0;
-        coordinates(arow + c * PQ_FILTER_ROW, cb + c * DS, y);
+        coordinates(coord + c * STRIDE, y);
 #pragma unroll
         for (int j = 0; j < DS; ++j) {
             const double diff = xd[j] - y[j];
@@ -218,12 +278,11 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const double *cb
         const auto bit = [](uint64_t mask, int value) { return __builtin_amdgcn_inverse_ballot_w64(mask) ? value : 0; };
         const int c0 = bit(bit_m[0], 32) | bit(bit_m[1], 64) | bit(bit_m[2], 128) | bit(bit_g[0], 8) | bit(bit_g[1], 16) |
                        bit(in_half1, 4);
-        const unsigned char *rows = arow + c0 * PQ_FILTER_ROW;
-        const double *wide = cb + c0 * DS;
+        const unsigned char *quad = coord + c0 * STRIDE;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             double y[DS], dist = 0.0;
-            coordinates(rows + k * PQ_FILTER_ROW, wide + k * DS, y);
+            coordinates(quad + k * STRIDE, y);
 #pragma unroll
             for (int j = 0; j < DS; ++j) {
                 const double diff = xd[j] - y[j];
