@@ -60,6 +60,8 @@ typedef struct {
     int32_t dtype;        /* pq_dtype of q, codebooks, recent K/V and new K/V               */
     int32_t device;       /* HIP device ordinal                                             */
     int32_t n_splits;     /* context splits per (sequence, query head); 0 = choose.         */
+                          /* "0 = choose" with 2..64 sequences of 8-bit codes: the decode     */
+                          /* kernel gives its workgroups to the sequences by their lengths   */
                           /* 4096-centroid contexts only: -k asks for the two-pass decode   */
                           /* (split by subspace group) with k token ranges; "0 = choose"    */
                           /* takes it by itself when (sequence, head) pairs are few         */
@@ -81,7 +83,8 @@ int64_t pq_attn_codes_bytes(const pq_attn_config *cfg /* host */);
 int pq_attn_create(const pq_attn_config *cfg /* host */, pq_attn_ctx **out /* host */);
 int pq_attn_destroy(pq_attn_ctx *ctx);
 
-/* Number of context splits the decode kernel uses (after "0 = choose"). */
+/* Number of context splits the decode kernel uses (after "0 = choose"; a batch whose workgroups follow the
+ * sequences' lengths: the number for equal lengths). */
 int pq_attn_n_splits(const pq_attn_ctx *ctx);
 
 /* Kernels one pq_attn_decode call launches: 1 (fused), or 2 for a 4096-centroid

@@ -137,6 +137,20 @@ int choose_splits(const pq_attn_config *c, int n_cu)
     return (int)s;
 }
 
+// Workgroups per head (KV head and sub-group in the grouped-query kernel) of a batch whose splits are left to the
+// library, given to the sequences by their lengths: the head's share of the compute units if that is more than one per
+// sequence, one per sequence if the batch makes between one and two rounds of the chip (pq_device_utils.h).
+int choose_jobs(const pq_attn_config *c, int n_cu)
+{
+    if (c->batch < 2 || c->batch > 64 || c->n_splits != 0 || pq_config_is_12bit(c))
+        return 0;
+    const int64_t heads = pq_config_uses_grouped_kernel(c)
+                              ? (int64_t)c->n_kv_heads * pq_grouped_sub_groups(c->n_q_heads / c->n_kv_heads)
+                              : c->n_q_heads;
+    const int64_t share = n_cu / heads < PQ_MAX_SPLITS ? n_cu / heads : PQ_MAX_SPLITS;
+    return share > c->batch ? (int)share : (share < c->batch && c->batch <= 2 * share ? c->batch : 0);
+}
+
 // Codebook pointers passed to an entry point are registered there and then: the context copies them on the
 // stream (its own natural-layout copy for the encode kernels, the centroid-major image for the decode
 // kernels) and never looks at the caller's tensors again.  NULL, NULL means "the registered ones".
@@ -200,6 +214,7 @@ int launch_decode(const pq_attn_ctx *ctx, const void *q, const uint8_t *k_codes,
     a.Gs = ctx->k_skew == PQ_K_SKEW_QUAD || ctx->grouped12 ? pq_grouped_heads_per_workgroup(ctx->group) : 0;
     a.n_sub = ctx->k_skew == PQ_K_SKEW_QUAD || ctx->grouped12 ? pq_grouped_sub_groups(ctx->group) : 0;
     a.S = ctx->n_splits;
+    a.jobs = ctx->jobs;
     a.max_context = ctx->cfg.max_context;
     a.max_recent = ctx->cfg.max_recent;
     a.n_cu = ctx->n_cu;
@@ -289,7 +304,9 @@ int pq_attn_create(const pq_attn_config *cfg, pq_attn_ctx **out)
 
     const size_t cb_bytes = (size_t)cfg->n_kv_heads * cfg->n_centroids * PQ_HEAD_DIM * ctx->elem_bytes;
     const size_t n_bh = (size_t)cfg->batch * cfg->n_q_heads;
-    const size_t part_bytes = n_bh * ctx->n_splits * PQ_PART_STRIDE * sizeof(float);
+    ctx->jobs = choose_jobs(cfg, ctx->n_cu);
+    const size_t slots = (size_t)(ctx->jobs > ctx->n_splits ? ctx->jobs : ctx->n_splits);  // partials per row
+    const size_t part_bytes = n_bh * slots * PQ_PART_STRIDE * sizeof(float);
     bool ok = hipMalloc(&ctx->kcb_packed, cb_bytes) == hipSuccess;
     ok = ok && hipMalloc(&ctx->vcb_packed, cb_bytes) == hipSuccess;
     ok = ok && hipMalloc((void **)&ctx->partials, part_bytes) == hipSuccess;

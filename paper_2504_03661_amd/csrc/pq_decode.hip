@@ -53,7 +53,9 @@ constexpr int F32_CHUNK = 64;        // blocks (of 64 tokens) per chunk
 constexpr int SBUF_OFF = SMEM_BYTES; // float [F32_CHUNK][64]
 constexpr int SMEM_BYTES_F32 = SBUF_OFF + F32_CHUNK * 256;
 static_assert(SMEM_BYTES_F32 <= 160 * 1024, "LDS budget of a gfx950 compute unit");
-template <int M, int DS, typename T, int NW, bool READ_ONCE>
+// BATCH: how a batch's workgroups are given to its sequences (pq_device_utils.h); BATCH_DEAL: the grid is (query heads x
+// a.S jobs).
+template <int M, int DS, typename T, int NW, bool READ_ONCE, int BATCH>
 __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args a)
 {
     static_assert(M * DS == PQ_HEAD_DIM, "head_dim 128 only");
@@ -73,18 +75,19 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     // dealt round-robin to the 8 XCDs; un-deal them so that all splits of a head (and
     // all query heads of a KV group) sit on one XCD and share its L2 for the
     // codebooks and, with grouped queries, the code stream itself.
+    const int max_context = a.max_context, max_recent = a.max_recent;
+    asm volatile("" ::"s"(max_context), "s"(max_recent));  // (read with the other arguments, not behind the barrier)
     const int S_grid = a.S;  // splits the grid was launched with (partials are laid out with this stride)
     // neighbours: the splits of a (sequence, query head), the query heads of its KV group, then the same
     // KV head of the other sequences (they load the same codebooks: once per XCD instead of once per sequence)
     uint32_t unit, split_u;
     unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
-    const int split = (int)split_u;
-    const uint32_t bkv = unit / (uint32_t)a.G;          // hkv * B + b
+    int split = (int)split_u;
+    const uint32_t bkv = unit / (uint32_t)a.G;          // hkv * B + b (BATCH_DEAL: hkv)
     const int gq = (int)(unit - bkv * (uint32_t)a.G);
-    const int hkv = (int)(bkv / (uint32_t)a.B);
-    const int b = (int)(bkv - (uint32_t)hkv * (uint32_t)a.B);
+    const int hkv = BATCH == BATCH_DEAL ? (int)bkv : (int)(bkv / (uint32_t)a.B);
+    int b = BATCH == BATCH_DEAL ? batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u) : (int)(bkv - (uint32_t)hkv * (uint32_t)a.B);
     const int hq = hkv * a.G + gq;
-    const int bh = b * a.Hq + hq;
 
     // The lengths are requested first and taken out of their registers only after the table loads
     // below have been issued.  The loads go through lane_zero(), which the compiler cannot see
@@ -92,9 +95,10 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     // wait for each of the two — two serial memory round trips before the first table load.
     const int zero = lane_zero();
     const bool has_recent = a.recent_k != nullptr && a.recent_len != nullptr;
-    const int n_vec = a.ctx_len[b + zero];
-    const int r_vec = (has_recent ? a.recent_len : a.ctx_len)[b + zero];
-    const float w_lane = (a.B > 1 && a.S > 1) ? batch_work_lane(a, has_recent, lane) : 0.f;  // one launched split: nothing to cap
+    const int len_at = BATCH != BATCH_NONE ? (lane < a.B ? lane : 0) : b + zero;  // a batch: lane = sequence
+    const int n_vec = a.ctx_len[len_at];
+    const int r_vec = (has_recent ? a.recent_len : a.ctx_len)[len_at];
+    const float w_lane = (BATCH == BATCH_NONE && a.B > 1 && a.S > 1) ? batch_work_lane(a, has_recent, lane) : 0.f;  // one launched split: nothing to cap
 
     // ---- prologue: LUT[c][x] for x = 0..63 (for M = 32 columns x and x+32 hold the same
     // subspace), and the value codebook image.  Order matters at this time scale:
@@ -126,15 +130,44 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
         for (int v = 0; v < VPT; ++v)
             vraw[v] = src[tid + v * (NW * 64)];
     }
+    auto load_q = [&]() {
 #pragma unroll
-    for (int v = 0; v < NV; ++v)
-        qraw[v] = *(const u32x4 *)((const char *)a.q + (((int64_t)b * a.Hq + hq) * PQ_HEAD_DIM + e0) * sizeof(T) + v * 16);
+        for (int v = 0; v < NV; ++v)
+            qraw[v] = *(const u32x4 *)((const char *)a.q + (((int64_t)b * a.Hq + hq) * PQ_HEAD_DIM + e0) * sizeof(T) + v * 16);
+    };
+    load_q();
     __builtin_amdgcn_s_barrier();
 
-    int N = __builtin_amdgcn_readfirstlane(n_vec);
-    int R = has_recent ? __builtin_amdgcn_readfirstlane(r_vec) : 0;
-    N = N < 0 ? 0 : (N > a.max_context ? a.max_context : N);
-    R = R < 0 ? 0 : (R > a.max_recent ? a.max_recent : R);
+    const auto clamp_to = [](int x, int most) { return x < 0 ? 0 : (x > most ? most : x); };
+    int N, R, S_job = 1;
+    if constexpr (BATCH != BATCH_NONE) {
+        const int n = clamp_to(n_vec, max_context), r = has_recent ? clamp_to(r_vec, max_recent) : 0;
+        int mine;
+        if constexpr (BATCH == BATCH_DEAL) {
+            const batch_job job = batch_deal(a.B, a.S, split, (uint32_t)n, (uint32_t)r, lane);
+            if (job.split >= job.S)
+                return;
+            split = job.split;
+            S_job = job.S;
+            mine = job.b;
+        } else {
+            mine = batch_order(a.B, b, (uint32_t)n, (uint32_t)r, lane);
+        }
+        N = __builtin_amdgcn_readlane(n, mine);
+        R = __builtin_amdgcn_readlane(r, mine);
+        if (mine != b) {
+            b = mine;
+            load_q();
+            // (waited for here: behind the join the compiler would wait in front of the code loads on every path)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                asm volatile("" ::"v"(qraw[v]));
+        }
+    } else {
+        N = clamp_to(__builtin_amdgcn_readfirstlane(n_vec), a.max_context);
+        R = has_recent ? clamp_to(__builtin_amdgcn_readfirstlane(r_vec), a.max_recent) : 0;
+    }
+    const int bh = b * a.Hq + hq;
     // 32-bit unsigned arithmetic: the capacities are limited to 2^24 tokens and S to 64, and a
     // 64-bit division costs more instructions than the whole table build
     const uint32_t nblk = (uint32_t)(N + 63) >> 6;
@@ -143,12 +176,12 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     // so a short sequence in a long cache uses the first few splits only and the others leave here, before
     // they build tables (every workgroup of the row computes the same count; the merge expects that many).
     uint32_t want = nblk / 4u > (uint32_t)R / 16u ? nblk / 4u : (uint32_t)R / 16u;  // ... or 16 recent rows
-    if (a.B > 1 && a.S > 1) {  // ... and in a batch no more than the sequence's share of the compute units
+    if (BATCH == BATCH_NONE && a.B > 1 && a.S > 1) {  // ... and in a batch no more than the sequence's share of the compute units
         const uint32_t cap = live_split_cap(a, a.Hq, N + R, w_lane);
         want = want < cap ? want : cap;
     }
-    const int S = (int)(want < 1u ? 1u : (want < (uint32_t)S_grid ? want : (uint32_t)S_grid));
-    if (split >= S)
+    const int S = BATCH != BATCH_NONE ? S_job : (int)(want < 1u ? 1u : (want < (uint32_t)S_grid ? want : (uint32_t)S_grid));
+    if (BATCH == BATCH_NONE && split >= S)
         return;
     const int blk0 = (int)(nblk * (uint32_t)split / (uint32_t)S);
     const int blk1 = (int)(nblk * (uint32_t)(split + 1) / (uint32_t)S);
@@ -672,8 +705,15 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
 template <int M, int DS, typename T, int NW, bool READ_ONCE>
 hipError_t launch(const pq_decode_args &a, hipStream_t s)
 {
-    const int grid = a.B * a.Hq * a.S;
-    hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE>), dim3(grid), dim3(NW * 64), 0, s, a);
+    const dim3 block(NW * 64);
+    pq_decode_args aj = a;
+    aj.S = a.jobs > a.B ? a.jobs : 1;
+    if (a.jobs > a.B)
+        hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_DEAL>), dim3(a.Hq * a.jobs), block, 0, s, aj);
+    else if (a.jobs > 0)
+        hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_ORDER>), dim3(a.B * a.Hq), block, 0, s, aj);
+    else
+        hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_NONE>), dim3(a.B * a.Hq * a.S), block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -688,13 +728,14 @@ hipError_t pq_launch_decode(const pq_attn_ctx *ctx, const pq_decode_args &a, hip
     // With grouped queries every code byte is scored by G workgroups out of one XCD's L2, the scan
     // is bound by the vector ALU and LDS, and 16 wavefronts (4 per SIMD) hide their latencies
     // better (79 us against 86 us at 32 query heads over 8 KV heads, 128K context).
+    // (fp16 contexts with grouped queries run the grouped-query kernel)
     const bool shared = ctx->group > 1;
     if (ctx->cfg.n_subspaces == 64) {
         if (shared)
-            return f16 ? launch<64, 2, __half, 16, false>(a, s) : launch<64, 2, float, 16, false>(a, s);
+            return launch<64, 2, float, 16, false>(a, s);
         return f16 ? launch<64, 2, __half, 8, true>(a, s) : launch<64, 2, float, 8, true>(a, s);
     }
     if (shared)
-        return f16 ? launch<32, 4, __half, 16, false>(a, s) : launch<32, 4, float, 16, false>(a, s);
+        return launch<32, 4, float, 16, false>(a, s);
     return f16 ? launch<32, 4, __half, 16, true>(a, s) : launch<32, 4, float, 16, true>(a, s);
 }

@@ -81,7 +81,9 @@ __device__ inline f16x4 as_f16x4(uint32_t lo, uint32_t hi)
 // real subspace v >> 1 and carries that subspace's code.  The packed codebook images are the same bytes either way
 // ([256][128 dims] fp16), so only the code loads differ: half the bytes per token, one K code byte serves two of
 // the four gathers of a score step, and two neighbouring lanes of the value pass share one V code stream.
-template <bool READ_ONCE, int M>
+// BATCH: how a batch's workgroups are given to its sequences (pq_device_utils.h); BATCH_DEAL: the grid is (KV heads x
+// sub-groups x a.S jobs).
+template <bool READ_ONCE, int M, int BATCH>
 __global__ __launch_bounds__(GNW * 64) void pq_decode_grouped_kernel(const pq_decode_args a)
 {
     static_assert(M == 64 || M == 32, "64 subspaces of 2 dims or 32 of 4");
@@ -94,33 +96,35 @@ __global__ __launch_bounds__(GNW * 64) void pq_decode_grouped_kernel(const pq_de
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
+    const int max_context = a.max_context, max_recent = a.max_recent;
+    asm volatile("" ::"s"(max_context), "s"(max_recent));  // (read with the other arguments, not behind the barrier)
     const int S_grid = a.S;  // splits the grid was launched with (partials are laid out with this stride)
     // workgroups of one KV head are neighbours: (sequence, KV head, sub-group of G query heads, split)
     uint32_t unit_u, split_u;
     unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit_u, split_u);
-    const int unit = (int)unit_u, split = (int)split_u;
+    const int unit = (int)unit_u;
+    int split = (int)split_u;
     const int n_sub = a.n_sub;                     // sub-groups per KV head
     // ... then the same KV head of the other sequences (same codebook images: once per XCD from memory)
-    const int hb = (int)((uint32_t)unit / (uint32_t)n_sub);  // hkv * B + b
+    const int hb = (int)((uint32_t)unit / (uint32_t)n_sub);  // hkv * B + b (BATCH_DEAL: hkv)
     const int sub_group = unit - hb * n_sub;
-    const int hkv = (int)((uint32_t)hb / (uint32_t)a.B);
-    const int b = hb - hkv * a.B;
-    const int bkv = b * a.Hkv + hkv;
+    const int hkv = BATCH == BATCH_DEAL ? hb : (int)((uint32_t)hb / (uint32_t)a.B);
+    int b = BATCH == BATCH_DEAL ? batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u) : hb - hkv * a.B;
     // the KV head's a.G query heads in n_sub sub-groups whose sizes differ by at most one (the first a.G % n_sub take
     // one more): this workgroup's heads are g_first .. g_first + G - 1, G = 2..4
     const int g_base = a.G / n_sub, g_rem = a.G - g_base * n_sub;
     const int G = g_base + (sub_group < g_rem ? 1 : 0);
     const int g_first = sub_group * g_base + (sub_group < g_rem ? sub_group : g_rem);
-    const int bh0 = b * a.Hq + hkv * a.G + g_first;  // first query head of this workgroup
     // The lengths are requested first and taken out of their registers only after the table loads
     // below have been issued.  The loads go through lane_zero(), which the compiler cannot see
     // through: a load from a wave-uniform address is otherwise made scalar on the spot, with a full
     // wait for each of the two — two serial memory round trips before the first table load.
     const int zero = lane_zero();
     const bool has_recent = a.recent_k != nullptr && a.recent_len != nullptr;
-    const int n_vec = a.ctx_len[b + zero];
-    const int r_vec = (has_recent ? a.recent_len : a.ctx_len)[b + zero];
-    const float w_lane = (a.B > 1 && a.S > 1) ? batch_work_lane(a, has_recent, lane) : 0.f;  // one launched split: nothing to cap
+    const int len_at = BATCH != BATCH_NONE ? (lane < a.B ? lane : 0) : b + zero;  // a batch: lane = sequence
+    const int n_vec = a.ctx_len[len_at];
+    const int r_vec = (has_recent ? a.recent_len : a.ctx_len)[len_at];
+    const float w_lane = (BATCH == BATCH_NONE && a.B > 1 && a.S > 1) ? batch_work_lane(a, has_recent, lane) : 0.f;  // one launched split: nothing to cap
 
     // ---- prologue: both codebook images and the group's queries; table loads first, bare
     // barrier, then the first code block (see the per-head kernel for why)
@@ -137,24 +141,52 @@ __global__ __launch_bounds__(GNW * 64) void pq_decode_grouped_kernel(const pq_de
     }
     // q of the group: G x 128 fp16 = G x 16 vectors; heads beyond G are zero rows
     u32x4 qraw = {0u, 0u, 0u, 0u};
-    if (tid < 16 * G)
-        qraw = *((const u32x4 *)((const __half *)a.q + (int64_t)bh0 * PQ_HEAD_DIM) + tid);
+    auto load_q = [&]() {
+        if (tid < 16 * G)
+            qraw = *((const u32x4 *)((const __half *)a.q + ((int64_t)b * a.Hq + hkv * a.G + g_first) * PQ_HEAD_DIM) + tid);
+    };
+    load_q();
     __builtin_amdgcn_s_barrier();
 
-    int N = __builtin_amdgcn_readfirstlane(n_vec);
-    int R = has_recent ? __builtin_amdgcn_readfirstlane(r_vec) : 0;
-    N = N < 0 ? 0 : (N > a.max_context ? a.max_context : N);
-    R = R < 0 ? 0 : (R > a.max_recent ? a.max_recent : R);
+    const auto clamp_to = [](int x, int most) { return x < 0 ? 0 : (x > most ? most : x); };
+    int N, R, S_job = 1;
+    if constexpr (BATCH != BATCH_NONE) {
+        const int n = clamp_to(n_vec, max_context), r = has_recent ? clamp_to(r_vec, max_recent) : 0;
+        int mine;
+        if constexpr (BATCH == BATCH_DEAL) {
+            const batch_job job = batch_deal(a.B, a.S, split, (uint32_t)n, (uint32_t)r, lane);
+            if (job.split >= job.S)
+                return;
+            split = job.split;
+            S_job = job.S;
+            mine = job.b;
+        } else {
+            mine = batch_order(a.B, b, (uint32_t)n, (uint32_t)r, lane);
+        }
+        N = __builtin_amdgcn_readlane(n, mine);
+        R = __builtin_amdgcn_readlane(r, mine);
+        if (mine != b) {
+            b = mine;
+            load_q();
+            // (waited for here: behind the join the compiler would wait in front of the code loads on every path)
+            asm volatile("" ::"v"(qraw));
+        }
+    } else {
+        N = clamp_to(__builtin_amdgcn_readfirstlane(n_vec), a.max_context);
+        R = has_recent ? clamp_to(__builtin_amdgcn_readfirstlane(r_vec), a.max_recent) : 0;
+    }
+    const int bkv = b * a.Hkv + hkv;
+    const int bh0 = b * a.Hq + hkv * a.G + g_first;  // first query head of this workgroup
     const uint32_t nblk = (uint32_t)(N + 63) >> 6;
     // live splits follow the length (at least 4 blocks or 16 recent rows each); the others leave before the images
     // are staged
     uint32_t want = nblk / 4u > (uint32_t)R / 16u ? nblk / 4u : (uint32_t)R / 16u;  // ... or 16 recent rows
-    if (a.B > 1 && a.S > 1) {  // ... and in a batch no more than the sequence's share of the compute units
+    if (BATCH == BATCH_NONE && a.B > 1 && a.S > 1) {  // ... and in a batch no more than the sequence's share of the compute units
         const uint32_t cap = live_split_cap(a, a.Hkv * a.n_sub, N + R, w_lane);
         want = want < cap ? want : cap;
     }
-    const int S = (int)(want < 1u ? 1u : (want < (uint32_t)S_grid ? want : (uint32_t)S_grid));
-    if (split >= S)
+    const int S = BATCH != BATCH_NONE ? S_job : (int)(want < 1u ? 1u : (want < (uint32_t)S_grid ? want : (uint32_t)S_grid));
+    if (BATCH == BATCH_NONE && split >= S)
         return;
     const int blk0 = (int)(nblk * (uint32_t)split / (uint32_t)S);
     const int blk1 = (int)(nblk * (uint32_t)(split + 1) / (uint32_t)S);
@@ -500,16 +532,30 @@ bool pq_config_uses_grouped_kernel(const pq_attn_config *cfg)
            pq_grouped_heads_per_workgroup(g) > 0;
 }
 
+template <int M, int BATCH>
+static hipError_t launch_grouped(const pq_decode_args &a, int units, hipStream_t s)
+{
+    const dim3 grid(units * a.S), block(GNW * 64);
+    if (a.n_sub == 1)
+        hipLaunchKernelGGL((pq_decode_grouped_kernel<true, M, BATCH>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((pq_decode_grouped_kernel<false, M, BATCH>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+template <int M> static hipError_t launch_grouped(const pq_decode_args &a, hipStream_t s)
+{
+    const int heads = a.Hkv * a.n_sub;
+    pq_decode_args aj = a;
+    aj.S = a.jobs > a.B ? a.jobs : 1;
+    if (a.jobs > a.B)
+        return launch_grouped<M, BATCH_DEAL>(aj, heads, s);
+    if (a.jobs > 0)
+        return launch_grouped<M, BATCH_ORDER>(aj, heads * a.B, s);
+    return launch_grouped<M, BATCH_NONE>(a, heads * a.B, s);
+}
+
 hipError_t pq_launch_decode_grouped(const pq_attn_ctx *ctx, const pq_decode_args &a, hipStream_t s)
 {
-    const int grid = a.B * a.Hkv * a.n_sub * a.S;
-    const bool once = a.n_sub == 1;
-    if (ctx->cfg.n_subspaces == 64) {
-        if (once) hipLaunchKernelGGL((pq_decode_grouped_kernel<true, 64>), dim3(grid), dim3(GNW * 64), 0, s, a);
-        else hipLaunchKernelGGL((pq_decode_grouped_kernel<false, 64>), dim3(grid), dim3(GNW * 64), 0, s, a);
-    } else {
-        if (once) hipLaunchKernelGGL((pq_decode_grouped_kernel<true, 32>), dim3(grid), dim3(GNW * 64), 0, s, a);
-        else hipLaunchKernelGGL((pq_decode_grouped_kernel<false, 32>), dim3(grid), dim3(GNW * 64), 0, s, a);
-    }
-    return hipGetLastError();
+    return ctx->cfg.n_subspaces == 64 ? launch_grouped<64>(a, s) : launch_grouped<32>(a, s);
 }

@@ -199,6 +199,94 @@ template <typename A> __device__ inline uint32_t live_split_cap(const A &a, int 
     return share >= 1.f ? (share < 64.f ? (uint32_t)share : 64u) : 1u;
 }
 
+// ---------------------------------------------------------------------------------------------------
+// Which workgroups a batch's sequences get ("0 = choose" splits, 2..64 sequences); every workgroup reads all lengths and
+// works it out in the same way.  Work is counted in 64-token blocks and 16 recent rows.
+//   BATCH_DEAL   (the head's share of the compute units is larger than the batch: that many workgroups per head)
+//       sequence b gets ceil(work / T) of them, T the smallest trial size whose sum fits, so that no workgroup has much
+//       more than its share, whatever the lengths (a fixed number of splits per sequence leaves the longest sequence's
+//       workgroups the last ones by far: 32 heads, three sequences of 30000, 15256 and 512 tokens 59.6 -> 39.1 us; 32
+//       query / 8 KV heads, eight sequences of 2.5K .. 20K: 33 -> 28 us).
+//   BATCH_ORDER  (one workgroup per sequence and head, more than one round of them on the chip but at most two) a head's
+//       longest sequences come first: a long one that starts in the second round would run alone (32 query / 8 KV heads,
+//       40 sequences of 200 .. 8000: 61 -> 49 us; 20 heads, 20 sequences of 100 .. 4096: 39.1 -> 36.9).  Ranking 64
+//       lengths and fetching the query behind them costs a workgroup 1.5 us, so lengths within a quarter of the first
+//       one's stay in their order, and with more rounds, where the last one matters less, nothing is ranked (32 heads,
+//       64 sequences of 3000 .. 4096: 181 us, ranked 190; of 97 .. 4001: 133 us, ranked 134).
+//   BATCH_NONE   splits per sequence as launched (one sequence, splits asked for, more than 64 sequences)
+// ---------------------------------------------------------------------------------------------------
+enum { BATCH_NONE = 0, BATCH_DEAL = 1, BATCH_ORDER = 2 };
+
+struct batch_job {
+    int b, split, S;  // sequence, split, splits of it (split >= S: nothing to do)
+};
+
+template <int CTRL, int ROWS> __device__ inline uint32_t dpp_add(uint32_t x)
+{
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+
+// running sum over the lanes (lane l: lanes 0 .. l)
+__device__ inline uint32_t wave_scan(uint32_t x)
+{
+    x = dpp_add<0x111, 0xf>(x);  // row_shr:1
+    x = dpp_add<0x112, 0xf>(x);  // row_shr:2
+    x = dpp_add<0x114, 0xf>(x);  // row_shr:4
+    x = dpp_add<0x118, 0xf>(x);  // row_shr:8
+    x = dpp_add<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    x = dpp_add<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// BATCH_DEAL: the sequence that job j has if all lengths are equal (its q is requested before the lengths are there)
+__device__ inline int batch_guess(uint32_t B, uint32_t jobs, uint32_t j)
+{
+    const uint32_t b = j / (jobs / B);
+    return (int)(b < B ? b : B - 1u);
+}
+
+__device__ inline uint32_t batch_work(uint32_t n, uint32_t r) { return ((n + 63u) >> 6) + ((r + 15u) >> 4); }
+
+// BATCH_DEAL: job j of `jobs` (n, r: clamped lengths of sequence `lane`; lanes beyond the batch: anything)
+__device__ inline batch_job batch_deal(int B, int jobs, int j, uint32_t n, uint32_t r, int lane)
+{
+    const bool in = lane < B;
+    const uint32_t work = in ? batch_work(n, r) : 0u;
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(work), 63);
+    // lane i tries T = 2^(i / 10.5) x the even share (at least 4 blocks): steps of 7 %, the last one 64 shares, which no
+    // sequence exceeds; in floats, the same in every workgroup
+    const float share = (float)total / (float)jobs;
+    const float least = share > 4.f ? share : 4.f;
+    const float inv = __builtin_amdgcn_rcpf(least * __builtin_amdgcn_exp2f((float)lane * (6.0f / 63.0f)));
+    uint32_t sum = 0;
+    for (int b = 0; b < B; ++b) {
+        const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)work, b);
+        sum += 1u + (uint32_t)((float)(w > 0u ? w - 1u : 0u) * inv);
+    }
+    const uint64_t fits = __builtin_amdgcn_ballot_w64(sum <= (uint32_t)jobs);
+    const float chosen = fits != 0 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv), __builtin_ctzll(fits))) : 0.f;
+    const uint32_t mine = in ? 1u + (uint32_t)((float)(work > 0u ? work - 1u : 0u) * chosen) : 0u;
+    const uint32_t upto = wave_scan(mine);
+    const uint32_t first = in ? upto - mine : ~0u;
+    const int b = __builtin_popcountll(__builtin_amdgcn_ballot_w64(first <= (uint32_t)j)) - 1;
+    return {b, j - __builtin_amdgcn_readlane((int)first, b), __builtin_amdgcn_readlane((int)mine, b)};
+}
+
+// BATCH_ORDER: the sequence of rank j by length (equal lengths by their number)
+__device__ inline int batch_order(int B, int j, uint32_t n, uint32_t r, int lane)
+{
+    const bool in = lane < B;
+    const uint32_t work = in ? batch_work(n, r) : 0u;  // below 2^21
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)work);
+    if (__builtin_amdgcn_ballot_w64(in && (work > w0 + w0 / 4u || work < w0 - w0 / 4u)) == 0)
+        return j;
+    const uint32_t key = in ? (work << 6) | (uint32_t)(63 - lane) : 0u;
+    uint32_t rank = 0;
+    for (int b = 0; b < B; ++b)
+        rank += (uint32_t)__builtin_amdgcn_readlane((int)key, b) > key ? 1u : 0u;
+    return (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(in && rank == (uint32_t)j));
+}
+
 // 16 code bytes of one lane.  Codes that are read once per launch are loaded with the
 // non-temporal hint: the stream then does not displace the tables and each other's lines in L2
 // and the memory-side cache, and HBM delivers markedly more (measured on the 8 x 32 heads x 32K

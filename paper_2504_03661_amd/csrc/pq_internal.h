@@ -114,6 +114,8 @@ struct pq_attn_ctx {
     float *scores12;
     bool grouped12;       // 12-bit context that runs the grouped-query kernel
     int n_cu;             // compute units of the device
+    int jobs;             // 8-bit contexts of 2..64 sequences with "0 = choose" splits: workgroups per head that the decode
+                          // kernel gives to the sequences by their lengths (= batch: one each); 0: splits per sequence
 };
 
 struct pq_decode_args {
@@ -131,6 +133,7 @@ struct pq_decode_args {
     int Gs;                // grouped-query kernels: the largest number of query heads a workgroup takes (2..4)
     int n_sub;             // ... and the sub-groups a KV head's G query heads are cut into: ceil(G / 4) groups whose
                            // sizes differ by at most one (7 = 4 + 3, 5 = 3 + 2, 10 = 4 + 3 + 3)
+    int jobs;              // pq_attn_ctx::jobs
     int max_context, max_recent;
     int n_cu;              // compute units of the device (the live split count of a batch's sequences follows it)
     int64_t head_stride;  // bytes of one (sequence, KV head) in a code tensor
