@@ -2,11 +2,9 @@
 // dimension setting, Section IV-A): nearest-centroid encode and the conversions between the logical
 // token-major form [B][Hkv][n][32] uint16 and the device layouts of pq_internal.h.
 //
-// Encode (Eq. 4 with Section II-C's nearest-centroid assignment) follows the 8-bit encode kernel: lane =
-// token, squared Euclidean distance decided in IEEE double as dist = fma(x_j - c_j, x_j - c_j, dist),
-// strict "<" on an ascending scan so that equal distances go to the lowest index.  A subspace's 4096
-// centroids, widened to double, take 128 KiB: they pass through LDS in four tiles of 1024.
-// Two 12-bit codes share bytes, so the kernel does not write the device layout itself: codes go to a
+// Encode (Eq. 4 with Section II-C's nearest-centroid assignment) decides as the 8-bit encode: squared Euclidean
+// distance in IEEE double as dist = fma(x_j - c_j, x_j - c_j, dist), equal distances to the lowest index.
+// Two 12-bit codes share bytes, so the kernel for many tokens does not write the device layout itself: codes go to a
 // token-major staging buffer and a second kernel packs them behind the current lengths, one thread per
 // 12-byte unit (a V unit holds 8 tokens of one subspace: the thread keeps the codes of tokens it does
 // not append).
@@ -15,12 +13,9 @@
 
 #include "pq_internal.h"
 #include "pq_device_utils.h"
-#include "pq_filter_constants.h"
+#include "pq_nearest_filter.h"
 
 namespace {
-
-constexpr int E12_WAVES = 4;
-constexpr int E12_TILE = 1024;  // centroids per LDS tile
 
 __device__ inline void pack8(const uint32_t (&c)[8], uint32_t (&w)[3])
 {
@@ -41,361 +36,264 @@ __device__ inline void unpack8(const uint32_t (&w)[3], uint32_t (&c)[8])
     c[7] = w[2] >> 20;
 }
 
-// One workgroup = (K or V, KV head, subspace) x 4 work items, one per wavefront; a work item is a 64-token
-// chunk of one sequence (the sequences of a batch share the head's codebook, so short appends of many
-// sequences still fill the workgroup).  x is [B][Hkv][x_head_stride >= n_new][d]; the codes of its first
-// n_new rows go to out [B][Hkv][n_new][32].
-__global__ __launch_bounds__(E12_WAVES * 64) void pq12_encode_kernel(const __half *x0, const __half *x1,
-                                                                    const __half *cb0, const __half *cb1,
-                                                                    uint16_t *out0, uint16_t *out1, int B, int Hkv,
-                                                                    int n_new, int groups_per_head, int64_t x_head_stride)
-{
-#pragma clang fp contract(off)
-    __shared__ double tile[E12_TILE * 4];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int which = blockIdx.z;  // 0: keys, 1: values
-    const int i = blockIdx.y;      // subspace
-    const int n_chunks = (n_new + 63) >> 6;
-    const int hkv = blockIdx.x / groups_per_head;
-    const int item = (blockIdx.x - hkv * groups_per_head) * E12_WAVES + wave;  // (sequence, chunk) of this wavefront
-    const int b = item / n_chunks;
-    const int chunk = item - b * n_chunks;
-    const int64_t head = (int64_t)b * Hkv + hkv;
-    const __half *x = which ? x1 : x0;
-    const __half *cb = (which ? cb1 : cb0) + ((int64_t)hkv * PQ12_M + i) * PQ12_CENTROIDS * 4;
-    uint16_t *out = which ? out1 : out0;
-
-    const int tok = chunk * 64 + lane;
-    const bool live = b < B && tok < n_new;
-    double xv[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        xv[j] = live ? (double)__half2float(x[(head * x_head_stride + tok) * PQ_HEAD_DIM + i * 4 + j]) : 0.0;
-
-    int best = 0;
-    double best_dist = __builtin_huge_val();
-    for (int t0 = 0; t0 < PQ12_CENTROIDS; t0 += E12_TILE) {
-        __syncthreads();  // the previous tile has been scanned by every wavefront
-        for (int e = tid; e < E12_TILE * 4; e += E12_WAVES * 64)
-            tile[e] = (double)__half2float(cb[t0 * 4 + e]);
-        __syncthreads();
-        for (int c = 0; c < E12_TILE; ++c) {
-            double dist = 0.0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double diff = xv[j] - tile[c * 4 + j];
-                dist = __builtin_fma(diff, diff, dist);
-            }
-            best = dist < best_dist ? t0 + c : best;  // ascending scan, strict "<": lowest index among equals
-            best_dist = __builtin_fmin(best_dist, dist);
-        }
-    }
-    if (live)
-        out[(head * n_new + tok) * PQ12_M + i] = (uint16_t)best;
-}
-
 // ---------------------------------------------------------------------------------------------------
-// The same codes with the matrix cores as a filter (see the 8-bit encode for the argument and the error bound;
-// here ds = 4, so an A row is (c_0 .. c_3) and (h, l, 0, 0), two matrix instructions per value quad, 6 fp32
-// adds).  A workgroup keeps the 4096 A rows of its (K or V, KV head, subspace) in LDS (64 KiB) and each of its 8
-// wavefronts takes up to NQ 64-token sub-chunks of the head's tokens over all sequences.  Pass 1: the minimum
-// of the 4096 computed values per token.  Pass 2: one bit per block of 16 centroids that holds a value
-// within tau of it (256 bits per token; the sign of the value once best + tau is folded into the C operand).
-// One or two marked blocks: their 16 or 32 centroids are evaluated in
-// the defining fp64 arithmetic, ascending, lowest index first; more: the lane walks all of its marked blocks the
-// same way.  A codebook whose |c|^2 / 2 leaves the fp16 range, or no marked block at all (non-finite values): the
-// sub-chunk runs the full fp64 scan.  About 1.1 vector instructions per (sub-vector, centroid)
-// instead of 11.
-// SPLIT (a head has at most 64 NQ tokens in the call — a decoding step of a batch): with one sub-chunk per
-// workgroup seven of its eight wavefronts would idle while one walks all 4096 centroids alone, each step waiting
-// out the latency of two dependent matrix instructions (17 tokens per head: 454 us).  Here all eight take the SAME
-// tokens and an eighth of the centroids each — 128 of the 1024 groups in pass 1, one of the eight 32-block mask
-// words in pass 2 — and exchange the per-token minimum and the mask words through LDS; the words are the ones the
-// unsplit walk computes, so the refinement (wavefront 0) and the codes are the same.
+// Codes of many tokens, with the matrix cores as a filter (pq_nearest_filter.h; the argument and the error bound are in
+// pq_encode.hip).  A workgroup keeps the 4096 A rows of its (K or V, KV head, subspace) in LDS (64 KiB) and each of its
+// 8 wavefronts takes 64-token chunks of the head's tokens over all sequences: 128 instructions of 32 centroids per 32
+// tokens.  The group of values here is the block of 16 that one instruction leaves in a lane; the 128 blocks of a lane
+// half form a grid of 16 rows and 8 columns, whose minima (24 numbers) name the blocks with a value near the smallest
+// one.  Nearly always that is one block: its 16 centroids are evaluated in the defining fp64 arithmetic.  Otherwise the
+// lane walks all blocks whose row and column are marked, and a codebook or token outside the bound's range the full fp64
+// scan.  Bound by vector-instruction issue: 9.5 per instruction and tile, some 2900 per 64 tokens and subspace, the
+// matrix instructions (256 x 32 cycles) in parallel.
+// SPLIT (a head has at most 128 tokens in the call — a decoding step of a batch): all eight wavefronts take the SAME
+// tokens and an eighth of the centroids each, keep their 16 block minima and exchange the smallest value and the
+// marked blocks (one word per token and wavefront) through LDS; wavefront 0 refines.
+// (16 x 32 heads x 64 tokens: 730 us with 4x4x4 instructions in two passes, 295 us now; 8192 tokens x 32
+// heads 5.57 -> 1.74 ms; 17 x 32 x 1, SPLIT, 80 -> 48 us.)
 // ---------------------------------------------------------------------------------------------------
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4e __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2e __attribute__((ext_vector_type(2)));
 
 constexpr int F12_WAVES = 8;  // wavefronts that share one set of A rows
+constexpr int F12_ROW = pq_filter_row_bytes<_Float16>();
 
-template <int NQ, bool SPLIT>
-__global__ __launch_bounds__(F12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void pq12_encode_fast_kernel(const __half *x0, const __half *x1,
-                                                                         const __half *cb0, const __half *cb1,
-                                                                         uint16_t *out0, uint16_t *out1, int B, int Hkv,
-                                                                         int n_new, int groups_per_head, int64_t x_head_stride)
+template <bool SPLIT>
+__global__ __launch_bounds__(F12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void pq12_encode_fast_kernel(
+    const __half *x0, const __half *x1, const __half *cb0, const __half *cb1, uint16_t *out0, uint16_t *out1, int B, int Hkv,
+    int n_new, int groups_per_head, int rounds, int64_t x_head_stride)
 {
 #pragma clang fp contract(off)
-    __shared__ __attribute__((aligned(16))) unsigned char arow[PQ12_CENTROIDS * 16];
-    __shared__ float red[2 * F12_WAVES + 1];
-    __shared__ uint32_t xchg[SPLIT ? F12_WAVES * NQ * 64 : 1];  // SPLIT: per wavefront, sub-chunk and token
+    __shared__ __attribute__((aligned(16))) unsigned char arow[PQ12_CENTROIDS * F12_ROW];
+    __shared__ uint32_t xchg[SPLIT ? F12_WAVES * 64 : 1];  // SPLIT: per wavefront and token
+    __shared__ int any_bad;
+    typedef pq_filter_token<4, _Float16> token;
+    typedef token::operand operand;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int which = blockIdx.z;  // 0: keys, 1: values
     const int i = blockIdx.y;      // subspace
     const int n_tok = B * n_new;   // tokens of one KV head over all sequences
+    const int n_chunks = (n_tok + 63) >> 6;
     const int hkv = blockIdx.x / groups_per_head;
-    // of 64 NQ tokens; SPLIT: the workgroup's eight wavefronts share one
-    const int chunk = SPLIT ? blockIdx.x - hkv * groups_per_head : (blockIdx.x - hkv * groups_per_head) * F12_WAVES + wave;
+    const int group = blockIdx.x - hkv * groups_per_head;
+    // SPLIT: the workgroup's eight wavefronts share the head's chunks; otherwise `rounds` chunks in a row each
+    const int chunk0 = SPLIT ? 0 : (group * F12_WAVES + wave) * rounds;
+    const int chunk1 = SPLIT ? n_chunks : (chunk0 + rounds < n_chunks ? chunk0 + rounds : n_chunks);
     const __half *x = which ? x1 : x0;
     const __half *cb = (which ? cb1 : cb0) + ((int64_t)hkv * PQ12_M + i) * PQ12_CENTROIDS * 4;
     uint16_t *out = which ? out1 : out0;
 
-    // ---- A rows of the 4096 centroids, their largest |c|^2 / 2 and coordinate
-    float n_max = 0.f, c_max = 0.f;
+    // ---- A rows of the 4096 centroids
+    if (tid == 0)
+        any_bad = 0;
+    __syncthreads();
     bool cb_bad = false;
     for (int c = tid; c < PQ12_CENTROIDS; c += F12_WAVES * 64) {
-        const u32x2e raw = *(const u32x2e *)(cb + c * 4);
-        const f16x4 v = __builtin_bit_cast(f16x4, raw);
-        float n = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float f = (float)v[j];
-            n += f * f;  // exact squares; the sum is rounded (covered by the bound)
-            c_max = fmaxf(c_max, fabsf(f));
-        }
-        const float h = 0.5f * n;
-        const _Float16 hh = (_Float16)h;
-        const _Float16 hl = (_Float16)(h - (float)hh);
-        cb_bad |= !(h < 60000.f);
-        n_max = fmaxf(n_max, h);
-        const f16x4 tail = {hh, hl, (_Float16)0.f, (_Float16)0.f};
-        *(f16x4 *)(arow + c * 16) = v;
-        *(f16x4 *)(arow + c * 16 + 8) = tail;
+        const f16x4 v = __builtin_bit_cast(f16x4, *(const u32x2e *)(cb + c * 4));
+        const _Float16 y[4] = {v[0], v[1], v[2], v[3]};
+        pq_filter_build_row<4>(y, 1.f, arow + c * F12_ROW, cb_bad);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        n_max = fmaxf(n_max, __shfl_xor(n_max, o));
-        c_max = fmaxf(c_max, __shfl_xor(c_max, o));
-    }
-    if (lane == 0) {
-        red[wave] = n_max;
-        red[F12_WAVES + wave] = __builtin_amdgcn_ballot_w64(cb_bad) != 0 ? -1.f : c_max;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < F12_WAVES; ++w) {
-        n_max = fmaxf(n_max, red[w]);
-        const float cw = red[F12_WAVES + w];
-        cb_bad |= cw < 0.f;
-        c_max = fmaxf(c_max, cw);
-    }
-    cb_bad = __builtin_amdgcn_ballot_w64(cb_bad) != 0;
     if (cb_bad)
-        c_max = 0.f;  // unused: every sub-chunk takes the full scan
+        any_bad = 1;
+    __syncthreads();
+    cb_bad = any_bad != 0;
 
-    // ---- this lane's tokens
-    bool live[NQ], bad[NQ];
-    f16x4 bop[NQ];
-    f32x4e off4[NQ];
-    float tau[NQ];
+    const unsigned char *my_row = arow + (lane & 31) * F12_ROW + (lane >> 5) * (F12_ROW / 2);
+    const auto block_min = [](const f32x16e &d) {
+        int b = min(__float_as_int(d[0]), __float_as_int(d[1]));
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int u = (chunk * NQ + q) * 64 + lane;
-        live[q] = u < n_tok;
-        const int uu = live[q] ? u : 0;
+        for (int k = 2; k < 16; k += 2)
+            b = min(min(b, __float_as_int(d[k])), __float_as_int(d[k + 1]));
+        return b;
+    };
+
+#pragma unroll 1
+    for (int chunk = chunk0; chunk < chunk1; ++chunk) {
+        const int u = chunk * 64 + lane;
+        const bool live = u < n_tok;
+        const int uu = live ? u : 0;
         const int b = uu / n_new;
         const int t = uu - b * n_new;
         // x is [B][Hkv][x_head_stride >= n_new][d]
-        const u32x2e raw = *(const u32x2e *)(x + ((((int64_t)b * Hkv + hkv) * x_head_stride + t) * PQ_HEAD_DIM + i * 4));
-        const f16x4 v = __builtin_bit_cast(f16x4, raw);
-        float x1s = 0.f, x2s = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float f = (float)v[j];
-            x1s += fabsf(f);
-            x2s += f * f;
-        }
-        u32x2e neg = raw ^ 0x80008000u;
-        asm volatile("" : "+v"(neg));  // keep the negated operand in its registers
-        bop[q] = __builtin_bit_cast(f16x4, neg);
-        const float t0 = n_max + x1s * c_max + PQ_FILTER_X2_FACTOR * x2s;
-        float off = PQ_FILTER_X2_FACTOR * x2s + 2.0f * (PQ_FILTER_TAU_REL * (2.0f * t0) + PQ_FILTER_TAU_ABS);
-        tau[q] = PQ_FILTER_TAU_REL * (t0 + off) + PQ_FILTER_TAU_ABS;
-        off += tau[q];
-        off4[q] = f32x4e{off, off, off, off};
-        bad[q] = cb_bad || !(off < 1.0e30f);
-    }
-    const f16x4 ones = {(_Float16)1.f, (_Float16)1.f, (_Float16)0.f, (_Float16)0.f};
-    const unsigned char *my_row = arow + (lane & 3) * 16;
-    auto values = [&](int m, int q) -> f32x4e {
-        const f16x4 A1 = *(const f16x4 *)(my_row + m * 64);
-        const f16x4 A2 = *(const f16x4 *)(my_row + m * 64 + 8);
-        return __builtin_amdgcn_mfma_f32_4x4x4f16(A2, ones, __builtin_amdgcn_mfma_f32_4x4x4f16(A1, bop[q], off4[q], 0, 0, 0), 0, 0, 0);
-    };
+        const f16x4 v = __builtin_bit_cast(
+            f16x4, *(const u32x2e *)(x + ((((int64_t)b * Hkv + hkv) * x_head_stride + t) * PQ_HEAD_DIM + i * 4)));
+        const _Float16 xv[4] = {v[0], v[1], v[2], v[3]};
+        token tok;
+        tok.set(xv, 1.f);
 
-    // ---- pass 1: smallest computed value per token (positive floats order like their bit patterns)
-    int best[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q)
-        best[q] = 0x7f800000;
-    constexpr int M_PER_WAVE = SPLIT ? PQ12_CENTROIDS / 4 / F12_WAVES : PQ12_CENTROIDS / 4;
-    const int m0 = SPLIT ? wave * M_PER_WAVE : 0;
-#pragma unroll 2
-    for (int m = m0; m < m0 + M_PER_WAVE; ++m) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const f32x4e d = values(m, q);
-            best[q] = min(min(best[q], __float_as_int(d[0])), __float_as_int(d[1]));
-            best[q] = min(min(best[q], __float_as_int(d[2])), __float_as_int(d[3]));
-        }
-    }
-    if (SPLIT) {  // the minimum over the eight wavefronts' shares
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-            xchg[(wave * NQ + q) * 64 + lane] = (uint32_t)best[q];
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-            for (int w = 0; w < F12_WAVES; ++w)
-                best[q] = min(best[q], (int)xchg[(w * NQ + q) * 64 + lane]);
-        __syncthreads();  // the words are written again below
-    }
-    // ---- pass 2: one bit per block of 16 centroids within tau of the minimum.  With off - (best + tau) in the C
-    // operand a computed value is negative exactly where it is a candidate: the OR of a block's 16 results carries
-    // that in its sign bit, which one v_alignbit shifts into the mask (block 32 wd + k lands in bit 31 - k).
-    uint32_t cand[NQ][8];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const float b = __int_as_float(best[q]);
-        bad[q] |= !(b > 0.f && b < 1.0e30f);
-        const float d = off4[q][0] - (b + tau[q]);
-        off4[q] = f32x4e{d, d, d, d};
-    }
-#pragma unroll
-    for (int wd = 0; wd < 8; ++wd) {
-        if (SPLIT && wd != wave)  // wave-uniform: this wavefront's word only
-            continue;
-        uint32_t bits[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-            bits[q] = 0u;
-#pragma unroll 1
-        for (int k = 0; k < 32; ++k) {  // block 32 wd + k: groups 4 (32 wd + k) .. + 3
-            uint32_t any[NQ];
-#pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                any[q] = 0u;
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    const f32x4e d = values(4 * (32 * wd + k) + g4, q);
-                    any[q] |= (__float_as_uint(d[0]) | __float_as_uint(d[1])) | (__float_as_uint(d[2]) | __float_as_uint(d[3]));
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                bits[q] = __builtin_amdgcn_alignbit(bits[q], any[q], 31);
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-            cand[q][wd] = bits[q];
-        if (SPLIT) {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                xchg[(wave * NQ + q) * 64 + lane] = bits[q];
-        }
-    }
-    if (SPLIT) {
-        __syncthreads();
-        if (wave != 0)
-            return;  // wavefront 0 refines and stores for the workgroup
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-            for (int wd = 0; wd < 8; ++wd)
-                cand[q][wd] = xchg[(wd * NQ + q) * 64 + lane];
-    }
-
-    // ---- refine / full scan, store
-    double xd[4];
-    auto exact = [&](int c, int &code, double &bd) {
-        const f16x4 v = *(const f16x4 *)(arow + c * 16);
-        double dist = 0.0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const double diff = xd[j] - (double)(float)v[j];
-            dist = __builtin_fma(diff, diff, dist);
-        }
-        code = dist < bd ? c : code;  // ascending callers, strict "<": the lowest index among equal distances stays
-        bd = __builtin_fmin(bd, dist);
-    };
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        // the token again (its registers were given up during the passes)
-        const int u = (chunk * NQ + q) * 64 + lane;
-        const int uu = live[q] ? u : 0;
-        const int b = uu / n_new;
-        const int t = uu - b * n_new;
-        {
-            const u32x2e raw = *(const u32x2e *)(x + ((((int64_t)b * Hkv + hkv) * x_head_stride + t) * PQ_HEAD_DIM + i * 4));
-            const f16x4 v = __builtin_bit_cast(f16x4, raw);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                xd[j] = (double)(float)v[j];
-        }
-        int cnt = 0, first = 0, last = 0;
-#pragma unroll
-        for (int wd = 7; wd >= 0; --wd) {
-            const uint32_t wbits = cand[q][wd];
-            cnt += __builtin_popcount(wbits);
-            first = wbits ? 32 * wd + __builtin_clz(wbits) : first;
-        }
-#pragma unroll
-        for (int wd = 0; wd < 8; ++wd) {
-            const uint32_t wbits = cand[q][wd];
-            last = wbits ? 32 * wd + 31 - __builtin_ctz(wbits) : last;
-        }
         int code = 0;
         double bd = __builtin_huge_val();
-        for (int k = 0; k < 16; ++k)
-            exact(16 * first + k, code, bd);
-        if (__builtin_amdgcn_ballot_w64(live[q] && cnt == 2) != 0) {  // wave-uniform; lanes with one block repeat it
-            for (int k = 0; k < 16; ++k)
-                exact(16 * last + k, code, bd);
-        }
-        // more than two marked blocks (a cluster of near-ties, a token far outside the codebook's range): this
-        // lane walks all of its marked blocks, ascending — the nearest centroid and every tie lie in them
-        const bool many = live[q] && !bad[q] && cnt > 2;
-        if (__builtin_amdgcn_ballot_w64(many) != 0) {  // wave-uniform
-            int code_m = 0;
-            double bd_m = __builtin_huge_val();
+        auto distance = [&](int c) {
+            const f16x4 y = *(const f16x4 *)(arow + c * F12_ROW);
+            double dist = 0.0;
 #pragma unroll
-            for (int wd = 0; wd < 8; ++wd) {
-                uint32_t wbits = many ? cand[q][wd] : 0u;
-                while (__builtin_amdgcn_ballot_w64(wbits != 0u) != 0) {  // block 32 wd + k sits in bit 31 - k
-                    const int k32 = wbits ? __builtin_clz(wbits) : 0;
-                    double bd_t = bd_m;
-                    int code_t = code_m;
-                    for (int k = 0; k < 16; ++k)
-                        exact(16 * (32 * wd + k32) + k, code_t, bd_t);
-                    if (wbits != 0u) {
-                        bd_m = bd_t;
-                        code_m = code_t;
+            for (int j = 0; j < 4; ++j) {
+                const double diff = (double)tok.x[j] - (double)(float)y[j];
+                dist = __builtin_fma(diff, diff, dist);
+            }
+            return dist;
+        };
+        // block m of lane half s: centroids c0 + 8 g + k, c0 = 32 m + 4 s, in ascending order; the smaller (distance,
+        // index) stays (strict "<" inside a block, but the blocks of the two halves interleave)
+        auto take_block = [&](int c0) {
+            double d = __builtin_huge_val();
+            int at = 0;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const double dist = distance(c0 + 8 * g + k);
+                    at = dist < d ? 8 * g + k : at;
+                    d = __builtin_fmin(d, dist);
+                }
+            at += c0;
+            const bool closer = (d < bd) | ((d == bd) & (at < code));
+            code = closer ? at : code;
+            bd = closer ? d : bd;
+        };
+
+        uint32_t words[8];     // word w: the marked blocks 16 w + k of half 0 (bit k) and half 1 (bit 16 + k)
+        bool many;             // this lane's token has several blocks to walk, in `words`
+        bool none;             // no mark at all
+        if constexpr (SPLIT) {
+            int blocks[2][16], low[2], limit[2];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const operand A = *(const operand *)(my_row + (16 * wave + k) * (32 * F12_ROW));
+#pragma unroll
+                for (int tile = 0; tile < 2; ++tile)
+                    blocks[tile][k] = block_min(tok.values(A, tile));
+            }
+#pragma unroll
+            for (int tile = 0; tile < 2; ++tile) {
+                low[tile] = blocks[tile][0];
+#pragma unroll
+                for (int k = 1; k < 16; ++k)
+                    low[tile] = min(low[tile], blocks[tile][k]);
+            }
+            int best = tok.best_of(low[0], low[1]);
+            xchg[wave * 64 + lane] = (uint32_t)best;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < F12_WAVES; ++w)
+                best = min(best, (int)xchg[w * 64 + lane]);
+            tok.limits(best, limit);
+            uint32_t word[2] = {0u, 0u};
+#pragma unroll
+            for (int tile = 0; tile < 2; ++tile)
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    word[tile] |= blocks[tile][k] <= limit[tile] ? 1u << k : 0u;
+            const auto halves = __builtin_amdgcn_permlane32_swap(word[0], word[1], false, false);
+            __syncthreads();  // every wavefront has read the minima
+            xchg[wave * 64 + lane] = halves[0] | (halves[1] << 16);
+            __syncthreads();
+            int count = 0, at = 0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                words[w] = xchg[w * 64 + lane];
+                count += __builtin_popcount(words[w]);
+                at = words[w] ? 32 * w + __builtin_ctz(words[w]) : at;
+            }
+            __syncthreads();  // ... and the words
+            many = count > 1;
+            none = count == 0;
+            if (wave == 0)  // wavefront 0 refines and stores for the workgroup
+                take_block(32 * (16 * (at >> 5) + (at & 15)) + ((at & 16) ? 4 : 0));
+        } else {
+            int by_row[2][16], by_col[2][8], limit[2];
+#pragma unroll
+            for (int tile = 0; tile < 2; ++tile)
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    by_col[tile][c] = 0x7f800000;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+#pragma unroll
+                for (int c = 0; c < 8; c += 2) {
+                    const operand A0 = *(const operand *)(my_row + (8 * r + c) * (32 * F12_ROW));
+                    const operand A1 = *(const operand *)(my_row + (8 * r + c + 1) * (32 * F12_ROW));
+#pragma unroll
+                    for (int tile = 0; tile < 2; ++tile) {
+                        const int m0 = block_min(tok.values(A0, tile));
+                        const int m1 = block_min(tok.values(A1, tile));
+                        by_row[tile][r] = c == 0 ? min(m0, m1) : min(min(by_row[tile][r], m0), m1);
+                        by_col[tile][c] = min(by_col[tile][c], m0);
+                        by_col[tile][c + 1] = min(by_col[tile][c + 1], m1);
                     }
-                    wbits &= ~(0x80000000u >> k32);
                 }
             }
-            if (many) {
-                code = code_m;
-                bd = bd_m;
+            int low[2];
+#pragma unroll
+            for (int tile = 0; tile < 2; ++tile) {
+                low[tile] = by_col[tile][0];
+#pragma unroll
+                for (int c = 1; c < 8; ++c)
+                    low[tile] = min(low[tile], by_col[tile][c]);
+            }
+            tok.limits(tok.best_of(low[0], low[1]), limit);
+            pq_filter_marks<16, 8> marks;
+#pragma unroll
+            for (int tile = 0; tile < 2; ++tile)
+                marks.add(tile, by_row[tile], by_col[tile], limit[tile]);
+            take_block(marks.index(256, 32, 4));
+            many = __builtin_amdgcn_inverse_ballot_w64(marks.several);
+            none = !__builtin_amdgcn_inverse_ballot_w64(marks.some);
+            if (marks.several != 0) {  // wave-uniform
+                const auto halves = __builtin_amdgcn_permlane32_swap(pq_filter_mark_word(by_row[0], by_col[0], limit[0]),
+                                                                     pq_filter_mark_word(by_row[1], by_col[1], limit[1]), false, false);
+#pragma unroll
+                for (int w = 0; w < 8; ++w) {  // rows 2 w and 2 w + 1
+                    words[w] = 0u;
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        const uint32_t cols = halves[s] & 0xffu, rows = (halves[s] >> (8 + 2 * w)) & 3u;
+                        words[w] |= ((rows & 1u ? cols : 0u) | (rows & 2u ? cols << 8 : 0u)) << (16 * s);
+                    }
+                }
             }
         }
-        const bool unsure = live[q] && (bad[q] || cnt < 1);
-        if (__builtin_amdgcn_ballot_w64(unsure) != 0) {  // wave-uniform: the defining scan for this sub-chunk
+        if (SPLIT && wave != 0)
+            continue;
+        const bool bad = cb_bad || tok.bad;
+        many = many && live && !bad;
+        if (__builtin_amdgcn_ballot_w64(many) != 0) {  // wave-uniform: every marked block of the lane's token
+            const int code_one = code;
+            const double bd_one = bd;
             code = 0;
             bd = __builtin_huge_val();
-            for (int c = 0; c < PQ12_CENTROIDS; ++c)
-                exact(c, code, bd);
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                uint32_t left = many ? words[w] : 0u;
+                while (__builtin_amdgcn_ballot_w64(left != 0u) != 0) {
+                    const int k = left ? __builtin_ctz(left) : 0;
+                    const int code_before = code;
+                    const double bd_before = bd;
+                    take_block(32 * (16 * w + (k & 15)) + ((k & 16) ? 4 : 0));
+                    if (left == 0u) {  // this lane had nothing left: keep what it had
+                        code = code_before;
+                        bd = bd_before;
+                    }
+                    left &= left - 1u;
+                }
+            }
+            if (!many) {
+                code = code_one;
+                bd = bd_one;
+            }
         }
-        if (live[q])
+        if (__builtin_amdgcn_ballot_w64(live && (bad || none)) != 0) {  // wave-uniform: the defining scan for this chunk
+            code = 0;
+            bd = __builtin_huge_val();
+            for (int c = 0; c < PQ12_CENTROIDS; ++c) {
+                const double dist = distance(c);
+                code = dist < bd ? c : code;  // ascending, strict "<": the lowest index among equal distances stays
+                bd = __builtin_fmin(bd, dist);
+            }
+        }
+        if (live)
             out[((((int64_t)b * Hkv + hkv) * n_new + t)) * PQ12_M + i] = (uint16_t)code;
     }
 }
@@ -412,8 +310,7 @@ __global__ __launch_bounds__(F12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
 // fields are disjoint, so the order of the workgroups does not matter.  Tokens beyond the capacity are not
 // written (the length update flags them).
 // ---------------------------------------------------------------------------------------------------
-constexpr int FEW12_TOKENS = 16;  // capacity of the kernel
-constexpr int FEW12_USED = 8;     // what the launcher gives it
+constexpr int FEW12_TOKENS = 4;  // tokens per head over all sequences
 constexpr int FEW12_WAVES = 16;
 
 __global__ __launch_bounds__(FEW12_WAVES * 64) void pq12_encode_few_kernel(const __half *x0, const __half *x1,
@@ -603,6 +500,30 @@ __global__ void pq12_unpack_kernel(const uint8_t *packed, uint16_t *token_major,
     token_major[x] = (uint16_t)((two >> (4 * (slot & 1))) & 0xfffu);
 }
 
+// codes of tensors 0 .. n_tensors - 1 (K and V, or samples alone) into out [B][Hkv][n_new][32]
+hipError_t launch_filter(const __half *x0, const __half *x1, const __half *cb0, const __half *cb1, uint16_t *out0, uint16_t *out1,
+                         int n_tensors, int B, int Hkv, int n_new, int64_t x_rows, hipStream_t s)
+{
+    const int64_t n_tok = (int64_t)B * n_new;  // of a head over all sequences
+    if (n_tok <= 128) {
+        // a decoding step of a batch: the head's one or two chunks, the centroids split over the workgroup's wavefronts
+        const dim3 grid((unsigned)Hkv, PQ12_M, (unsigned)n_tensors);
+        hipLaunchKernelGGL(pq12_encode_fast_kernel<true>, grid, dim3(F12_WAVES * 64), 0, s, x0, x1, cb0, cb1, out0, out1, B, Hkv,
+                           n_new, 1, 1, x_rows);
+    } else {
+        // up to 8 chunks in a row per wavefront while at least 1024 workgroups (two rounds of the chip) remain
+        const int64_t chunks = (n_tok + 63) / 64;
+        const int64_t groups1 = (chunks + F12_WAVES - 1) / F12_WAVES;
+        const int64_t most = Hkv * groups1 * PQ12_M * n_tensors / 1024;
+        const int rounds = (int)(most < 1 ? 1 : most > 8 ? 8 : most);
+        const int groups = (int)((chunks + F12_WAVES * rounds - 1) / (F12_WAVES * rounds));
+        const dim3 grid((unsigned)(Hkv * groups), PQ12_M, (unsigned)n_tensors);
+        hipLaunchKernelGGL(pq12_encode_fast_kernel<false>, grid, dim3(F12_WAVES * 64), 0, s, x0, x1, cb0, cb1, out0, out1, B, Hkv,
+                           n_new, groups, rounds, x_rows);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_pack(const pq_attn_ctx *ctx, int kind, const uint16_t *src, int n, uint8_t *dst, const int32_t *pos0,
                        hipStream_t s)
 {
@@ -645,9 +566,10 @@ hipError_t pq12_launch_encode_append(const pq_attn_ctx *ctx, const pq_encode_arg
                                      unsigned int *dev_err, hipStream_t s)
 {
     const int64_t n_tok = (int64_t)a.B * a.n_new;  // tokens of a head over all sequences
-    // measured, 32 heads, one new token per sequence: 1 sequence 17 us, 8 sequences 62 us with the kernel below
-    // (6.6 us per token: fp64 arithmetic); 17 .. 64 sequences 74 .. 82 us with the split filter kernel
-    if (n_tok <= FEW12_USED) {
+    // 32 heads, one new token per sequence, with the length reset and all launches: 1 sequence 21 us, 2 27 us, 4 39 us, 8
+    // 66 us with the kernel below (6.6 us per token: fp64 arithmetic); 44 .. 48 us for 1 .. 17 sequences with the split
+    // filter kernel
+    if (n_tok <= FEW12_TOKENS) {
         // a decoding step: encode and write the device layouts in one kernel, then the lengths
         hipLaunchKernelGGL(pq12_encode_few_kernel, dim3((unsigned)a.Hkv, PQ12_M, 2), dim3(FEW12_WAVES * 64), 0, s,
                            (const __half *)a.x[0], (const __half *)a.x[1], (const __half *)a.codebook[0],
@@ -657,42 +579,13 @@ hipError_t pq12_launch_encode_append(const pq_attn_ctx *ctx, const pq_encode_arg
         if (e != hipSuccess)
             return e;
         return pq_launch_bump_len(ctx_len, a.B, a.n_new, a.max_context, dev_err, s);
-    } else if (n_tok <= 128) {
-        // a decoding step of a batch: one sub-chunk per head, its centroids split over the workgroup's wavefronts
-        const dim3 grid((unsigned)a.Hkv, PQ12_M, 2);
-        if (n_tok > 64)
-            hipLaunchKernelGGL((pq12_encode_fast_kernel<2, true>), grid, dim3(F12_WAVES * 64), 0, s, (const __half *)a.x[0],
-                               (const __half *)a.x[1], (const __half *)a.codebook[0], (const __half *)a.codebook[1],
-                               ctx->stage[0], ctx->stage[1], a.B, a.Hkv, a.n_new, 1, x_rows);
-        else
-            hipLaunchKernelGGL((pq12_encode_fast_kernel<1, true>), grid, dim3(F12_WAVES * 64), 0, s, (const __half *)a.x[0],
-                               (const __half *)a.x[1], (const __half *)a.codebook[0], (const __half *)a.codebook[1],
-                               ctx->stage[0], ctx->stage[1], a.B, a.Hkv, a.n_new, 1, x_rows);
-    } else if (n_tok < ((int64_t)1 << 30)) {
-        // matrix-core filter: 8 wavefronts per workgroup, each takes 64 NQ tokens of the head
-        const int nq = n_tok > 64 * F12_WAVES ? 2 : 1;
-        const int groups_per_head = (int)((n_tok + 64 * nq * F12_WAVES - 1) / (64 * nq * F12_WAVES));
-        const dim3 grid((unsigned)(a.Hkv * groups_per_head), PQ12_M, 2);
-        if (nq == 2)
-            hipLaunchKernelGGL((pq12_encode_fast_kernel<2, false>), grid, dim3(F12_WAVES * 64), 0, s, (const __half *)a.x[0],
-                               (const __half *)a.x[1], (const __half *)a.codebook[0], (const __half *)a.codebook[1],
-                               ctx->stage[0], ctx->stage[1], a.B, a.Hkv, a.n_new, groups_per_head, x_rows);
-        else
-            hipLaunchKernelGGL((pq12_encode_fast_kernel<1, false>), grid, dim3(F12_WAVES * 64), 0, s, (const __half *)a.x[0],
-                               (const __half *)a.x[1], (const __half *)a.codebook[0], (const __half *)a.codebook[1],
-                               ctx->stage[0], ctx->stage[1], a.B, a.Hkv, a.n_new, groups_per_head, x_rows);
-    } else {
-        const int n_chunks = (a.n_new + 63) >> 6;
-        const int groups_per_head = (a.B * n_chunks + E12_WAVES - 1) / E12_WAVES;
-        const dim3 grid((unsigned)(a.Hkv * groups_per_head), PQ12_M, 2);
-        hipLaunchKernelGGL(pq12_encode_kernel, grid, dim3(E12_WAVES * 64), 0, s, (const __half *)a.x[0],
-                           (const __half *)a.x[1], (const __half *)a.codebook[0], (const __half *)a.codebook[1],
-                           ctx->stage[0], ctx->stage[1], a.B, a.Hkv, a.n_new, groups_per_head, x_rows);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    e = launch_pack(ctx, PQ_CODES_K, ctx->stage[0], a.n_new, a.codes[0], a.ctx_len, s);
+    const hipError_t enc = launch_filter((const __half *)a.x[0], (const __half *)a.x[1], (const __half *)a.codebook[0],
+                                         (const __half *)a.codebook[1], ctx->stage[0], ctx->stage[1], 2, a.B, a.Hkv, a.n_new,
+                                         x_rows, s);
+    if (enc != hipSuccess)
+        return enc;
+    hipError_t e = launch_pack(ctx, PQ_CODES_K, ctx->stage[0], a.n_new, a.codes[0], a.ctx_len, s);
     if (e != hipSuccess)
         return e;
     e = launch_pack(ctx, PQ_CODES_V, ctx->stage[1], a.n_new, a.codes[1], a.ctx_len, s);
@@ -757,11 +650,11 @@ hipError_t pq12_launch_kmeans(const pq_attn_ctx *ctx, const void *samples, int n
         for (int c0 = 0; c0 < n_samples; c0 += KM12_CHUNK) {
             const int nc = n_samples - c0 < KM12_CHUNK ? n_samples - c0 : KM12_CHUNK;
             const __half *x = (const __half *)samples + (int64_t)c0 * PQ_HEAD_DIM;
-            // assignment = the encode's matrix-core filter (one sequence, grid.z = 1: only the first pointers are used)
-            const int groups_per_head = (nc + 128 * F12_WAVES - 1) / (128 * F12_WAVES);
-            hipLaunchKernelGGL((pq12_encode_fast_kernel<2, false>), dim3((unsigned)(Hkv * groups_per_head), PQ12_M, 1),
-                               dim3(F12_WAVES * 64), 0, s, x, x, (const __half *)codebook, (const __half *)codebook, codes,
-                               codes, 1, Hkv, nc, groups_per_head, (int64_t)n_samples);
+            // assignment = the encode's matrix-core filter (one sequence, one tensor)
+            e = launch_filter(x, x, (const __half *)codebook, (const __half *)codebook, codes, codes, 1, 1, Hkv, nc,
+                              (int64_t)n_samples, s);
+            if (e != hipSuccess)
+                return e;
             const int64_t total = (int64_t)Hkv * nc * PQ12_M;
             hipLaunchKernelGGL(pq12_kmeans_accumulate_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, x, codes,
                                sums, counts, (int64_t)n_samples, nc, total);

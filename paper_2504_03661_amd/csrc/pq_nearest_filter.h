@@ -73,29 +73,25 @@ __device__ inline void pq_filter_build_row(const T (&c)[DS], const float scale, 
     __builtin_memcpy(arow_c, row, pq_filter_row_bytes<T>());
 }
 
-// code of this lane's token (xin: its sub-vector; a dead lane passes any finite values and live = false).
-// `coord`: the centroids' coordinates as W (double, float, or _Float16 = inside the fp16 A rows)
-template <int DS, typename T, typename W>
-__device__ inline int pq_filter_code(const unsigned char *arow, const unsigned char *coord, const float scale, const bool cb_bad,
-                                     const T (&xin)[DS], const bool live)
-{
-#pragma clang fp contract(off)
-    constexpr bool F16 = sizeof(T) == 2;
-    constexpr int ROW = pq_filter_row_bytes<T>();
-    constexpr int STRIDE = sizeof(W) == 2 ? ROW : DS * (int)sizeof(W);  // of a centroid's coordinates
-    constexpr float TAU_NEAR = F16 ? PQ_FILTER_TAU_NEAR : PQ_FILTER_TAU_NEAR_F32;
+// What the matrix instruction and the refinement need of this lane's token
+template <int DS, typename T> struct pq_filter_token {
+    static constexpr bool F16 = sizeof(T) == 2;
+    static constexpr float TAU_NEAR = F16 ? PQ_FILTER_TAU_NEAR : PQ_FILTER_TAU_NEAR_F32;
     typedef typename std::conditional<F16, f16x4, f16x8>::type operand;
-    const int lane = threadIdx.x & 63;
-    bool bad = cb_bad;
-    double xd[DS];
-    float tau_x;
-    operand bop[2];  // the columns of tokens 0..31 and 32..63
+    operand col[2];  // the columns of tokens 0..31 and 32..63 of the wavefront
+    float x[DS];  // (widened where it is used)
+    float tau_x;  // the token's share of tau
+    bool bad;     // outside the range that the bound covers
+
+    // xin: the token's sub-vector (fp32: unscaled)
+    __device__ __forceinline__ void set(const T (&xin)[DS], const float scale)
     {
+#pragma clang fp contract(off)
         float x2 = 0.f, xs[DS];
 #pragma unroll
         for (int j = 0; j < DS; ++j) {
-            xd[j] = (double)(float)xin[j];
-            xs[j] = F16 ? (float)xin[j] : (float)xin[j] * scale;
+            x[j] = (float)xin[j];
+            xs[j] = F16 ? x[j] : x[j] * scale;
             x2 = __builtin_fmaf(xs[j], xs[j], x2);
         }
         // off: |x|^2/2 with half a per cent on top and a floor, so that every computed value stays above zero, rounded
@@ -104,12 +100,13 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
         const float off = __builtin_fmaf(PQ_FILTER_X2_FACTOR, x2, 3.0f * PQ_FILTER_TAU_ABS);
         const float up = __builtin_fmaf(off, 1.003f, 6.0e-8f);
         tau_x = __builtin_fmaf(TAU_NEAR, x2, PQ_FILTER_TAU_ABS);
+        bad = false;
         _Float16 o0 = (_Float16)up, o1 = (_Float16)0.f;
         if (__builtin_amdgcn_ballot_w64(!(off < 60000.f)) != 0) {  // wave-uniform, rare: (scaled) length beyond 340
             const bool large = !(off < 60000.f);
             o0 = large ? (_Float16)0.f : o0;
             o1 = large ? (_Float16)(up * (1.0f / 32768.f)) : (_Float16)0.f;
-            bad |= !(off < 2.0e9f);
+            bad = !(off < 2.0e9f);
         }
         const _Float16 one = (_Float16)1.f, zero = (_Float16)0.f;
         operand lo, hi;
@@ -146,21 +143,147 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
             b0[k] = s[0];
             b1[k] = s[1];
         }
-        bop[0] = __builtin_bit_cast(operand, b0);
-        bop[1] = __builtin_bit_cast(operand, b1);
+        col[0] = __builtin_bit_cast(operand, b0);
+        col[1] = __builtin_bit_cast(operand, b1);
     }
-    auto values = [&](const operand &A, const operand &B) -> f32x16e {
+
+    // 32 computed values of each of 32 tokens: lane l ends with those of token l mod 32 of the tile whose centroids lie
+    // in its half: rows 8 g + 4 (l / 32) + 0..3 of A in registers 4 g .. 4 g + 3 ("quad" g)
+    __device__ __forceinline__ f32x16e values(const operand &A, const int tile) const
+    {
         const f32x16e none = {};
         if constexpr (F16)
-            return __builtin_amdgcn_mfma_f32_32x32x8f16(A, B, none, 0, 0, 0);
+            return __builtin_amdgcn_mfma_f32_32x32x8f16(A, col[tile], none, 0, 0, 0);
         else
-            return __builtin_amdgcn_mfma_f32_32x32x16_f16(A, B, none, 0, 0, 0);
-    };
+            return __builtin_amdgcn_mfma_f32_32x32x16_f16(A, col[tile], none, 0, 0, 0);
+    }
 
-    // ---- the 256 computed values of every token, 32 centroids per instruction.  Lane l ends with those of token
-    // l mod 32 of the tile whose centroids lie in its half: 32 m + 8 g + 4 (l / 32) + 0..3 in registers 4 g .. 4 g + 3
-    // ("quad" (m, g)).  Kept are the minima over g per m and over m per g (positive floats order like their bit
-    // patterns): 12 numbers that name every quad with a value near the smallest one without a second pass.
+    // The smallest value of this lane's token from the smallest of either tile in this lane; and what every value
+    // within tau of it does not exceed, for both tiles.  (Positive floats order like their bit patterns.)
+    __device__ inline int best_of(const int b0, const int b1) const
+    {
+        const auto s = __builtin_amdgcn_permlane32_swap(b0, b1, false, false);
+        return min((int)s[0], (int)s[1]);
+    }
+    __device__ __forceinline__ void limits(const int best_bits, int (&limit)[2])
+    {
+        const float best = __int_as_float(best_bits);
+        bad |= !(best > 0.f && best < 1.0e30f);  // the offset did not keep the values positive and finite
+        // best + tau, tau = TAU_NEAR (|x|^2 + best) + TAU_ABS
+        const int lim = __float_as_int(__builtin_fmaf(best, 1.0f + TAU_NEAR, tau_x));
+        const auto r = __builtin_amdgcn_permlane32_swap(lim, lim, false, false);
+        limit[0] = (int)r[0];
+        limit[1] = (int)r[1];
+    }
+};
+
+// Which minima of a token lie within tau of its best value, as masks over the 64 tokens in scalar registers.  Per tile,
+// NR row minima and NC column minima of a grid of value groups stand in every lane; a group can hold such a value only
+// if both its row and its column are marked.  One comparison per minimum leaves a mask over the lanes (bits 0..31: the
+// tile's tokens against the centroids of lane half 0, bits 32..63: half 1); what follows per mark is scalar work beside
+// the other wavefronts' vector instructions: the bits of the marked indices (right where one is marked) and which tokens
+// have a second mark.
+template <int NR, int NC> struct pq_filter_marks {
+    static constexpr int RB = __builtin_ctz(NR), CB = __builtin_ctz(NC);
+    uint64_t bit_r[RB], bit_c[CB];             // bit k of the marked row / column
+    uint64_t some = 0, in_half1 = 0, several = 0;  // any mark; in lane half 1; more than one group possible
+
+    __device__ inline pq_filter_marks()
+    {
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+            bit_r[k] = 0;
+#pragma unroll
+        for (int k = 0; k < CB; ++k)
+            bit_c[k] = 0;
+    }
+    __device__ __forceinline__ void add(const int t, const int (&by_r)[NR], const int (&by_c)[NC], const int limit)
+    {
+        uint64_t ones = 0, ones_c = 0, twos = 0, of_r[RB], of_c[CB];
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+            of_r[k] = 0;
+#pragma unroll
+        for (int k = 0; k < CB; ++k)
+            of_c[k] = 0;
+#pragma unroll
+        for (int m = 0; m < NR; ++m) {
+            const uint64_t a = __builtin_amdgcn_ballot_w64(by_r[m] <= limit);
+            twos |= ones & a;
+            ones |= a;
+#pragma unroll
+            for (int k = 0; k < RB; ++k)
+                of_r[k] |= (m >> k) & 1 ? a : 0;
+        }
+#pragma unroll
+        for (int g = 0; g < NC; ++g) {
+            const uint64_t a = __builtin_amdgcn_ballot_w64(by_c[g] <= limit);
+            twos |= ones_c & a;
+            ones_c |= a;
+#pragma unroll
+            for (int k = 0; k < CB; ++k)
+                of_c[k] |= (g >> k) & 1 ? a : 0;
+        }
+        const auto either = [&](uint64_t a) { return (uint64_t)((uint32_t)a | (uint32_t)(a >> 32)) << (32 * t); };
+        ones &= ones_c;
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+            bit_r[k] |= either(of_r[k]);
+#pragma unroll
+        for (int k = 0; k < CB; ++k)
+            bit_c[k] |= either(of_c[k]);
+        some |= either(ones);
+        in_half1 |= (uint64_t)(uint32_t)(ones >> 32) << (32 * t);
+        several |= (uint64_t)((uint32_t)twos | (uint32_t)(twos >> 32) | ((uint32_t)ones & (uint32_t)(ones >> 32))) << (32 * t);
+    }
+    // row_step x the token's marked row + col_step x its column + half_step x its half (steps: powers of two)
+    __device__ __forceinline__ int index(const int row_step, const int col_step, const int half_step) const
+    {
+        const auto bit = [](uint64_t mask, int value) { return __builtin_amdgcn_inverse_ballot_w64(mask) ? value : 0; };
+        int c = bit(in_half1, half_step);
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+            c |= bit(bit_r[k], row_step << k);
+#pragma unroll
+        for (int k = 0; k < CB; ++k)
+            c |= bit(bit_c[k], col_step << k);
+        return c;
+    }
+};
+
+// the same marks of one tile as a word per lane, for the rare walk over several groups: bit g a mark of by_c[g], bit
+// NC + m one of by_r[m]
+template <int NR, int NC>
+__device__ inline uint32_t pq_filter_mark_word(const int (&by_r)[NR], const int (&by_c)[NC], int limit)
+{
+    asm volatile("" : "+v"(limit));  // (keeps these selects inside the branch they are used in)
+    uint32_t w = 0;
+#pragma unroll
+    for (int m = 0; m < NR; ++m)
+        w |= by_r[m] <= limit ? 1u << (NC + m) : 0u;
+#pragma unroll
+    for (int g = 0; g < NC; ++g)
+        w |= by_c[g] <= limit ? 1u << g : 0u;
+    return w;
+}
+
+// code of this lane's token among 256 centroids (xin: its sub-vector; a dead lane passes any finite values and live =
+// false).  `coord`: the centroids' coordinates as W (double, float, or _Float16 = inside the fp16 A rows)
+template <int DS, typename T, typename W>
+__device__ __forceinline__ int pq_filter_code(const unsigned char *arow, const unsigned char *coord, const float scale, const bool cb_bad,
+                                     const T (&xin)[DS], const bool live)
+{
+#pragma clang fp contract(off)
+    typedef pq_filter_token<DS, T> token;
+    typedef typename token::operand operand;
+    constexpr int ROW = pq_filter_row_bytes<T>();
+    constexpr int STRIDE = sizeof(W) == 2 ? ROW : DS * (int)sizeof(W);  // of a centroid's coordinates
+    const int lane = threadIdx.x & 63;
+    token tok;
+    tok.set(xin, scale);
+
+    // ---- the 256 computed values of every token, 32 centroids per instruction m.  Kept are the minima over the quads g
+    // per m and over m per g: 12 numbers that name every quad with a value near the smallest one without a second pass.
     int by_m[2][8], by_g[2][4];
     const unsigned char *my_row = arow + (lane & 31) * ROW + (lane >> 5) * (ROW / 2);
 #pragma unroll
@@ -174,8 +297,8 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
         const operand A1 = *(const operand *)(my_row + (m + 1) * (32 * ROW));
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const f32x16e d0 = values(A0, bop[t]);
-            const f32x16e d1 = values(A1, bop[t]);
+            const f32x16e d0 = tok.values(A0, t);
+            const f32x16e d1 = tok.values(A1, t);
             int q0[4], q1[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -192,62 +315,16 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
             by_m[t][m + 1] = min(min(min(q1[0], q1[1]), q1[2]), q1[3]);
         }
     }
-    // the smallest value of each token (its two lane halves together), and the threshold back to both halves
-    int limit[2];
-    {
-        int b[2];
+    int b[2], limit[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-            b[t] = min(min(min(by_g[t][0], by_g[t][1]), by_g[t][2]), by_g[t][3]);
-        const auto s = __builtin_amdgcn_permlane32_swap(b[0], b[1], false, false);
-        const float best = __int_as_float(min((int)s[0], (int)s[1]));
-        bad |= !(best > 0.f && best < 1.0e30f);  // the offset did not keep the values positive and finite
-        // best + tau, tau = TAU_NEAR (|x|^2 + best) + TAU_ABS
-        const int lim = __float_as_int(__builtin_fmaf(best, 1.0f + TAU_NEAR, tau_x));
-        const auto r = __builtin_amdgcn_permlane32_swap(lim, lim, false, false);
-        limit[0] = (int)r[0];
-        limit[1] = (int)r[1];
-    }
-    // Marks: which minima lie within tau of the best.  A quad can hold such a value only if both its by_m and its
-    // by_g minimum are marked.  One comparison per minimum leaves a mask over the lanes (bits 0..31: the tile's tokens
-    // against the centroids of lane half 0, bits 32..63: half 1) in scalar registers; what follows per mark is scalar
-    // work beside the other wavefronts' vector instructions: the bits of the marked indices (right where one is
-    // marked) and which lanes have a second mark.
-    uint64_t bit_m[3] = {0, 0, 0}, bit_g[2] = {0, 0};  // masks over the 64 tokens from here on
-    uint64_t some = 0, in_half1 = 0, several = 0;
+    for (int t = 0; t < 2; ++t)
+        b[t] = min(min(min(by_g[t][0], by_g[t][1]), by_g[t][2]), by_g[t][3]);
+    tok.limits(tok.best_of(b[0], b[1]), limit);
+    const bool bad = tok.bad || cb_bad;
+    pq_filter_marks<8, 4> marks;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        uint64_t ones = 0, ones_g = 0, twos = 0, of_m[3] = {0, 0, 0}, of_g[2] = {0, 0};
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const uint64_t a = __builtin_amdgcn_ballot_w64(by_m[t][m] <= limit[t]);
-            twos |= ones & a;
-            ones |= a;
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                of_m[k] |= (m >> k) & 1 ? a : 0;
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const uint64_t a = __builtin_amdgcn_ballot_w64(by_g[t][g] <= limit[t]);
-            twos |= ones_g & a;
-            ones_g |= a;
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                of_g[k] |= (g >> k) & 1 ? a : 0;
-        }
-        const auto either = [&](uint64_t a) { return (uint64_t)((uint32_t)a | (uint32_t)(a >> 32)) << (32 * t); };
-        ones &= ones_g;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            bit_m[k] |= either(of_m[k]);
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            bit_g[k] |= either(of_g[k]);
-        some |= either(ones);
-        in_half1 |= (uint64_t)(uint32_t)(ones >> 32) << (32 * t);
-        several |= (uint64_t)((uint32_t)twos | (uint32_t)(twos >> 32) | ((uint32_t)ones & (uint32_t)(ones >> 32))) << (32 * t);
-    }
+    for (int t = 0; t < 2; ++t)
+        marks.add(t, by_m[t], by_g[t], limit[t]);
 
     // ---- refine: the defining arithmetic on the marked quads, ascending
     int code = 0;
@@ -266,7 +343,7 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
         coordinates(coord + c * STRIDE, y);
 #pragma unroll
         for (int j = 0; j < DS; ++j) {
-            const double diff = xd[j] - y[j];
+            const double diff = (double)tok.x[j] - y[j];
             dist = __builtin_fma(diff, diff, dist);
         }
         code = dist < bd ? c : code;  // strict: the lowest index among equal distances stays
@@ -275,9 +352,7 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
     // nearly always one quad is marked, in one of the halves: (m, g) of half s is centroids 32 m + 8 g + 4 s .. + 3
     // (where several are, the sum below is some quad's index all the same)
     {
-        const auto bit = [](uint64_t mask, int value) { return __builtin_amdgcn_inverse_ballot_w64(mask) ? value : 0; };
-        const int c0 = bit(bit_m[0], 32) | bit(bit_m[1], 64) | bit(bit_m[2], 128) | bit(bit_g[0], 8) | bit(bit_g[1], 16) |
-                       bit(in_half1, 4);
+        const int c0 = marks.index(32, 8, 4);
         const unsigned char *quad = coord + c0 * STRIDE;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -285,7 +360,7 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
             coordinates(quad + k * STRIDE, y);
 #pragma unroll
             for (int j = 0; j < DS; ++j) {
-                const double diff = xd[j] - y[j];
+                const double diff = (double)tok.x[j] - y[j];
                 dist = __builtin_fma(diff, diff, dist);
             }
             code = k > 0 && dist < bd ? k : code;
@@ -295,23 +370,11 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
     }
     // several (ties, near-ties, a token far outside the codebook's range): the lane walks every quad whose two bits
     // are set — quad (m, g) of half s is centroids 4 (8 m + 2 g + s) .. + 3
-    several &= __builtin_amdgcn_ballot_w64(live && !bad);
+    const uint64_t several = marks.several & __builtin_amdgcn_ballot_w64(live && !bad);
     if (several != 0) {  // wave-uniform
         const bool mine = __builtin_amdgcn_inverse_ballot_w64(several);
-        uint32_t w[2];  // per tile: bit g a mark of by_g, bit 4 + m one of by_m
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            int lim = limit[t];
-            asm volatile("" : "+v"(lim));  // (keeps these selects inside the branch)
-            w[t] = 0;
-#pragma unroll
-            for (int m = 0; m < 8; ++m)
-                w[t] |= by_m[t][m] <= lim ? 16u << m : 0u;
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                w[t] |= by_g[t][g] <= lim ? 1u << g : 0u;
-        }
-        const auto halves = __builtin_amdgcn_permlane32_swap(w[0], w[1], false, false);  // of this lane's token
+        const auto halves = __builtin_amdgcn_permlane32_swap(pq_filter_mark_word(by_m[0], by_g[0], limit[0]),
+                                                             pq_filter_mark_word(by_m[1], by_g[1], limit[1]), false, false);
         uint64_t left = 0;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -341,7 +404,7 @@ __device__ inline int pq_filter_code(const unsigned char *arow, const unsigned c
         if (!mine)
             code = code_one;
     }
-    const uint64_t unsure = __builtin_amdgcn_ballot_w64(live && bad) | (__builtin_amdgcn_ballot_w64(live) & ~some);
+    const uint64_t unsure = __builtin_amdgcn_ballot_w64(live && bad) | (__builtin_amdgcn_ballot_w64(live) & ~marks.some);
     if (unsure != 0) {  // wave-uniform: the defining scan for this sub-chunk
         code = 0;
         bd = __builtin_huge_val();
