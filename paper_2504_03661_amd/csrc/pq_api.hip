@@ -137,9 +137,15 @@ int choose_splits(const pq_attn_config *c, int n_cu)
     return (int)s;
 }
 
-// Workgroups per head (KV head and sub-group in the grouped-query kernel) of a batch whose splits are left to the
-// library, given to the sequences by their lengths: the head's share of the compute units if that is more than one per
-// sequence, one per sequence if the batch makes between one and two rounds of the chip (pq_device_utils.h).
+// How the workgroups of a batch whose splits are left to the library follow its sequences' lengths (pq_device_utils.h has
+// the ways and what they measured), from the head's share of the compute units (a head being a KV head's sub-group in the
+// grouped-query kernel):
+//   share > batch    positive, > batch: that many workgroups per head, dealt out (BATCH_DEAL)
+//   share < batch    negative: - workgroups per head that walk the sequences (BATCH_WALK): the per-head fp16 kernel of
+//                    64 subspaces (the 16-wavefront kernel of 32 has no registers for it: 55 -> 87 us), where whole
+//                    shares fill at least 92 % of the chip; else = batch: one each, the longest first (BATCH_ORDER),
+//                    up to two rounds of the chip
+//   otherwise        0
 int choose_jobs(const pq_attn_config *c, int n_cu)
 {
     if (c->batch < 2 || c->batch > 64 || c->n_splits != 0 || pq_config_is_12bit(c))
@@ -148,7 +154,13 @@ int choose_jobs(const pq_attn_config *c, int n_cu)
                               ? (int64_t)c->n_kv_heads * pq_grouped_sub_groups(c->n_q_heads / c->n_kv_heads)
                               : c->n_q_heads;
     const int64_t share = n_cu / heads < PQ_MAX_SPLITS ? n_cu / heads : PQ_MAX_SPLITS;
-    return share > c->batch ? (int)share : (share < c->batch && c->batch <= 2 * share ? c->batch : 0);
+    if (share > c->batch)
+        return (int)share;
+    if (share == c->batch)
+        return 0;
+    if (c->dtype == PQ_F16 && c->n_subspaces == 64 && c->n_q_heads == c->n_kv_heads && share * heads * 100 >= (int64_t)n_cu * 92)
+        return -(int)share;
+    return c->batch <= 2 * share ? c->batch : 0;
 }
 
 // Codebook pointers passed to an entry point are registered there and then: the context copies them on the

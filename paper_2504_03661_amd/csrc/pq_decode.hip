@@ -83,10 +83,12 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     uint32_t unit, split_u;
     unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
     int split = (int)split_u;
-    const uint32_t bkv = unit / (uint32_t)a.G;          // hkv * B + b (BATCH_DEAL: hkv)
+    const uint32_t bkv = unit / (uint32_t)a.G;          // hkv * B + b (BATCH_DEAL, BATCH_WALK: hkv)
     const int gq = (int)(unit - bkv * (uint32_t)a.G);
-    const int hkv = BATCH == BATCH_DEAL ? (int)bkv : (int)(bkv / (uint32_t)a.B);
-    int b = BATCH == BATCH_DEAL ? batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u) : (int)(bkv - (uint32_t)hkv * (uint32_t)a.B);
+    const int hkv = BATCH == BATCH_DEAL || BATCH == BATCH_WALK ? (int)bkv : (int)(bkv / (uint32_t)a.B);
+    int b = BATCH == BATCH_WALK   ? split
+            : BATCH == BATCH_DEAL ? batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u)
+                                  : (int)(bkv - (uint32_t)hkv * (uint32_t)a.B);
     const int hq = hkv * a.G + gq;
 
     // The lengths are requested first and taken out of their registers only after the table loads
@@ -118,11 +120,14 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     const char *kcb = (const char *)a.kcb_packed + (int64_t)hkv * 256 * PQ_HEAD_DIM * sizeof(T);
     u32x4 kraw[PASSES][NV];
     u32x4 qraw[NV];  // the query elements of columns 4g .. 4g+3 (converted after the barrier)
+    auto load_kraw = [&](const int row0) {
 #pragma unroll
-    for (int k = 0; k < PASSES; ++k)
+        for (int k = 0; k < PASSES; ++k)
 #pragma unroll
-        for (int v = 0; v < NV; ++v)
-            kraw[k][v] = *(const u32x4 *)(kcb + ((row0 + k * ROWS_PER_PASS) * PQ_HEAD_DIM + e0) * sizeof(T) + v * 16);
+            for (int v = 0; v < NV; ++v)
+                kraw[k][v] = *(const u32x4 *)(kcb + ((row0 + k * ROWS_PER_PASS) * PQ_HEAD_DIM + e0) * sizeof(T) + v * 16);
+    };
+    load_kraw(row0);
     u32x4 vraw[VPT];
     if (F16) {
         const u32x4 *src = (const u32x4 *)((const __half *)a.vcb_packed + (int64_t)hkv * 256 * PQ_HEAD_DIM);
@@ -140,6 +145,7 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
 
     const auto clamp_to = [](int x, int most) { return x < 0 ? 0 : (x > most ? most : x); };
     int N, R, S_job = 1;
+    int n_of = 0, r_of = 0, rank_of = 0;  // BATCH_WALK: lengths and rank of sequence `lane`
     if constexpr (BATCH != BATCH_NONE) {
         const int n = clamp_to(n_vec, max_context), r = has_recent ? clamp_to(r_vec, max_recent) : 0;
         int mine;
@@ -150,8 +156,13 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
             split = job.split;
             S_job = job.S;
             mine = job.b;
+        } else if constexpr (BATCH == BATCH_WALK) {
+            n_of = n;
+            r_of = r;
+            rank_of = batch_rank(a.B, (uint32_t)n, (uint32_t)r, lane);
+            mine = batch_of_rank(rank_of, split);
         } else {
-            mine = batch_order(a.B, b, (uint32_t)n, (uint32_t)r, lane);
+            mine = batch_of_rank(batch_rank(a.B, (uint32_t)n, (uint32_t)r, lane), b);
         }
         N = __builtin_amdgcn_readlane(n, mine);
         R = __builtin_amdgcn_readlane(r, mine);
@@ -167,7 +178,7 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
         N = clamp_to(__builtin_amdgcn_readfirstlane(n_vec), a.max_context);
         R = has_recent ? clamp_to(__builtin_amdgcn_readfirstlane(r_vec), a.max_recent) : 0;
     }
-    const int bh = b * a.Hq + hq;
+    int bh = b * a.Hq + hq;
     // 32-bit unsigned arithmetic: the capacities are limited to 2^24 tokens and S to 64, and a
     // 64-bit division costs more instructions than the whole table build
     const uint32_t nblk = (uint32_t)(N + 63) >> 6;
@@ -183,10 +194,11 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     const int S = BATCH != BATCH_NONE ? S_job : (int)(want < 1u ? 1u : (want < (uint32_t)S_grid ? want : (uint32_t)S_grid));
     if (BATCH == BATCH_NONE && split >= S)
         return;
-    const int blk0 = (int)(nblk * (uint32_t)split / (uint32_t)S);
-    const int blk1 = (int)(nblk * (uint32_t)(split + 1) / (uint32_t)S);
-    const int r0 = (int)((uint32_t)R * (uint32_t)split / (uint32_t)S);
-    const int r1 = (int)((uint32_t)R * (uint32_t)(split + 1) / (uint32_t)S);
+    // (BATCH_WALK: whole sequences)
+    int blk0 = BATCH == BATCH_WALK ? 0 : (int)(nblk * (uint32_t)split / (uint32_t)S);
+    int blk1 = BATCH == BATCH_WALK ? (int)nblk : (int)(nblk * (uint32_t)(split + 1) / (uint32_t)S);
+    int r0 = BATCH == BATCH_WALK ? 0 : (int)((uint32_t)R * (uint32_t)split / (uint32_t)S);
+    int r1 = BATCH == BATCH_WALK ? R : (int)((uint32_t)R * (uint32_t)(split + 1) / (uint32_t)S);
 
     const uint8_t *k_head = a.k_codes + ((int64_t)b * a.Hkv + hkv) * a.head_stride;
     const uint8_t *v_head = a.v_codes + ((int64_t)b * a.Hkv + hkv) * a.head_stride;
@@ -229,18 +241,24 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     int blk = blk0 + wave;
     *(lds_u32 *)(lbase + CTR_OFF) = (uint32_t)(blk0 + NW);  // same value from every thread: no branch
     const uint32_t ctr_addr = (uint32_t)(uintptr_t)(lbase + CTR_OFF);
-    load_k(kbuf[0], blk < blk1 ? blk : 0, blk < blk1);
-    if (F16 && NBUF == 2)
-        load_v(vbuf[0], blk < blk1 ? blk : 0, blk < blk1);
+    auto first_loads = [&]() {
+        load_k(kbuf[0], blk < blk1 ? blk : 0, blk < blk1);
+        if (F16 && NBUF == 2)
+            load_v(vbuf[0], blk < blk1 ? blk : 0, blk < blk1);
+    };
+    first_loads();
 
     // ---- this lane's query sub-vector, pre-multiplied by scale * log2(e)
     const int sub = lane & (M - 1);
     float qs[DS];
+    auto load_qs = [&]() {
 #pragma unroll
-    for (int j = 0; j < DS; ++j)
-        qs[j] = elem<T>::ld(a.q, ((int64_t)b * a.Hq + hq) * PQ_HEAD_DIM + sub * DS + j) * a.scale_log2e;
+        for (int j = 0; j < DS; ++j)
+            qs[j] = elem<T>::ld(a.q, ((int64_t)b * a.Hq + hq) * PQ_HEAD_DIM + sub * DS + j) * a.scale_log2e;
+    };
+    load_qs();
 
-    {
+    auto build_table = [&]() {
         float qv[4 * DS];
 #pragma unroll
         for (int e = 0; e < 4 * DS; ++e)
@@ -258,11 +276,12 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
             }
             *(lds_f32x4 *)(lbase + LUT_OFF + (row0 + k * ROWS_PER_PASS) * 256 + g * 16) = ent;
         }
-        if (F16) {
+    };
+    build_table();
+    if (F16) {
 #pragma unroll
-            for (int v = 0; v < VPT; ++v)
-                *(lds_u32x4 *)(lbase + VCB_OFF + (tid + v * (NW * 64)) * 16) = vraw[v];
-        }
+        for (int v = 0; v < VPT; ++v)
+            *(lds_u32x4 *)(lbase + VCB_OFF + (tid + v * (NW * 64)) * 16) = vraw[v];
     }
     __syncthreads();
 
@@ -371,6 +390,7 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
         __builtin_amdgcn_wave_barrier();
     };
 
+    for (int turn = 0;;) {  // BATCH_WALK: the sequences of this workgroup; once otherwise
     if constexpr (!F16) {
         // fp32 contexts.  The table (64 KiB) and the fp32 value codebook image (128 KiB) do not fit LDS together, so
         // the split is scanned in chunks of F32_CHUNK blocks, each in two phases with the whole workgroup in step:
@@ -629,24 +649,67 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     __syncthreads();
 
     // From here on only wavefront 0 works: it merges the workgroup's wavefronts (lane l owns
-    // output dims 2l, 2l+1), publishes the split partial and takes a ticket.
-    if (wave != 0)
+    // output dims 2l, 2l+1), publishes the split partial and takes a ticket.  (BATCH_WALK: the others go on to the next
+    // sequence's table.)
+    if (BATCH != BATCH_WALK && wave != 0)
         return;
-    float *gpart = a.partials + ((int64_t)bh * S_grid + split) * PQ_PART_STRIDE;
     float *orow = a.out + (int64_t)bh * PQ_HEAD_DIM;
     const lds_f32 *parts = (const lds_f32 *)(lbase + PART_OFF);
     float mx = NEG_BIG;
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-        mx = fmaxf(mx, parts[w * PQ_PART_STRIDE]);
     float o0 = 0.f, o1 = 0.f, l = 0.f;
+    auto merge_wavefronts = [&]() {
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const float f = __builtin_amdgcn_exp2f(parts[w * PQ_PART_STRIDE] - mx);
-        o0 = fmaf(parts[w * PQ_PART_STRIDE + 4 + 2 * lane], f, o0);
-        o1 = fmaf(parts[w * PQ_PART_STRIDE + 5 + 2 * lane], f, o1);
-        l = fmaf(parts[w * PQ_PART_STRIDE + 1], f, l);
+        for (int w = 0; w < NW; ++w)
+            mx = fmaxf(mx, parts[w * PQ_PART_STRIDE]);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float f = __builtin_amdgcn_exp2f(parts[w * PQ_PART_STRIDE] - mx);
+            o0 = fmaf(parts[w * PQ_PART_STRIDE + 4 + 2 * lane], f, o0);
+            o1 = fmaf(parts[w * PQ_PART_STRIDE + 5 + 2 * lane], f, o1);
+            l = fmaf(parts[w * PQ_PART_STRIDE + 1], f, l);
+        }
+    };
+    if constexpr (BATCH == BATCH_WALK) {
+        // sequences by rank, dealt to the head's a.S workgroups to and fro
+        ++turn;
+        const int j = turn * a.S + ((turn & 1) ? a.S - 1 - split : split);
+        const bool more = j < a.B;
+        if (more) {  // the next sequence's requests go out before the merge
+            b = batch_of_rank(rank_of, j);
+            bh = b * a.Hq + hq;
+            N = __builtin_amdgcn_readlane(n_of, b);
+            R = __builtin_amdgcn_readlane(r_of, b);
+            blk1 = (int)((uint32_t)(N + 63) >> 6);
+            r1 = R;
+            k_head = a.k_codes + ((int64_t)b * a.Hkv + hkv) * a.head_stride;
+            v_head = a.v_codes + ((int64_t)b * a.Hkv + hkv) * a.head_stride;
+            load_q();
+            int row_again = row0;
+            asm volatile("" : "+v"(row_again));  // (the addresses are worked out here, not kept through the scan)
+            load_kraw(row_again);
+            blk = wave;
+            first_loads();
+            load_qs();
+        }
+        if (wave == 0) {
+            merge_wavefronts();
+            const float inv = l > 0.f ? 1.f / l : 0.f;
+            *(float2 *)(orow + 2 * lane) = make_float2(o0 * inv, o1 * inv);
+        }
+        if (!more)
+            return;
+        build_table();
+        *(lds_u32 *)(lbase + CTR_OFF) = (uint32_t)NW;
+        m_run = NEG_BIG;
+        l_lane = 0.f;
+#pragma unroll
+        for (int jj = 0; jj < DS; ++jj)
+            acc[jj] = 0.f;
+        __syncthreads();
+        continue;
     }
+    float *gpart = a.partials + ((int64_t)bh * S_grid + split) * PQ_PART_STRIDE;
+    merge_wavefronts();
     if (S == 1) {
         const float inv = l > 0.f ? 1.f / l : 0.f;
         *(float2 *)(orow + 2 * lane) = make_float2(o0 * inv, o1 * inv);
@@ -700,6 +763,8 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     *(float2 *)(orow + 2 * lane) = make_float2(o0 * inv, o1 * inv);
     if (lane == 0)
         ticket_reset(a.tickets + bh);
+    return;
+    }
 }
 
 template <int M, int DS, typename T, int NW, bool READ_ONCE>
@@ -708,6 +773,13 @@ hipError_t launch(const pq_decode_args &a, hipStream_t s)
     const dim3 block(NW * 64);
     pq_decode_args aj = a;
     aj.S = a.jobs > a.B ? a.jobs : 1;
+    if constexpr (sizeof(T) == 2 && M == 64) {
+        if (a.jobs < 0) {
+            aj.S = -a.jobs;
+            hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_WALK>), dim3(a.Hq * aj.S), block, 0, s, aj);
+            return hipGetLastError();
+        }
+    }
     if (a.jobs > a.B)
         hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_DEAL>), dim3(a.Hq * a.jobs), block, 0, s, aj);
     else if (a.jobs > 0)

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(GNW * 64) void pq_decode_grouped_kernel(const pq_de
             S_job = job.S;
             mine = job.b;
         } else {
-            mine = batch_order(a.B, b, (uint32_t)n, (uint32_t)r, lane);
+            mine = batch_of_rank(batch_rank(a.B, (uint32_t)n, (uint32_t)r, lane), b);
         }
         N = __builtin_amdgcn_readlane(n, mine);
         R = __builtin_amdgcn_readlane(r, mine);

@@ -207,15 +207,21 @@ template <typename A> __device__ inline uint32_t live_split_cap(const A &a, int 
 //       more than its share, whatever the lengths (a fixed number of splits per sequence leaves the longest sequence's
 //       workgroups the last ones by far: 32 heads, three sequences of 30000, 15256 and 512 tokens 59.6 -> 39.1 us; 32
 //       query / 8 KV heads, eight sequences of 2.5K .. 20K: 33 -> 28 us).
-//   BATCH_ORDER  (one workgroup per sequence and head, more than one round of them on the chip but at most two) a head's
+//   BATCH_ORDER  (other kernels: one workgroup per sequence and head, more than one round of them but at most two) a head's
 //       longest sequences come first: a long one that starts in the second round would run alone (32 query / 8 KV heads,
-//       40 sequences of 200 .. 8000: 61 -> 49 us; 20 heads, 20 sequences of 100 .. 4096: 39.1 -> 36.9).  Ranking 64
+//       40 sequences of 200 .. 8000: 61 -> 49 us).  Ranking 64
 //       lengths and fetching the query behind them costs a workgroup 1.5 us, so lengths within a quarter of the first
 //       one's stay in their order, and with more rounds, where the last one matters less, nothing is ranked (32 heads,
 //       64 sequences of 3000 .. 4096: 181 us, ranked 190; of 97 .. 4001: 133 us, ranked 134).
+//   BATCH_WALK   (the per-head kernel, more sequences than the head's share of the compute units) as many workgroups per
+//       head as the chip holds at once; workgroup w walks whole sequences, those of rank w, 2 S - 1 - w, 2 S + w, ... by
+//       length.  What a workgroup pays before its first block — 4 us: launch, lengths, 128 KiB of codebook images through
+//       the compute unit's address pipeline — it pays once; the next sequence needs its query, the key codebook again
+//       (L2) and a new table, requested before the wavefronts' merge of the previous one (32 heads, 64 sequences of 97
+//       .. 4001 tokens: 131.5 -> 118.5 us; 20 of 700 .. 8000: 84 -> 69; 16 of them 63 -> 53.5; 64 of 4096: 201 -> 193).
 //   BATCH_NONE   splits per sequence as launched (one sequence, splits asked for, more than 64 sequences)
 // ---------------------------------------------------------------------------------------------------
-enum { BATCH_NONE = 0, BATCH_DEAL = 1, BATCH_ORDER = 2 };
+enum { BATCH_NONE = 0, BATCH_DEAL = 1, BATCH_ORDER = 2, BATCH_WALK = 3 };
 
 struct batch_job {
     int b, split, S;  // sequence, split, splits of it (split >= S: nothing to do)
@@ -272,20 +278,23 @@ __device__ inline batch_job batch_deal(int B, int jobs, int j, uint32_t n, uint3
     return {b, j - __builtin_amdgcn_readlane((int)first, b), __builtin_amdgcn_readlane((int)mine, b)};
 }
 
-// BATCH_ORDER: the sequence of rank j by length (equal lengths by their number)
-__device__ inline int batch_order(int B, int j, uint32_t n, uint32_t r, int lane)
+// Rank of sequence `lane` by length, the longest first, equal ones by their number; lengths within a quarter of the
+// first one's are ranked by number alone.  Lanes beyond the batch: 64.
+__device__ inline int batch_rank(int B, uint32_t n, uint32_t r, int lane)
 {
     const bool in = lane < B;
     const uint32_t work = in ? batch_work(n, r) : 0u;  // below 2^21
     const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)work);
     if (__builtin_amdgcn_ballot_w64(in && (work > w0 + w0 / 4u || work < w0 - w0 / 4u)) == 0)
-        return j;
+        return in ? lane : 64;
     const uint32_t key = in ? (work << 6) | (uint32_t)(63 - lane) : 0u;
-    uint32_t rank = 0;
+    int rank = 0;
     for (int b = 0; b < B; ++b)
-        rank += (uint32_t)__builtin_amdgcn_readlane((int)key, b) > key ? 1u : 0u;
-    return (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(in && rank == (uint32_t)j));
+        rank += (uint32_t)__builtin_amdgcn_readlane((int)key, b) > key ? 1 : 0;
+    return in ? rank : 64;
 }
+
+__device__ inline int batch_of_rank(int rank, int j) { return (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(rank == j)); }
 
 // 16 code bytes of one lane.  Codes that are read once per launch are loaded with the
 // non-temporal hint: the stream then does not displace the tables and each other's lines in L2

@@ -114,8 +114,8 @@ struct pq_attn_ctx {
     float *scores12;
     bool grouped12;       // 12-bit context that runs the grouped-query kernel
     int n_cu;             // compute units of the device
-    int jobs;             // 8-bit contexts of 2..64 sequences with "0 = choose" splits: workgroups per head that the decode
-                          // kernel gives to the sequences by their lengths (= batch: one each); 0: splits per sequence
+    int jobs;             // 8-bit contexts of 2..64 sequences with "0 = choose" splits: how the decode kernel's workgroups
+                          // follow the sequences' lengths (choose_jobs in pq_api.hip); 0: splits per sequence
 };
 
 struct pq_decode_args {

@@ -1,6 +1,6 @@
 """Batches whose workgroups follow the sequences' lengths: fewer sequences than a head's share of the compute units (the
-workgroups are dealt out by length), between one and two rounds of them (longest first), more.  Against the oracle, and
-twice on one context (the tickets are back at zero)."""
+workgroups are dealt out by length), more (workgroups that walk several sequences, or one each, longest first).  Against the
+oracle, and twice on one context (the tickets are back at zero)."""
 import numpy as np
 import pytest
 
@@ -24,7 +24,7 @@ def _lengths(kind, B, longest, rng):
 @pytest.mark.parametrize("M,dtype", [(64, "f16"), (32, "f16"), (64, "f32"), (32, "f32")])
 @pytest.mark.parametrize("B,Hq,Hkv,longest", [(2, 2, 2, 3000), (3, 8, 2, 2500), (7, 16, 16, 700), (63, 4, 4, 1500), (64, 4, 4, 300),
                                               (5, 14, 2, 1200), (10, 32, 32, 400), (40, 32, 8, 260), (9, 32, 32, 130),
-                                              (17, 32, 32, 200)])
+                                              (17, 32, 32, 200), (40, 20, 20, 90), (64, 32, 32, 70)])
 @pytest.mark.parametrize("kind", ["equal", "one long", "powers", "random"])
 def test_batches_of_any_lengths(M, dtype, B, Hq, Hkv, longest, kind):
     rng = np.random.default_rng(B + Hq + longest + M)
