@@ -183,11 +183,14 @@ hipError_t pq_launch_kmeans(const pq_attn_ctx *ctx, const void *samples, int n_s
     const int64_t words = pq_kmeans_accumulator_bytes(ctx) / 4;
     hipLaunchKernelGGL(pq_clear_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s,
                        (uint32_t *)workspace, words);
-    // a wavefront takes up to 64 chunks of 64 samples in a row while at least 8192 wavefronts remain: one codebook set-up
-    // and one pass of the memory atomics for all of them
+    // A wavefront takes several chunks of 64 samples in a row: one codebook set-up and one pass of up to 256 (ds + 1)
+    // memory atomics for all of them.  At 3 workgroups per compute unit 3072 wavefronts are resident: few samples make one
+    // round of them (8 heads x 2000: 31.5 us; 40 with 8192 wavefronts, 33 with one subspace per workgroup), many between
+    // two and three (8 heads x 30000: 209 us; 236 with 3072 wavefronts, whose last round is a third full).
     const int n_chunks = (n_samples + 63) / 64;
     const int64_t waves = (int64_t)Hkv * n_chunks * M;
-    const int rounds = (int)(waves / 8192 < 1 ? 1 : waves / 8192 > 64 ? 64 : waves / 8192);
+    const int64_t one_round = (waves + 3071) / 3072, several = waves / 8192;
+    const int rounds = (int)(several > 64 ? 64 : several > 16 ? several : one_round < 16 ? one_round : 16);
     const int n_slices = (n_chunks + rounds - 1) / rounds;
     const dim3 grid((unsigned)(Hkv * n_slices), (unsigned)(M / KM_SUB)), block(KM_SUB * 64);
     for (int it = 0; it < n_iters; ++it) {
