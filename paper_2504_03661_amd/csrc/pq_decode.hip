@@ -56,7 +56,7 @@ static_assert(SMEM_BYTES_F32 <= 160 * 1024, "LDS budget of a gfx950 compute unit
 // BATCH: how a batch's workgroups are given to its sequences (pq_device_utils.h); BATCH_DEAL: the grid is (query heads x
 // a.S jobs).
 template <int M, int DS, typename T, int NW, bool READ_ONCE, int BATCH>
-__global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args a)
+__device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
 {
     static_assert(M * DS == PQ_HEAD_DIM, "head_dim 128 only");
     static_assert((M == 64 && DS == 2) || (M == 32 && DS == 4), "supported PQ shapes");
@@ -767,6 +767,20 @@ __global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args
     }
 }
 
+// workgroups that may share a sequence (BATCH_NONE, BATCH_DEAL): the last one merges the splits
+template <int M, int DS, typename T, int NW, bool READ_ONCE, int BATCH>
+__global__ __launch_bounds__(NW * 64) void pq_decode_kernel(const pq_decode_args a)
+{
+    decode_workgroup<M, DS, T, NW, READ_ONCE, BATCH>(a);
+}
+
+// workgroups that take whole sequences (BATCH_ORDER, BATCH_WALK): nothing is exchanged
+template <int M, int DS, typename T, int NW, bool READ_ONCE, int BATCH>
+__global__ __launch_bounds__(NW * 64) void pq_decode_whole_kernel(const pq_decode_args a)
+{
+    decode_workgroup<M, DS, T, NW, READ_ONCE, BATCH>(a);
+}
+
 template <int M, int DS, typename T, int NW, bool READ_ONCE>
 hipError_t launch(const pq_decode_args &a, hipStream_t s)
 {
@@ -776,14 +790,14 @@ hipError_t launch(const pq_decode_args &a, hipStream_t s)
     if constexpr (sizeof(T) == 2 && M == 64) {
         if (a.jobs < 0) {
             aj.S = -a.jobs;
-            hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_WALK>), dim3(a.Hq * aj.S), block, 0, s, aj);
+            hipLaunchKernelGGL((pq_decode_whole_kernel<M, DS, T, NW, READ_ONCE, BATCH_WALK>), dim3(a.Hq * aj.S), block, 0, s, aj);
             return hipGetLastError();
         }
     }
     if (a.jobs > a.B)
         hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_DEAL>), dim3(a.Hq * a.jobs), block, 0, s, aj);
     else if (a.jobs > 0)
-        hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_ORDER>), dim3(a.B * a.Hq), block, 0, s, aj);
+        hipLaunchKernelGGL((pq_decode_whole_kernel<M, DS, T, NW, READ_ONCE, BATCH_ORDER>), dim3(a.B * a.Hq), block, 0, s, aj);
     else
         hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_NONE>), dim3(a.B * a.Hq * a.S), block, 0, s, a);
     return hipGetLastError();

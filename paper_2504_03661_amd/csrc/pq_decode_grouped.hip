@@ -84,7 +84,7 @@ __device__ inline f16x4 as_f16x4(uint32_t lo, uint32_t hi)
 // BATCH: how a batch's workgroups are given to its sequences (pq_device_utils.h); BATCH_DEAL: the grid is (KV heads x
 // sub-groups x a.S jobs).
 template <bool READ_ONCE, int M, int BATCH>
-__global__ __launch_bounds__(GNW * 64) void pq_decode_grouped_kernel(const pq_decode_args a)
+__device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
 {
     static_assert(M == 64 || M == 32, "64 subspaces of 2 dims or 32 of 4");
     constexpr int KVEC = M / 16;  // 16-byte vectors of K codes per lane and block
@@ -524,6 +524,22 @@ int pq_grouped_heads_per_workgroup(int g)
     return n == 0 ? 0 : (g + n - 1) / n;
 }
 
+namespace {
+// workgroups that may share a sequence (BATCH_NONE, BATCH_DEAL): the last one merges the splits
+template <bool READ_ONCE, int M, int BATCH>
+__global__ __launch_bounds__(GNW * 64) void pq_decode_grouped_kernel(const pq_decode_args a)
+{
+    grouped_workgroup<READ_ONCE, M, BATCH>(a);
+}
+
+// workgroups that take whole sequences (BATCH_ORDER): nothing is exchanged
+template <bool READ_ONCE, int M, int BATCH>
+__global__ __launch_bounds__(GNW * 64) void pq_decode_grouped_whole_kernel(const pq_decode_args a)
+{
+    grouped_workgroup<READ_ONCE, M, BATCH>(a);
+}
+}  // namespace
+
 bool pq_config_uses_grouped_kernel(const pq_attn_config *cfg)
 {
     const int g = cfg->n_kv_heads > 0 ? cfg->n_q_heads / cfg->n_kv_heads : 0;
@@ -536,10 +552,16 @@ template <int M, int BATCH>
 static hipError_t launch_grouped(const pq_decode_args &a, int units, hipStream_t s)
 {
     const dim3 grid(units * a.S), block(GNW * 64);
-    if (a.n_sub == 1)
+    if constexpr (BATCH == BATCH_ORDER) {
+        if (a.n_sub == 1)
+            hipLaunchKernelGGL((pq_decode_grouped_whole_kernel<true, M, BATCH>), grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL((pq_decode_grouped_whole_kernel<false, M, BATCH>), grid, block, 0, s, a);
+    } else if (a.n_sub == 1) {
         hipLaunchKernelGGL((pq_decode_grouped_kernel<true, M, BATCH>), grid, block, 0, s, a);
-    else
+    } else {
         hipLaunchKernelGGL((pq_decode_grouped_kernel<false, M, BATCH>), grid, block, 0, s, a);
+    }
     return hipGetLastError();
 }
 
