@@ -1,4 +1,5 @@
-"""ctypes binding of libpq_attn.so: argument marshalling only.
+"""Binding of libpq_attn.so: argument marshalling only — through ctypes, and for the two calls of a decoding step
+through a small extension module (csrc/pq_binding.cpp) that takes the same arguments apart natively.
 
 Function names and argument order are those of include/pq_attn.h.  Tensor
 arguments may be torch tensors (their data_ptr() is passed), raw integer device
@@ -18,6 +19,8 @@ PQ_CODES_K, PQ_CODES_V = 0, 1
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libpq_attn.so")
 _lib = None
+_calls = None               # the extension module, and the addresses of the two functions in the loaded library
+_decode_at = _append_at = 0
 
 
 class PQAttnError(RuntimeError):
@@ -57,13 +60,19 @@ def library_path() -> str:
 
 def load_library():
     """Loads the in-tree library; raises if it has not been built (no fallback exists)."""
-    global _lib
+    global _lib, _calls, _decode_at, _append_at
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
         raise FileNotFoundError(
             f"{_LIB_PATH} is missing: build it with `python -m paper_2504_03661_amd.build` "
             "(or __graft_entry__.build()); there is no CPU fallback")
+    try:
+        from . import _pq_calls
+    except ImportError as e:
+        raise FileNotFoundError(
+            "the extension module _pq_calls is missing: build it with `python -m paper_2504_03661_amd.build` "
+            "(or __graft_entry__.build())") from e
     L = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
     cfgp = ctypes.POINTER(_Config)
@@ -103,6 +112,9 @@ def load_library():
     L.pq_attn_device_error.argtypes = [vp, ctypes.POINTER(ctypes.c_uint32)]
     L.pq_status_string.restype = ctypes.c_char_p
     L.pq_status_string.argtypes = [ctypes.c_int]
+    _calls = _pq_calls
+    _decode_at = ctypes.cast(L.pq_attn_decode, vp).value
+    _append_at = ctypes.cast(L.pq_encode_append, vp).value
     _lib = L
     return L
 
@@ -122,6 +134,21 @@ def _stream(stream) -> Optional[int]:
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
+
+
+_raw_stream = _raw_device = None    # torch's getters, once torch has a GPU context
+
+
+def _current_stream() -> int:
+    """The raw handle of torch's current stream on the current device."""
+    global _raw_stream, _raw_device
+    if _raw_stream is not None:
+        return _raw_stream(_raw_device())
+    import torch
+    handle = int(torch.cuda.current_stream().cuda_stream)       # (starts torch's GPU context if need be)
+    _raw_device = torch._C._cuda_getDevice
+    _raw_stream = torch._C._cuda_getCurrentRawStream
+    return handle
 
 
 def _check(status: int, where: str) -> None:
@@ -173,10 +200,12 @@ def pq_attn_set_codebooks(ctx, k_codebook, v_codebook, stream=None) -> None:
 
 def pq_attn_decode(ctx, q, k_codes, v_codes, ctx_len, k_codebook, v_codebook, recent_k, recent_v, recent_len,
                    scale, out, stream=None) -> None:
-    _check(load_library().pq_attn_decode(ctx, _addr(q), _addr(k_codes), _addr(v_codes), _addr(ctx_len),
-                                         _addr(k_codebook), _addr(v_codebook), _addr(recent_k), _addr(recent_v),
-                                         _addr(recent_len), float(scale), _addr(out), _stream(stream)),
-           "pq_attn_decode")
+    if _calls is None or _lib is None:
+        load_library()
+    rc = _calls.decode(_decode_at, _current_stream, ctx, q, k_codes, v_codes, ctx_len, k_codebook, v_codebook, recent_k,
+                       recent_v, recent_len, scale, out, stream)
+    if rc:
+        raise PQAttnError(rc, "pq_attn_decode")
 
 
 def pq_attn_decode_noalloc(cfg: PQAttnConfig, q, k_codes, v_codes, ctx_len, k_codebook, v_codebook, recent_k, recent_v,
@@ -189,9 +218,12 @@ def pq_attn_decode_noalloc(cfg: PQAttnConfig, q, k_codes, v_codes, ctx_len, k_co
 
 def pq_encode_append(ctx, new_k, new_v, n_new, k_codebook, v_codebook, k_codes, v_codes, ctx_len,
                      stream=None) -> None:
-    _check(load_library().pq_encode_append(ctx, _addr(new_k), _addr(new_v), int(n_new), _addr(k_codebook),
-                                           _addr(v_codebook), _addr(k_codes), _addr(v_codes), _addr(ctx_len),
-                                           _stream(stream)), "pq_encode_append")
+    if _calls is None or _lib is None:
+        load_library()
+    rc = _calls.append(_append_at, _current_stream, ctx, new_k, new_v, n_new, k_codebook, v_codebook, k_codes, v_codes,
+                       ctx_len, stream)
+    if rc:
+        raise PQAttnError(rc, "pq_encode_append")
 
 
 def pq_pack_codes(ctx, kind, token_major, n_tokens, packed, stream=None) -> None:

@@ -1,12 +1,15 @@
-"""Compile libpq_attn.so for gfx950 with hipcc, in-tree."""
+"""Compile libpq_attn.so for gfx950 with hipcc and the binding's extension module with the host compiler, in-tree."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpq_attn.so")
+CALLS_SOURCE = os.path.join(CSRC, "pq_binding.cpp")
+CALLS = os.path.join(HERE, "_pq_calls.so")
 SOURCES = ["pq12_codes.hip", "pq12_decode.hip", "pq12_decode_grouped.hip", "pq_api.hip", "pq_decode.hip", "pq_decode_grouped.hip", "pq_encode.hip", "pq_kmeans.hip", "pq_layout.hip"]
 HEADERS = [os.path.join(CSRC, "pq_internal.h"), os.path.join(CSRC, "pq_device_utils.h"), os.path.join(CSRC, "pq_nearest_filter.h"), os.path.join(CSRC, "pq_filter_constants.h"),
            os.path.join(ROOT, "include", "pq_attn.h")]
@@ -21,16 +24,27 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(CALLS) or os.path.getmtime(CALLS_SOURCE) > os.path.getmtime(CALLS):
         return True
     t = os.path.getmtime(LIB)
     deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def build_calls() -> str:
+    """The extension module of the per-step calls (CPython C API only: it gets the library's addresses at run time)."""
+    cxx = os.environ.get("CXX", "g++")
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"], "-o", CALLS, CALLS_SOURCE]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("the host compiler failed:\n" + res.stdout)
+    return CALLS
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
     if not force and not stale():
         return LIB
+    build_calls()
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc] + FLAGS + ["-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
     if verbose:

@@ -1,0 +1,68 @@
+"""The extension module of the per-step calls hands the library exactly what the caller passed: its function
+addresses are pointed at Python callbacks of the C signatures, no GPU involved."""
+import ctypes
+
+import pytest
+
+from paper_2504_03661_amd import binding as B
+
+vp, i32 = ctypes.c_void_p, ctypes.c_int32
+DECODE = ctypes.CFUNCTYPE(i32, *([vp] * 10), ctypes.c_float, vp, vp)
+APPEND = ctypes.CFUNCTYPE(i32, vp, vp, vp, i32, *([vp] * 6))
+
+
+class Tensor:
+    def __init__(self, at):
+        self.at = at
+
+    def data_ptr(self):
+        return self.at
+
+
+class Stream:
+    def __init__(self, raw):
+        self.cuda_stream = raw
+
+
+def recorder(monkeypatch, name, kind, status):
+    seen = []
+    fn = kind(lambda *a: seen.append(a) or status)
+    B.load_library()
+    monkeypatch.setattr(B, name, ctypes.cast(fn, vp).value)
+    return seen, fn
+
+
+HIGH = 0xFFFF_8000_0000_1000      # an address with the top bit set
+
+
+@pytest.mark.parametrize("ctx", [vp(HIGH), HIGH, None])
+@pytest.mark.parametrize("stream,raw", [(0, None), (7, 7), (Stream(HIGH), HIGH), (Stream(0), None)])
+def test_arguments_arrive_as_passed(monkeypatch, ctx, stream, raw):
+    seen, _fn = recorder(monkeypatch, "_decode_at", DECODE, 0)
+    B.pq_attn_decode(ctx, Tensor(1), Tensor(HIGH), 3, 4, None, Tensor(0), Tensor(7), None, 9, 1 / 8, Tensor(11), stream)
+    at = ctx.value if isinstance(ctx, vp) else ctx
+    assert seen == [(at, 1, HIGH, 3, 4, None, None, 7, None, 9, 0.125, 11, raw)]
+    for n_new in (0, 1, -1, 2**31 - 1):
+        seen, _fn = recorder(monkeypatch, "_append_at", APPEND, 0)
+        B.pq_encode_append(ctx, Tensor(1), 2, n_new, None, Tensor(HIGH), Tensor(6), 7, Tensor(8), stream)
+        assert seen == [(at, 1, 2, n_new, None, HIGH, 6, 7, 8, raw)]
+
+
+def test_the_default_stream_is_the_current_one_at_each_call(monkeypatch):
+    seen, _fn = recorder(monkeypatch, "_append_at", APPEND, 0)
+    for current in (5, 6):
+        monkeypatch.setattr(B, "_current_stream", lambda: current)
+        B.pq_encode_append(None, 1, 2, 1, None, None, 3, 4, 5)
+    assert [a[-1] for a in seen] == [5, 6]
+
+
+def test_a_status_raises_and_a_wrong_type_is_refused(monkeypatch):
+    _seen, _fn = recorder(monkeypatch, "_decode_at", DECODE, -1)
+    with pytest.raises(B.PQAttnError):
+        B.pq_attn_decode(None, 1, 2, 3, 4, None, None, None, None, None, 1.0, 5, 0)
+    seen, _fn = recorder(monkeypatch, "_decode_at", DECODE, 0)
+    with pytest.raises(AttributeError):
+        B.pq_attn_decode(None, 1.5, 2, 3, 4, None, None, None, None, None, 1.0, 5, 0)
+    with pytest.raises(TypeError):
+        B.pq_attn_decode(None, 1, 2, 3, 4, None, None, None, None, None, None, 5, 0)
+    assert not seen
