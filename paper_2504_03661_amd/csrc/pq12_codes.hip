@@ -53,6 +53,7 @@ __device__ inline void unpack8(const uint32_t (&w)[3], uint32_t (&c)[8])
 // heads 5.57 -> 1.74 ms; 17 x 32 x 1, SPLIT, 80 -> 48 us.)
 // ---------------------------------------------------------------------------------------------------
 typedef uint32_t u32x2e __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8e __attribute__((ext_vector_type(8)));
 
 constexpr int F12_WAVES = 8;  // wavefronts that share one set of A rows
 constexpr int F12_ROW = pq_filter_row_bytes<_Float16>();
@@ -299,21 +300,26 @@ __global__ __launch_bounds__(F12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
 }
 
 // ---------------------------------------------------------------------------------------------------
-// A handful of tokens per KV head (one decoding step of a small batch): thread = CENTROID.  The filter kernel
-// above would build 4096 rows and run both passes for a wavefront with a few live lanes; here the 1024 threads
-// of a workgroup hold 4 centroids each in registers, evaluate the defining fp64 distances of the token at hand
-// (ascending index per thread, strict "<") and the workgroup takes the lexicographic minimum of (distance,
-// index): the lowest index among equal distances, as in the scan.  The floor is reading the codebooks once
+// A handful of tokens per KV head (one decoding step of a small batch): thread = CENTROIDS.  The filter kernel
+// above would build 4096 rows for a wavefront with a few live lanes; here the 512 threads of a workgroup hold 8
+// centroids each as fp16 in registers.  Two phases: fp32 distances, whose least over the workgroup bounds the
+// centroids that can be the nearest (a bound relative to the distance itself), then the defining fp64 distances
+// of those alone (ascending index per thread, strict "<"); the workgroup takes the lexicographic minimum of
+// (distance, index): the lowest index among equal distances, as in the scan.  The floor is reading the codebooks
+// once (9.5 us at 7.05 TB/s). At 50 registers and 8 wavefronts per workgroup all workgroups of 32 heads are
+// resident in two rounds, with 128 KiB of loads under way per compute unit; 4 wavefronts per workgroup took 1.4 us
+// longer.  An append of one token with the length update, 32 heads: 21.3 us when every distance was taken in fp64
+// by 1024 threads, 17.4 us so; 4 tokens 39.2 and 27.6 us
 // (64 MiB for K and V of 32 heads).  The code goes straight into the device layout — no staging, no packing
 // kernels: a 12-bit field of a unit that other workgroups (K: the token's other subspaces) or nobody else in
 // this call (V) writes, so it is cleared and set with two device-scope atomics per 32-bit word it touches;
 // fields are disjoint, so the order of the workgroups does not matter.  Tokens beyond the capacity are not
 // written (the length update flags them).
 // ---------------------------------------------------------------------------------------------------
-constexpr int FEW12_TOKENS = 4;  // tokens per head over all sequences
-constexpr int FEW12_WAVES = 16;
+constexpr int FEW12_TOKENS = 8;  // tokens per head over all sequences
+constexpr int FEW12_WAVES = 8;
 
-__global__ __launch_bounds__(FEW12_WAVES * 64) void pq12_encode_few_kernel(const __half *x0, const __half *x1,
+__global__ __launch_bounds__(FEW12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(8))) void pq12_encode_few_kernel(const __half *x0, const __half *x1,
                                                                           const __half *cb0, const __half *cb1,
                                                                           uint8_t *codes0, uint8_t *codes1,
                                                                           const int32_t *ctx_len, int B, int Hkv, int n_new,
@@ -321,7 +327,8 @@ __global__ __launch_bounds__(FEW12_WAVES * 64) void pq12_encode_few_kernel(const
                                                                           int64_t head_stride)
 {
 #pragma clang fp contract(off)
-    static_assert(FEW12_TOKENS <= 64, "lane u fetches token u");
+    static_assert(FEW12_WAVES == 8 && FEW12_TOKENS <= FEW12_WAVES, "lane u fetches token u, wavefront u finishes it");
+    __shared__ float red_f[64 / FEW12_WAVES][FEW12_WAVES];
     __shared__ double red_d[FEW12_TOKENS][FEW12_WAVES];
     __shared__ int red_c[FEW12_TOKENS][FEW12_WAVES];
 
@@ -336,55 +343,101 @@ __global__ __launch_bounds__(FEW12_WAVES * 64) void pq12_encode_few_kernel(const
     const __half *cb = (which ? cb1 : cb0) + ((int64_t)hkv * PQ12_M + i) * PQ12_CENTROIDS * 4;
     uint8_t *codes = which ? codes1 : codes0;
 
-    double c[4][4];
+    // vector r: centroids 2 * (64 * FEW12_WAVES * r + tid) and the next one, 16 bytes
+    constexpr int NV = PQ12_CENTROIDS / (2 * 64 * FEW12_WAVES);
+    f16x8e raw[NV];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const u32x2e raw = *(const u32x2e *)(cb + (int64_t)(tid + 1024 * r) * 4);
-        const f16x4 v = __builtin_bit_cast(f16x4, raw);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            c[r][j] = (double)(float)v[j];
-    }
+    for (int r = 0; r < NV; ++r)
+        raw[r] = *(const f16x8e *)(cb + (int64_t)(64 * FEW12_WAVES * r + tid) * 8);
     // lane u < n_tok of every wavefront fetches token u's sub-vector
     const int u_mine = lane < n_tok ? lane : 0;
     const int b_mine = u_mine / n_new;
     const int t_mine = u_mine - b_mine * n_new;
-    double x_mine[4];
+    const int p0_mine = ctx_len[b_mine];
+    float x_mine[4];
     {
-        const u32x2e raw = *(const u32x2e *)(x + ((((int64_t)b_mine * Hkv + hkv) * x_head_stride + t_mine) * PQ_HEAD_DIM + i * 4));
-        const f16x4 v = __builtin_bit_cast(f16x4, raw);
+        const u32x2e raw_x = *(const u32x2e *)(x + ((((int64_t)b_mine * Hkv + hkv) * x_head_stride + t_mine) * PQ_HEAD_DIM + i * 4));
+        const f16x4 v = __builtin_bit_cast(f16x4, raw_x);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            x_mine[j] = (double)(float)v[j];
+            x_mine[j] = (float)v[j];
     }
 
-    for (int u = 0; u < n_tok; ++u) {
-        double xv[4];
+    // fp32 distances: differences and sums of squares, each rounding relative to its own result, so that a distance is
+    // within (2 + 4) * 2^-24 of its exact value; fp16 inputs reach neither the fp32 subnormals nor the overflow
+    const auto token = [&](const int u, float (&xv)[4]) {
+#pragma unroll
+        for (int r = 0; r < NV; ++r)
+            asm volatile("" : "+v"(raw[r]));  // converted for each token: held as fp32 the centroids would take 64 registers
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            xv[j] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x_mine[j]), u),
-                                     __builtin_amdgcn_readlane(__double2loint(x_mine[j]), u));
-        double bd = __builtin_huge_val();
-        int bc = tid;
+            xv[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x_mine[j]), u));
+    };
+    float minus_one = -1.f;  // not a constant to the compiler: v_fma_mix_f32 subtracts the fp16 value in one instruction
+    asm("" : "+s"(minus_one));
+    const auto rounded = [&](const int k, const float (&xv)[4]) {
+        float d = 0.f;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            double dist = 0.0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double diff = xv[j] - c[r][j];
-                dist = __builtin_fma(diff, diff, dist);
-            }
-            bc = dist < bd ? tid + 1024 * r : bc;  // ascending index inside the thread, strict "<"
-            bd = __builtin_fmin(bd, dist);
+        for (int j = 0; j < 4; ++j) {
+            const float diff = __builtin_fmaf((float)raw[k >> 1][4 * (k & 1) + j], minus_one, xv[j]);
+            d = j == 0 ? diff * diff : __builtin_fmaf(diff, diff, d);
         }
-        wave_argmin(bd, bc);
+        return d;
+    };
+    for (int u = 0; u < n_tok; ++u) {
+        float xv[4];
+        token(u, xv);
+        float least = __builtin_huge_valf();
+#pragma unroll
+        for (int k = 0; k < 2 * NV; ++k)
+            least = __builtin_fminf(least, rounded(k, xv));  // (a NaN is never the minimum)
+        least = -wave_max(-least);
+        if (lane == 0)
+            red_f[u][wave] = least;
+    }
+    __syncthreads();
+    // the defining distances of the centroids that can be the nearest: most wavefronts have none
+    // lane 8 u + w: wavefront w's least for token u, the token's least over the 8 wavefronts, the limit
+    const float leasts = (&red_f[0][0])[lane];
+    float limits = leasts;
+    limits = __builtin_fminf(limits, dpp_move<0xB1>(limits));   // quad_perm [1,0,3,2]
+    limits = __builtin_fminf(limits, dpp_move<0x4E>(limits));   // quad_perm [2,3,0,1]
+    limits = __builtin_fminf(limits, dpp_move<0x141>(limits));  // row_half_mirror
+    // 16 * 2^-24 covers the error of both distances of a comparison (12 * 2^-24) and the roundings of the limit
+    limits *= 1.f + 0x1p-20f;
+    const int first = __builtin_amdgcn_readfirstlane(wave);
+    for (int u = 0; u < n_tok; ++u) {
+        const int limit_bits = __builtin_amdgcn_readlane(__float_as_int(limits), FEW12_WAVES * u);
+        const float limit = __int_as_float(limit_bits);
+        double bd = __builtin_huge_val();
+        int bc = PQ12_CENTROIDS;
+        if (__builtin_amdgcn_readlane(__float_as_int(leasts), FEW12_WAVES * u + first) <= limit_bits) {  // (both >= +0)
+            float xv[4];
+            token(u, xv);
+            bc = 2 * tid;  // (no distance below infinity: the lowest index)
+#pragma unroll
+            for (int k = 0; k < 2 * NV; ++k) {
+                if (rounded(k, xv) <= limit) {
+                    double d = 0.0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const double diff = (double)xv[j] - (double)(float)raw[k >> 1][4 * (k & 1) + j];
+                        d = __builtin_fma(diff, diff, d);
+                    }
+                    // ascending index inside the thread, strict "<"
+                    bc = d < bd ? 2 * (64 * FEW12_WAVES * (k >> 1) + tid) + (k & 1) : bc;
+                    bd = __builtin_fmin(bd, d);
+                }
+            }
+            wave_argmin(bd, bc);
+        }
         if (lane == 0) {
             red_d[u][wave] = bd;
             red_c[u][wave] = bc;
         }
     }
     __syncthreads();
-    // wavefront u finishes token u: the 16 wavefronts' candidates sit in every row of 16 lanes
+    // wavefront u finishes token u: the wavefronts' candidates are repeated over its lanes
     if (wave < n_tok) {
         double d = red_d[wave][lane & (FEW12_WAVES - 1)];
         int cc = red_c[wave][lane & (FEW12_WAVES - 1)];
@@ -392,7 +445,7 @@ __global__ __launch_bounds__(FEW12_WAVES * 64) void pq12_encode_few_kernel(const
         if (lane == 0) {
             const int b = wave / n_new;
             const int t = wave - b * n_new;
-            int p0 = ctx_len[b];
+            int p0 = __builtin_amdgcn_readlane(p0_mine, wave);
             p0 = p0 < 0 ? 0 : p0;
             const int64_t pos = (int64_t)p0 + t;
             if (pos < max_context) {
@@ -566,9 +619,9 @@ hipError_t pq12_launch_encode_append(const pq_attn_ctx *ctx, const pq_encode_arg
                                      unsigned int *dev_err, hipStream_t s)
 {
     const int64_t n_tok = (int64_t)a.B * a.n_new;  // tokens of a head over all sequences
-    // 32 heads, one new token per sequence, with the length reset and all launches: 1 sequence 21 us, 2 27 us, 4 39 us, 8
-    // 66 us with the kernel below (6.6 us per token: fp64 arithmetic); 44 .. 48 us for 1 .. 17 sequences with the split
-    // filter kernel
+    // 32 heads, one new token per sequence, with the length reset and all launches: 1 sequence 17 us, 2 20 us, 4 28 us, 8
+    // 43 us with the kernel below; 44 .. 48 us for 1 .. 17 sequences with the split filter kernel.  8 heads, 8 sequences:
+    // 19 us and 20 us
     if (n_tok <= FEW12_TOKENS) {
         // a decoding step: encode and write the device layouts in one kernel, then the lengths
         hipLaunchKernelGGL(pq12_encode_few_kernel, dim3((unsigned)a.Hkv, PQ12_M, 2), dim3(FEW12_WAVES * 64), 0, s,

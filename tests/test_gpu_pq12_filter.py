@@ -1,4 +1,4 @@
-"""12-bit encode through the matrix-core filter: token counts at the edges of its paths (4 / 5 tokens per head: per-token
+"""12-bit encode through the matrix-core filter: token counts at the edges of its paths (8 / 9 tokens per head: per-token
 kernel / split; 64 / 65; 128 / 129: split / unsplit; several chunks per wavefront), with ties inside a block of 16, across
 the interleaved blocks of the two lane halves and across rows and columns of blocks, near-ties, a codebook of norms
 beyond fp16, subnormals, and tokens up to the largest fp16."""
@@ -14,7 +14,7 @@ from synth import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,Hkv,n_new", [(1, 2, 4), (5, 2, 1), (1, 2, 64), (5, 1, 13), (2, 1, 64), (1, 1, 129), (3, 2, 171),
+@pytest.mark.parametrize("B,Hkv,n_new", [(1, 2, 4), (5, 2, 1), (1, 3, 1), (4, 2, 2), (9, 2, 1), (1, 2, 64), (5, 1, 13), (2, 1, 64), (1, 1, 129), (3, 2, 171),
                                          (1, 8, 1700)])
 def test_codes_of_every_path_are_the_oracles(B, Hkv, n_new):
     rng = np.random.default_rng(B + n_new)
@@ -53,3 +53,26 @@ def test_codes_of_every_path_are_the_oracles(B, Hkv, n_new):
         np.testing.assert_array_equal(got_k[b, :, n:n + n_new], exp_k[b])
         np.testing.assert_array_equal(got_v[b, :, n:n + n_new], exp_v[b])
         np.testing.assert_array_equal(got_k[b, :, :n], data["k_codes"][b, :, :n])
+
+
+@pytest.mark.parametrize("n_new", [1, 5, 8, 9])
+def test_tokens_and_centroids_that_are_not_finite(n_new):
+    """The lowest index among the least distances, infinite ones and NaN never below another: code 0 if there is none."""
+    w = W.Workload("f12n", 1, 2, 2, 128, 32, 64, "f16", n_new=n_new, seed=n_new, ctx_lens=(9,), n_centroids=4096)
+    data = W.generate(w, ctx_cap=64)
+    for cb in (data["k_codebook"], data["v_codebook"]):
+        cb[:, 0, 1:3000] = np.nan
+        cb[:, 1, 1::2, 1] = np.inf
+        cb[:, 2] = -np.inf
+        cb[:, 3, 4095] = np.nan
+    for x in (data["new_k"], data["new_v"]):
+        x[..., 16:20] = np.nan
+        x[..., 20] = -np.inf
+    with PQSession(data, 2, "f16", max_context=64) as s:
+        s.append(torch.from_numpy(data["new_k"]).cuda(), torch.from_numpy(data["new_v"]).cuda())
+        torch.cuda.synchronize()
+        got_k, got_v = s.unpack(PQ_CODES_K, 64), s.unpack(PQ_CODES_V, 64)
+    exp_k, exp_v = O.encode(data["new_k"], data["k_codebook"]), O.encode(data["new_v"], data["v_codebook"])
+    assert (exp_k[..., 2] == 0).all() and (exp_k[..., 4] == 0).all()
+    np.testing.assert_array_equal(got_k[0, :, 9:9 + n_new], exp_k[0])
+    np.testing.assert_array_equal(got_v[0, :, 9:9 + n_new], exp_v[0])
