@@ -1,5 +1,6 @@
 """Binding of libpq_attn.so: argument marshalling only — through ctypes, and for the two calls of a decoding step
-through a small extension module (csrc/pq_binding.cpp) that takes the same arguments apart natively.
+through a small extension module (csrc/pq_binding.cpp) that takes the same arguments apart natively, where that module
+has been built for this interpreter.
 
 Function names and argument order are those of include/pq_attn.h.  Tensor
 arguments may be torch tensors (their data_ptr() is passed), raw integer device
@@ -9,6 +10,7 @@ not been built the import of this module still works, but the first call raises.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -19,7 +21,7 @@ PQ_CODES_K, PQ_CODES_V = 0, 1
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libpq_attn.so")
 _lib = None
-_calls = None               # the extension module, and the addresses of the two functions in the loaded library
+_calls = None               # the extension module if there is one, and the addresses of its two functions in the library
 _decode_at = _append_at = 0
 
 
@@ -68,11 +70,9 @@ def load_library():
             f"{_LIB_PATH} is missing: build it with `python -m paper_2504_03661_amd.build` "
             "(or __graft_entry__.build()); there is no CPU fallback")
     try:
-        from . import _pq_calls
-    except ImportError as e:
-        raise FileNotFoundError(
-            "the extension module _pq_calls is missing: build it with `python -m paper_2504_03661_amd.build` "
-            "(or __graft_entry__.build())") from e
+        calls = importlib.import_module(__package__ + "._pq_calls")
+    except ModuleNotFoundError:                     # not built for this interpreter: the same calls through ctypes
+        calls = None
     L = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
     cfgp = ctypes.POINTER(_Config)
@@ -112,7 +112,7 @@ def load_library():
     L.pq_attn_device_error.argtypes = [vp, ctypes.POINTER(ctypes.c_uint32)]
     L.pq_status_string.restype = ctypes.c_char_p
     L.pq_status_string.argtypes = [ctypes.c_int]
-    _calls = _pq_calls
+    _calls = calls
     _decode_at = ctypes.cast(L.pq_attn_decode, vp).value
     _append_at = ctypes.cast(L.pq_encode_append, vp).value
     _lib = L
@@ -200,10 +200,14 @@ def pq_attn_set_codebooks(ctx, k_codebook, v_codebook, stream=None) -> None:
 
 def pq_attn_decode(ctx, q, k_codes, v_codes, ctx_len, k_codebook, v_codebook, recent_k, recent_v, recent_len,
                    scale, out, stream=None) -> None:
-    if _calls is None or _lib is None:
-        load_library()
-    rc = _calls.decode(_decode_at, _current_stream, ctx, q, k_codes, v_codes, ctx_len, k_codebook, v_codebook, recent_k,
-                       recent_v, recent_len, scale, out, stream)
+    L = _lib or load_library()
+    if _calls is not None:
+        rc = _calls.decode(_decode_at, _current_stream, ctx, q, k_codes, v_codes, ctx_len, k_codebook, v_codebook,
+                           recent_k, recent_v, recent_len, scale, out, stream)
+    else:
+        rc = L.pq_attn_decode(ctx, _addr(q), _addr(k_codes), _addr(v_codes), _addr(ctx_len), _addr(k_codebook),
+                              _addr(v_codebook), _addr(recent_k), _addr(recent_v), _addr(recent_len), float(scale),
+                              _addr(out), _stream(stream))
     if rc:
         raise PQAttnError(rc, "pq_attn_decode")
 
@@ -218,10 +222,13 @@ def pq_attn_decode_noalloc(cfg: PQAttnConfig, q, k_codes, v_codes, ctx_len, k_co
 
 def pq_encode_append(ctx, new_k, new_v, n_new, k_codebook, v_codebook, k_codes, v_codes, ctx_len,
                      stream=None) -> None:
-    if _calls is None or _lib is None:
-        load_library()
-    rc = _calls.append(_append_at, _current_stream, ctx, new_k, new_v, n_new, k_codebook, v_codebook, k_codes, v_codes,
-                       ctx_len, stream)
+    L = _lib or load_library()
+    if _calls is not None:
+        rc = _calls.append(_append_at, _current_stream, ctx, new_k, new_v, n_new, k_codebook, v_codebook, k_codes,
+                           v_codes, ctx_len, stream)
+    else:
+        rc = L.pq_encode_append(ctx, _addr(new_k), _addr(new_v), int(n_new), _addr(k_codebook), _addr(v_codebook),
+                                _addr(k_codes), _addr(v_codes), _addr(ctx_len), _stream(stream))
     if rc:
         raise PQAttnError(rc, "pq_encode_append")
 

@@ -1,5 +1,6 @@
 """Compile libpq_attn.so for gfx950 with hipcc and the binding's extension module with the host compiler, in-tree."""
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -9,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpq_attn.so")
 CALLS_SOURCE = os.path.join(CSRC, "pq_binding.cpp")
-CALLS = os.path.join(HERE, "_pq_calls.so")
+CALLS = os.path.join(HERE, "_pq_calls" + sysconfig.get_config_var("EXT_SUFFIX"))    # for this interpreter
 SOURCES = ["pq12_codes.hip", "pq12_decode.hip", "pq12_decode_grouped.hip", "pq_api.hip", "pq_decode.hip", "pq_decode_grouped.hip", "pq_encode.hip", "pq_kmeans.hip", "pq_layout.hip"]
 HEADERS = [os.path.join(CSRC, "pq_internal.h"), os.path.join(CSRC, "pq_device_utils.h"), os.path.join(CSRC, "pq_nearest_filter.h"), os.path.join(CSRC, "pq_filter_constants.h"),
            os.path.join(ROOT, "include", "pq_attn.h")]
@@ -24,17 +25,30 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(CALLS) or os.path.getmtime(CALLS_SOURCE) > os.path.getmtime(CALLS):
+    if not os.path.exists(LIB):
+        return True
+    if can_build_calls() and (not os.path.exists(CALLS) or os.path.getmtime(CALLS_SOURCE) > os.path.getmtime(CALLS)):
         return True
     t = os.path.getmtime(LIB)
     deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def _host_compiler() -> str:
+    return os.environ.get("CXX", "g++")
+
+
+def can_build_calls() -> bool:
+    """Whether this box has what the extension module needs: a host compiler and the interpreter's headers."""
+    command = _host_compiler().split()
+    return bool(command) and shutil.which(command[0]) is not None and \
+        os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h"))
+
+
 def build_calls() -> str:
     """The extension module of the per-step calls (CPython C API only: it gets the library's addresses at run time)."""
-    cxx = os.environ.get("CXX", "g++")
-    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"], "-o", CALLS, CALLS_SOURCE]
+    cmd = _host_compiler().split() + ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                                      "-I" + sysconfig.get_paths()["include"], "-o", CALLS, CALLS_SOURCE]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if res.returncode != 0:
         raise RuntimeError("the host compiler failed:\n" + res.stdout)
@@ -44,7 +58,6 @@ def build_calls() -> str:
 def build(force: bool = True, verbose: bool = False) -> str:
     if not force and not stale():
         return LIB
-    build_calls()
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc] + FLAGS + ["-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
     if verbose:
@@ -57,6 +70,8 @@ def build(force: bool = True, verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + out)
     if out.strip() and verbose:
         print(out)
+    if can_build_calls():       # the library stands without it: the binding then makes the same calls through ctypes
+        build_calls()
     return LIB
 
 

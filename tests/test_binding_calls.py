@@ -1,10 +1,15 @@
 """The extension module of the per-step calls hands the library exactly what the caller passed: its function
 addresses are pointed at Python callbacks of the C signatures, no GPU involved."""
 import ctypes
+import os
+import sys
+import sysconfig
+import types
 
 import pytest
 
 from paper_2504_03661_amd import binding as B
+from paper_2504_03661_amd import build as lib_build
 
 vp, i32 = ctypes.c_void_p, ctypes.c_int32
 DECODE = ctypes.CFUNCTYPE(i32, *([vp] * 10), ctypes.c_float, vp, vp)
@@ -66,3 +71,36 @@ def test_a_status_raises_and_a_wrong_type_is_refused(monkeypatch):
     with pytest.raises(TypeError):
         B.pq_attn_decode(None, 1, 2, 3, 4, None, None, None, None, None, None, 5, 0)
     assert not seen
+
+
+def test_the_library_serves_without_the_extension_module(monkeypatch):
+    for name in ("_lib", "_calls"):
+        monkeypatch.setattr(B, name, None)
+    monkeypatch.setitem(sys.modules, B.__package__ + "._pq_calls", None)       # its import raises ModuleNotFoundError
+    assert B.load_library() is B._lib and B._calls is None
+    assert B.pq_status_string(0)
+    seen = []
+    monkeypatch.setattr(B, "_lib", types.SimpleNamespace(pq_attn_decode=DECODE(lambda *a: seen.append(a) or 0),
+                                                         pq_encode_append=APPEND(lambda *a: seen.append(a) or 0)))
+    B.pq_attn_decode(HIGH, Tensor(1), Tensor(HIGH), 3, 4, None, Tensor(0), Tensor(7), None, 9, 1 / 8, Tensor(11), Stream(6))
+    B.pq_encode_append(HIGH, Tensor(1), 2, 5, None, Tensor(HIGH), Tensor(6), 7, Tensor(8), 0)
+    assert seen == [(HIGH, 1, HIGH, 3, 4, None, None, 7, None, 9, 0.125, 11, 6), (HIGH, 1, 2, 5, None, HIGH, 6, 7, 8, None)]
+
+
+@pytest.mark.parametrize("missing", ["headers", "compiler"])
+def test_the_library_builds_where_the_extension_module_cannot(monkeypatch, tmp_path, missing):
+    """hipcc stands in as a command that succeeds; what is looked at is that nothing else is asked for."""
+    monkeypatch.setenv("HIPCC", "/bin/true")
+    monkeypatch.setattr(lib_build, "CALLS", str(tmp_path / "_pq_calls.so"))
+    if missing == "headers":
+        monkeypatch.setattr(sysconfig, "get_paths", lambda *a, **k: {"include": str(tmp_path)})
+    else:
+        monkeypatch.setenv("CXX", str(tmp_path / "no_such_compiler"))
+    assert lib_build.build(force=True) == lib_build.LIB
+    assert not os.path.exists(lib_build.CALLS)
+    assert lib_build.stale() == any(os.path.getmtime(f) > os.path.getmtime(lib_build.LIB) for f in
+                                    [os.path.join(lib_build.CSRC, s) for s in lib_build.SOURCES] + lib_build.HEADERS)
+
+
+def test_the_extension_module_is_named_for_its_interpreter():
+    assert os.path.basename(lib_build.CALLS) == "_pq_calls" + sysconfig.get_config_var("EXT_SUFFIX")
