@@ -23,6 +23,7 @@ _LIB_PATH = os.path.join(_HERE, "libpq_attn.so")
 _lib = None
 _calls = None               # the extension module if there is one, and the addresses of its two functions in the library
 _decode_at = _append_at = 0
+_CONTEXT = (int, ctypes.c_void_p, type(None))   # what the extension module takes as a context; ctypes decides on others
 
 
 class PQAttnError(RuntimeError):
@@ -201,7 +202,7 @@ def pq_attn_set_codebooks(ctx, k_codebook, v_codebook, stream=None) -> None:
 def pq_attn_decode(ctx, q, k_codes, v_codes, ctx_len, k_codebook, v_codebook, recent_k, recent_v, recent_len,
                    scale, out, stream=None) -> None:
     L = _lib or load_library()
-    if _calls is not None:
+    if _calls is not None and isinstance(ctx, _CONTEXT):
         rc = _calls.decode(_decode_at, _current_stream, ctx, q, k_codes, v_codes, ctx_len, k_codebook, v_codebook,
                            recent_k, recent_v, recent_len, scale, out, stream)
     else:
@@ -223,7 +224,7 @@ def pq_attn_decode_noalloc(cfg: PQAttnConfig, q, k_codes, v_codes, ctx_len, k_co
 def pq_encode_append(ctx, new_k, new_v, n_new, k_codebook, v_codebook, k_codes, v_codes, ctx_len,
                      stream=None) -> None:
     L = _lib or load_library()
-    if _calls is not None:
+    if _calls is not None and isinstance(ctx, _CONTEXT):
         rc = _calls.append(_append_at, _current_stream, ctx, new_k, new_v, n_new, k_codebook, v_codebook, k_codes,
                            v_codes, ctx_len, stream)
     else:

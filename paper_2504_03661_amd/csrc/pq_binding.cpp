@@ -43,7 +43,7 @@ bool pointer(PyObject *o, void **out)
     return !PyErr_Occurred();
 }
 
-// the context: None, an int, or a ctypes pointer
+// the context: None, an int, or a ctypes.c_void_p (binding.py hands over no other)
 bool handle(PyObject *o, void **out)
 {
     if (o == Py_None || PyLong_Check(o))

@@ -73,6 +73,25 @@ def test_a_status_raises_and_a_wrong_type_is_refused(monkeypatch):
     assert not seen
 
 
+def test_contexts_are_taken_as_ctypes_takes_them(monkeypatch):
+    """A pointer object is an address; an object that is none is refused, whatever attributes it has."""
+    cell = ctypes.c_int32(5)
+    seen = []
+    lib = types.SimpleNamespace(pq_attn_decode=DECODE(lambda *a: seen.append(a[0]) or 0),
+                                pq_encode_append=APPEND(lambda *a: seen.append(a[0]) or 0))
+    B.load_library()
+    monkeypatch.setattr(B, "_lib", lib)
+    for name in ("_decode_at", "_append_at"):           # (the extension module must not see these)
+        monkeypatch.setattr(B, name, 0)
+    decode = lambda ctx: B.pq_attn_decode(ctx, 1, 2, 3, 4, None, None, None, None, None, 1.0, 5, 0)
+    append = lambda ctx: B.pq_encode_append(ctx, 1, 2, 1, None, None, 3, 4, 5, 0)
+    for call in (decode, append):
+        call(ctypes.pointer(cell))
+        with pytest.raises(ctypes.ArgumentError):
+            call(ctypes.c_uint64(64))
+    assert seen == [ctypes.addressof(cell)] * 2
+
+
 def test_the_library_serves_without_the_extension_module(monkeypatch):
     for name in ("_lib", "_calls"):
         monkeypatch.setattr(B, name, None)
