@@ -137,7 +137,7 @@ def _stream(stream) -> Optional[int]:
     return int(stream.cuda_stream) or None
 
 
-_raw_stream = _raw_device = None    # torch's getters, once torch has a GPU context
+_raw_stream = _raw_device = None    # torch's own getters (not public: a torch may have none), once it has a GPU context
 
 
 def _current_stream() -> int:
@@ -147,8 +147,8 @@ def _current_stream() -> int:
         return _raw_stream(_raw_device())
     import torch
     handle = int(torch.cuda.current_stream().cuda_stream)       # (starts torch's GPU context if need be)
-    _raw_device = torch._C._cuda_getDevice
-    _raw_stream = torch._C._cuda_getCurrentRawStream
+    _raw_device = getattr(torch._C, "_cuda_getDevice", None)
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if _raw_device is not None else None
     return handle
 
 

@@ -73,6 +73,24 @@ def test_a_status_raises_and_a_wrong_type_is_refused(monkeypatch):
     assert not seen
 
 
+@pytest.mark.parametrize("missing", [None, "_cuda_getDevice", "_cuda_getCurrentRawStream"])
+def test_the_current_stream_without_torchs_private_getters(monkeypatch, missing):
+    """torch's own accessors are a shortcut: where a torch has none, its public call answers at each call."""
+    import torch
+    current = [5]
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream(current[0]))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 1, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 10 * device + current[0], raising=False)
+    for name in ("_raw_stream", "_raw_device"):
+        monkeypatch.setattr(B, name, None)
+    if missing:
+        monkeypatch.delattr(torch._C, missing)
+    seen = [B._current_stream()]                        # the first call starts torch's GPU context through the public one
+    current[0] = 6
+    seen += [B._current_stream(), B._current_stream()]
+    assert seen == ([5, 16, 16] if missing is None else [5, 6, 6])
+
+
 def test_contexts_are_taken_as_ctypes_takes_them(monkeypatch):
     """A pointer object is an address; an object that is none is refused, whatever attributes it has."""
     cell = ctypes.c_int32(5)
