@@ -123,3 +123,11 @@ def test_status_strings():
     assert P.pq_status_string(0) == "ok"
     for s in (-1, -2, -3, -4, -6, -7, -99):
         assert P.pq_status_string(s)
+
+
+def test_the_header_names_the_token_count_that_bypasses_the_staging_memory():
+    """12-bit appends: the number in the public header is the one the launcher compares with."""
+    header = open(os.path.join(ROOT, "include", "pq_attn.h")).read()
+    source = open(os.path.join(ROOT, "paper_2504_03661_amd", "csrc", "pq12_codes.hip")).read()
+    documented = re.search(r"(\d+) or fewer new tokens per KV head", header).group(1)
+    assert documented == re.search(r"FEW12_TOKENS = (\d+);", source).group(1)
