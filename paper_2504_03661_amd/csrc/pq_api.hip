@@ -317,8 +317,10 @@ int pq_attn_create(const pq_attn_config *cfg, pq_attn_ctx **out)
     const size_t cb_bytes = (size_t)cfg->n_kv_heads * cfg->n_centroids * PQ_HEAD_DIM * ctx->elem_bytes;
     const size_t n_bh = (size_t)cfg->batch * cfg->n_q_heads;
     ctx->jobs = choose_jobs(cfg, ctx->n_cu);
-    const size_t slots = (size_t)(ctx->jobs > ctx->n_splits ? ctx->jobs : ctx->n_splits);  // partials per row
-    const size_t part_bytes = n_bh * slots * PQ_PART_STRIDE * sizeof(float);
+    // slots of split partials: the launched splits of every row, or, where a head's jobs are dealt out, one per head and
+    // job — a job has one sequence (63 sequences x 4 heads, 64 jobs each: 132 KiB, 8.3 MiB with a slot per row and job)
+    const size_t slots = ctx->jobs > cfg->batch ? (size_t)cfg->n_q_heads * ctx->jobs : n_bh * ctx->n_splits;
+    const size_t part_bytes = slots * PQ_PART_STRIDE * sizeof(float);
     bool ok = hipMalloc(&ctx->kcb_packed, cb_bytes) == hipSuccess;
     ok = ok && hipMalloc(&ctx->vcb_packed, cb_bytes) == hipSuccess;
     ok = ok && hipMalloc((void **)&ctx->partials, part_bytes) == hipSuccess;

@@ -144,7 +144,7 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
     __builtin_amdgcn_s_barrier();
 
     const auto clamp_to = [](int x, int most) { return x < 0 ? 0 : (x > most ? most : x); };
-    int N, R, S_job = 1;
+    int N, R, S_job = 1, first_job = 0;  // BATCH_DEAL: the sequence's splits are the head's jobs first_job ..
     int n_of = 0, r_of = 0, rank_of = 0;  // BATCH_WALK: lengths and rank of sequence `lane`
     if constexpr (BATCH != BATCH_NONE) {
         const int n = clamp_to(n_vec, max_context), r = has_recent ? clamp_to(r_vec, max_recent) : 0;
@@ -153,6 +153,7 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
             const batch_job job = batch_deal(a.B, a.S, split, (uint32_t)n, (uint32_t)r, lane);
             if (job.split >= job.S)
                 return;
+            first_job = split - job.split;
             split = job.split;
             S_job = job.S;
             mine = job.b;
@@ -708,7 +709,9 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
         __syncthreads();
         continue;
     }
-    float *gpart = a.partials + ((int64_t)bh * S_grid + split) * PQ_PART_STRIDE;
+    // the row's partials: one slot per launched split of every row, or per job of the head
+    float *row_parts = a.partials + (BATCH == BATCH_DEAL ? (int64_t)hq * S_grid + first_job : (int64_t)bh * S_grid) * PQ_PART_STRIDE;
+    float *gpart = row_parts + split * PQ_PART_STRIDE;
     merge_wavefronts();
     if (S == 1) {
         const float inv = l > 0.f ? 1.f / l : 0.f;
@@ -733,7 +736,7 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
         return;
     asm volatile("" ::: "memory");  // the loads below stay behind the ticket in the instruction stream
     // the other splits' partials: device-scope loads, issued after the ticket has returned
-    const float *ps = a.partials + (int64_t)bh * S_grid * PQ_PART_STRIDE;
+    const float *ps = row_parts;
     // Lane s holds (maximum, weight sum) of split s.  The first eight splits' output loads are issued
     // together with that load, so the merge costs one memory round trip for up to eight splits.
     float2 o[8];

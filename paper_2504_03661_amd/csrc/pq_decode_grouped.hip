@@ -149,7 +149,7 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
     __builtin_amdgcn_s_barrier();
 
     const auto clamp_to = [](int x, int most) { return x < 0 ? 0 : (x > most ? most : x); };
-    int N, R, S_job = 1;
+    int N, R, S_job = 1, first_job = 0;  // BATCH_DEAL: the sequence's splits are the head's jobs first_job ..
     if constexpr (BATCH != BATCH_NONE) {
         const int n = clamp_to(n_vec, max_context), r = has_recent ? clamp_to(r_vec, max_recent) : 0;
         int mine;
@@ -157,6 +157,7 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
             const batch_job job = batch_deal(a.B, a.S, split, (uint32_t)n, (uint32_t)r, lane);
             if (job.split >= job.S)
                 return;
+            first_job = split - job.split;
             split = job.split;
             S_job = job.S;
             mine = job.b;
@@ -426,6 +427,9 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
     typedef __attribute__((address_space(3))) int lds_i32;
     lds_i32 *last_flag = (lds_i32 *)(lbase + GCTR_OFF + 4);
     const int g = wave;
+    // the row's partials: one slot per launched split of every row, or per job of the head
+    float *row_parts = a.partials + (BATCH == BATCH_DEAL ? (int64_t)(hkv * a.G + g_first + g) * S_grid + first_job
+                                                         : (int64_t)(bh0 + g) * S_grid) * PQ_PART_STRIDE;
     if (g < G) {
         const lds_f32 *parts = (const lds_f32 *)(lbase + GPART_OFF);
         float mx = NEG_BIG;
@@ -445,7 +449,7 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
             const float inv = l > 0.f ? 1.f / l : 0.f;
             *(float2 *)(a.out + (int64_t)(bh0 + g) * PQ_HEAD_DIM + 2 * lane) = make_float2(o0 * inv, o1 * inv);
         } else {
-            float *gpart = a.partials + ((int64_t)(bh0 + g) * S_grid + split) * PQ_PART_STRIDE;
+            float *gpart = row_parts + split * PQ_PART_STRIDE;
             // device-scope stores, complete (performed where every XCD sees them) before the barrier
             publish(gpart + 4 + 2 * lane, o0, o1);
             if (lane == 0)
@@ -473,7 +477,7 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
         // splits' outputs together with the (maximum, weight sum) pairs, so that the merge costs one memory round
         // trip instead of three.  Loads of splits beyond S repeat the last split (unconditional loads from
         // wave-uniform bases); their factor is zero.
-        const float *ps = a.partials + (int64_t)(bh0 + g) * S_grid * PQ_PART_STRIDE;
+        const float *ps = row_parts;
         float2 o[32];
 #pragma unroll
         for (int u = 0; u < 32; ++u)

@@ -102,7 +102,7 @@ struct pq_attn_ctx {
     void *kcb_natural;    // the context's own copy of the registered codebooks in the caller's layout
     void *vcb_natural;    // [Hkv][M][C][ds] (what the encode kernels read); 12-bit contexts: = *_packed
     bool registered;      // codebooks have been registered (the copies above hold them)
-    float *partials;      // [B*Hq][n_splits][PQ_PART_STRIDE]
+    float *partials;      // [B*Hq][n_splits][PQ_PART_STRIDE]; jobs > B: [Hq][jobs][PQ_PART_STRIDE]
     unsigned int *tickets;  // [B*Hq], zero between calls
     unsigned int *dev_err;  // sticky error word
     // 12-bit contexts: token-major uint16 staging of an append's codes, sized once at creation; a longer
