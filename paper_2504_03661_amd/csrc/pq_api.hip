@@ -153,7 +153,9 @@ int choose_jobs(const pq_attn_config *c, int n_cu)
     const int64_t heads = pq_config_uses_grouped_kernel(c)
                               ? (int64_t)c->n_kv_heads * pq_grouped_sub_groups(c->n_q_heads / c->n_kv_heads)
                               : c->n_q_heads;
-    const int64_t share = n_cu / heads < PQ_MAX_SPLITS ? n_cu / heads : PQ_MAX_SPLITS;
+    // (the whole share: PQ_MAX_SPLITS bounds the splits of one sequence, not a head's workgroups — with 64 of them one head
+    // left three quarters of the chip idle, 63 sequences of 8K tokens 36.9 us, 17.7 with 4 splits each)
+    const int64_t share = n_cu / heads;
     if (share > c->batch)
         return (int)share;
     if (share == c->batch)

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pq_internal.h"
+
 namespace {
 
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
@@ -203,8 +205,8 @@ template <typename A> __device__ inline uint32_t live_split_cap(const A &a, int 
 // Which workgroups a batch's sequences get ("0 = choose" splits, 2..64 sequences); every workgroup reads all lengths and
 // works it out in the same way.  Work is counted in 64-token blocks and 16 recent rows.
 //   BATCH_DEAL   (the head's share of the compute units is larger than the batch: that many workgroups per head)
-//       sequence b gets ceil(work / T) of them, T the smallest trial size whose sum fits, so that no workgroup has much
-//       more than its share, whatever the lengths (a fixed number of splits per sequence leaves the longest sequence's
+//       sequence b gets ceil(work / T) of them, at most PQ_MAX_SPLITS, T the smallest trial size whose sum fits, so that
+//       no workgroup has much more than its share, whatever the lengths (a fixed number of splits per sequence leaves the longest sequence's
 //       workgroups the last ones by far: 32 heads, three sequences of 30000, 15256 and 512 tokens 59.6 -> 39.1 us; 32
 //       query / 8 KV heads, eight sequences of 2.5K .. 20K: 33 -> 28 us).
 //   BATCH_ORDER  (other kernels: one workgroup per sequence and head, more than one round of them but at most two) a head's
@@ -259,19 +261,21 @@ __device__ inline batch_job batch_deal(int B, int jobs, int j, uint32_t n, uint3
     const bool in = lane < B;
     const uint32_t work = in ? batch_work(n, r) : 0u;
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(work), 63);
-    // lane i tries T = 2^(i / 10.5) x the even share (at least 4 blocks): steps of 7 %, the last one 64 shares, which no
-    // sequence exceeds; in floats, the same in every workgroup
+    // lane i tries T = 2^(i / 10.5) x the even share (at least 4 blocks): steps of 7 %, the last one 64 shares, which fits:
+    // jobs / 64 workgroups beyond one per sequence at most; in floats, the same in every workgroup
     const float share = (float)total / (float)jobs;
     const float least = share > 4.f ? share : 4.f;
     const float inv = __builtin_amdgcn_rcpf(least * __builtin_amdgcn_exp2f((float)lane * (6.0f / 63.0f)));
+    const auto splits_of = [](uint32_t w, float inv_t) {
+        const uint32_t more = (uint32_t)((float)(w > 0u ? w - 1u : 0u) * inv_t);
+        return 1u + (more < PQ_MAX_SPLITS - 1u ? more : PQ_MAX_SPLITS - 1u);
+    };
     uint32_t sum = 0;
-    for (int b = 0; b < B; ++b) {
-        const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)work, b);
-        sum += 1u + (uint32_t)((float)(w > 0u ? w - 1u : 0u) * inv);
-    }
+    for (int b = 0; b < B; ++b)
+        sum += splits_of((uint32_t)__builtin_amdgcn_readlane((int)work, b), inv);
     const uint64_t fits = __builtin_amdgcn_ballot_w64(sum <= (uint32_t)jobs);
     const float chosen = fits != 0 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv), __builtin_ctzll(fits))) : 0.f;
-    const uint32_t mine = in ? 1u + (uint32_t)((float)(work > 0u ? work - 1u : 0u) * chosen) : 0u;
+    const uint32_t mine = in ? splits_of(work, chosen) : 0u;
     const uint32_t upto = wave_scan(mine);
     const uint32_t first = in ? upto - mine : ~0u;
     const int b = __builtin_popcountll(__builtin_amdgcn_ballot_w64(first <= (uint32_t)j)) - 1;

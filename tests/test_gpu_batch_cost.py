@@ -22,3 +22,44 @@ def test_contexts_of_a_batch_hold_one_partial_per_head_and_job(B, Hq, Hkv):
         P.pq_attn_destroy(c)
     codebooks = 8 * 4 * Hkv * 256 * 128 * 2
     assert used <= codebooks + (16 << 20), used
+
+
+def _ratio(B, Hq, Hkv, lengths, M=64, dtype=torch.float16, recent=0):
+    """Time of a decode at the library's own choice over that of the same call with the reported splits asked for."""
+    gen = torch.Generator(device="cuda").manual_seed(B + Hq + M)
+    ctx = []
+    for splits in (0, None):
+        cfg = P.PQAttnConfig(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, n_subspaces=M, max_context=max(lengths), max_recent=recent,
+                             dtype=P.PQ_F16 if dtype == torch.float16 else P.PQ_F32,
+                             n_splits=P.pq_attn_n_splits(ctx[0]) if splits is None else splits)
+        ctx.append(P.pq_attn_create(cfg))
+    normal = lambda *shape: torch.randn(shape, generator=gen, device="cuda", dtype=torch.float32).to(dtype)
+    books = normal(2, Hkv, M, 256, 128 // M)
+    codes = torch.randint(0, 256, (2, P.pq_attn_codes_bytes(cfg)), generator=gen, device="cuda", dtype=torch.uint8)
+    q, out = normal(B, Hq, 128), torch.empty(B, Hq, 128, device="cuda")
+    n = torch.tensor(lengths, dtype=torch.int32, device="cuda")
+    rows = [None] * 3 if recent == 0 else [normal(B, Hkv, recent, 128), normal(B, Hkv, recent, 128), torch.full_like(n, recent)]
+    for c in ctx:
+        P.pq_attn_set_codebooks(c, books[0], books[1])
+    best = [float("inf")] * 2
+    begin, end = torch.cuda.Event(True), torch.cuda.Event(True)
+    for rep in range(8):                                    # in turn; the first round warms up
+        for k, c in enumerate(ctx):
+            begin.record()
+            for _ in range(60):
+                P.pq_attn_decode(c, q, codes[0], codes[1], n, None, None, *rows, 0.088, out)
+            end.record()
+            end.synchronize()
+            if rep:
+                best[k] = min(best[k], begin.elapsed_time(end))
+    for c in ctx:
+        P.pq_attn_destroy(c)
+    return best[0] / best[1]
+
+
+# the two sides do the same work, so what is allowed is a quarter of the time: the runs of one side differ by a few per cent
+
+@pytest.mark.parametrize("B,Hq,Hkv", [(63, 1, 1), (24, 1, 1), (48, 2, 2), (48, 8, 1), (30, 8, 2)])
+def test_few_heads_have_the_whole_chip(B, Hq, Hkv):
+    """Batches of few heads: the workgroups of a head are its share of the compute units, however many that are."""
+    assert _ratio(B, Hq, Hkv, [8192] * B) <= 1.25

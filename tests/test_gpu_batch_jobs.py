@@ -42,3 +42,10 @@ def test_batches_of_any_lengths(M, dtype, B, Hq, Hkv, longest, kind):
             err, norm = np.abs(out - ref).max(), np.linalg.norm(ref)
             # fp32 sums against double: 1e-6 relative, a few 1e-6 absolute on values of order one
             assert np.isfinite(out).all() and err <= 2e-5 and np.linalg.norm(out - ref) <= 1e-5 * norm, (call, err)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("B,Hq,Hkv", [(2, 1, 1), (3, 4, 1), (2, 2, 2)])
+def test_a_sequence_takes_no_more_splits_than_a_merge_holds(B, Hq, Hkv, dtype):
+    """More jobs per head (128, 256) than one sequence may have splits (64), and a sequence long enough to ask for more."""
+    test_batches_of_any_lengths(64, dtype, B, Hq, Hkv, 40000, "one long")
