@@ -81,7 +81,10 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
     // neighbours: the splits of a (sequence, query head), the query heads of its KV group, then the same
     // KV head of the other sequences (they load the same codebooks: once per XCD instead of once per sequence)
     uint32_t unit, split_u;
-    unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
+    if (BATCH == BATCH_DEAL)
+        unit_and_job(blockIdx.x, gridDim.x, (uint32_t)S_grid, (uint32_t)a.G, unit, split_u);
+    else
+        unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
     int split = (int)split_u;
     const uint32_t bkv = unit / (uint32_t)a.G;          // hkv * B + b (BATCH_DEAL, BATCH_WALK: hkv)
     const int gq = (int)(unit - bkv * (uint32_t)a.G);

@@ -101,7 +101,10 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
     const int S_grid = a.S;  // splits the grid was launched with (partials are laid out with this stride)
     // workgroups of one KV head are neighbours: (sequence, KV head, sub-group of G query heads, split)
     uint32_t unit_u, split_u;
-    unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit_u, split_u);
+    if (BATCH == BATCH_DEAL)
+        unit_and_job(blockIdx.x, gridDim.x, (uint32_t)S_grid, (uint32_t)a.n_sub, unit_u, split_u);
+    else
+        unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit_u, split_u);
     const int unit = (int)unit_u;
     int split = (int)split_u;
     const int n_sub = a.n_sub;                     // sub-groups per KV head

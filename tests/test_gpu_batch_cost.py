@@ -63,3 +63,8 @@ def _ratio(B, Hq, Hkv, lengths, M=64, dtype=torch.float16, recent=0):
 def test_few_heads_have_the_whole_chip(B, Hq, Hkv):
     """Batches of few heads: the workgroups of a head are its share of the compute units, however many that are."""
     assert _ratio(B, Hq, Hkv, [8192] * B) <= 1.25
+
+
+def test_workgroups_that_share_codes_are_neighbours():
+    """More query heads per KV head than one workgroup takes: those of the same job read the same codes out of one L2."""
+    assert _ratio(31, 8, 1, [4096] * 31, dtype=torch.float32) <= 1.25
