@@ -24,36 +24,38 @@ def test_contexts_of_a_batch_hold_one_partial_per_head_and_job(B, Hq, Hkv):
     assert used <= codebooks + (16 << 20), used
 
 
-def _ratio(B, Hq, Hkv, lengths, M=64, dtype=torch.float16, recent=0):
-    """Time of a decode at the library's own choice over that of the same call with the reported splits asked for."""
+def _ratio(B, Hq, Hkv, lengths, M=64, dtype=torch.float16, recent=0, layers=4):
+    """Time of a decode at the library's own choice over that of the same call with the reported splits asked for; each
+    side has `layers` contexts that take turns, as a model's layers do, with codebooks and codes of their own."""
     gen = torch.Generator(device="cuda").manual_seed(B + Hq + M)
-    ctx = []
-    for splits in (0, None):
-        cfg = P.PQAttnConfig(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, n_subspaces=M, max_context=max(lengths), max_recent=recent,
-                             dtype=P.PQ_F16 if dtype == torch.float16 else P.PQ_F32,
-                             n_splits=P.pq_attn_n_splits(ctx[0]) if splits is None else splits)
-        ctx.append(P.pq_attn_create(cfg))
+    cfg = P.PQAttnConfig(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, n_subspaces=M, max_context=max(lengths), max_recent=recent,
+                         dtype=P.PQ_F16 if dtype == torch.float16 else P.PQ_F32)
+    sides = [[P.pq_attn_create(cfg) for _ in range(layers)]]
+    cfg.n_splits = P.pq_attn_n_splits(sides[0][0])
+    sides.append([P.pq_attn_create(cfg) for _ in range(layers)])
     normal = lambda *shape: torch.randn(shape, generator=gen, device="cuda", dtype=torch.float32).to(dtype)
-    books = normal(2, Hkv, M, 256, 128 // M)
-    codes = torch.randint(0, 256, (2, P.pq_attn_codes_bytes(cfg)), generator=gen, device="cuda", dtype=torch.uint8)
+    codes = torch.randint(0, 256, (layers, 2, P.pq_attn_codes_bytes(cfg)), generator=gen, device="cuda", dtype=torch.uint8)
     q, out = normal(B, Hq, 128), torch.empty(B, Hq, 128, device="cuda")
     n = torch.tensor(lengths, dtype=torch.int32, device="cuda")
     rows = [None] * 3 if recent == 0 else [normal(B, Hkv, recent, 128), normal(B, Hkv, recent, 128), torch.full_like(n, recent)]
-    for c in ctx:
-        P.pq_attn_set_codebooks(c, books[0], books[1])
+    for side in sides:
+        for c in side:
+            P.pq_attn_set_codebooks(c, normal(Hkv, M, 256, 128 // M), normal(Hkv, M, 256, 128 // M))
     best = [float("inf")] * 2
     begin, end = torch.cuda.Event(True), torch.cuda.Event(True)
     for rep in range(8):                                    # in turn; the first round warms up
-        for k, c in enumerate(ctx):
+        for k, side in enumerate(sides):
             begin.record()
-            for _ in range(60):
-                P.pq_attn_decode(c, q, codes[0], codes[1], n, None, None, *rows, 0.088, out)
+            for i in range(60):
+                j = i % layers
+                P.pq_attn_decode(side[j], q, codes[j][0], codes[j][1], n, None, None, *rows, 0.088, out)
             end.record()
             end.synchronize()
             if rep:
                 best[k] = min(best[k], begin.elapsed_time(end))
-    for c in ctx:
-        P.pq_attn_destroy(c)
+    for side in sides:
+        for c in side:
+            P.pq_attn_destroy(c)
     return best[0] / best[1]
 
 
@@ -68,3 +70,9 @@ def test_few_heads_have_the_whole_chip(B, Hq, Hkv):
 def test_workgroups_that_share_codes_are_neighbours():
     """More query heads per KV head than one workgroup takes: those of the same job read the same codes out of one L2."""
     assert _ratio(31, 8, 1, [4096] * 31, dtype=torch.float32) <= 1.25
+
+
+@pytest.mark.parametrize("B", [2, 3])
+def test_a_heads_workgroups_share_an_xcd_in_any_grid(B):
+    """28 heads have 9 workgroups each: 252 of them, which 8 does not divide."""
+    assert _ratio(B, 28, 28, [200] * B) <= 1.25
