@@ -80,19 +80,24 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
     const int S_grid = a.S;  // splits the grid was launched with (partials are laid out with this stride)
     // neighbours: the splits of a (sequence, query head), the query heads of its KV group, then the same
     // KV head of the other sequences (they load the same codebooks: once per XCD instead of once per sequence)
-    uint32_t unit, split_u;
-    if (BATCH == BATCH_DEAL)
-        unit_and_job(blockIdx.x, gridDim.x, (uint32_t)S_grid, (uint32_t)a.G, unit, split_u);
-    else
-        unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
-    int split = (int)split_u;
-    const uint32_t bkv = unit / (uint32_t)a.G;          // hkv * B + b (BATCH_DEAL, BATCH_WALK: hkv)
-    const int gq = (int)(unit - bkv * (uint32_t)a.G);
-    const int hkv = BATCH == BATCH_DEAL || BATCH == BATCH_WALK ? (int)bkv : (int)(bkv / (uint32_t)a.B);
-    int b = BATCH == BATCH_WALK   ? split
-            : BATCH == BATCH_DEAL ? batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u)
-                                  : (int)(bkv - (uint32_t)hkv * (uint32_t)a.B);
-    const int hq = hkv * a.G + gq;
+    uint32_t hkv_u, gq_u, b_u, split_u = 0;
+    if (BATCH == BATCH_ORDER) {
+        unit_and_place(blockIdx.x, (uint32_t)a.B, (uint32_t)a.Hkv, (uint32_t)a.G, hkv_u, gq_u, b_u);
+    } else {
+        uint32_t unit;
+        if (BATCH == BATCH_DEAL)
+            unit_and_job(blockIdx.x, gridDim.x, (uint32_t)S_grid, (uint32_t)a.G, unit, split_u);
+        else
+            unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
+        const uint32_t bkv = unit / (uint32_t)a.G;      // hkv * B + b (BATCH_DEAL, BATCH_WALK: hkv)
+        gq_u = unit - bkv * (uint32_t)a.G;
+        hkv_u = BATCH == BATCH_DEAL || BATCH == BATCH_WALK ? bkv : bkv / (uint32_t)a.B;
+        b_u = BATCH == BATCH_WALK   ? split_u
+              : BATCH == BATCH_DEAL ? (uint32_t)batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u)
+                                    : bkv - hkv_u * (uint32_t)a.B;
+    }
+    int split = (int)split_u, b = (int)b_u;
+    const int hkv = (int)hkv_u, hq = hkv * a.G + (int)gq_u;
 
     // The lengths are requested first and taken out of their registers only after the table loads
     // below have been issued.  The loads go through lane_zero(), which the compiler cannot see

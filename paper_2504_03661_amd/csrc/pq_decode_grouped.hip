@@ -100,19 +100,24 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
     asm volatile("" ::"s"(max_context), "s"(max_recent));  // (read with the other arguments, not behind the barrier)
     const int S_grid = a.S;  // splits the grid was launched with (partials are laid out with this stride)
     // workgroups of one KV head are neighbours: (sequence, KV head, sub-group of G query heads, split)
-    uint32_t unit_u, split_u;
-    if (BATCH == BATCH_DEAL)
-        unit_and_job(blockIdx.x, gridDim.x, (uint32_t)S_grid, (uint32_t)a.n_sub, unit_u, split_u);
-    else
-        unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit_u, split_u);
-    const int unit = (int)unit_u;
-    int split = (int)split_u;
     const int n_sub = a.n_sub;                     // sub-groups per KV head
-    // ... then the same KV head of the other sequences (same codebook images: once per XCD from memory)
-    const int hb = (int)((uint32_t)unit / (uint32_t)n_sub);  // hkv * B + b (BATCH_DEAL: hkv)
-    const int sub_group = unit - hb * n_sub;
-    const int hkv = BATCH == BATCH_DEAL ? hb : (int)((uint32_t)hb / (uint32_t)a.B);
-    int b = BATCH == BATCH_DEAL ? batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u) : hb - hkv * a.B;
+    uint32_t hkv_u, sub_u, b_u, split_u = 0;
+    if (BATCH == BATCH_ORDER) {
+        unit_and_place(blockIdx.x, (uint32_t)a.B, (uint32_t)a.Hkv, (uint32_t)n_sub, hkv_u, sub_u, b_u);
+    } else {
+        uint32_t unit;
+        if (BATCH == BATCH_DEAL)
+            unit_and_job(blockIdx.x, gridDim.x, (uint32_t)S_grid, (uint32_t)n_sub, unit, split_u);
+        else
+            unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
+        // ... then the same KV head of the other sequences (same codebook images: once per XCD from memory)
+        const uint32_t hb = unit / (uint32_t)n_sub;  // hkv * B + b (BATCH_DEAL: hkv)
+        sub_u = unit - hb * (uint32_t)n_sub;
+        hkv_u = BATCH == BATCH_DEAL ? hb : hb / (uint32_t)a.B;
+        b_u = BATCH == BATCH_DEAL ? (uint32_t)batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u) : hb - hkv_u * (uint32_t)a.B;
+    }
+    int split = (int)split_u, b = (int)b_u;
+    const int hkv = (int)hkv_u, sub_group = (int)sub_u;
     // the KV head's a.G query heads in n_sub sub-groups whose sizes differ by at most one (the first a.G % n_sub take
     // one more): this workgroup's heads are g_first .. g_first + G - 1, G = 2..4
     const int g_base = a.G / n_sub, g_rem = a.G - g_base * n_sub;

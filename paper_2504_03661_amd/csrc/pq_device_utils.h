@@ -190,6 +190,23 @@ __device__ inline void unit_and_job(uint32_t bid, uint32_t grid, uint32_t S, uin
     }
 }
 
+// ... BATCH_ORDER: one workgroup per sequence and query head (or group of them, n per KV head).  The (place, KV head) pairs,
+// place-major — the longest sequences of all heads first — are dealt to the XCDs one by one, and an XCD runs the n
+// workgroups of a pair, which read the same codes, in a row: 8 / gcd(8, Hkv) XCDs share a head, each has long and short
+// sequences.  (Head-major, a stretch of the units per XCD: one XCD had all the long sequences of a head that several
+// shared — 8 query heads of one KV head, fp32, 40 sequences of 1000 .. 10000 tokens 94 us, unranked 68, now 50 — and the
+// last heads' longest sequences began in the second round: 28 heads of 32 subspaces, 16 sequences 46 -> 39.)
+__device__ inline void unit_and_place(uint32_t bid, uint32_t B, uint32_t Hkv, uint32_t n, uint32_t &hkv, uint32_t &sub, uint32_t &place)
+{
+    const uint32_t pairs = B * Hkv, whole = (pairs & ~7u) * n;  // the last pairs % 8 as dealt
+    const bool row = bid < whole;
+    const uint32_t at = row ? bid >> 3 : bid - whole, step = at / n;
+    sub = at - step * n;
+    const uint32_t pair = row ? step * 8u + (bid & 7u) : (pairs & ~7u) + step;
+    place = pair / Hkv;
+    hkv = pair - place * Hkv;
+}
+
 // Sum over the batch of (cached tokens + recent rows), each clamped like the sequence's own lengths: lane l adds
 // sequences l, l + 64, ...; the loads go out with the workgroup's own lengths.  Only batches need it (the live
 // split count of a sequence follows its share of the batch's work).

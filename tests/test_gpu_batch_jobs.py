@@ -49,3 +49,12 @@ def test_batches_of_any_lengths(M, dtype, B, Hq, Hkv, longest, kind):
 def test_a_sequence_takes_no_more_splits_than_a_merge_holds(B, Hq, Hkv, dtype):
     """More jobs per head (128, 256) than one sequence may have splits (64), and a sequence long enough to ask for more."""
     test_batches_of_any_lengths(64, dtype, B, Hq, Hkv, 40000, "one long")
+
+
+@pytest.mark.parametrize("M,dtype,B,Hq,Hkv", [(64, "f32", 12, 28, 4), (64, "f32", 40, 8, 1), (64, "f32", 44, 8, 1), (32, "f16", 16, 20, 20),
+                                              (32, "f32", 18, 20, 20), (64, "f16", 33, 32, 4), (64, "f16", 60, 12, 3), (64, "f32", 13, 20, 20)])
+def test_one_workgroup_per_sequence_and_head_in_any_numbering(M, dtype, B, Hq, Hkv):
+    """Heads whose sequences lie on 1, 2 or 8 XCDs, one, two, three and more workgroups per KV head and sequence, pair counts
+    that 8 divides and does not."""
+    for kind in ("random", "powers"):
+        test_batches_of_any_lengths(M, dtype, B, Hq, Hkv, 150, kind)
