@@ -81,20 +81,22 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
     // neighbours: the splits of a (sequence, query head), the query heads of its KV group, then the same
     // KV head of the other sequences (they load the same codebooks: once per XCD instead of once per sequence)
     uint32_t hkv_u, gq_u, b_u, split_u = 0;
-    if (BATCH == BATCH_ORDER) {
-        unit_and_place(blockIdx.x, (uint32_t)a.B, (uint32_t)a.Hkv, (uint32_t)a.G, hkv_u, gq_u, b_u);
+    if constexpr (BATCH == BATCH_ORDER) {
+        unit_and_place(blockIdx.x, (uint32_t)a.B, (uint32_t)a.Hkv, (uint32_t)a.G, a.div, hkv_u, gq_u, b_u);
+    } else if constexpr (BATCH == BATCH_DEAL) {
+        unit_and_job(blockIdx.x, (uint32_t)a.Hkv, (uint32_t)S_grid, (uint32_t)a.G, a.div, hkv_u, gq_u, split_u);
+        b_u = (uint32_t)batch_guess(a.B, a.div, (int)split_u);
+    } else if constexpr (BATCH == BATCH_WALK) {
+        unit_and_walker(blockIdx.x, (uint32_t)a.Hq, (uint32_t)S_grid, a.div, hkv_u, split_u);
+        gq_u = 0;
+        b_u = split_u;
     } else {
         uint32_t unit;
-        if (BATCH == BATCH_DEAL)
-            unit_and_job(blockIdx.x, gridDim.x, (uint32_t)S_grid, (uint32_t)a.G, unit, split_u);
-        else
-            unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
-        const uint32_t bkv = unit / (uint32_t)a.G;      // hkv * B + b (BATCH_DEAL, BATCH_WALK: hkv)
+        unit_and_split(blockIdx.x, (uint32_t)(a.B * a.Hq), (uint32_t)S_grid, unit, split_u);
+        const uint32_t bkv = unit / (uint32_t)a.G;  // hkv * B + b
         gq_u = unit - bkv * (uint32_t)a.G;
-        hkv_u = BATCH == BATCH_DEAL || BATCH == BATCH_WALK ? bkv : bkv / (uint32_t)a.B;
-        b_u = BATCH == BATCH_WALK   ? split_u
-              : BATCH == BATCH_DEAL ? (uint32_t)batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u)
-                                    : bkv - hkv_u * (uint32_t)a.B;
+        hkv_u = bkv / (uint32_t)a.B;
+        b_u = bkv - hkv_u * (uint32_t)a.B;
     }
     int split = (int)split_u, b = (int)b_u;
     const int hkv = (int)hkv_u, hq = hkv * a.G + (int)gq_u;
@@ -158,7 +160,7 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
         const int n = clamp_to(n_vec, max_context), r = has_recent ? clamp_to(r_vec, max_recent) : 0;
         int mine;
         if constexpr (BATCH == BATCH_DEAL) {
-            const batch_job job = batch_deal(a.B, a.S, split, (uint32_t)n, (uint32_t)r, lane);
+            const batch_job job = batch_deal<F16 && NW == 16 ? 24 : 16, 8, NW == 16 ? 3 : 6>(a.B, a.S, a.div, split, (uint32_t)n, (uint32_t)r, lane);
             if (job.split >= job.S)
                 return;
             first_job = split - job.split;
@@ -797,20 +799,28 @@ hipError_t launch(const pq_decode_args &a, hipStream_t s)
 {
     const dim3 block(NW * 64);
     pq_decode_args aj = a;
-    aj.S = a.jobs > a.B ? a.jobs : 1;
+    aj.div.sub = pq_divisor(a.G);
     if constexpr (sizeof(T) == 2 && M == 64) {
         if (a.jobs < 0) {
             aj.S = -a.jobs;
+            aj.div.unit = pq_unit_divisor(a.Hq, aj.S);
             hipLaunchKernelGGL((pq_decode_whole_kernel<M, DS, T, NW, READ_ONCE, BATCH_WALK>), dim3(a.Hq * aj.S), block, 0, s, aj);
             return hipGetLastError();
         }
     }
-    if (a.jobs > a.B)
+    if (a.jobs > a.B) {
+        aj.S = a.jobs;
+        aj.div.unit = pq_unit_divisor(a.Hkv, (int64_t)a.jobs * a.G);
+        aj.div.even_jobs = (uint32_t)(a.jobs / a.B);
+        aj.div.even = pq_divisor(a.jobs / a.B);
         hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_DEAL>), dim3(a.Hq * a.jobs), block, 0, s, aj);
-    else if (a.jobs > 0)
+    } else if (a.jobs > 0) {
+        aj.S = 1;
+        aj.div.unit = pq_divisor(a.Hkv);
         hipLaunchKernelGGL((pq_decode_whole_kernel<M, DS, T, NW, READ_ONCE, BATCH_ORDER>), dim3(a.B * a.Hq), block, 0, s, aj);
-    else
+    } else {
         hipLaunchKernelGGL((pq_decode_kernel<M, DS, T, NW, READ_ONCE, BATCH_NONE>), dim3(a.B * a.Hq * a.S), block, 0, s, a);
+    }
     return hipGetLastError();
 }
 

@@ -102,19 +102,19 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
     // workgroups of one KV head are neighbours: (sequence, KV head, sub-group of G query heads, split)
     const int n_sub = a.n_sub;                     // sub-groups per KV head
     uint32_t hkv_u, sub_u, b_u, split_u = 0;
-    if (BATCH == BATCH_ORDER) {
-        unit_and_place(blockIdx.x, (uint32_t)a.B, (uint32_t)a.Hkv, (uint32_t)n_sub, hkv_u, sub_u, b_u);
+    if constexpr (BATCH == BATCH_ORDER) {
+        unit_and_place(blockIdx.x, (uint32_t)a.B, (uint32_t)a.Hkv, (uint32_t)n_sub, a.div, hkv_u, sub_u, b_u);
+    } else if constexpr (BATCH == BATCH_DEAL) {
+        unit_and_job(blockIdx.x, (uint32_t)a.Hkv, (uint32_t)S_grid, (uint32_t)n_sub, a.div, hkv_u, sub_u, split_u);
+        b_u = (uint32_t)batch_guess(a.B, a.div, (int)split_u);
     } else {
         uint32_t unit;
-        if (BATCH == BATCH_DEAL)
-            unit_and_job(blockIdx.x, gridDim.x, (uint32_t)S_grid, (uint32_t)n_sub, unit, split_u);
-        else
-            unit_and_split(blockIdx.x, gridDim.x, (uint32_t)S_grid, unit, split_u);
+        unit_and_split(blockIdx.x, (uint32_t)(a.B * a.Hkv * n_sub), (uint32_t)S_grid, unit, split_u);
         // ... then the same KV head of the other sequences (same codebook images: once per XCD from memory)
-        const uint32_t hb = unit / (uint32_t)n_sub;  // hkv * B + b (BATCH_DEAL: hkv)
+        const uint32_t hb = unit / (uint32_t)n_sub;  // hkv * B + b
         sub_u = unit - hb * (uint32_t)n_sub;
-        hkv_u = BATCH == BATCH_DEAL ? hb : hb / (uint32_t)a.B;
-        b_u = BATCH == BATCH_DEAL ? (uint32_t)batch_guess((uint32_t)a.B, (uint32_t)a.S, split_u) : hb - hkv_u * (uint32_t)a.B;
+        hkv_u = hb / (uint32_t)a.B;
+        b_u = hb - hkv_u * (uint32_t)a.B;
     }
     int split = (int)split_u, b = (int)b_u;
     const int hkv = (int)hkv_u, sub_group = (int)sub_u;
@@ -162,7 +162,7 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
         const int n = clamp_to(n_vec, max_context), r = has_recent ? clamp_to(r_vec, max_recent) : 0;
         int mine;
         if constexpr (BATCH == BATCH_DEAL) {
-            const batch_job job = batch_deal(a.B, a.S, split, (uint32_t)n, (uint32_t)r, lane);
+            const batch_job job = batch_deal<16, 32, 6>(a.B, a.S, a.div, split, (uint32_t)n, (uint32_t)r, lane);
             if (job.split >= job.S)
                 return;
             first_job = split - job.split;
@@ -581,11 +581,19 @@ template <int M> static hipError_t launch_grouped(const pq_decode_args &a, hipSt
 {
     const int heads = a.Hkv * a.n_sub;
     pq_decode_args aj = a;
-    aj.S = a.jobs > a.B ? a.jobs : 1;
-    if (a.jobs > a.B)
+    aj.div.sub = pq_divisor(a.n_sub);
+    if (a.jobs > a.B) {
+        aj.S = a.jobs;
+        aj.div.unit = pq_unit_divisor(a.Hkv, (int64_t)a.jobs * a.n_sub);
+        aj.div.even_jobs = (uint32_t)(a.jobs / a.B);
+        aj.div.even = pq_divisor(a.jobs / a.B);
         return launch_grouped<M, BATCH_DEAL>(aj, heads, s);
-    if (a.jobs > 0)
+    }
+    if (a.jobs > 0) {
+        aj.S = 1;
+        aj.div.unit = pq_divisor(a.Hkv);
         return launch_grouped<M, BATCH_ORDER>(aj, heads * a.B, s);
+    }
     return launch_grouped<M, BATCH_NONE>(a, heads * a.B, s);
 }
 

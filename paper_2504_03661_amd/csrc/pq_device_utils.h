@@ -148,12 +148,14 @@ __device__ inline int lds_grab(uint32_t lds_addr)
 // live workgroups of an oversubscribed grid whose surplus splits leave at once (8 launched splits, 1 live) sit 8
 // apart, and the dispatcher, which deals consecutive workgroups to the shader engines in turn, put them all on one
 // engine's compute units: 8 x 32 heads x 32K with 8 launched splits took 483 us instead of 165.
-__device__ inline void unit_and_split(uint32_t bid, uint32_t grid, uint32_t S, uint32_t &unit, uint32_t &split)
+//   BY: divides by n_units / 8 where 8 divides n_units, else by S
+template <typename BY>
+__device__ inline void unit_and_split(uint32_t bid, uint32_t n_units, uint32_t S, const BY &by, uint32_t &unit, uint32_t &split)
 {
-    const uint32_t n_units = grid / S;
+    const uint32_t xcd = bid & 7u;
     if ((n_units & 7u) == 0) {
-        const uint32_t per_xcd = n_units >> 3, xcd = bid & 7u, local = bid >> 3;
-        split = local / per_xcd;
+        const uint32_t per_xcd = n_units >> 3, local = bid >> 3;
+        split = by(local, per_xcd);
         uint32_t j = local - split * per_xcd;
         // ... and where the XCD's unit count is a power of two, the units are visited in a scrambled order (low 3
         // bits XOR the next 3): the long sequences of a ragged batch sit at a fixed stride in the unit numbering
@@ -168,42 +170,59 @@ __device__ inline void unit_and_split(uint32_t bid, uint32_t grid, uint32_t S, u
         // sequence of 10000 tokens 15.8 us, now 12.6).  Only workgroups with a sequence each stay as dealt: they share
         // less, and neighbouring sequences of a ragged batch are better spread (5 heads, 65 sequences of 500 .. 30000
         // tokens: 149 us, un-dealt 162).
-        const uint32_t xcd = bid & 7u, extra = grid & 7u;
+        const uint32_t grid = n_units * S, extra = grid & 7u;
         const uint32_t logical = S == 1u ? bid : xcd * (grid >> 3) + (xcd < extra ? xcd : extra) + (bid >> 3);
-        unit = logical / S;
+        unit = by(logical, S);
         split = logical - unit * S;
     }
 }
 
-// ... of a KV head's `n` query heads (or groups of them), BATCH_DEAL: unit = KV head x n + query head, split = job of it.
+__device__ inline void unit_and_split(uint32_t bid, uint32_t n_units, uint32_t S, uint32_t &unit, uint32_t &split)
+{
+    unit_and_split(bid, n_units, S, [](uint32_t x, uint32_t d) { return x / d; }, unit, split);
+}
+
+// The numberings of a batch divide by multiplying (pq_batch_divisors, set by the host): the compiler divides uniform
+// numbers on the vector ALU, some 25 instructions of every wavefront before its first load — two or three such divisions
+// cost a workgroup of 16 wavefronts 0.4 us.
+__device__ inline uint32_t divided(uint32_t x, uint32_t by) { return by != 0u ? __umulhi(x, by) : x; }
+
+// BATCH_WALK: unit = query head (one per KV head), split = workgroup of it
+__device__ inline void unit_and_walker(uint32_t bid, uint32_t n_units, uint32_t S, const pq_batch_divisors &d, uint32_t &unit,
+                                       uint32_t &walker)
+{
+    unit_and_split(bid, n_units, S, [&](uint32_t x, uint32_t) { return divided(x, d.unit); }, unit, walker);
+}
+
+// BATCH_DEAL: job `job` of query head (or group of them) `sub` of the n per KV head.
 // The n workgroups that read the same codes — the same job of each query head — are neighbours and share an XCD's L2, as
 // the query heads of a sequence are in the other numbering.  (With a head's jobs in a row they were S workgroups apart:
 // 8 query heads of one KV head, 31 sequences of 4K tokens, fp32, 1.39 times the time of splits per sequence, 1.13 so; 12
 // of 30K, fp16, 1.06 and 0.98 times.)
-__device__ inline void unit_and_job(uint32_t bid, uint32_t grid, uint32_t S, uint32_t n, uint32_t &unit, uint32_t &job)
+__device__ inline void unit_and_job(uint32_t bid, uint32_t Hkv, uint32_t S, uint32_t n, const pq_batch_divisors &d, uint32_t &hkv,
+                                    uint32_t &sub, uint32_t &job)
 {
-    unit_and_split(bid, grid, S * n, unit, job);
-    if (n > 1u) {
-        const uint32_t both = job;
-        job = both / n;
-        unit = unit * n + (both - job * n);
-    }
+    uint32_t both;
+    unit_and_split(bid, Hkv, S * n, [&](uint32_t x, uint32_t) { return divided(x, d.unit); }, hkv, both);
+    job = divided(both, d.sub);
+    sub = both - job * n;
 }
 
-// ... BATCH_ORDER: one workgroup per sequence and query head (or group of them, n per KV head).  The (place, KV head) pairs,
+// BATCH_ORDER: one workgroup per sequence and query head (or group of them, n per KV head).  The (place, KV head) pairs,
 // place-major — the longest sequences of all heads first — are dealt to the XCDs one by one, and an XCD runs the n
 // workgroups of a pair, which read the same codes, in a row: 8 / gcd(8, Hkv) XCDs share a head, each has long and short
 // sequences.  (Head-major, a stretch of the units per XCD: one XCD had all the long sequences of a head that several
 // shared — 8 query heads of one KV head, fp32, 40 sequences of 1000 .. 10000 tokens 94 us, unranked 68, now 50 — and the
 // last heads' longest sequences began in the second round: 28 heads of 32 subspaces, 16 sequences 46 -> 39.)
-__device__ inline void unit_and_place(uint32_t bid, uint32_t B, uint32_t Hkv, uint32_t n, uint32_t &hkv, uint32_t &sub, uint32_t &place)
+__device__ inline void unit_and_place(uint32_t bid, uint32_t B, uint32_t Hkv, uint32_t n, const pq_batch_divisors &d, uint32_t &hkv,
+                                      uint32_t &sub, uint32_t &place)
 {
     const uint32_t pairs = B * Hkv, whole = (pairs & ~7u) * n;  // the last pairs % 8 as dealt
     const bool row = bid < whole;
-    const uint32_t at = row ? bid >> 3 : bid - whole, step = at / n;
+    const uint32_t at = row ? bid >> 3 : bid - whole, step = divided(at, d.sub);
     sub = at - step * n;
     const uint32_t pair = row ? step * 8u + (bid & 7u) : (pairs & ~7u) + step;
-    place = pair / Hkv;
+    place = divided(pair, d.unit);
     hkv = pair - place * Hkv;
 }
 
@@ -244,7 +263,7 @@ template <typename A> __device__ inline uint32_t live_split_cap(const A &a, int 
 // Which workgroups a batch's sequences get ("0 = choose" splits, 2..64 sequences); every workgroup reads all lengths and
 // works it out in the same way.  Work is counted in 64-token blocks and 16 recent rows.
 //   BATCH_DEAL   (the head's share of the compute units is larger than the batch: that many workgroups per head)
-//       sequence b gets ceil(work / T) of them, at most PQ_MAX_SPLITS, T the smallest trial size whose sum fits, so that
+//       sequence b gets ceil(work / T) of them, no more than pay, T the smallest trial size whose sum fits, so that
 //       no workgroup has much more than its share, whatever the lengths (a fixed number of splits per sequence leaves the longest sequence's
 //       workgroups the last ones by far: 32 heads, three sequences of 30000, 15256 and 512 tokens 59.6 -> 39.1 us; 32
 //       query / 8 KV heads, eight sequences of 2.5K .. 20K: 33 -> 28 us).
@@ -286,35 +305,76 @@ __device__ inline uint32_t wave_scan(uint32_t x)
 }
 
 // BATCH_DEAL: the sequence that job j has if all lengths are equal (its q is requested before the lengths are there)
-__device__ inline int batch_guess(uint32_t B, uint32_t jobs, uint32_t j)
+__device__ inline int batch_guess(int B, const pq_batch_divisors &d, int j)
 {
-    const uint32_t b = j / (jobs / B);
-    return (int)(b < B ? b : B - 1u);
+    const int b = (int)divided((uint32_t)j, d.even);
+    return b < B ? b : B - 1;
 }
 
 __device__ inline uint32_t batch_work(uint32_t n, uint32_t r) { return ((n + 63u) >> 6) + ((r + 15u) >> 4); }
 
-// BATCH_DEAL: job j of `jobs` (n, r: clamped lengths of sequence `lane`; lanes beyond the batch: anything)
-__device__ inline batch_job batch_deal(int B, int jobs, int j, uint32_t n, uint32_t r, int lane)
+// BATCH_DEAL: job j of `jobs` (n, r: clamped lengths of sequence `lane`; lanes beyond the batch: anything).  WHOLE: blocks
+// below which a sequence has one workgroup; AT_ONCE: partials that the kernel's merge loads in one round trip; ROOT: see below.
+template <int WHOLE, int AT_ONCE, int ROOT>
+__device__ inline batch_job batch_deal(int B, int jobs, const pq_batch_divisors &d, int j, uint32_t n, uint32_t r, int lane)
 {
     const bool in = lane < B;
     const uint32_t work = in ? batch_work(n, r) : 0u;
+    // The splits that pay.  Exchanging partials costs 1 .. 3 us and the merge another round trip for every AT_ONCE of them,
+    // a block of the scan 0.15 us.  Measured on one sequence: 16 heads of 64 subspaces, 12 blocks 7.5 us, split in two 7.8,
+    // 16 blocks 8.6 and 8.0 (32 subspaces, 16 wavefronts: 8.9 and 9.4, 24 blocks 9.6 and 9.3; 32 query / 8 KV heads, 12
+    // blocks 10.7 and 12.0, 16 blocks in four 11.8 and 11.3); the best number from there about ROOT / 4 times the square root of
+    // the blocks, ROOT = 6 (4 heads: 8 splits of 2K tokens 7.4 us; 16 of 8K 8.5, 32 10.1; 24 of 16K 10.2, 64 13.7; 48 of 64K
+    // 15.4, 64 16.1), 3 for the per-head kernels of 16 wavefronts (32 subspaces: 6 of 8K 10.6, 16 11.9; 12 of 16K 12.2).
+    const uint32_t root = (uint32_t)(0.25f * (float)ROOT * __builtin_amdgcn_sqrtf((float)work));
+    const uint32_t paying = root < (uint32_t)AT_ONCE ? (uint32_t)AT_ONCE : root < PQ_MAX_SPLITS ? root : PQ_MAX_SPLITS;
+    const uint32_t most = work < (uint32_t)WHOLE ? 1u : paying;
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)work);
+    if (__builtin_amdgcn_ballot_w64(most > 1u) == 0 ||
+        __builtin_amdgcn_ballot_w64(in && (work > w0 + w0 / 8u || work < w0 - w0 / 8u)) == 0) {
+        // nothing to cut, or lengths within an eighth: the same number of jobs for all, at least 4 blocks each
+        const int b = batch_guess(B, d, j);
+        const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)work, b), by_4 = (mine + 3u) >> 2;
+        uint32_t splits = (uint32_t)__builtin_amdgcn_readlane((int)most, b);
+        splits = splits < d.even_jobs ? splits : d.even_jobs;
+        splits = splits > 1u && splits > by_4 ? by_4 : splits;
+        return {b, j - b * (int)d.even_jobs, (int)splits};
+    }
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(work), 63);
-    // lane i tries T = 2^(i / 10.5) x the even share (at least 4 blocks): steps of 7 %, the last one 64 shares, which fits:
-    // jobs / 64 workgroups beyond one per sequence at most; in floats, the same in every workgroup
+    // T is 2^(i / 10.5) x the even share (at least 4 blocks), i the first of 0 .. 63 whose sum fits: steps of 7 %, the last
+    // one 64 shares, which fits (jobs / 64 workgroups beyond one per sequence at most).  In floats, the same in every
+    // workgroup.
     const float share = (float)total / (float)jobs;
     const float least = share > 4.f ? share : 4.f;
-    const float inv = __builtin_amdgcn_rcpf(least * __builtin_amdgcn_exp2f((float)lane * (6.0f / 63.0f)));
-    const auto splits_of = [](uint32_t w, float inv_t) {
-        const uint32_t more = (uint32_t)((float)(w > 0u ? w - 1u : 0u) * inv_t);
-        return 1u + (more < PQ_MAX_SPLITS - 1u ? more : PQ_MAX_SPLITS - 1u);
+    const float beyond = (float)(work > 0u ? work - 1u : 0u);
+    const auto size_inv = [&](int i) { return __builtin_amdgcn_rcpf(least * __builtin_amdgcn_exp2f((float)i * (6.0f / 63.0f))); };
+    const auto splits_of = [](float more, uint32_t limit, float inv) {
+        const uint32_t splits = 1u + (uint32_t)(more * inv);
+        return splits < limit ? splits : limit;
     };
-    uint32_t sum = 0;
-    for (int b = 0; b < B; ++b)
-        sum += splits_of((uint32_t)__builtin_amdgcn_readlane((int)work, b), inv);
-    const uint64_t fits = __builtin_amdgcn_ballot_w64(sum <= (uint32_t)jobs);
-    const float chosen = fits != 0 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv), __builtin_ctzll(fits))) : 0.f;
-    const uint32_t mine = in ? splits_of(work, chosen) : 0u;
+    int trial = 0;
+    if (B <= 24) {  // a lane per trial, all sequences in turn
+        const float inv = size_inv(lane);
+        uint32_t sum = 0;
+#pragma unroll 4
+        for (int b = 0; b < B; ++b)
+            sum += splits_of(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(beyond), b)),
+                             (uint32_t)__builtin_amdgcn_readlane((int)most, b), inv);
+        const uint64_t fits = __builtin_amdgcn_ballot_w64(sum <= (uint32_t)jobs) | 1ull << 63;
+        trial = __builtin_ctzll(fits);
+    } else {
+        // a lane per sequence, three rounds of three trials whose latencies overlap, two sums (each at most 64 x 64) in one
+        // scan (4 heads x 1000 tokens, against fixed splits: 63 sequences 1.19 with the loop, 1.08 so; 10 sequences 1.03, 1.09)
+#pragma unroll
+        for (int step = 16; step > 0; step >>= 2) {
+            const auto at = [&](int i) { return in ? splits_of(beyond, most, size_inv(trial + i * step - 1)) : 0u; };
+            const uint32_t sums = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(at(1) | at(2) << 16), 63);
+            const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(at(3)), 63);
+            const uint32_t fit = (uint32_t)jobs;
+            trial += ((sums & 0xffffu) > fit ? step : 0) + ((sums >> 16) > fit ? step : 0) + (last > fit ? step : 0);
+        }
+    }
+    const uint32_t mine = in ? splits_of(beyond, most, size_inv(trial)) : 0u;
     const uint32_t upto = wave_scan(mine);
     const uint32_t first = in ? upto - mine : ~0u;
     const int b = __builtin_popcountll(__builtin_amdgcn_ballot_w64(first <= (uint32_t)j)) - 1;

@@ -118,6 +118,21 @@ struct pq_attn_ctx {
                           // follow the sequences' lengths (choose_jobs in pq_api.hip); 0: splits per sequence
 };
 
+// What the numberings of a batch's workgroups divide by: for a divisor d above 1 the multiplier m = ceil(2^32 / d), with which
+// x / d is the high half of x m for every x with x d < 2^32; 0 for d = 1.  (Workgroup numbers are below 2^20, divisors
+// below 2^10 here.)
+struct pq_batch_divisors {
+    uint32_t unit;       // BATCH_DEAL, BATCH_WALK: as in unit_and_split; BATCH_ORDER: KV heads
+    uint32_t sub;        // query heads (or groups of them) per KV head
+    uint32_t even;       // BATCH_DEAL: even_jobs
+    uint32_t even_jobs;  // BATCH_DEAL: jobs of a sequence if all get the same number
+};
+
+inline uint32_t pq_divisor(int64_t d) { return d > 1 ? (uint32_t)((((int64_t)1 << 32) + d - 1) / d) : 0u; }
+
+// divisors of unit_and_split for n_units units of S workgroups each
+inline uint32_t pq_unit_divisor(int64_t n_units, int64_t S) { return pq_divisor(n_units % 8 == 0 ? n_units / 8 : S); }
+
 struct pq_decode_args {
     const void *q;
     const uint8_t *k_codes, *v_codes;
@@ -134,6 +149,7 @@ struct pq_decode_args {
     int n_sub;             // ... and the sub-groups a KV head's G query heads are cut into: ceil(G / 4) groups whose
                            // sizes differ by at most one (7 = 4 + 3, 5 = 3 + 2, 10 = 4 + 3 + 3)
     int jobs;              // pq_attn_ctx::jobs
+    pq_batch_divisors div;
     int max_context, max_recent;
     int n_cu;              // compute units of the device (the live split count of a batch's sequences follows it)
     int64_t head_stride;  // bytes of one (sequence, KV head) in a code tensor

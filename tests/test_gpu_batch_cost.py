@@ -59,7 +59,7 @@ def _ratio(B, Hq, Hkv, lengths, M=64, dtype=torch.float16, recent=0, layers=4):
     return best[0] / best[1]
 
 
-# the two sides do the same work, so what is allowed is a tenth or a quarter of the time: the runs of one side differ by a few per cent
+# the two sides do the same work, so what is allowed is a tenth to a quarter of the time: the runs of one side differ by a few per cent
 
 @pytest.mark.parametrize("B,Hq,Hkv", [(63, 1, 1), (24, 1, 1), (48, 2, 2), (48, 8, 1), (30, 8, 2)])
 def test_few_heads_have_the_whole_chip(B, Hq, Hkv):
@@ -86,3 +86,10 @@ def _spread(lo, hi, n):
 def test_the_long_sequences_of_a_batch_are_spread_over_the_xcds(B, Hq, Hkv):
     """A KV head whose sequences lie on several XCDs, one workgroup each, longest first."""
     assert _ratio(B, Hq, Hkv, _spread(1000, 10000, B), dtype=torch.float32) <= 1.1
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,lo,hi", [(5, 32, 8, 30, 200), (63, 8, 1, 60, 60), (2, 4, 4, 500, 16000), (63, 4, 4, 1000, 1000)])
+def test_dealing_costs_little_where_it_gains_little(B, Hq, Hkv, lo, hi):
+    """Short sequences keep one workgroup, a long one gets no more splits than its merge is worth, equal lengths are cut
+    without a search."""
+    assert _ratio(B, Hq, Hkv, _spread(lo, hi, B)) <= 1.15
