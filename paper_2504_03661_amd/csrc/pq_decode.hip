@@ -417,12 +417,15 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
         const u32x4 *vimg = (const u32x4 *)((const float *)a.vcb_packed + (int64_t)hkv * 256 * PQ_HEAD_DIM);
         const uint32_t vcol32 = (uint32_t)(sub * DS * 4);
         // the table again, for the chunks after the first (the prologue's steps in one go)
+        // (here and below the addresses are worked out where they are used: kept through the scan they spill)
         auto rebuild_table = [&]() {
+            int row0_now = row0;
+            asm volatile("" : "+v"(row0_now));
 #pragma unroll
             for (int k = 0; k < PASSES; ++k)
 #pragma unroll
                 for (int v = 0; v < NV; ++v)
-                    kraw[k][v] = *(const u32x4 *)(kcb + ((row0 + k * ROWS_PER_PASS) * PQ_HEAD_DIM + e0) * sizeof(T) + v * 16);
+                    kraw[k][v] = *(const u32x4 *)(kcb + ((row0_now + k * ROWS_PER_PASS) * PQ_HEAD_DIM + e0) * sizeof(T) + v * 16);
 #pragma unroll
             for (int v = 0; v < NV; ++v)
                 qraw[v] = *(const u32x4 *)((const char *)a.q + (((int64_t)b * a.Hq + hq) * PQ_HEAD_DIM + e0) * sizeof(T) + v * 16);
@@ -527,15 +530,17 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
             cur = c0 + wave;
             load_v(vbuf[0], cur < c1 ? cur : c0, cur < c1);
             __syncthreads();  // nobody reads the table any more
+            int tid_now = tid;
+            asm volatile("" : "+v"(tid_now));
 #pragma unroll
             for (int h = 0; h < IMG_VEC; h += 8) {
                 u32x4 t[8];
 #pragma unroll
                 for (int v = 0; v < 8; ++v)
-                    t[v] = vimg[tid + (h + v) * (NW * 64)];
+                    t[v] = vimg[tid_now + (h + v) * (NW * 64)];
 #pragma unroll
                 for (int v = 0; v < 8; ++v)
-                    *(lds_u32x4 *)(lbase + (tid + (h + v) * (NW * 64)) * 16) = t[v];
+                    *(lds_u32x4 *)(lbase + (tid_now + (h + v) * (NW * 64)) * 16) = t[v];
             }
             __syncthreads();
             // ---- phase 2: softmax and value pass over the same blocks
