@@ -170,10 +170,10 @@ __device__ __forceinline__ void decode_workgroup(const pq_decode_args &a)
         } else if constexpr (BATCH == BATCH_WALK) {
             n_of = n;
             r_of = r;
-            rank_of = batch_rank(a.B, (uint32_t)n, (uint32_t)r, lane);
+            rank_of = batch_rank<0>(a.B, (uint32_t)n, (uint32_t)r, lane);
             mine = batch_of_rank(rank_of, split);
         } else {
-            mine = batch_of_rank(batch_rank(a.B, (uint32_t)n, (uint32_t)r, lane), b);
+            mine = batch_of_rank(batch_rank<20>(a.B, (uint32_t)n, (uint32_t)r, lane), b);
         }
         N = __builtin_amdgcn_readlane(n, mine);
         R = __builtin_amdgcn_readlane(r, mine);

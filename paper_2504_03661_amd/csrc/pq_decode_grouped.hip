@@ -170,7 +170,7 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
             S_job = job.S;
             mine = job.b;
         } else {
-            mine = batch_of_rank(batch_rank(a.B, (uint32_t)n, (uint32_t)r, lane), b);
+            mine = batch_of_rank(batch_rank<20>(a.B, (uint32_t)n, (uint32_t)r, lane), b);
         }
         N = __builtin_amdgcn_readlane(n, mine);
         R = __builtin_amdgcn_readlane(r, mine);

@@ -267,12 +267,14 @@ template <typename A> __device__ inline uint32_t live_split_cap(const A &a, int 
 //       no workgroup has much more than its share, whatever the lengths (a fixed number of splits per sequence leaves the longest sequence's
 //       workgroups the last ones by far: 32 heads, three sequences of 30000, 15256 and 512 tokens 59.6 -> 39.1 us; 32
 //       query / 8 KV heads, eight sequences of 2.5K .. 20K: 33 -> 28 us).
-//   BATCH_ORDER  (other kernels: one workgroup per sequence and head, more than one round of them but at most two) a head's
+//   BATCH_ORDER  (other kernels: one workgroup per sequence and head, more than one round of them but at most two) the
 //       longest sequences come first: a long one that starts in the second round would run alone (32 query / 8 KV heads,
-//       40 sequences of 200 .. 8000: 61 -> 49 us).  Ranking 64
-//       lengths and fetching the query behind them costs a workgroup 1.5 us, so lengths within a quarter of the first
-//       one's stay in their order, and with more rounds, where the last one matters less, nothing is ranked (32 heads,
-//       64 sequences of 3000 .. 4096: 181 us, ranked 190; of 97 .. 4001: 133 us, ranked 134).
+//       40 sequences of 200 .. 8000: 61 -> 49 us).  Ranking 64 lengths and fetching the query behind them costs a workgroup
+//       1.5 us, so lengths within a quarter of the first one's stay in their order, and so does a batch without a sequence
+//       of 20 blocks (63 sequences, 32 query / 8 KV heads, of 30 .. 200 tokens 20.0 us, 16.5 unranked; of 300 .. 1000 27.2
+//       and 25.5; of 200 .. 1500 29.5 and 28.3, but 7 of 56 heads 16.9 and 18.3); with more rounds, where the last one
+//       matters less, nothing is ranked (32 heads, 64 sequences of 3000 .. 4096: 181 us, ranked 190; of 97 .. 4001: 133 us,
+//       ranked 134).
 //   BATCH_WALK   (the per-head kernel, more sequences than the head's share of the compute units) as many workgroups per
 //       head as the chip holds at once; workgroup w walks whole sequences, those of rank w, 2 S - 1 - w, 2 S + w, ... by
 //       length.  What a workgroup pays before its first block — 4 us: launch, lengths, 128 KiB of codebook images through
@@ -382,13 +384,16 @@ __device__ inline batch_job batch_deal(int B, int jobs, const pq_batch_divisors 
 }
 
 // Rank of sequence `lane` by length, the longest first, equal ones by their number; lengths within a quarter of the
-// first one's are ranked by number alone.  Lanes beyond the batch: 64.
+// first one's are ranked by number alone, and so are those of a batch without a sequence of SHORT blocks.  Lanes beyond the
+// batch: 64.
+template <uint32_t SHORT>
 __device__ inline int batch_rank(int B, uint32_t n, uint32_t r, int lane)
 {
     const bool in = lane < B;
     const uint32_t work = in ? batch_work(n, r) : 0u;  // below 2^21
     const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)work);
-    if (__builtin_amdgcn_ballot_w64(in && (work > w0 + w0 / 4u || work < w0 - w0 / 4u)) == 0)
+    if (__builtin_amdgcn_ballot_w64(in && (work > w0 + w0 / 4u || work < w0 - w0 / 4u)) == 0 ||
+        (SHORT > 0 && __builtin_amdgcn_ballot_w64(work >= SHORT) == 0))
         return in ? lane : 64;
     const uint32_t key = in ? (work << 6) | (uint32_t)(63 - lane) : 0u;
     int rank = 0;

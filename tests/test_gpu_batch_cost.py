@@ -93,3 +93,8 @@ def test_dealing_costs_little_where_it_gains_little(B, Hq, Hkv, lo, hi):
     """Short sequences keep one workgroup, a long one gets no more splits than its merge is worth, equal lengths are cut
     without a search."""
     assert _ratio(B, Hq, Hkv, _spread(lo, hi, B)) <= 1.15
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,M", [(63, 32, 8, 64), (15, 32, 32, 32)])
+def test_short_sequences_are_not_ranked(B, Hq, Hkv, M):
+    assert _ratio(B, Hq, Hkv, _spread(30, 200, B), M=M) <= 1.1
