@@ -67,6 +67,7 @@ __global__ __launch_bounds__(F12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     __shared__ __attribute__((aligned(16))) unsigned char arow[PQ12_CENTROIDS * F12_ROW];
     __shared__ uint32_t xchg[SPLIT ? F12_WAVES * 64 : 1];  // SPLIT: per wavefront and token
     __shared__ int any_bad;
+    __shared__ float wave_c_max[F12_WAVES];
     typedef pq_filter_token<4, _Float16> token;
     typedef token::operand operand;
 
@@ -87,14 +88,31 @@ __global__ __launch_bounds__(F12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
     uint16_t *out = which ? out1 : out0;
 
     // ---- A rows of the 4096 centroids
+    constexpr int PER_THREAD = PQ12_CENTROIDS / (F12_WAVES * 64);
+    f16x4 y[PER_THREAD];
+    float c_max = 0.f;
+#pragma unroll
+    for (int r = 0; r < PER_THREAD; ++r) {
+        y[r] = __builtin_bit_cast(f16x4, *(const u32x2e *)(cb + (tid + r * (F12_WAVES * 64)) * 4));
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            c_max = fmaxf(c_max, fabsf((float)y[r][j]));
+    }
+    c_max = pq_filter_wave_max(c_max);
+    if (lane == 0)
+        wave_c_max[wave] = c_max;
     if (tid == 0)
         any_bad = 0;
     __syncthreads();
+#pragma unroll
+    for (int w = 0; w < F12_WAVES; ++w)
+        c_max = fmaxf(c_max, wave_c_max[w]);
+    const float scale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pq_filter_scale<_Float16>(c_max))));
     bool cb_bad = false;
-    for (int c = tid; c < PQ12_CENTROIDS; c += F12_WAVES * 64) {
-        const f16x4 v = __builtin_bit_cast(f16x4, *(const u32x2e *)(cb + c * 4));
-        const _Float16 y[4] = {v[0], v[1], v[2], v[3]};
-        pq_filter_build_row<4>(y, 1.f, arow + c * F12_ROW, cb_bad);
+#pragma unroll
+    for (int r = 0; r < PER_THREAD; ++r) {
+        const _Float16 c[4] = {y[r][0], y[r][1], y[r][2], y[r][3]};
+        pq_filter_build_row<4>(c, scale, arow + (tid + r * (F12_WAVES * 64)) * F12_ROW, cb_bad);
     }
     if (cb_bad)
         any_bad = 1;
@@ -122,7 +140,7 @@ __global__ __launch_bounds__(F12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
             f16x4, *(const u32x2e *)(x + ((((int64_t)b * Hkv + hkv) * x_head_stride + t) * PQ_HEAD_DIM + i * 4)));
         const _Float16 xv[4] = {v[0], v[1], v[2], v[3]};
         token tok;
-        tok.set(xv, 1.f);
+        tok.set(xv, scale);
 
         int code = 0;
         double bd = __builtin_huge_val();

@@ -68,6 +68,9 @@ template <> __device__ inline double widen<float>(const void *p, int64_t i)
 // v(c) >= off - |x|^2/2 >= 0.0025 |x|^2 + 7e-7 > e_c.  (A tau from the largest norm of the codebook, some 7 times as
 // wide, sent a quarter of all chunks through the walk over several quads.)
 // The matrix instruction takes fp16 subnormals as they are (no flush: measured, and the default mode of a HIP kernel).
+// Codebooks of small numbers: rows and offset carry a gain g = s^2 (pq_filter_scale), with which the above holds for s x and
+// s c in the place of x and c — the products x_j (g c_j) are as exact, and no gain makes a coordinate of a row inexact.  The
+// refinement compares the distances of g x and g c, g^2 times the true ones: the same order and the same ties.
 //
 // fp32 inputs run the same filter on split operands: coordinates are scaled by a power of two that brings the
 // codebook's largest into [32, 64) and split into two fp16, v = v' + v'' (to 2^-22 of v, or 2^-25), and
@@ -123,19 +126,13 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
 #pragma unroll
         for (int j = 0; j < DS; ++j)
             y[r][j] = src[(lane + 64 * r) * DS + j];
-    float scale = 1.f;
-    if constexpr (sizeof(T) == 4) {
-        float c_max = 0.f;
+    float c_max = 0.f;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int j = 0; j < DS; ++j)
-                c_max = fmaxf(c_max, fabsf(y[r][j]));
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-            c_max = fmaxf(c_max, __shfl_xor(c_max, o));
-        scale = pq_filter_scale(c_max);
-    }
+        for (int j = 0; j < DS; ++j)
+            c_max = fmaxf(c_max, fabsf((float)y[r][j]));
+    const float scale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pq_filter_scale<T>(pq_filter_wave_max(c_max)))));
     bool cb_bad = false;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -144,7 +141,7 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
         if constexpr (sizeof(W) > 2) {
 #pragma unroll
             for (int j = 0; j < DS; ++j)
-                coord[c * DS + j] = (W)(float)y[r][j];
+                coord[c * DS + j] = (W)(sizeof(T) == 2 ? (float)y[r][j] * scale : (float)y[r][j]);
         }
     }
     cb_bad = __builtin_amdgcn_ballot_w64(cb_bad) != 0;

@@ -1,6 +1,6 @@
 // Constants of the matrix-core nearest-centroid filter (pq_nearest_filter.h; the argument is in pq_encode.hip), in one
 // place: the encode and training kernels include this file and the host-side bound tests parse it, so they cannot drift
-// apart.  Per token, with X2 = sum x_j^2 and `best` its smallest computed value:
+// apart.  Per token, with X2 = sum x_j^2 (of scaled numbers: pq_filter_scale) and `best` its smallest computed value:
 //   off = PQ_FILTER_X2_FACTOR X2 + 3 PQ_FILTER_TAU_ABS, rounded up      (keeps every value positive)
 //   tau = PQ_FILTER_TAU_NEAR (X2 + best) + PQ_FILTER_TAU_ABS            (fp32 inputs: PQ_FILTER_TAU_NEAR_F32)
 // PQ_FILTER_TAU_REL belongs to the form of tau that needs no `best`, from the codebook's largest norm N and coordinate

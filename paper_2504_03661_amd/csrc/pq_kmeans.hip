@@ -52,19 +52,25 @@ __global__ __launch_bounds__(KM_SUB * 64) void pq_kmeans_assign_kernel(const __h
     // matrix-instruction rows of this (head, subspace)'s codebook for the nearest-centroid filter of the encode
     // (pq_nearest_filter.h); accumulators cleared
     const int64_t cb_base = ((int64_t)head * M + i) * 256 * DS;
-    bool cb_bad = false;
+    _Float16 y[4][DS];
+    float c_max = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int c = lane + 64 * r;
-        _Float16 y[DS];
 #pragma unroll
         for (int j = 0; j < DS; ++j) {
-            y[j] = ((const _Float16 *)codebook)[cb_base + c * DS + j];
+            y[r][j] = ((const _Float16 *)codebook)[cb_base + c * DS + j];
+            c_max = fmaxf(c_max, fabsf((float)y[r][j]));
             part_sum[c * DS + j] = 0ull;
         }
-        pq_filter_build_row<DS>(y, 1.f, arow + c * pq_filter_row_bytes<_Float16>(), cb_bad);
         part_cnt[c] = 0u;
     }
+    const float scale =
+        __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pq_filter_scale<_Float16>(pq_filter_wave_max(c_max)))));
+    bool cb_bad = false;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        pq_filter_build_row<DS>(y[r], scale, arow + (lane + 64 * r) * pq_filter_row_bytes<_Float16>(), cb_bad);
     cb_bad = __builtin_amdgcn_ballot_w64(cb_bad) != 0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
@@ -92,7 +98,7 @@ __global__ __launch_bounds__(KM_SUB * 64) void pq_kmeans_assign_kernel(const __h
             xv[j] = next[j];
         fetch(s + 64);
         const bool live = s < s1;
-        const int code = pq_filter_code<DS, _Float16, _Float16>(arow, arow, 1.f, cb_bad, xv, live);
+        const int code = pq_filter_code<DS, _Float16, _Float16>(arow, arow, scale, cb_bad, xv, live);
         if (live) {
 #pragma unroll
             for (int j = 0; j < DS; ++j) {

@@ -23,7 +23,8 @@ typedef uint32_t u32x4e __attribute__((ext_vector_type(4)));
 
 // An A row holds the inner indices of one matrix instruction: lanes 0..31 of the wavefront read its first half, lanes
 // 32..63 its second.  h + l = |c|^2 / 2, o_0 + 2^15 o_1 = the token's offset.
-//   fp16 (v_mfma_f32_32x32x8_f16, 16 bytes)
+//   fp16 (v_mfma_f32_32x32x8_f16, 16 bytes), the values of a codebook of small numbers multiplied by a gain: c and
+//   |c|^2 / 2 are, which is exact, and so is the offset; x need not be
 //     ds = 2   c_0 c_1 h l | 1 2^15 0 0        against the column   -x_0 -x_1 1 1 | o_0 o_1 0 0
 //     ds = 4   c_0 c_1 c_2 c_3 | h l 1 2^15    against              -x_0 .. -x_3 | 1 1 o_0 o_1
 //   fp32 (v_mfma_f32_32x32x16_f16, 32 bytes), coordinates scaled by a power of two per codebook and split into two
@@ -34,17 +35,35 @@ typedef uint32_t u32x4e __attribute__((ext_vector_type(4)));
 //                                    against -x'_0 .. -x'_3 -x'_0 .. -x'_3 | -x''_0 .. -x''_3 1 1 o_0 o_1
 template <typename T> constexpr int pq_filter_row_bytes() { return sizeof(T) == 2 ? 16 : 32; }
 
-// the power of two that brings the largest coordinate of an fp32 codebook into [32, 64)
-__device__ inline float pq_filter_scale(float c_max)
+// What a codebook's values are scaled by, from its largest coordinate.
+// fp32: the power of two s that brings it into [32, 64); coordinates of centroids and tokens are multiplied by s.
+// fp16: with s the power of two that brings it into [2, 4), the gain s^2 of the values, and 1 for larger coordinates.
+// Without it the absolute part of tau, there for the roundings of the smallest numbers, is what decides for small ones: at
+// a standard deviation of 0.01 every second token marked a second quad, at 0.001 all quads near it (8192 tokens x 32 heads
+// 394 us at 1, 804 and 3443 us there; 392 with the gain).  c s^2 stays below 2^15 for the smallest s allowed.
+template <typename T> __device__ inline float pq_filter_scale(float c_max)
 {
     int e = 0;
     (void)__builtin_frexpf(c_max, &e);
-    e = e < -100 ? -100 : e;  // (a codebook this small is one cluster of near-ties to the filter)
-    return c_max > 0.f ? __builtin_ldexpf(1.0f, 6 - e) : 1.0f;
+    if constexpr (sizeof(T) == 4) {
+        e = e < -100 ? -100 : e;  // (a codebook this small is one cluster of near-ties to the filter)
+        return c_max > 0.f ? __builtin_ldexpf(1.0f, 6 - e) : 1.0f;
+    } else {
+        e = e < -11 ? -11 : e;
+        return c_max > 0.f && c_max < 2.0f ? __builtin_ldexpf(1.0f, 4 - 2 * e) : 1.0f;  // (not infinite)
+    }
 }
 
-// A row of a centroid (c: its ds coordinates; fp32: scaled by `scale`); sets `bad` when |c|^2 / 2 does not split into
-// two fp16
+// the largest over the wavefront
+__device__ inline float pq_filter_wave_max(float x)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        x = fmaxf(x, __shfl_xor(x, o));
+    return x;
+}
+
+// A row of a centroid (c: its ds coordinates; scale: pq_filter_scale); sets `bad` when |c|^2 / 2 does not split into two fp16
 template <int DS, typename T>
 __device__ inline void pq_filter_build_row(const T (&c)[DS], const float scale, unsigned char *arow_c, bool &bad)
 {
@@ -56,13 +75,13 @@ __device__ inline void pq_filter_build_row(const T (&c)[DS], const float scale, 
     for (int j = 0; j < DS; ++j) {
         const float f = sizeof(T) == 2 ? (float)c[j] : (float)c[j] * scale;
         n += f * f;  // (the roundings are covered by the bound)
-        row[j] = (_Float16)f;
+        row[j] = (_Float16)(sizeof(T) == 2 ? f * scale : f);
         if constexpr (sizeof(T) == 4) {
             row[DS + j] = (_Float16)(f - (float)row[j]);
             row[2 * DS + j] = row[j];
         }
     }
-    const float h = 0.5f * n;
+    const float h = (sizeof(T) == 2 ? 0.5f * scale : 0.5f) * n;
     const _Float16 hh = (_Float16)h;
     const _Float16 hl = (_Float16)(h - (float)hh);
     row[N_AT] = hh;
@@ -79,30 +98,32 @@ template <int DS, typename T> struct pq_filter_token {
     static constexpr float TAU_NEAR = F16 ? PQ_FILTER_TAU_NEAR : PQ_FILTER_TAU_NEAR_F32;
     typedef typename std::conditional<F16, f16x4, f16x8>::type operand;
     operand col[2];  // the columns of tokens 0..31 and 32..63 of the wavefront
-    float x[DS];  // (widened where it is used)
+    float x[DS];  // (widened where it is used; fp16: times the gain, as the rows)
     float tau_x;  // the token's share of tau
     bool bad;     // outside the range that the bound covers
 
-    // xin: the token's sub-vector (fp32: unscaled)
+    // xin: the token's sub-vector, unscaled
     __device__ __forceinline__ void set(const T (&xin)[DS], const float scale)
     {
 #pragma clang fp contract(off)
         float x2 = 0.f, xs[DS];
 #pragma unroll
         for (int j = 0; j < DS; ++j) {
-            x[j] = (float)xin[j];
+            x[j] = F16 ? __builtin_fmaf((float)xin[j], scale, 0.f) : (float)xin[j];  // (fp16: one instruction, exact)
             xs[j] = F16 ? x[j] : x[j] * scale;
             x2 = __builtin_fmaf(xs[j], xs[j], x2);
         }
+        // fp16: x2 has the gain twice; 1 / scale of a power of two
+        const float x2_to_value = F16 ? __int_as_float(0x7f000000 - __float_as_int(scale)) : 1.f;
         // off: |x|^2/2 with half a per cent on top and a floor, so that every computed value stays above zero, rounded
         // UP to o_0 + 2^15 o_1 (one of the two is zero) by 0.3 % against the half step (2^-11) of the conversion and a
         // subnormal step
-        const float off = __builtin_fmaf(PQ_FILTER_X2_FACTOR, x2, 3.0f * PQ_FILTER_TAU_ABS);
+        const float off = __builtin_fmaf(PQ_FILTER_X2_FACTOR * x2_to_value, x2, 3.0f * PQ_FILTER_TAU_ABS);
         const float up = __builtin_fmaf(off, 1.003f, 6.0e-8f);
-        tau_x = __builtin_fmaf(TAU_NEAR, x2, PQ_FILTER_TAU_ABS);
+        tau_x = __builtin_fmaf(TAU_NEAR * x2_to_value, x2, PQ_FILTER_TAU_ABS);
         bad = false;
         _Float16 o0 = (_Float16)up, o1 = (_Float16)0.f;
-        if (__builtin_amdgcn_ballot_w64(!(off < 60000.f)) != 0) {  // wave-uniform, rare: (scaled) length beyond 340
+        if (__builtin_amdgcn_ballot_w64(!(off < 60000.f)) != 0) {  // wave-uniform, rare: scaled length beyond 340
             const bool large = !(off < 60000.f);
             o0 = large ? (_Float16)0.f : o0;
             o1 = large ? (_Float16)(up * (1.0f / 32768.f)) : (_Float16)0.f;
