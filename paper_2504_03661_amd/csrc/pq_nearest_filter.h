@@ -359,9 +359,8 @@ __device__ __forceinline__ int pq_filter_code(const unsigned char *arow, const u
                 c[j] = (double)((const W *)at)[j];
         }
     };
-    auto take = [&](int c) {
-        double y[DS], dist = 0.0;
-        coordinates(coord + c * STRIDE, y);
+    auto closer = [&](int c, const double (&y)[DS]) {
+        double dist = 0.0;
 #pragma unroll
         for (int j = 0; j < DS; ++j) {
             const double diff = (double)tok.x[j] - y[j];
@@ -392,6 +391,7 @@ __device__ __forceinline__ int pq_filter_code(const unsigned char *arow, const u
     // several (ties, near-ties, a token far outside the codebook's range): the lane walks every quad whose two bits
     // are set — quad (m, g) of half s is centroids 4 (8 m + 2 g + s) .. + 3
     const uint64_t several = marks.several & __builtin_amdgcn_ballot_w64(live && !bad);
+    uint64_t all = 0;  // tokens for which all centroids are the shorter way
     if (several != 0) {  // wave-uniform
         const bool mine = __builtin_amdgcn_inverse_ballot_w64(several);
         const auto halves = __builtin_amdgcn_permlane32_swap(pq_filter_mark_word(by_m[0], by_g[0], limit[0]),
@@ -406,31 +406,41 @@ __device__ __forceinline__ int pq_filter_code(const unsigned char *arow, const u
                 left |= (uint64_t)((h >> (4 + m)) & 1u ? of_g : 0u) << (8 * m);
         }
         left = mine ? left : 0;
+        all = __builtin_amdgcn_ballot_w64(__builtin_popcountll(left) > 40);
         const int code_one = code;
         code = 0;
         bd = __builtin_huge_val();
-        while (__builtin_amdgcn_ballot_w64(left != 0) != 0) {
-            const int quad = left ? __builtin_ctzll(left) : 0;
-            const int code_before = code;
-            const double bd_before = bd;
+        // two quads at a time, the second's coordinates under way with the first's (a lane with nothing left takes its last
+        // quad again: no change)
+        int quad = 0;
+        while (all == 0 && __builtin_amdgcn_ballot_w64(left != 0) != 0) {
+            const uint64_t rest = left & (left - 1);
+            const int first = left ? __builtin_ctzll(left) : quad;
+            quad = rest ? __builtin_ctzll(rest) : first;
+            double y[8][DS];
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                take(4 * quad + k);
-            if (left == 0) {  // this lane had nothing left: keep what it had
-                code = code_before;
-                bd = bd_before;
-            }
-            left &= left - 1;
+            for (int k = 0; k < 8; ++k)
+                coordinates(coord + (4 * (k < 4 ? first : quad) + (k & 3)) * STRIDE, y[k]);
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                closer(4 * (k < 4 ? first : quad) + (k & 3), y[k]);
+            left = rest & (rest - 1);
         }
         if (!mine)
             code = code_one;
     }
-    const uint64_t unsure = __builtin_amdgcn_ballot_w64(live && bad) | (__builtin_amdgcn_ballot_w64(live) & ~marks.some);
-    if (unsure != 0) {  // wave-uniform: the defining scan for this sub-chunk
+    // ... the defining scan for this sub-chunk, also where a token has more than 40 of the 64 quads to walk (4096 tokens x 8
+    // heads, a codebook of equal centroids: 436 us walked, 301 scanned; half of them equal: 194 us with one quad at a time
+    // and the lanes that are done kept out of it, 168)
+    const uint64_t unsure = all | __builtin_amdgcn_ballot_w64(live && bad) | (__builtin_amdgcn_ballot_w64(live) & ~marks.some);
+    if (unsure != 0) {  // wave-uniform
         code = 0;
         bd = __builtin_huge_val();
-        for (int c = 0; c < 256; ++c)
-            take(c);
+        for (int c = 0; c < 256; ++c) {
+            double y[DS];
+            coordinates(coord + c * STRIDE, y);
+            closer(c, y);
+        }
     }
     return code;
 }

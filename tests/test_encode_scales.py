@@ -129,3 +129,40 @@ def test_small_numbers_take_no_longer(M, C):
     unit = _encode_ms(M, C, 1.0)
     for scale in (0.01, 1e-3):
         assert _encode_ms(M, C, scale) <= 1.25 * unit, scale
+
+
+@pytest.mark.gpu
+def test_a_codebook_of_equal_centroids_takes_one_scan():
+    """All numbers zero, so every centroid is as near as any: the scan of all costs 4.8 times a pass of the filter, a walk over
+    all of its 64 quads 6.9 times."""
+    assert _encode_ms(64, 256, 0.0) <= 5.8 * _encode_ms(64, 256, 1.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,dtype", [(64, "f16"), (32, "f16"), (64, "f32"), (32, "f32")])
+def test_tokens_as_near_to_many_quads(M, dtype):
+    """1 to 64 quads with the token's nearest centroid, several times inside some: an even and an odd number, 40 and 41, in one
+    lane half or both; the lowest index of all is the code."""
+    ds, n_new = 128 // M, 130
+    w = W.Workload("quads", 1, 2, 2, 128, M, n_new, dtype, n_new=n_new, seed=M)
+    data = W.generate(w)
+    rng = np.random.default_rng(M)
+    lowest = np.zeros((2, 2, M), int)
+    for t, (cb, x) in enumerate(((data["k_codebook"], data["new_k"]), (data["v_codebook"], data["new_v"]))):
+        for h in range(2):
+            for i in range(M):
+                n = [1, 2, 3, 4, 7, 16, 31, 32, 33, 39, 40, 41, 42, 63, 64][i % 15]
+                quads = np.sort(rng.choice(64, n, False)) if i % 2 else np.sort(rng.permutation(np.r_[0:64:2, 1:64:2][:max(n, 32)])[:n])
+                at = np.unique(4 * quads[:, None] + rng.integers(0, 4, (n, 2)))
+                point = cb[h, i, at[0]].copy()
+                cb[h, i, at] = point
+                lowest[t, h, i] = at.min()
+                x[0, h, ::2, i * ds:(i + 1) * ds] = point
+    with PQSession(data, 2, dtype) as s:
+        s.ctx_len.zero_()
+        s.append(torch.from_numpy(data["new_k"]).cuda(), torch.from_numpy(data["new_v"]).cuda())
+        torch.cuda.synchronize()
+        got = s.unpack(PQ_CODES_K, n_new), s.unpack(PQ_CODES_V, n_new)
+    for t, (x, cb) in enumerate(((data["new_k"], data["k_codebook"]), (data["new_v"], data["v_codebook"]))):
+        np.testing.assert_array_equal(got[t], O.encode(x, cb))
+        assert (got[t][0, :, ::2] == lowest[t][:, None]).all()
