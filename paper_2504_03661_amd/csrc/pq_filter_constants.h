@@ -3,14 +3,9 @@
 // apart.  Per token, with X2 = sum x_j^2 (of scaled numbers: pq_filter_scale) and `best` its smallest computed value:
 //   off = PQ_FILTER_X2_FACTOR X2 + 3 PQ_FILTER_TAU_ABS, rounded up      (keeps every value positive)
 //   tau = PQ_FILTER_TAU_NEAR (X2 + best) + PQ_FILTER_TAU_ABS            (fp32 inputs: PQ_FILTER_TAU_NEAR_F32)
-// PQ_FILTER_TAU_REL belongs to the form of tau that needs no `best`, from the codebook's largest norm N and coordinate
-// C (X1 = sum |x_j|): off' = X2_FACTOR X2 + 2 (TAU_REL (2 T0) + TAU_ABS), T0 = N + X1 C + X2_FACTOR X2, and
-// tau' = TAU_REL (T0 + off') + TAU_ABS.  The kernels do not use it (it is some 7 times as wide); the host-side test keeps
-// its bound of the same sums.
 #pragma once
 
 #define PQ_FILTER_X2_FACTOR 0.5025f
-#define PQ_FILTER_TAU_REL 3.1e-06f
 #define PQ_FILTER_TAU_ABS 2.4e-07f
 #define PQ_FILTER_TAU_NEAR 1.05e-05f
 #define PQ_FILTER_TAU_NEAR_F32 2.5e-05f
