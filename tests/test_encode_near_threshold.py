@@ -120,11 +120,13 @@ def test_fp32_codes_over_magnitudes_and_near_ties(M):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f16", "f32"])
 @pytest.mark.parametrize("M", [64, 32])
-@pytest.mark.parametrize("B_,n_new", [(3, 56), (3, 57), (2, 63), (2, 64), (2, 65), (3, 113), (3, 114), (1, 70), (40, 7)])
+@pytest.mark.parametrize("B_,n_new", [(3, 56), (3, 57), (2, 63), (2, 64), (2, 65), (3, 113), (3, 114), (1, 70), (40, 7),
+                                      (1, 6), (6, 1), (1, 7), (7, 1), (2, 3), (4, 2)])
 def test_codes_at_the_edges_of_the_mapping_and_of_the_offset(M, B_, n_new, dtype):
     """Token counts on both sides of the rule that gives every sequence its own 64-token chunks (57 and 114 are the first
-    to have them), remainders, several chunks per wavefront's job; sub-vectors up to the largest fp16 (beyond a length of
-    345 the offset moves to its second slot, beyond 6e4 the chunk takes the full scan)."""
+    to have them) and of the one between the per-token kernel (up to 6 tokens per head) and the filter, remainders;
+    sub-vectors up to the largest fp16 (beyond a length of 345 the offset moves to its second slot, beyond 6e4 the chunk
+    takes the full scan)."""
     ds = 128 // M
     lens = tuple(int(v) for v in np.random.default_rng(B_).integers(0, 90, B_))
     w = W.Workload("edge", B_, 4, 4, 128, M, 90 + n_new, dtype, n_new=n_new, seed=70 + M + n_new, ctx_lens=lens)
@@ -140,6 +142,33 @@ def test_codes_at_the_edges_of_the_mapping_and_of_the_offset(M, B_, n_new, dtype
         torch.cuda.synchronize()
         assert s.ctx_len.cpu().tolist() == [n + n_new for n in lens]
         got_k, got_v = s.unpack(PQ_CODES_K, 90 + n_new), s.unpack(PQ_CODES_V, 90 + n_new)
+    exp_k, exp_v = O.encode(data["new_k"], data["k_codebook"]), O.encode(data["new_v"], data["v_codebook"])
+    for b, n in enumerate(lens):
+        np.testing.assert_array_equal(got_k[b, :, n:n + n_new], exp_k[b])
+        np.testing.assert_array_equal(got_v[b, :, n:n + n_new], exp_v[b])
+        np.testing.assert_array_equal(got_k[b, :, :n], data["k_codes"][b, :, :n])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("M,B_,Hkv,n_new,per_seq", [(64, 64, 32, 5, False), (64, 40, 32, 70, False), (32, 70, 32, 11, False),
+                                                    (32, 130, 16, 37, False), (64, 1, 16, 1100, True), (64, 5, 32, 127, True),
+                                                    (32, 2, 32, 600, True)])
+def test_codes_with_several_chunks_per_wavefront(M, B_, Hkv, n_new, per_seq, dtype):
+    """Enough 64-token chunks that a wavefront takes two or more in a row: the step from one to the next, where the tokens of
+    all sequences are in a row (several sequences or none passed on the way) and where every sequence has its own chunks."""
+    seq_chunks = (n_new + 63) // 64
+    assert per_seq == (seq_chunks * 512 <= n_new * 9 or B_ == 1)                # the launcher's rule, and ...
+    chunks = B_ * seq_chunks if per_seq else (B_ * n_new + 63) // 64
+    assert Hkv * chunks * M * 2 // 8192 >= 2                                    # ... its chunks per wavefront
+    lens = tuple(int(v) for v in np.random.default_rng(B_).integers(0, 20, B_))
+    w = W.Workload("rounds", B_, Hkv, Hkv, 128, M, 20 + n_new, dtype, n_new=n_new, seed=M + n_new, ctx_lens=lens)
+    data = W.generate(w, ctx_cap=20 + n_new)
+    with PQSession(data, Hkv, dtype, max_context=20 + n_new) as s:
+        s.append(torch.from_numpy(data["new_k"]).cuda(), torch.from_numpy(data["new_v"]).cuda())
+        torch.cuda.synchronize()
+        assert s.ctx_len.cpu().tolist() == [n + n_new for n in lens]
+        got_k, got_v = s.unpack(PQ_CODES_K, 20 + n_new), s.unpack(PQ_CODES_V, 20 + n_new)
     exp_k, exp_v = O.encode(data["new_k"], data["k_codebook"]), O.encode(data["new_v"], data["v_codebook"])
     for b, n in enumerate(lens):
         np.testing.assert_array_equal(got_k[b, :, n:n + n_new], exp_k[b])

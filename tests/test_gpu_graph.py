@@ -89,3 +89,41 @@ def test_append_and_decode_in_one_graph(M, C):
             assert s.ctx_len.cpu().tolist() == (base + 3).cpu().tolist()
             assert (s.out - want).abs().max().item() <= 4e-6
             np.testing.assert_array_equal(s.unpack(PQ_CODES_K, 700), want_codes)
+
+
+@pytest.mark.parametrize("name,B_,Hq,Hkv,M,dtype", [("deal", 5, 16, 16, 64, "f16"), ("deal_grouped", 3, 14, 2, 64, "f16"),
+                                                    ("order_grouped", 40, 32, 8, 64, "f16"), ("order", 10, 32, 32, 32, "f16"),
+                                                    ("order_f32", 40, 8, 1, 64, "f32"), ("walk", 20, 32, 32, 64, "f16")])
+def test_a_graph_follows_lengths_that_change_between_replays(name, B_, Hq, Hkv, M, dtype):
+    """The library's own choice for a batch: the workgroups read the lengths when they run, so a captured call serves other
+    lengths — more, fewer and no workgroups per sequence than at capture — as the eager call does, and leaves the tickets
+    at zero."""
+    cap = 2600
+    w = W.Workload("graph_" + name, B_, Hq, Hkv, 128, M, cap, dtype, recent_cap=24, recent_uniform=True, seed=79)
+    data = W.generate(w)
+    scale = W.attention_scale(w)
+    rng = np.random.default_rng(B_)
+    lengths = [rng.integers(0, cap + 1, B_), np.full(B_, 300), np.r_[cap, np.arange(B_ - 1) % 2], rng.integers(0, 90, B_)]
+    with PQSession(data, Hq, dtype) as s:
+        want = []
+        for n in lengths:
+            s.ctx_len.copy_(torch.from_numpy(n.astype(np.int32)))
+            want.append(s.decode(scale).clone())
+            torch.cuda.synchronize()
+            ref = O.decode(data["q"], data["k_codes"], data["v_codes"], n.astype(np.int32), data["k_codebook"], data["v_codebook"],
+                           data["recent_k"], data["recent_v"], data["recent_len"], scale=scale)
+            assert np.abs(want[-1].cpu().numpy() - ref).max() <= 2e-5
+        s.ctx_len.copy_(torch.from_numpy(lengths[0].astype(np.int32)))
+        torch.cuda.synchronize()
+        side = torch.cuda.Stream()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            s.decode(scale)
+        for rep in range(8):
+            i = (3 * rep + 1) % 4
+            s.ctx_len.copy_(torch.from_numpy(lengths[i].astype(np.int32)))
+            s.out.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            dev = (s.out - want[i]).abs().max().item()
+            assert dev <= 4e-6, f"{name}: replay {rep} differs from the eager call by {dev:.3e}"

@@ -361,7 +361,7 @@ def test_bulk_encode_at_prefill_shape_is_bit_exact():
 
 @pytest.mark.parametrize("M,n_new", [(64, 7000), (32, 9300)])
 def test_bulk_encode_with_several_chunks_per_wavefront(M, n_new):
-    """Enough 256-token chunks that a wavefront of the filter kernel takes several in a row, the last
+    """Enough 64-token chunks that a wavefront of the filter kernel takes several in a row, the last
     wavefront of a head fewer than the others."""
     w = W.Workload("pre_rounds", 1, 8, 8, 128, M, n_new, "f16", n_new=n_new, seed=310 + M)
     data = W.generate(w)
@@ -378,10 +378,10 @@ def test_bulk_encode_with_several_chunks_per_wavefront(M, n_new):
                                        (1, 257), (16, 1), (1, 16), (2, 5), (1, 17)])
 def test_encode_filter_paths_are_bit_exact(M, B_, n_new):
     """fp16 encode = matrix-core filter + fp64 decision: every way through it gives the oracle's codes — ties inside
-    one group of 4 centroids, across two groups, across three and more (full scan), clusters of near-ties far
+    one quad of centroids, across two quads, across three and more (a walk over them), clusters of near-ties far
     below the filter's resolution, subnormal and zero inputs, a codebook whose norms leave the fp16 range (full
-    scan), tokens that are far outliers; token counts per head that take the 1-, 2- and 4-chunk instantiations, and (16 tokens or fewer)
-    the centroid-per-lane kernel."""
+    scan), tokens that are far outliers; token counts per head of one chunk and of several, with chunks of each
+    sequence and with all sequences' tokens in a row, and (6 tokens or fewer) the centroid-per-lane kernel."""
     ds = 128 // M
     w = W.Workload("filt", B_, 4, 2, 128, M, n_new + 3, "f16", n_new=n_new, seed=900 + M + n_new)
     data = W.generate(w)
