@@ -162,7 +162,7 @@ __device__ __forceinline__ void grouped_workgroup(const pq_decode_args &a)
         const int n = clamp_to(n_vec, max_context), r = has_recent ? clamp_to(r_vec, max_recent) : 0;
         int mine;
         if constexpr (BATCH == BATCH_DEAL) {
-            const batch_job job = batch_deal<16, 32, 6>(a.B, a.S, a.div, split, (uint32_t)n, (uint32_t)r, lane);
+            const batch_job job = batch_deal<16, 32, 6, 3>(a.B, a.S, a.div, split, (uint32_t)n, (uint32_t)r, lane);
             if (job.split >= job.S)
                 return;
             first_job = split - job.split;

@@ -316,8 +316,9 @@ __device__ inline int batch_guess(int B, const pq_batch_divisors &d, int j)
 __device__ inline uint32_t batch_work(uint32_t n, uint32_t r) { return ((n + 63u) >> 6) + ((r + 15u) >> 4); }
 
 // BATCH_DEAL: job j of `jobs` (n, r: clamped lengths of sequence `lane`; lanes beyond the batch: anything).  WHOLE: blocks
-// below which a sequence has one workgroup; AT_ONCE: partials that the kernel's merge loads in one round trip; ROOT: see below.
-template <int WHOLE, int AT_ONCE, int ROOT>
+// below which a sequence has one workgroup; AT_ONCE: partials that the kernel's merge loads in one round trip; ROOT,
+// ROWS: see below.
+template <int WHOLE, int AT_ONCE, int ROOT, int ROWS>
 __device__ inline batch_job batch_deal(int B, int jobs, const pq_batch_divisors &d, int j, uint32_t n, uint32_t r, int lane)
 {
     const bool in = lane < B;
@@ -330,7 +331,11 @@ __device__ inline batch_job batch_deal(int B, int jobs, const pq_batch_divisors 
     // 15.4, 64 16.1), 3 for the per-head kernels of 16 wavefronts (32 subspaces: 6 of 8K 10.6, 16 11.9; 12 of 16K 12.2).
     const uint32_t root = (uint32_t)(0.25f * (float)ROOT * __builtin_amdgcn_sqrtf((float)work));
     const uint32_t paying = root < (uint32_t)AT_ONCE ? (uint32_t)AT_ONCE : root < PQ_MAX_SPLITS ? root : PQ_MAX_SPLITS;
-    const uint32_t most = work < (uint32_t)WHOLE ? 1u : paying;
+    // 16 recent rows count as a block, and from the ROWS-th on as three: 3 sequences of 300 tokens and up to 128 rows, 32 query
+    // / 8 KV heads, whole 14.9 us, in four 11.9; per head 5 of 200 and up to 128 whole 8.1, cut 9.4, up to 200 whole 10.9, cut 9.8
+    const uint32_t rows = in ? (r + 15u) >> 4 : 0u;
+    const uint32_t long_rows = rows > (uint32_t)ROWS ? 2u * (rows - (uint32_t)ROWS) : 0u;
+    const uint32_t most = work + long_rows < (uint32_t)WHOLE ? 1u : paying;
     const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)work);
     if (__builtin_amdgcn_ballot_w64(most > 1u) == 0 ||
         __builtin_amdgcn_ballot_w64(in && (work > w0 + w0 / 8u || work < w0 - w0 / 8u)) == 0) {
