@@ -268,7 +268,9 @@ def main():
     if os.path.exists(tpath):
         traffic = json.load(open(tpath)).get("hbm_bytes_per_launch")
         traffic_source = f"profiles/traffic_{w.name}.txt (static: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command, not measured in this run)"
-    kernel_name = {True: "pq_decode_grouped_kernel", False: "pq_decode_kernel"}[w.n_q_heads != w.n_kv_heads and w.dtype == "f16"]
+    # (the 2-bit batch: one workgroup per sequence and head)
+    kernel_name = "pq_decode_whole_kernel" if w.name == "cfg4_2bit_encode_16x64k" else \
+        {True: "pq_decode_grouped_kernel", False: "pq_decode_kernel"}[w.n_q_heads != w.n_kv_heads and w.dtype == "f16"]
     roofline = {"bound": "hbm", "kernel": kernel_name, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic,
                 "traffic_source": traffic_source,

@@ -85,8 +85,8 @@ def prefill():
         ms = _span_ms(step, 5)
     vectors = 2 * w.batch * w.n_kv_heads * n_new
     # vector instructions the filter kernel issues per (token, subspace), its 16 matrix instructions per 64 of them
-    # included (rocprofv3 SQ_INSTS_VALU: 354)
-    ops_per_subvector = 354
+    # included (rocprofv3 SQ_INSTS_VALU: 355)
+    ops_per_subvector = 355
     ops = vectors * w.n_subspaces * ops_per_subvector
     achieved = ops / (ms * 1e-3)
     scan_ops = vectors * w.n_subspaces * 256 * (2 * w.sub_dim + 3)
@@ -170,9 +170,9 @@ def train():
 
     ms = _span_ms(run, 3, warmup=1) / iters
     ds = 128 // M
-    # vector instructions of the assignment per (sample, subspace): the encode's matrix-core filter (the LDS atomics of
-    # the member sums come on top)
-    ops = Hkv * M * n * 354
+    # vector instructions of the assignment per (sample, subspace): the encode's matrix-core filter and the member sums
+    # (rocprofv3 SQ_INSTS_VALU: 394)
+    ops = Hkv * M * n * 394
     scan_ops = Hkv * M * n * 256 * (2 * ds + 3)
     trained = cb.cpu().numpy()
     B.pq_attn_destroy(ctx)

@@ -44,8 +44,9 @@ __device__ inline void unpack8(const uint32_t (&w)[3], uint32_t (&c)[8])
 // half form a grid of 16 rows and 8 columns, whose minima (24 numbers) name the blocks with a value near the smallest
 // one.  Nearly always that is one block: its 16 centroids are evaluated in the defining fp64 arithmetic.  Otherwise the
 // lane walks all blocks whose row and column are marked, and a codebook or token outside the bound's range the full fp64
-// scan.  Bound by vector-instruction issue: 9.5 per instruction and tile, some 2900 per 64 tokens and subspace, the
-// matrix instructions (256 x 32 cycles) in parallel.
+// scan.  9.5 vector instructions per matrix instruction and tile, 3177 per 64 tokens and subspace counted with the 256 matrix
+// instructions among them: 63 % of the issue slots, the matrix cores busy 40 % of the time (2048 tokens x 32 heads, K and V,
+// 550 us).
 // SPLIT (a head has at most 128 tokens in the call — a decoding step of a batch): all eight wavefronts take the SAME
 // tokens and an eighth of the centroids each, keep their 16 block minima and exchange the smallest value and the
 // marked blocks (one word per token and wavefront) through LDS; wavefront 0 refines.
@@ -324,12 +325,11 @@ __global__ __launch_bounds__(F12_WAVES * 64) __attribute__((amdgpu_waves_per_eu(
 // centroids that can be the nearest (a bound relative to the distance itself), then the defining fp64 distances
 // of those alone (ascending index per thread, strict "<"); the workgroup takes the lexicographic minimum of
 // (distance, index): the lowest index among equal distances, as in the scan.  The floor is reading the codebooks
-// once (9.5 us at 7.05 TB/s). At 50 registers and 8 wavefronts per workgroup all workgroups of 32 heads are
+// once (64 MiB for K and V of 32 heads, 9.5 us at 7.05 TB/s).  At 50 registers and 8 wavefronts per workgroup all workgroups of 32 heads are
 // resident in two rounds, with 128 KiB of loads under way per compute unit; 4 wavefronts per workgroup took 1.4 us
 // longer.  An append of one token with the length update, 32 heads: 21.3 us when every distance was taken in fp64
-// by 1024 threads, 17.4 us so; 4 tokens 39.2 and 27.6 us
-// (64 MiB for K and V of 32 heads).  The code goes straight into the device layout — no staging, no packing
-// kernels: a 12-bit field of a unit that other workgroups (K: the token's other subspaces) or nobody else in
+// by 1024 threads, 17.4 us so; 4 tokens 39.2 and 27.6 us.  The code goes straight into the device layout — no staging, no
+// packing kernels: a 12-bit field of a unit that other workgroups (K: the token's other subspaces) or nobody else in
 // this call (V) writes, so it is cleared and set with two device-scope atomics per 32-bit word it touches;
 // fields are disjoint, so the order of the workgroups does not matter.  Tokens beyond the capacity are not
 // written (the length update flags them).

@@ -146,6 +146,10 @@ int choose_splits(const pq_attn_config *c, int n_cu)
 //                    shares fill at least 92 % of the chip; else = batch: one each, the longest first (BATCH_ORDER),
 //                    up to two rounds of the chip
 //   otherwise        0
+// Walking against one workgroup each, times as fast: up to two rounds 0.96 to 1.05 in every case; beyond, 28 and 36 heads
+// (shares fill 98 %) 1.04 to 1.07 with equal lengths, 1.13 to 1.23 with lengths of 500 .. 6000; 24 to 60 heads (93 %) 0.91 to
+// 1.11 and 1.07 to 1.22; 44 to 56 heads (81 .. 88 %) 0.93 to 1.15 and 1.08 to 1.19; 88 heads (68 %) 0.87 to 0.92 and 0.95.  So
+// the line could lie lower; what a lower one gains with unequal lengths it loses with equal ones in four rounds.
 int choose_jobs(const pq_attn_config *c, int n_cu)
 {
     if (c->batch < 2 || c->batch > 64 || c->n_splits != 0 || pq_config_is_12bit(c))

@@ -82,10 +82,11 @@ template <> __device__ inline double widen<float>(const void *p, int64_t i)
 // (8192 tokens x 32 heads x (K, V), fp32: the full scan for every token 1.79 ms at M = 64 and 1.50 ms at M = 32, now
 // 0.46 and 0.26 ms.)
 //
-// Cost per (sub-vector, centroid): 1.3 vector operations instead of 2 ds + 3 in fp64, the matrix instructions in
-// parallel; bound by the issue of the vector instructions (about 340 per 64 tokens and subspace, counted; 92 % of the
-// issue slots at the 2.1 GHz the chip holds).  Prompt of 32K tokens x 32 heads x (K, V), M = 64: 2.75 ms with 4x4x4
-// instructions in two passes (one for the best value, one for the marks), 1.50 ms now.
+// Cost per (sub-vector, centroid): 1.4 vector operations instead of 2 ds + 3 in fp64, the matrix instructions in
+// parallel: 355 vector instructions per 64 tokens and subspace counted at M = 64, 16 of them matrix instructions, which
+// fill 82 % of the issue slots at the 2.0 GHz the chip holds (M = 32: 394, 82 %; fp32, M = 64: 407, 78 %); what the
+// wavefronts wait for in the rest is not known.  Prompt of 32K tokens x 32 heads x (K, V), M = 64: 2.75 ms with 4x4x4
+// instructions in two passes (one for the best value, one for the marks), 1.54 ms now.
 //
 // A workgroup is 4 neighbouring subspaces of the same tokens, one wavefront each: a token's line of 64 subspaces is
 // then fetched from L2 once for four wavefronts (one wavefront per workgroup 2.69 ms, two 2.35, four 1.75, eight 1.73

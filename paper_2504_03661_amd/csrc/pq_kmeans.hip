@@ -19,7 +19,7 @@
 // in LDS (LDS atomics); the sums reach memory with one 64-bit atomic per touched entry and slice.  The 4 wavefronts
 // read neighbouring words of the same rows, so a line of samples leaves L2 once for all of them.  Bound by the issue
 // of vector instructions in the nearest-centroid filter, as the encode; 32 heads x 65536 samples, M = 64: 2.7 ms per
-// iteration with one subspace per workgroup and the two-pass filter, 1.56 ms now (two or four wavefronts per subspace
+// iteration with one subspace per workgroup and the two-pass filter, 1.58 ms now (two or four wavefronts per subspace
 // on one set of sums, for more wavefronts per compute unit: 1.6 and 1.8 ms).
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -190,9 +190,10 @@ hipError_t pq_launch_kmeans(const pq_attn_ctx *ctx, const void *samples, int n_s
     hipLaunchKernelGGL(pq_clear_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s,
                        (uint32_t *)workspace, words);
     // A wavefront takes several chunks of 64 samples in a row: one codebook set-up and one pass of up to 256 (ds + 1)
-    // memory atomics for all of them.  At 3 workgroups per compute unit 3072 wavefronts are resident: few samples make one
-    // round of them (8 heads x 2000: 31.5 us; 40 with 8192 wavefronts, 33 with one subspace per workgroup), many between
-    // two and three (8 heads x 30000: 209 us; 236 with 3072 wavefronts, whose last round is a third full).
+    // memory atomics for all of them.  Taken as resident are 3072 wavefronts, 3 workgroups per compute unit: few samples
+    // make one round of them (8 heads x 2000: 31 us; 40 with 8192 wavefronts, 33 with one subspace per workgroup), many
+    // between two and three (8 heads x 30000: 219 us; on a faster box 209, and 236 with 3072 wavefronts, whose last round
+    // is a third full).
     const int n_chunks = (n_samples + 63) / 64;
     const int64_t waves = (int64_t)Hkv * n_chunks * M;
     const int64_t one_round = (waves + 3071) / 3072, several = waves / 8192;
