@@ -197,8 +197,8 @@ __device__ inline void unit_and_walker(uint32_t bid, uint32_t n_units, uint32_t 
 // BATCH_DEAL: job `job` of query head (or group of them) `sub` of the n per KV head.
 // The n workgroups that read the same codes — the same job of each query head — are neighbours and share an XCD's L2, as
 // the query heads of a sequence are in the other numbering.  (With a head's jobs in a row they were S workgroups apart:
-// 8 query heads of one KV head, 31 sequences of 4K tokens, fp32, 1.39 times the time of splits per sequence, 1.13 so; 12
-// of 30K, fp16, 1.06 and 0.98 times.)
+// 8 query heads of one KV head, 31 sequences of 4K tokens, fp32, 1.37 times the time of splits per sequence, 1.01 so;
+// 12 of 30K, fp16, 1.06 and 0.98 times.)
 __device__ inline void unit_and_job(uint32_t bid, uint32_t Hkv, uint32_t S, uint32_t n, const pq_batch_divisors &d, uint32_t &hkv,
                                     uint32_t &sub, uint32_t &job)
 {
