@@ -84,7 +84,7 @@ int pq_attn_create(const pq_attn_config *cfg /* host */, pq_attn_ctx **out /* ho
 int pq_attn_destroy(pq_attn_ctx *ctx);
 
 /* Number of context splits the decode kernel uses (after "0 = choose"; a batch whose workgroups follow the
- * sequences' lengths: the number for equal lengths). */
+ * sequences' lengths has no such number: the one that fills the chip with equal lengths is returned). */
 int pq_attn_n_splits(const pq_attn_ctx *ctx);
 
 /* Kernels one pq_attn_decode call launches: 1 (fused), or 2 for a 4096-centroid
