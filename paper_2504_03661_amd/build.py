@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libpq_attn.so")
 CALLS_SOURCE = os.path.join(CSRC, "pq_binding.cpp")
 CALLS = os.path.join(HERE, "_pq_calls" + sysconfig.get_config_var("EXT_SUFFIX"))    # for this interpreter
 SOURCES = ["pq12_codes.hip", "pq12_decode.hip", "pq12_decode_grouped.hip", "pq_api.hip", "pq_decode.hip", "pq_decode_grouped.hip", "pq_encode.hip", "pq_kmeans.hip", "pq_layout.hip"]
-HEADERS = [os.path.join(CSRC, "pq_internal.h"), os.path.join(CSRC, "pq_device_utils.h"), os.path.join(CSRC, "pq_nearest_filter.h"), os.path.join(CSRC, "pq_filter_constants.h"),
+HEADERS = [os.path.join(CSRC, "pq_internal.h"), os.path.join(CSRC, "pq_device_utils.h"), os.path.join(CSRC, "pq_nearest_filter.h"), os.path.join(CSRC, "pq_nearest_grid.h"), os.path.join(CSRC, "pq_filter_constants.h"),
            os.path.join(ROOT, "include", "pq_attn.h")]
 
 # packed-fp32 instructions are switched off for all device code; -ffp-contract=off keeps

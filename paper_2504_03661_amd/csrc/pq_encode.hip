@@ -20,6 +20,7 @@
 #include "pq_internal.h"
 #include "pq_device_utils.h"
 #include "pq_nearest_filter.h"
+#include "pq_nearest_grid.h"
 
 namespace {
 
@@ -224,6 +225,106 @@ __global__ __launch_bounds__(FAST_WAVES * 64) void pq_encode_fast_kernel(const p
 }
 
 // ---------------------------------------------------------------------------------
+// Long appends at ds = 2: the grid of pq_nearest_grid.h.  A workgroup is 4 neighbouring subspaces of one head (K or V) and a
+// slice of the tokens: it builds their 4 grids and then walks the tokens, one 16-byte load (fp16; fp32: two) of a token for
+// the 4 subspaces.  The 16 workgroups of the same tokens run on one XCD at about the same time, so a token's row comes from
+// memory once.  Chunks are the 64-token blocks of the code layout: a lane's 4 offsets inside a block never change.
+template <typename T> struct grid_token {
+    T x[GRID_SUB][2];
+    bool live;
+    int64_t block;  // byte offset of the chunk's block of codes
+};
+
+template <typename T>
+__global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const pq_encode_args a, const int seq_chunks, const int slices,
+                                                                         const int slice_chunks)
+{
+    constexpr int M = 64;
+    __shared__ __attribute__((aligned(16))) pq_grid<T> grid[GRID_SUB];
+    __shared__ uint32_t queue[GRID_WAVES][GRID_QUEUE];
+    __shared__ float2 box[GRID_SIDE];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // an XCD takes whole units of 16 workgroups, one after the other
+    const int local = blockIdx.x >> 3;
+    const int unit = (local >> 4) * 8 + (blockIdx.x & 7);
+    if (unit >= 2 * a.Hkv * slices)
+        return;
+    const int i0 = (local & 15) * GRID_SUB;
+    const int head = unit / slices, slice = unit - head * slices;
+    const int which = head >= a.Hkv, hkv = which ? head - a.Hkv : head;
+    const int n_chunks = a.B * seq_chunks;
+    const int first = slice * slice_chunks;
+    const int last = first + slice_chunks < n_chunks ? first + slice_chunks : n_chunks;
+
+    pq_grid_build(grid, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
+
+    const T *x = (const T *)a.x[which] + i0 * 2;
+    uint8_t *codes = a.codes[which];
+    const int n_new = a.n_new, cap = a.max_context;
+    int in_block[GRID_SUB];
+#pragma unroll
+    for (int j = 0; j < GRID_SUB; ++j)
+        in_block[j] = which == 0 ? (int)pq_k_code_offset((uint32_t)lane, i0 + j, M, a.k_skew) : (int)pq_v_code_offset((uint32_t)lane, i0 + j, M);
+    // the next chunk: sequence b, block r of it
+    int b = (first + wave) / seq_chunks;
+    int r = first + wave - b * seq_chunks;
+    auto length = [&](int seq) {
+        const int n = a.ctx_len[seq];
+        return n < 0 ? 0 : n < cap ? n : cap;
+    };
+    auto fetch = [&](int, grid_token<T> &k) {
+        const bool any = b < a.B;
+        const int seq = any ? b : a.B - 1;
+        const int n_old = length(seq);
+        const int t = r * 64 + lane - (n_old & 63);  // position among the new tokens
+        const int pos = (n_old & ~63) + r * 64 + lane;
+        k.live = any && t >= 0 && t < n_new && pos < cap;
+        const int row = t < 0 ? 0 : t < n_new ? t : n_new - 1;
+        const T *xp = x + (((int64_t)seq * a.Hkv + hkv) * n_new + row) * PQ_HEAD_DIM;
+        typedef T quad __attribute__((ext_vector_type(16 / sizeof(T))));
+        quad part[sizeof(T) / 2];
+#pragma unroll
+        for (int v = 0; v < (int)sizeof(T) / 2; ++v)
+            part[v] = ((const quad *)xp)[v];
+        __builtin_memcpy(k.x, part, sizeof(k.x));
+        k.block = ((int64_t)seq * a.Hkv + hkv) * a.head_stride + (int64_t)((n_old >> 6) + r) * (64 * M);
+        r += GRID_WAVES;
+        while (r >= seq_chunks && b < a.B) {
+            r -= seq_chunks;
+            ++b;
+        }
+    };
+    auto place = [&](uint32_t id, int &seq, int &t, int &pos) {
+        const uint32_t chunk = (uint32_t)first + (id >> 8);
+        seq = a.B == 1 ? 0 : (int)(chunk / (uint32_t)seq_chunks);  // (a division is some 25 instructions)
+        const int block = (int)(chunk - (uint32_t)seq * (uint32_t)seq_chunks), n_old = length(seq);
+        t = block * 64 + (int)((id >> 2) & 63u) - (n_old & 63);
+        pos = n_old + t;
+    };
+    pq_grid_scan<T, grid_token<T>>(
+        grid, queue[wave], first, last, fetch,
+        [&](const grid_token<T> &k, int j, int code) {
+            codes[k.block + (uint32_t)pq_grid_pick(j, in_block[0], in_block[1], in_block[2], in_block[3])] = (uint8_t)code;
+        },
+        [&](uint32_t id, T &x0, T &x1) {
+            int seq, t, pos;
+            place(id, seq, t, pos);
+            const T *xp = x + (((int64_t)seq * a.Hkv + hkv) * n_new + t) * PQ_HEAD_DIM + (id & 3u) * 2;
+            x0 = xp[0];
+            x1 = xp[1];
+        },
+        [&](uint32_t id, T, T, int code) {
+            int seq, t, pos;
+            place(id, seq, t, pos);
+            const int i = i0 + (int)(id & 3u);
+            const uint32_t off = which == 0 ? pq_k_code_offset((uint32_t)pos, i, M, a.k_skew) : pq_v_code_offset((uint32_t)pos, i, M);
+            codes[((int64_t)seq * a.Hkv + hkv) * a.head_stride + off] = (uint8_t)code;
+        });
+}
+
+// ---------------------------------------------------------------------------------
 // A handful of tokens per KV head (one decoding step of a small batch): lane = CENTROID.  With one token per
 // lane a wavefront would walk 256 centroids for a few live lanes; here every lane holds 4 centroids in
 // registers, evaluates the defining fp64 distances of the token at hand to its 4 (ascending, strict "<") and
@@ -331,6 +432,15 @@ void launch_fast(const pq_encode_args &a, hipStream_t s)
         hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, false>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
 }
 
+template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, int slices, hipStream_t s)
+{
+    const int n_chunks = a.B * seq_chunks;
+    const int slice_chunks = (n_chunks + slices - 1) / slices;
+    const int units = 2 * a.Hkv * slices;
+    hipLaunchKernelGGL((pq_encode_grid_kernel<T>), dim3((unsigned)((units + 7) / 8 * 128)), dim3(64 * GRID_WAVES), 0, s, a, seq_chunks, slices,
+                       slice_chunks);
+}
+
 hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,
                             hipStream_t s)
 {
@@ -352,7 +462,14 @@ hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int
             return e;
         return pq_launch_bump_len(ctx_len, a.B, a.n_new, a.max_context, dev_err, s);
     }
-    if (ctx->cfg.n_subspaces == 64) {
+    const int seq_chunks = (int)(((int64_t)a.n_new + 126) >> 6);  // blocks of 64 positions that n_new tokens can touch
+    // its 16-byte loads ask for rows that start at such an address
+    const bool grid_can = ctx->cfg.n_subspaces == 64 && (((uintptr_t)a.x[0] | (uintptr_t)a.x[1]) & 15) == 0 &&
+                          (int64_t)a.B * seq_chunks < (1 << 30);
+    const int slices = grid_can ? pq_grid_slices((int64_t)a.B * seq_chunks, ((int64_t)a.B * a.n_new + 63) / 64, (int64_t)2 * a.Hkv * 16, ctx->n_cu) : 0;
+    if (slices > 0) {
+        if (f16) launch_grid<_Float16>(a, seq_chunks, slices, s); else launch_grid<float>(a, seq_chunks, slices, s);
+    } else if (ctx->cfg.n_subspaces == 64) {
         if (f16) launch_fast<64, 2, _Float16>(a, s); else launch_fast<64, 2, float>(a, s);
     } else {
         if (f16) launch_fast<32, 4, _Float16>(a, s); else launch_fast<32, 4, float>(a, s);

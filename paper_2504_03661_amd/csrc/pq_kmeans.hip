@@ -26,6 +26,7 @@
 
 #include "pq_internal.h"
 #include "pq_nearest_filter.h"
+#include "pq_nearest_grid.h"
 
 namespace {
 
@@ -122,6 +123,82 @@ __global__ __launch_bounds__(KM_SUB * 64) void pq_kmeans_assign_kernel(const __h
             atomicAdd(&counts[acc_base + e], part_cnt[e]);
 }
 
+// Many samples at ds = 2: the same through the grid of pq_nearest_grid.h.  A workgroup is 4 neighbouring subspaces of a head and
+// a slice of the samples; sums and counts of the 4 in LDS.  A coordinate enters its sum as the bits of the double
+// x 2^24 + 1.5 2^52: an integer with a constant on top, which the count takes out again.
+struct pq_sample {
+    _Float16 x[GRID_SUB][2];
+    bool live;
+};
+
+__global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _Float16 *samples, const _Float16 *codebook,
+                                                                         unsigned long long *sums, unsigned int *counts, const int n_heads,
+                                                                         const int n_samples, const int slices, const int slice_chunks)
+{
+    constexpr int M = 64;
+    __shared__ __attribute__((aligned(16))) pq_grid<_Float16> grid[GRID_SUB];
+    __shared__ uint32_t queue[GRID_WAVES][GRID_QUEUE];
+    __shared__ float2 box[GRID_SIDE];
+    __shared__ unsigned long long sum[GRID_SUB][512];
+    __shared__ unsigned int count[GRID_SUB][256];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // an XCD takes whole units of the 16 workgroups that share their samples, one after the other
+    const int local = blockIdx.x >> 3;
+    const int unit = (local >> 4) * 8 + (blockIdx.x & 7);
+    if (unit >= n_heads * slices)
+        return;
+    const int i0 = (local & 15) * GRID_SUB;
+    const int head = unit / slices, slice = unit - head * slices;
+    const int n_chunks = (n_samples + 63) >> 6;
+    const int first = slice * slice_chunks;
+    const int last = first + slice_chunks < n_chunks ? first + slice_chunks : n_chunks;
+
+    for (int e = threadIdx.x; e < GRID_SUB * 512; e += GRID_WAVES * 64)
+        ((unsigned long long *)sum)[e] = 0ull;
+    for (int e = threadIdx.x; e < GRID_SUB * 256; e += GRID_WAVES * 64)
+        ((unsigned int *)count)[e] = 0u;
+    pq_grid_build(grid, box, codebook + ((int64_t)head * M + i0) * 512);
+
+    constexpr uint64_t BASE = 0x4338000000000000ull;  // the bits of 1.5 2^52
+    const _Float16 *x = samples + (int64_t)head * n_samples * PQ_HEAD_DIM + i0 * 2;
+    auto add = [&](int j, int code, _Float16 x0, _Float16 x1) {
+        atomicAdd(&sum[j][code * 2], (unsigned long long)__double_as_longlong(__builtin_fma((double)(float)x0, 16777216.0, 6755399441055744.0)));
+        atomicAdd(&sum[j][code * 2 + 1], (unsigned long long)__double_as_longlong(__builtin_fma((double)(float)x1, 16777216.0, 6755399441055744.0)));
+        atomicAdd(&count[j][code], 1u);
+    };
+    pq_grid_scan<_Float16, pq_sample>(
+        grid, queue[wave], first, last,
+        [&](int chunk, pq_sample &k) {
+            const int s = chunk * 64 + lane;
+            k.live = s < n_samples;
+            const f16x8 row = *(const f16x8 *)(x + (int64_t)(k.live ? s : n_samples - 1) * PQ_HEAD_DIM);
+            __builtin_memcpy(k.x, &row, sizeof(k.x));
+        },
+        [&](const pq_sample &k, int j, int code) {
+            add(j, code, pq_grid_pick(j, k.x[0][0], k.x[1][0], k.x[2][0], k.x[3][0]), pq_grid_pick(j, k.x[0][1], k.x[1][1], k.x[2][1], k.x[3][1]));
+        },
+        [&](uint32_t id, _Float16 &x0, _Float16 &x1) {
+            const _Float16 *xp = x + ((int64_t)(first + (int)(id >> 8)) * 64 + (id >> 2 & 63u)) * PQ_HEAD_DIM + (id & 3u) * 2;
+            x0 = xp[0];
+            x1 = xp[1];
+        },
+        [&](uint32_t id, _Float16 x0, _Float16 x1, int code) { add((int)(id & 3u), code, x0, x1); });
+    __syncthreads();
+
+    const int64_t acc = ((int64_t)head * M + i0) * 256;
+    for (int e = threadIdx.x; e < GRID_SUB * 256; e += GRID_WAVES * 64) {
+        const unsigned int n = ((const unsigned int *)count)[e];
+        if (n == 0u)
+            continue;
+#pragma unroll
+        for (int d = 0; d < 2; ++d)
+            atomicAdd(&sums[(acc + e) * 2 + d], ((const unsigned long long *)sum)[e * 2 + d] - n * BASE);
+        atomicAdd(&counts[acc + e], n);
+    }
+}
+
 // one thread per (head, subspace, centroid)
 template <int DS>
 __global__ void pq_kmeans_update_kernel(__half *codebook, unsigned long long *sums, unsigned int *counts, int64_t n)
@@ -200,8 +277,16 @@ hipError_t pq_launch_kmeans(const pq_attn_ctx *ctx, const void *samples, int n_s
     const int rounds = (int)(several > 64 ? 64 : several > 16 ? several : one_round < 16 ? one_round : 16);
     const int n_slices = (n_chunks + rounds - 1) / rounds;
     const dim3 grid((unsigned)(Hkv * n_slices), (unsigned)(M / KM_SUB)), block(KM_SUB * 64);
+    // (its 16-byte loads ask for samples that start at such an address)
+    const int grid_slices = M == 64 && ((uintptr_t)samples & 15) == 0 ? pq_grid_slices(n_chunks, n_chunks, (int64_t)Hkv * 16, ctx->n_cu) : 0;
     for (int it = 0; it < n_iters; ++it) {
-        if (M == 64) {
+        if (grid_slices > 0) {
+            hipLaunchKernelGGL(pq_kmeans_grid_kernel, dim3((unsigned)((Hkv * grid_slices + 7) / 8 * 128)), dim3(GRID_WAVES * 64), 0, s,
+                               (const _Float16 *)samples, (const _Float16 *)codebook, sums, counts, Hkv, n_samples, grid_slices,
+                               (n_chunks + grid_slices - 1) / grid_slices);
+            hipLaunchKernelGGL(pq_kmeans_update_kernel<2>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                               (__half *)codebook, sums, counts, n);
+        } else if (M == 64) {
             hipLaunchKernelGGL((pq_kmeans_assign_kernel<64, 2>), grid, block, 0, s, (const __half *)samples,
                                (const __half *)codebook, sums, counts, n_samples, n_slices, rounds);
             hipLaunchKernelGGL(pq_kmeans_update_kernel<2>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,

@@ -1,0 +1,670 @@
+// Nearest centroid of many 2-dim sub-vectors among 256 centroids: a grid over the plane that names, for every cell, the
+// centroids that can be the nearest of a point in it.  Shared by the encode of long appends and the k-means assignment;
+// the decision is the same fp64 expression as everywhere (pq_encode.hip), so codes are bit-exact.
+//
+// The filter of pq_nearest_filter.h looks at all 256 values of every token: 355 vector instructions per 64 tokens.  In two
+// dimensions the plane can be cut up once per codebook instead, and a token then looks at the 2 or 3 centroids of its cell:
+// some 60 instructions.  Building a grid costs as much as 70 chunks of 64 tokens through the filter, so the grid serves
+// appends and trainings of thousands of tokens per head (pq_grid_slices below).
+//
+// Map.  Per axis u = s x + o, fp32, chosen from the codebook (mean and mean deviation of its coordinates without outliers):
+// |u| <= 28 holds what lies within some 4 standard deviations.  The cell coordinate is five bits of the float |u| + 2 — 8
+// cells in each of the four octaves [2, 4) .. [16, 32), fine in the middle and coarse outside, for an addition and a shift —
+// and the sign.  64 x 64 cells of 4 bytes.  The last cell on each side takes everything beyond: no list, "outside".
+// Lists.  A centroid c can be the nearest of a point of a box only if the bisector of c and some reference centroid r leaves
+// part of the box on its side: F_c(g) - F_r(g) <= |da_x| h_x + |da_y| h_y with F_c(p) = |c|^2 / 2 - p . c, g and h the box's
+// centre and half sides, da the difference of the gradients.  r is the nearest centroid of the box's centre (any r is safe).
+// First for 16 x 16 blocks of 4 x 4 cells, all 256 centroids each; then for every cell, the centroids of its block.
+// The test runs in fp32 in u space, where a squared distance is w_x du_x^2 + w_y du_y^2: every F is lowered by 2^-18 of its
+// |c|^2 / 2 and the threshold raised by 2^-17 (|r|^2 / 2 + |g|^2 + ..), 16 times what the roundings of u, F and w amount to;
+// boxes are 2^-17 wider on each side than the cells (the float |u| + 2 is good to 2^-19).
+// A cell's word holds its codes if they are at most 4, filled up with codes that are not in its list; otherwise the two low
+// bytes are equal (which the distinct codes of a list never are): the number of words, and in the upper half where they
+// stand in the pool.  No words: outside, or no room, or more than 64 candidates in the block.
+// Tokens.  The four distances in fp32 (relative error below 2^-21), their 8 low bits replaced by the code: one unsigned
+// minimum gives the least and its code, one median keeps the second.  More than 2^-16 apart, the order is that of the fp64
+// distances; otherwise, and for tokens outside, all 64 lanes evaluate the token's fp64 distances to all centroids together
+// (four per lane); where a chunk has many such tokens, or the codebook gave no useful grid, the filter takes the chunk.
+// Tokens of cells with longer lists (7 % with a codebook of random vectors, 1 % with a trained one) wait in LDS until 64 are
+// there and are then worked on as one.
+#pragma once
+
+#include "pq_device_utils.h"
+#include "pq_nearest_filter.h"
+
+namespace {
+
+constexpr int GRID_SUB = 4;       // neighbouring subspaces of a workgroup: 16 bytes of every token's fp16 row
+constexpr int GRID_WAVES = 16;    // 4 wavefronts build each subspace's grid; then all take tokens, 4 subspaces at a time
+constexpr int GRID_SIDE = 64;
+constexpr int GRID_POOL = 1024;   // words of longer lists per subspace
+constexpr int GRID_QUEUE = 320;   // waiting tokens of a wavefront: fewer than 64, and up to 64 of each subspace
+constexpr int GRID_SHIFT = 20;    // 8 cells per octave
+constexpr float GRID_BIAS = 2.0f;
+constexpr uint32_t GRID_FIRST = 0x40000000u, GRID_LAST = 0x41ffffffu;  // float bits of 2 .. just below 32
+constexpr float GRID_COVER = 28.0f;  // where the outermost cell starts, less the bias
+constexpr uint32_t GRID_NONE = 0x01000100u;  // a cell without a list: two codes, twice, so that the least has an equal
+constexpr uint32_t GRID_SURE = 512;  // keys at least this far apart are in the right order
+
+template <typename T> struct pq_grid {
+    uint32_t cell[GRID_SIDE * GRID_SIDE];  // [u_x][u_y]; while building, the 64 bytes of a 4 x 4 block are its list
+    unsigned char arow[256 * pq_filter_row_bytes<T>()];
+    float table[256][4];  // a_x, a_y, |c|^2 / 2 lowered, |c|^2 / 2
+    T coord[256][2];
+    uint32_t pool[GRID_POOL];
+    float sx, ox, sy, oy;  // the map
+    float scale;           // of the filter
+    uint32_t pool_used, unserved, bad;  // bad: 1 no grid, 2 codebook outside the filter's range
+};
+
+// bits 20 .. 25: the cell coordinate, 0 .. 31 upwards from zero, 63 .. 32 downwards
+__device__ __forceinline__ uint32_t pq_grid_axis(const float u)
+{
+    const uint32_t b = min(__float_as_uint(__builtin_fabsf(u) + GRID_BIAS), GRID_LAST);
+    return b ^ (uint32_t)(__float_as_int(u) >> 31);
+}
+
+// byte offset of the cell of a point
+template <typename T>
+__device__ __forceinline__ uint32_t pq_grid_cell(const T x, const T y, const float sx, const float ox, const float sy, const float oy)
+{
+    const uint32_t ex = pq_grid_axis(__builtin_fmaf((float)x, sx, ox));
+    const uint32_t ey = pq_grid_axis(__builtin_fmaf((float)y, sy, oy));
+    static_assert(GRID_SHIFT == 20 && GRID_SIDE == 64, "the shifts below");
+    return ((ex >> 12) & 0x3f00u) | ((ey >> 18) & 0xfcu);
+}
+
+// lower edge of cell coordinate k = -32 .. 32 (31 and -32: the open ones, given an end)
+__device__ __forceinline__ float pq_grid_edge(const int k)
+{
+    const float e = __uint_as_float(GRID_FIRST + ((uint32_t)(k < 0 ? -k : k) << GRID_SHIFT)) - GRID_BIAS;
+    return k < 0 ? -e : e;
+}
+
+// one of four candidates of a list word: its fp32 distance with the code in the low byte
+template <int K, typename T>
+__device__ __forceinline__ uint32_t pq_grid_key(const T (&coord)[256][2], const uint32_t word, const T x, const T y, const float minus_one)
+{
+#pragma clang fp contract(off)
+    const uint32_t c = (word >> (8 * K)) & 255u;
+    float dx, dy;
+    if constexpr (sizeof(T) == 2) {
+        const uint32_t both = *(const uint32_t *)&coord[c][0];
+        const _Float16 cx = __builtin_bit_cast(_Float16, (uint16_t)both), cy = __builtin_bit_cast(_Float16, (uint16_t)(both >> 16));
+        dx = __builtin_fmaf((float)cx, minus_one, (float)x);  // (one instruction takes both halves)
+        dy = __builtin_fmaf((float)cy, minus_one, (float)y);
+    } else {
+        const float2 both = *(const float2 *)&coord[c][0];
+        dx = x - both.x;
+        dy = y - both.y;
+    }
+    const float d = __builtin_fmaf(dy, dy, dx * dx);
+    return __builtin_amdgcn_perm(__float_as_uint(d), word, 0x07060500u | (uint32_t)K);
+}
+
+__device__ __forceinline__ void pq_grid_take(uint32_t &m1, uint32_t &m2, const uint32_t key)
+{
+    asm("v_med3_u32 %0, %1, %0, %2" : "+v"(m2) : "v"(m1), "v"(key));  // m1 <= m2: the middle one of three
+    m1 = min(m1, key);
+}
+
+// whether the order of the two least fp32 distances may differ from that of the fp64 ones
+template <typename T> __device__ __forceinline__ bool pq_grid_unsure(const uint32_t m1, const uint32_t m2)
+{
+    // fp32 coordinates: squares below 2^-100 are not good to 2^-21 any more
+    return m2 - m1 < GRID_SURE || (sizeof(T) == 4 && m2 < 0x0d800000u);
+}
+
+// A wavefront's part of a subspace's tables: the map, which all 4 wavefronts work out alike, and the rows and numbers of
+// centroids 64 part .. 64 part + 63.  src: [256][2]
+template <typename T> __device__ inline void pq_grid_tables(pq_grid<T> &g, const T *src, const int part)
+{
+    const int lane = threadIdx.x & 63;
+    float x[4], y[4];
+    T mine[2] = {};
+    float c_max = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const T cx = src[(lane + 64 * r) * 2], cy = src[(lane + 64 * r) * 2 + 1];
+        x[r] = (float)cx;
+        y[r] = (float)cy;
+        c_max = fmaxf(c_max, fmaxf(fabsf(x[r]), fabsf(y[r])));
+        if (r == part) {
+            mine[0] = cx;
+            mine[1] = cy;
+        }
+    }
+    c_max = wave_max(c_max);
+    const float scale = pq_filter_scale<T>(c_max);
+    // mean and mean deviation, then those of the coordinates within 3 mean deviations
+    float mx = 0.f, my = 0.f, ex = 3.0e38f, ey = 3.0e38f, dx = 0.f, dy = 0.f;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        float sx = 0.f, sy = 0.f, nx = 0.f, ny = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool in_x = fabsf(x[r] - mx) <= ex, in_y = fabsf(y[r] - my) <= ey;
+            sx += in_x ? x[r] : 0.f;
+            sy += in_y ? y[r] : 0.f;
+            nx += in_x ? 1.f : 0.f;
+            ny += in_y ? 1.f : 0.f;
+        }
+        nx = 1.0f / wave_sum(nx);
+        ny = 1.0f / wave_sum(ny);
+        const float new_mx = wave_sum(sx) * nx, new_my = wave_sum(sy) * ny;
+        dx = dy = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            dx += fabsf(x[r] - mx) <= ex ? fabsf(x[r] - new_mx) : 0.f;
+            dy += fabsf(y[r] - my) <= ey ? fabsf(y[r] - new_my) : 0.f;
+        }
+        dx = wave_sum(dx) * nx;
+        dy = wave_sum(dy) * ny;
+        mx = new_mx;
+        my = new_my;
+        ex = 3.0f * dx;
+        ey = 3.0f * dy;
+    }
+    // 5 of these mean deviations are 3.75 standard deviations of normal coordinates
+    const float sx = GRID_COVER / (5.0f * dx), sy = GRID_COVER / (5.0f * dy);
+    const float ox = -mx * sx, oy = -my * sy;
+    // squared distances in units of 1 / s_x^2
+    const float ratio = sx / sy, wy = ratio * ratio;
+    bool usable = dx > 1.0e-30f && dy > 1.0e-30f && c_max < 1.0e30f && wy > 1.0e-9f && wy < 1.0e9f;
+    bool far_out = false, cb_bad = false;
+    const int c = 64 * part + lane;
+    pq_filter_build_row<2>(mine, scale, g.arow + c * pq_filter_row_bytes<T>(), cb_bad);
+    const float ux = __builtin_fmaf((float)mine[0], sx, ox), uy = __builtin_fmaf((float)mine[1], sy, oy);
+    far_out = !(fabsf(ux) < 1.0e6f && fabsf(uy) < 1.0e6f);
+    const float ay = wy * uy, n = 0.5f * (ux * ux + uy * ay);
+    g.table[c][0] = ux;
+    g.table[c][1] = ay;
+    g.table[c][2] = n * (1.0f - 3.814697265625e-06f);  // 2^-18
+    g.table[c][3] = n;
+    g.coord[c][0] = mine[0];
+    g.coord[c][1] = mine[1];
+    const uint32_t bad = (__builtin_amdgcn_ballot_w64(far_out) != 0 || !usable ? 1u : 0u) |
+                         (__builtin_amdgcn_ballot_w64(cb_bad) != 0 ? 3u : 0u);
+    if (lane == 0) {
+        if (part == 0) {
+            g.sx = sx;
+            g.ox = ox;
+            g.sy = sy;
+            g.oy = oy;
+            g.scale = scale;
+        }
+        if (bad)
+            atomicOr(&g.bad, bad);
+    }
+}
+
+__device__ __forceinline__ void pq_grid_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// centre and half side of cell coordinates e .. e + n - 1 (e as in pq_grid_axis)
+__device__ __forceinline__ void pq_grid_box(const int e, const int n, float &g, float &h)
+{
+    const int k = e < 32 ? e : e - 64;
+    const float lo = pq_grid_edge(k), hi = pq_grid_edge(k + n);
+    g = 0.5f * (lo + hi);
+    h = 0.5f * (hi - lo) + 7.62939453125e-06f;  // 2^-17
+}
+
+// appends the bit t <= limit to a mask
+__device__ __forceinline__ void pq_grid_mark(uint32_t &mask, const float t, const float limit)
+{
+    asm("v_cmp_le_f32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(mask) : "v"(t), "v"(limit) : "vcc");
+}
+
+// the same, and shifts a code into a word of the last four that were marked
+__device__ __forceinline__ void pq_grid_mark(uint32_t &mask, uint32_t &word, const uint32_t code, const float t, const float limit)
+{
+    const uint32_t next = word << 8 | code;
+    uint64_t carry;
+    asm("v_cmp_le_f32_e32 vcc, %4, %5\n\tv_addc_co_u32_e64 %0, %2, %0, %0, vcc\n\tv_cndmask_b32_e32 %1, %1, %3, vcc"
+        : "+v"(mask), "+v"(word), "=&s"(carry)
+        : "v"(next), "v"(t), "v"(limit)
+        : "vcc");
+}
+
+// lane K's value in every row of 16 lanes
+template <int K> __device__ __forceinline__ float pq_grid_row(const float x) { return dpp_move<0x150 + K>(x); }
+
+// v += x (lane K's in every row of 16 lanes) ax + y (lane K's) ay; two wait states after a vector write of x or y are due
+// before they are read across lanes
+template <int K> __device__ __forceinline__ void pq_grid_row_fma(float &v, const float x, const float ax, const float y, const float ay)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+        : "+&v"(v) : "v"(x), "v"(ax), "v"(y), "v"(ay), "n"(K));
+}
+
+// calls f(integral constant 0 .. N - 1), four at a time while the first of the four is below `most` (uniform)
+template <int K, int N, typename F> __device__ __forceinline__ void pq_grid_fours(const int most, F f)
+{
+    if constexpr (K < N) {
+        if (K < most) {
+            f(std::integral_constant<int, K>());
+            f(std::integral_constant<int, K + 1>());
+            f(std::integral_constant<int, K + 2>());
+            f(std::integral_constant<int, K + 3>());
+            pq_grid_fours<K + 4, N>(most, f);
+        }
+    }
+}
+
+// The lists of one quarter of the grid (cell rows 16 part .. 16 part + 15), by one wavefront.  box: centre and half side of
+// the 64 cell coordinates
+template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const float2 (&box)[GRID_SIDE], const int part)
+{
+    const int lane = threadIdx.x & 63;
+    unsigned char *bytes = (unsigned char *)g.cell;
+    const float sx = g.sx, ox = g.ox, sy = g.sy, oy = g.oy;
+    const float ratio = sx / sy, wy = ratio * ratio;
+    constexpr float MARGIN = 1.52587890625e-05f;  // 2^-16
+
+    // ---- lane = block of 4 x 4 cells, all centroids
+    int count = 0;
+    uint32_t fill = 0;  // a code that is not in the block's list
+    {
+        const int bx = part * 4 + (lane >> 4), by = lane & 15;
+        const uint32_t list = (uint32_t)(bx * 1024 + by * 16);  // its bytes: 16 at each of list + 256 k
+        float gx, hx, gy, hy;
+        pq_grid_box(4 * bx, 4, gx, hx);
+        pq_grid_box(4 * by, 4, gy, hy);
+        const float px = (gx - ox) / sx, py = (gy - oy) / sy;
+        const float end = sizeof(T) == 2 ? 60000.f : 3.0e37f;
+        const T p[2] = {(T)fminf(fmaxf(px, -end), end), (T)fminf(fmaxf(py, -end), end)};
+        typedef typename std::conditional<sizeof(T) == 4, float, _Float16>::type W;
+        const int r = pq_filter_code<2, T, W>(g.arow, sizeof(T) == 4 ? (const unsigned char *)g.coord : g.arow, g.scale, false, p, true);
+        const float4 ref = *(const float4 *)g.table[r];
+        const float far_x = fabsf(gx) + hx, far_y = fabsf(gy) + hy;
+        const float limit = __builtin_fmaf(-gy, ref.y, __builtin_fmaf(-gx, ref.x, ref.z)) +
+                            MARGIN * (ref.w + far_x * far_x + wy * far_y * far_y);
+        uint32_t used = 0;  // which of codes 0 .. 31 are in the list
+#pragma unroll 1
+        for (int w = 0; w < 256; w += 32) {
+            uint32_t mask = 0;  // candidate w + k in bit 31 - k
+#pragma unroll 8
+            for (int k = 0; k < 32; ++k) {
+                const float4 c = *(const float4 *)g.table[w + k];
+                float t = __builtin_fmaf(-gy, c.y, __builtin_fmaf(-gx, c.x, c.z));
+                t = __builtin_fmaf(-fabsf(c.x - ref.x), hx, t);
+                t = __builtin_fmaf(-fabsf(c.y - ref.y), hy, t);
+                pq_grid_mark(mask, t, limit);
+            }
+            used = w == 0 ? __builtin_bitreverse32(mask) : used;
+            while (__builtin_amdgcn_ballot_w64(mask != 0) != 0) {
+                const int k = __builtin_clz(mask | 1u);
+                if (mask != 0) {
+                    if (count < 64)
+                        bytes[list + (uint32_t)((count >> 4) * 256 + (count & 15))] = (unsigned char)(w + k);
+                    ++count;
+                }
+                mask &= ~(0x80000000u >> k);
+            }
+        }
+        // Lists are filled up to whole words with a code that is not in them: it is never the least, and being there more
+        // than once it hides no second least.
+        fill = (uint32_t)__builtin_ctz(~used | 0x80000000u);
+        for (int k = count; (k & 3) != 0 && k < 64; ++k)
+            bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))] = (unsigned char)fill;
+        count = used == 0xffffffffu ? 65 : count;  // (none to fill up with: no list)
+    }
+    pq_grid_fence();
+
+    // The blocks in the order of their lists' lengths: the 4 that a step takes are then about equally long.
+    int order = 0;  // lane n: the n-th block
+    {
+        const int key = count * 64 + lane;
+        int rank = 0;
+#pragma unroll 8
+        for (int l = 0; l < 64; ++l)
+            rank += __builtin_amdgcn_readlane(key, l) < key ? 1 : 0;
+        order = __builtin_amdgcn_ds_permute(rank * 4, lane);
+    }
+
+    // ---- 16 lanes = the cells of a block, 4 blocks at a time, the centroids of its list: lane k of the 16 holds the k-th
+#pragma unroll 1
+    for (int it = 0; it < 16; ++it) {
+        const int in_row = lane & 15;
+        const int block = __shfl(order, it * 4 + (lane >> 4));
+        const int n = __shfl(count, block);
+        const int cell_x = 4 * (part * 4 + (block >> 4)) + (in_row >> 2);
+        const int cell_y = 4 * (block & 15) + (in_row & 3);
+        const uint32_t list = (uint32_t)((part * 4 + (block >> 4)) * 1024 + (block & 15) * 16);
+        const int longest = __builtin_amdgcn_readlane(n, 63);  // of the 4 blocks: the last
+        uint32_t word = 0;
+        const bool inside = cell_x != 31 && cell_x != 32 && cell_y != 31 && cell_y != 32;
+        const float2 x = box[cell_x], y = box[cell_y];
+        const float far_x = fabsf(x.x) + x.y, far_y = fabsf(y.x) + y.y;
+        const float half = 0.5f * (x.x * x.x + wy * y.x * y.x);
+        const float minus_gx = -x.x, minus_gy = -y.x;
+        const float far = far_x * far_x + wy * far_y * far_y;
+        const uint32_t fill_cell = (uint32_t)__shfl((int)fill, block) * 0x01010101u;
+        // more than four candidates: written to the pool from a mask of the block's list (candidate k in the k-th bit from
+        // the top)
+        auto write_list = [&](auto mask, const bool listed) {
+            constexpr bool LONG = sizeof(mask) == 8;
+            const int total = LONG ? __builtin_popcountll(mask) : __builtin_popcount((uint32_t)mask);
+            const uint32_t words = (uint32_t)(total + 3) >> 2;
+            uint32_t at = GRID_POOL;
+            if (listed)
+                at = atomicAdd(&g.pool_used, words);
+            const bool fits = listed && at + words <= GRID_POOL;
+            mask = fits ? mask : 0;
+            for (uint32_t w = 0; __builtin_amdgcn_ballot_w64(mask != 0) != 0; ++w) {
+                uint32_t four = fill_cell;
+                const bool any = mask != 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = LONG ? __builtin_clzll(mask | 1u) : __builtin_clz((uint32_t)mask | 1u);
+                    const uint32_t c = bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))];
+                    four = mask != 0 ? __builtin_amdgcn_perm(c, four, 0x03020100u + ((4u - (uint32_t)j) << (8 * j))) : four;
+                    mask &= ~((decltype(mask))1 << (LONG ? 63 - k : 31 - k));
+                }
+                if (any)
+                    g.pool[at + w] = four;
+            }
+            if (listed)
+                word = fits ? words | words << 8 | at << 16 : GRID_NONE;
+        };
+        if (__builtin_amdgcn_readlane(n, 0) <= 32) {
+            const int most = longest < 32 ? longest : 32;
+            const uint32_t code1 = bytes[list + (uint32_t)in_row];
+            float4 first = *(const float4 *)g.table[code1];
+            first.z = in_row < n ? first.z : 1.0e30f;  // behind the block's own list: far away
+            uint32_t code2 = code1;
+            float4 second = first;
+            if (most > 16) {
+                code2 = bytes[list + 256u + (uint32_t)in_row];
+                second = *(const float4 *)g.table[code2];
+                second.z = in_row + 16 < n ? second.z : 1.0e30f;
+            }
+            // half the squared distances of its centre; the least, with its place in the list in the low bits
+            float v[32];
+            int least = 0x7f7fffff;
+            pq_grid_fours<0, 32>(most, [&](auto K) {
+                const float4 &e = K < 16 ? first : second;
+                constexpr int k = K & 15;
+                v[K] = pq_grid_row<k>(e.z) + half;
+                pq_grid_row_fma<k>(v[K], e.x, minus_gx, e.y, minus_gy);
+                least = min(least, (__float_as_int(v[K]) & ~31) | (int)K);
+            });
+            const float4 ref = *(const float4 *)g.table[bytes[list + (uint32_t)(((least >> 4) & 1) * 256 + (least & 15))]];
+            const float nearest = __int_as_float(least & ~31);
+            const float limit = nearest + MARGIN * (2.f * fabsf(nearest) + ref.w + far);
+            uint32_t mask = 0, marked = fill_cell;
+            pq_grid_fours<0, 32>(most, [&](auto K) {
+                const float4 &e = K < 16 ? first : second;
+                constexpr int k = K & 15;
+                float t = __builtin_fmaf(-fabsf(pq_grid_row<k>(e.x) - ref.x), x.y, v[K]);
+                t = __builtin_fmaf(-fabsf(pq_grid_row<k>(e.y) - ref.y), y.y, t);
+                pq_grid_mark(mask, marked, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(K < 16 ? code1 : code2), 0x150 + k, 0xf, 0xf, true),
+                             t, limit);
+            });
+            mask <<= 32 - ((most + 3) & ~3);
+            word = n <= 32 ? marked : word;
+            const bool listed = n <= 32 && inside && __builtin_popcount(mask) > 4;
+            if (__builtin_amdgcn_ballot_w64(listed) != 0)  // wave-uniform
+                write_list(mask, listed);
+        }
+        if (longest > 32 && __builtin_amdgcn_ballot_w64(n > 32 && n <= 64) != 0) {  // rare
+            const int most = longest < 64 ? longest : 64;
+            float nearest = 3.0e38f;
+            int r = 0;
+#pragma unroll 4
+            for (int k = 0; k < most; ++k) {
+                const int c = bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))];
+                const float v = __builtin_fmaf(g.table[c][1], minus_gy, __builtin_fmaf(g.table[c][0], minus_gx, g.table[c][2] + half));
+                r = v < nearest ? c : r;
+                nearest = fminf(nearest, v);
+            }
+            const float4 ref = *(const float4 *)g.table[r];
+            const float limit = nearest + MARGIN * (2.f * fabsf(nearest) + ref.w + far);
+            uint64_t mask = 0;
+#pragma unroll 4
+            for (int k = 0; k < most; ++k) {
+                const int c = bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))];
+                float t = __builtin_fmaf(g.table[c][1], minus_gy, __builtin_fmaf(g.table[c][0], minus_gx, g.table[c][2] + half));
+                t = __builtin_fmaf(-fabsf(g.table[c][0] - ref.x), x.y, t);
+                t = __builtin_fmaf(-fabsf(g.table[c][1] - ref.y), y.y, t);
+                mask |= (uint64_t)(t <= limit ? 1 : 0) << (63 - k);
+            }
+            mask = n < 64 ? mask & ~(~0ull >> n) : mask;
+            const bool own = n > 32 && n <= 64 && inside;
+            if (own && __builtin_popcountll(mask) <= 4) {
+                word = fill_cell;
+                for (uint64_t left = mask; left != 0;) {
+                    const int k = __builtin_clzll(left);
+                    word = word << 8 | bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))];
+                    left &= ~(1ull << (63 - k));
+                }
+            }
+            const bool listed = own && __builtin_popcountll(mask) > 4;
+            if (__builtin_amdgcn_ballot_w64(listed) != 0)
+                write_list(mask, listed);
+        }
+        g.cell[cell_x * GRID_SIDE + cell_y] = inside && n <= 64 ? word : GRID_NONE;
+    }
+}
+
+// Builds the grids of a workgroup's 4 subspaces.  src: the codebook of the first of them, [4][256][2]
+template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GRID_SUB], float2 (&box)[GRID_SIDE], const T *src)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    pq_grid<T> &g = grid[wave >> 2];
+    const int part = wave & 3;
+    if (threadIdx.x < GRID_SUB) {
+        grid[threadIdx.x].pool_used = 0;
+        grid[threadIdx.x].unserved = 0;
+        grid[threadIdx.x].bad = 0;
+    }
+    if (threadIdx.x < GRID_SIDE)
+        pq_grid_box((int)threadIdx.x, 1, box[threadIdx.x].x, box[threadIdx.x].y);
+    __syncthreads();
+    pq_grid_tables(g, src + (wave >> 2) * 512, part);
+    __syncthreads();
+    if (g.bad == 0)  // (the same for the 4 wavefronts)
+        pq_grid_lists(g, box, part);
+    __syncthreads();
+    // The tokens are taken to lie where the centroids do: with more than 24 of 256 in cells without a list the filter does
+    // the work
+    if (g.bad == 0) {
+        const T(&c)[2] = g.coord[64 * part + lane];
+        const uint32_t word = *(const uint32_t *)((const char *)g.cell + pq_grid_cell(c[0], c[1], g.sx, g.ox, g.sy, g.oy));
+        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(word == GRID_NONE));
+        if (lane == 0 && n != 0)
+            atomicAdd(&g.unserved, (uint32_t)n);
+    }
+    __syncthreads();
+    if (g.bad != 0 || g.unserved > 24) {
+        for (int k = part * 64 + lane; k < GRID_SIDE * GRID_SIDE; k += 256)
+            g.cell[k] = GRID_NONE;
+    }
+    __syncthreads();
+}
+
+// The code of the tokens in `lanes`, one after the other, by all lanes together: the defining fp64 distances, four
+// centroids a lane, the lowest index among equal ones.  grid_of_lane: each lane's grid
+template <typename T>
+__device__ inline int pq_grid_exact(const pq_grid<T> (&grid)[GRID_SUB], uint64_t lanes, const int grid_of_lane, const T x, const T y)
+{
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x & 63;
+    int code = 0;
+    while (lanes != 0) {
+        const int l = __builtin_ctzll(lanes);
+        lanes &= lanes - 1;
+        const auto &coord = grid[__builtin_amdgcn_readlane(grid_of_lane, l)].coord;
+        const double px = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int((float)x), l));
+        const double py = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int((float)y), l));
+        double bd = __builtin_huge_val();
+        int bc = lane;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double dx = px - (double)(float)coord[lane + 64 * r][0];
+            const double dy = py - (double)(float)coord[lane + 64 * r][1];
+            const double dist = __builtin_fma(dy, dy, __builtin_fma(dx, dx, 0.0));
+            bc = dist < bd ? lane + 64 * r : bc;
+            bd = __builtin_fmin(bd, dist);
+        }
+        wave_argmin(bd, bc);
+        code = lane == l ? bc : code;
+    }
+    return code;
+}
+
+// the value of subspace j of the group (as values: a choice among array elements would put the array into memory)
+template <typename V> __device__ __forceinline__ V pq_grid_pick(const int j, const V a, const V b, const V c, const V d)
+{
+    return j == 0 ? a : j == 1 ? b : j == 2 ? c : d;
+}
+
+// All tokens of a workgroup, 64 at a time, chunks first + wave, first + wave + 16, .. below last.
+//   fetch(chunk, token &)    the chunk's tokens, lane = token: x[4][2] and live; called for one chunk more than there are,
+//                            in ascending order
+//   store(token, j, code)    the code of this lane's token for subspace j of the group
+//   waiting(id, x, y)        the sub-vector of a token that was put off: id = (chunk - first) << 8 | lane << 2 | j
+//   store_waiting(id, x, y, code)
+template <typename T, typename TOKEN, typename FETCH, typename STORE, typename WAITING, typename STORE_WAITING>
+__device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB], uint32_t (&queue)[GRID_QUEUE], const int first,
+                                             const int last, FETCH fetch, STORE store, WAITING waiting, STORE_WAITING store_waiting)
+{
+    typedef typename std::conditional<sizeof(T) == 4, float, _Float16>::type W;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float sx[GRID_SUB], ox[GRID_SUB], sy[GRID_SUB], oy[GRID_SUB];
+#pragma unroll
+    for (int j = 0; j < GRID_SUB; ++j) {
+        const auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
+        sx[j] = uniform(grid[j].sx);
+        sy[j] = uniform(grid[j].sy);
+        ox[j] = grid[j].ox;
+        oy[j] = grid[j].oy;
+    }
+    float minus_one = -1.0f;
+    asm volatile("" : "+s"(minus_one));  // (a difference of two halves in one instruction, not two conversions more)
+
+    int n_waiting = 0;
+    auto work_off = [&](const int n) {  // the last n
+        n_waiting -= n;
+        const bool live = lane < n;
+        const uint32_t id = queue[n_waiting + (live ? lane : 0)];
+        T x, y;
+        waiting(id, x, y);
+        const int j = (int)(id & 3u);
+        const pq_grid<T> &g = grid[j];
+        const uint32_t word = *(const uint32_t *)((const char *)g.cell + pq_grid_cell(x, y, g.sx, g.ox, g.sy, g.oy));
+        const uint32_t words = word & 255u, at = word >> 16;
+        uint32_t m1 = 0xffffffffu, m2 = 0xffffffffu;
+        for (uint32_t k = 0; __builtin_amdgcn_ballot_w64(k < words) != 0; ++k) {
+            if (k < words) {
+                const uint32_t four = g.pool[at + k];
+                pq_grid_take(m1, m2, pq_grid_key<0>(g.coord, four, x, y, minus_one));
+                pq_grid_take(m1, m2, pq_grid_key<1>(g.coord, four, x, y, minus_one));
+                pq_grid_take(m1, m2, pq_grid_key<2>(g.coord, four, x, y, minus_one));
+                pq_grid_take(m1, m2, pq_grid_key<3>(g.coord, four, x, y, minus_one));
+            }
+        }
+        int code = (int)(m1 & 255u);
+        const uint64_t hard = __builtin_amdgcn_ballot_w64(live && pq_grid_unsure<T>(m1, m2));
+        if (hard != 0) {
+            const int exact = pq_grid_exact(grid, hard, j, x, y);
+            code = __builtin_amdgcn_inverse_ballot_w64(hard) ? exact : code;
+        }
+        if (live)
+            store_waiting(id, x, y, code);
+    };
+
+    TOKEN next;
+    fetch(first + wave, next);
+#pragma unroll 1
+    for (int chunk = first + wave; chunk < last; chunk += GRID_WAVES) {
+        const TOKEN k = next;
+        fetch(chunk + GRID_WAVES, next);  // in flight while this chunk is worked on
+        uint32_t word[GRID_SUB], m1[GRID_SUB], m2[GRID_SUB];
+#pragma unroll
+        for (int j = 0; j < GRID_SUB; ++j)
+            word[j] = *(const uint32_t *)((const char *)grid[j].cell + pq_grid_cell(k.x[j][0], k.x[j][1], sx[j], ox[j], sy[j], oy[j]));
+#pragma unroll
+        for (int j = 0; j < GRID_SUB; ++j) {
+            const uint32_t k0 = pq_grid_key<0>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one);
+            const uint32_t k1 = pq_grid_key<1>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one);
+            m1[j] = min(k0, k1);
+            m2[j] = max(k0, k1);
+            pq_grid_take(m1[j], m2[j], pq_grid_key<2>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one));
+            pq_grid_take(m1[j], m2[j], pq_grid_key<3>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one));
+        }
+        uint64_t hard[GRID_SUB], any = 0;
+        const uint64_t live = __builtin_amdgcn_ballot_w64(k.live);
+#pragma unroll
+        for (int j = 0; j < GRID_SUB; ++j) {
+            const uint64_t listed = __builtin_amdgcn_ballot_w64(((word[j] ^ (word[j] >> 8)) & 255u) == 0) & live;
+            hard[j] = __builtin_amdgcn_ballot_w64(pq_grid_unsure<T>(m1[j], m2[j])) & live & ~listed;
+            any |= hard[j];
+            if (__builtin_amdgcn_inverse_ballot_w64(live & ~(hard[j] | listed)))
+                store(k, j, (int)(m1[j] & 255u));
+            if (__builtin_amdgcn_inverse_ballot_w64(listed)) {
+                const int at = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(listed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)listed, (uint32_t)n_waiting));
+                queue[at] = (uint32_t)(chunk - first) << 8 | (uint32_t)lane << 2 | (uint32_t)j;
+            }
+            n_waiting += __builtin_popcountll(listed);
+        }
+        if (any != 0) {  // wave-uniform
+#pragma unroll 1
+            for (int j = 0; j < GRID_SUB; ++j) {
+                const uint64_t lanes = pq_grid_pick(j, hard[0], hard[1], hard[2], hard[3]);
+                if (lanes == 0)
+                    continue;
+                const T x[2] = {pq_grid_pick(j, k.x[0][0], k.x[1][0], k.x[2][0], k.x[3][0]),
+                                pq_grid_pick(j, k.x[0][1], k.x[1][1], k.x[2][1], k.x[3][1])};
+                int code;
+                if (__builtin_popcountll(lanes) <= 5)  // 80 instructions each
+                    code = pq_grid_exact(grid, lanes, j, x[0], x[1]);
+                else
+                    code = pq_filter_code<2, T, W>(grid[j].arow, sizeof(T) == 4 ? (const unsigned char *)grid[j].coord : grid[j].arow,
+                                                   grid[j].scale, (grid[j].bad & 2u) != 0, x, k.live);
+                if (__builtin_amdgcn_inverse_ballot_w64(lanes))
+                    store(k, j, code);
+            }
+        }
+        if (n_waiting >= 64) {
+            pq_grid_fence();
+            while (n_waiting >= 64)
+                work_off(64);
+            pq_grid_fence();
+        }
+    }
+    pq_grid_fence();
+    if (n_waiting != 0)
+        work_off(n_waiting);
+}
+
+// In how many slices the tokens of a head (groups: workgroups per slice; chunks: 64-token chunks that all slices together
+// walk) go through grid workgroups; 0: the filter, which walks filter_chunks, does better.  Modelled from 32K and 8K tokens x
+// 32 heads (MI355X): a workgroup, which fills a compute unit, takes 70 us to build and 0.19 us per chunk; through the
+// filter a chunk of 4 subspaces takes 0.72 us of a compute unit.
+inline int pq_grid_slices(const int64_t chunks, const int64_t filter_chunks, const int64_t groups, const int n_cu)
+{
+    int64_t best = filter_chunks * groups * 72 / n_cu;  // 10 ns
+    int slices = 0;
+    for (int s = 1; s <= 32; ++s) {
+        const int64_t rounds = (groups * s + n_cu - 1) / n_cu;
+        const int64_t time = rounds * (7000 + (chunks + s - 1) / s * 19);
+        // (chunk numbers of a slice and workgroup numbers have their limits)
+        if (time < best && chunks / s < (1 << 20) && groups * s < (1 << 24)) {
+            best = time;
+            slices = s;
+        }
+    }
+    return slices;
+}
+
+}  // namespace

@@ -1,0 +1,203 @@
+"""The grid that names, for every cell of a subspace's plane, the centroids that can be the nearest of a point in it (long
+appends and large trainings at two dims per subspace).  On the CPU: the cell lists, built in fp32 as the kernel builds them,
+hold the fp64-nearest centroid of every point.  On the GPU: codes and trained codebooks against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import pq_kmeans_oracle as K
+from oracle import pq_oracle as O
+from paper_2504_03661_amd import PQ_CODES_K, PQ_CODES_V
+from paper_2504_03661_amd import binding as B
+from paper_2504_03661_amd.harness import PQSession
+from synth import workloads as W
+from tests.test_gpu_kmeans import gpu_fit, make_ctx
+
+F = np.float32
+KINDS = ["normal", "lattice", "duplicates", "outliers", "line", "tiny", "two clusters", "far from zero", "diagonal", "stretched",
+         "heavy tails", "equal", "sixteen values"]
+
+
+def codebook_and_points(kind, n, seed, dtype=np.float16):
+    """256 centroids of one kind and n points: of the same distribution, centroids themselves, the middles between two
+    neighbouring ones (ties), points far outside, zeros."""
+    rng = np.random.default_rng(seed)
+    normal = lambda m: rng.standard_normal((m, 2))
+    draw = {
+        "normal": normal,
+        "lattice": lambda m: rng.integers(-8, 8, (m, 2)) * 0.25,
+        "duplicates": normal,
+        "outliers": lambda m: np.where(rng.random((m, 2)) < 0.02, 20.0, 1.0) * normal(m),
+        "line": lambda m: normal(m) * [1, 0] + [0, 0.5],
+        "tiny": lambda m: normal(m) * 1e-4,
+        "two clusters": lambda m: normal(m) * 0.01 + np.where(rng.random((m, 1)) < 0.5, -30.0, 30.0),
+        "far from zero": lambda m: normal(m) * 0.1 + [50, -3],
+        "diagonal": lambda m: normal(m)[:, :1] * [1, 1] + normal(m) * 0.01,
+        "stretched": lambda m: normal(m) * [100, 0.3],
+        "heavy tails": lambda m: np.clip(rng.standard_cauchy((m, 2)), -3e4, 3e4),
+        "equal": lambda m: normal(m) * 0 + 0.75,
+        "sixteen values": lambda m: rng.integers(0, 4, (m, 2)) * 0.5,
+    }[kind]
+    c = draw(256)
+    if kind == "lattice":
+        c = np.stack(np.meshgrid(np.arange(-8, 8), np.arange(-8, 8)), -1).reshape(256, 2) * 0.25
+    if kind == "duplicates":
+        c[200:] = c[:56]
+    c = c.astype(dtype)
+    x = draw(n)
+    share = n // 8
+    x[:share] = c[rng.integers(0, 256, share)]
+    wide = c.astype(np.float64)
+    neighbour = np.argsort(((wide[:, None] - wide[None]) ** 2).sum(-1), 1)[:, 1]
+    first = rng.integers(0, 256, share)
+    x[share:2 * share] = 0.5 * (wide[first] + wide[neighbour[first]])
+    x[2 * share:2 * share + 40] *= 50
+    x[2 * share + 40:2 * share + 60] = 0
+    if dtype == np.float16:
+        x = np.clip(x, -65504, 65504)
+    return c, rng.permutation(x).astype(dtype)
+
+
+def _edge(k):
+    e = (np.uint32(0x40000000) + (np.abs(k).astype(np.uint32) << np.uint32(20))).astype(np.uint32).view(F) - F(2)
+    return np.where(k < 0, -e, e)
+
+
+def _cells(x, s, o):
+    u = (x.astype(np.float64) * s + o).astype(F)                # one rounding, as the fused multiply-add
+    b = np.minimum((np.abs(u) + F(2)).astype(F).view(np.uint32), np.uint32(0x41ffffff))
+    e = ((b >> np.uint32(20)) & np.uint32(63)).astype(np.int64)
+    return np.where(np.signbit(u), 63 - e, e)
+
+
+def _lists(c):
+    """(s, o, [64, 64, 256] bool) in fp32, as pq_grid_tables and pq_grid_lists; None: no grid for this codebook."""
+    c = c.astype(F)
+    mean, end = np.zeros(2, F), np.full(2, 3e38, F)
+    for _ in range(2):
+        near = np.abs(c - mean) <= end
+        n = near.sum(0).astype(F)
+        new = (c * near).sum(0, dtype=F) / n
+        dev = (np.abs(c - new) * near).sum(0, dtype=F) / n
+        mean, end = new, F(3) * dev
+    if not (dev > 1e-30).all():
+        return None
+    s = F(28) / (F(5) * dev)
+    o = -mean * s
+    w = F(s[0] / s[1]) ** 2
+    u = (c.astype(np.float64) * s + o).astype(F)
+    if not (np.abs(u) < 1e6).all() or not 1e-9 < w < 1e9:
+        return None
+    a = np.stack([u[:, 0], w * u[:, 1]], 1)
+    norm = F(0.5) * (u * a).sum(1, dtype=F)
+    low = norm * F(1 - 2.0 ** -18)
+
+    def candidates(size):                                       # of boxes of size x size cells
+        e = np.arange(0, 64, size)
+        k = np.where(e < 32, e, e - 64)
+        lo, hi = _edge(k), _edge(k + size)
+        g, h = (F(0.5) * (lo + hi)).astype(F), (F(0.5) * (hi - lo) + F(2.0 ** -17)).astype(F)
+        gx, gy, hx, hy = g[:, None, None], g[None, :, None], h[:, None, None], h[None, :, None]
+        v = low - gx * a[:, 0] - gy * a[:, 1]
+        r = v.argmin(2)
+        far = (np.abs(gx) + hx) ** 2 + w * (np.abs(gy) + hy) ** 2
+        limit = v.min(2)[..., None] + F(2.0 ** -16) * (norm[r][..., None] + far)
+        t = v - np.abs(a[:, 0] - a[r, 0][..., None]) * hx - np.abs(a[:, 1] - a[r, 1][..., None]) * hy
+        return t <= limit
+
+    block = candidates(4)
+    return s, o, candidates(1) & block.repeat(4, 0).repeat(4, 1)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("kind", KINDS)
+def test_lists_hold_the_nearest_centroid_of_every_point(kind, dtype):
+    for seed in range(3):
+        c, x = codebook_and_points(kind, 8000, seed, dtype)
+        grid = _lists(c)
+        if grid is None:
+            assert kind in ("line", "equal")
+            continue
+        s, o, lists = grid
+        ix, iy = _cells(x[:, 0], s[0], o[0]), _cells(x[:, 1], s[1], o[1])
+        inside = ~(np.isin(ix, (31, 32)) | np.isin(iy, (31, 32)))
+        d = ((x.astype(np.float64)[:, None] - c.astype(np.float64)[None]) ** 2).sum(-1)
+        nearest = d == d.min(1)[:, None]                         # with all ties
+        assert not (nearest & ~lists[ix, iy])[inside].any()
+        if kind == "normal":
+            assert inside.mean() > 0.98 and (lists[ix, iy].sum(1) > 4)[inside].mean() < 0.15
+
+
+def _data(Hq, Hkv, B_, n_new, dtype, start):
+    w = W.Workload("grid", B_, Hq, Hkv, 128, 64, 64, "f16" if dtype == np.float16 else "f32", n_new=8, seed=n_new)
+    data = W.generate(w)
+    for book, new in (("k_codebook", "new_k"), ("v_codebook", "new_v")):
+        cb = np.empty((Hkv, 64, 256, 2), dtype)
+        x = np.empty((B_, Hkv, n_new, 128), dtype)
+        for h in range(Hkv):
+            for i in range(64):
+                c, p = codebook_and_points(KINDS[(i + h) % len(KINDS)], B_ * n_new, 1000 * h + i + len(book), dtype)
+                cb[h, i] = c
+                x[:, h, :, 2 * i:2 * i + 2] = p.reshape(B_, n_new, 2)
+        if book == "k_codebook":
+            cb[0, 20, 7, 1] = np.inf
+        data[book], data[new] = cb, x
+    data["ctx_len"] = np.asarray(start, np.int32)
+    return data
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,B_,n_new,dtype,start,room", [
+    (2, 1, 68001, np.float16, [0], 68001),
+    (8, 3, 23003, np.float16, [0, 77, 63], 23070),                # K codes by lane quads; the second sequence overflows
+    (2, 2, 34000, np.float32, [5, 64], 40000),
+])
+def test_long_appends_equal_the_oracle(Hq, B_, n_new, dtype, start, room):
+    data = _data(Hq, 2, B_, n_new, dtype, start)
+    with PQSession(data, Hq, "f16" if dtype == np.float16 else "f32", max_context=room) as s:
+        s.append(torch.from_numpy(data["new_k"]).cuda(), torch.from_numpy(data["new_v"]).cuda())
+        torch.cuda.synchronize()
+        got = {"k": s.unpack(PQ_CODES_K, room), "v": s.unpack(PQ_CODES_V, room)}
+        assert s.ctx_len.cpu().tolist() == [min(room, n + n_new) for n in start]
+    for name, codes in got.items():
+        want = O.encode(data["new_" + name], data[name + "_codebook"])
+        for b, n in enumerate(start):
+            wrong = codes[b, :, n:n + n_new] != want[b, :, :room - n]
+            assert not wrong.any(), [(h, KINDS[(i + h) % len(KINDS)]) for h, i in set(zip(*np.nonzero(wrong.any(1))))]
+
+
+@pytest.mark.gpu
+def test_rows_that_start_off_a_16_byte_address():
+    data = _data(2, 2, 1, 68001, np.float16, [0])
+    shifted = {}
+    for name in ("new_k", "new_v"):
+        flat = torch.empty(data[name].size + 1, dtype=torch.float16, device="cuda")
+        shifted[name] = flat[1:].view(data[name].shape)
+        shifted[name].copy_(torch.from_numpy(data[name]))
+    with PQSession(data, 2, "f16", max_context=68001) as s:
+        s.append(shifted["new_k"], shifted["new_v"])
+        torch.cuda.synchronize()
+        off = [s.unpack(kind, 68001) for kind in (PQ_CODES_K, PQ_CODES_V)]
+        s.ctx_len.zero_()
+        s.append(torch.from_numpy(data["new_k"]).cuda(), torch.from_numpy(data["new_v"]).cuda())
+        torch.cuda.synchronize()
+        for kind, codes in zip((PQ_CODES_K, PQ_CODES_V), off):
+            np.testing.assert_array_equal(codes, s.unpack(kind, 68001))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hkv,n,iters", [(2, 68003, 1), (5, 45000, 2)])
+def test_training_on_many_samples_equals_the_oracle(Hkv, n, iters):
+    samples = np.empty((Hkv, n, 128), np.float16)
+    init = np.empty((Hkv, 64, 256, 2), np.float16)
+    for h in range(Hkv):
+        for i in range(64):
+            init[h, i], samples[h, :, 2 * i:2 * i + 2] = codebook_and_points(KINDS[(i + 3 * h) % len(KINDS)], n, 100 * h + i)
+    ctx = make_ctx(Hkv, 64)
+    try:
+        got = gpu_fit(ctx, samples, init, iters)
+    finally:
+        B.pq_attn_destroy(ctx)
+    want, _ = K.kmeans_lloyd(samples, init, iters)
+    wrong = (got.view(np.uint16) != want.view(np.uint16)).any((2, 3))
+    assert not wrong.any(), [(h, KINDS[(i + 3 * h) % len(KINDS)]) for h, i in zip(*np.nonzero(wrong))]
