@@ -418,18 +418,23 @@ hipError_t pq_launch_bump_len(int32_t *ctx_len, int B, int n_new, int max_contex
 template <int M, int DS, typename T>
 void launch_fast(const pq_encode_args &a, hipStream_t s)
 {
-    // whole 64-token chunks of each sequence unless that leaves more than an eighth of the lanes without a token; a
-    // wavefront takes up to 32 chunks in a row while at least 8192 wavefronts remain
+    // Whole 64-token chunks of each sequence unless that leaves more than an eighth of the lanes without a token.  A
+    // wavefront takes up to 32 chunks in a row, so that there are 8192 wavefronts or more, and all about the same number (63
+    // chunks of 32 heads as 31 + 31 + 1: 222 us, as 3 x 21: 198).  Up to 16384 chunks in all go to 4096 wavefronts, which
+    // are resident at once: setting up a codebook costs about a chunk (2 x 96 tokens x 32 heads, fp32: 23.7 -> 21.3 us; 8 x 16
+    // tokens x 32 heads, fp16: 16.0 -> 14.8; at 32768 chunks 8192 wavefronts are as good or better).
     const int64_t seq_chunks = ((int64_t)a.n_new + 63) / 64;
     const bool per_seq = seq_chunks * 512 <= (int64_t)a.n_new * 9 || a.B == 1;
     const int64_t n_chunks = per_seq ? a.B * seq_chunks : ((int64_t)a.B * a.n_new + 63) / 64;
     const int64_t waves = a.Hkv * n_chunks * M * 2;
-    const int rounds = (int)(waves / 8192 < 1 ? 1 : waves / 8192 > 32 ? 32 : waves / 8192);
+    int64_t rounds = waves <= 16384 ? (waves + 4095) / 4096 : waves / 8192 > 32 ? 32 : waves / 8192;
+    const int64_t jobs = (n_chunks + rounds - 1) / rounds;
+    rounds = (n_chunks + jobs - 1) / jobs;
     dim3 grid((unsigned)(a.Hkv * ((n_chunks + rounds - 1) / rounds)), M / FAST_WAVES, 2);
     if (per_seq)
-        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, true>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
+        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, true>), grid, dim3(64 * FAST_WAVES), 0, s, a, (int)rounds);
     else
-        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, false>), grid, dim3(64 * FAST_WAVES), 0, s, a, rounds);
+        hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, false>), grid, dim3(64 * FAST_WAVES), 0, s, a, (int)rounds);
 }
 
 template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, int slices, hipStream_t s)
