@@ -241,7 +241,8 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
 {
     constexpr int M = 64;
     __shared__ __attribute__((aligned(16))) pq_grid<T> grid[GRID_SUB];
-    __shared__ uint32_t queue[GRID_WAVES][GRID_QUEUE];
+    constexpr bool KEEP = sizeof(T) == 2;
+    __shared__ pq_grid_waiting<KEEP> queue[GRID_WAVES][GRID_QUEUE<KEEP>];
     __shared__ float2 box[GRID_SIDE];
 
     const int lane = threadIdx.x & 63;
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
         t = block * 64 + (int)((id >> 2) & 63u) - (n_old & 63);
         pos = n_old + t;
     };
-    pq_grid_scan<T, grid_token<T>>(
+    pq_grid_scan<T, KEEP, grid_token<T>>(
         grid, queue[wave], first, last, fetch,
         [&](const grid_token<T> &k, int j, int code) {
             codes[k.block + (uint32_t)pq_grid_pick(j, in_block[0], in_block[1], in_block[2], in_block[3])] = (uint8_t)code;

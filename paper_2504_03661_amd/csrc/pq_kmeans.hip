@@ -137,7 +137,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
 {
     constexpr int M = 64;
     __shared__ __attribute__((aligned(16))) pq_grid<_Float16> grid[GRID_SUB];
-    __shared__ uint32_t queue[GRID_WAVES][GRID_QUEUE];
+    __shared__ pq_grid_waiting<false> queue[GRID_WAVES][GRID_QUEUE<false>];
     __shared__ float2 box[GRID_SIDE];
     __shared__ unsigned long long sum[GRID_SUB][512];
     __shared__ unsigned int count[GRID_SUB][256];
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
         atomicAdd(&sum[j][code * 2 + 1], (unsigned long long)__double_as_longlong(__builtin_fma((double)(float)x1, 16777216.0, 6755399441055744.0)));
         atomicAdd(&count[j][code], 1u);
     };
-    pq_grid_scan<_Float16, pq_sample>(
+    pq_grid_scan<_Float16, false, pq_sample>(
         grid, queue[wave], first, last,
         [&](int chunk, pq_sample &k) {
             const int s = chunk * 64 + lane;

@@ -4,8 +4,11 @@
 //
 // The filter of pq_nearest_filter.h looks at all 256 values of every token: 355 vector instructions per 64 tokens.  In two
 // dimensions the plane can be cut up once per codebook instead, and a token then looks at the 2 or 3 centroids of its cell:
-// some 60 instructions.  Building a grid costs as much as 70 chunks of 64 tokens through the filter, so the grid serves
-// appends and trainings of thousands of tokens per head (pq_grid_slices below).
+// 86 instructions with codebooks of random vectors, whose cells have long lists more often than trained ones'.  Building a
+// grid takes 34 000, as many as 100 chunks of 64 tokens through the filter, so the grid serves appends and trainings of
+// thousands of tokens per head (pq_grid_slices below).  Encode (K and V), 32 heads x 32K tokens: 1549 -> 660 us, of which
+// 295 us are the grids (vector issue 76 % busy, the rest latencies between barriers) and 365 us the tokens (87 %).  k-means,
+// 32 heads x 64K samples, 2 iterations: 3148 -> 1000 us.
 //
 // Map.  Per axis u = s x + o, fp32, chosen from the codebook (mean and mean deviation of its coordinates without outliers):
 // |u| <= 28 holds what lies within some 4 standard deviations.  The cell coordinate is five bits of the float |u| + 2 — 8
@@ -14,13 +17,15 @@
 // Lists.  A centroid c can be the nearest of a point of a box only if the bisector of c and some reference centroid r leaves
 // part of the box on its side: F_c(g) - F_r(g) <= |da_x| h_x + |da_y| h_y with F_c(p) = |c|^2 / 2 - p . c, g and h the box's
 // centre and half sides, da the difference of the gradients.  r is the nearest centroid of the box's centre (any r is safe).
-// First for 16 x 16 blocks of 4 x 4 cells, all 256 centroids each; then for every cell, the centroids of its block.
+// First for 16 x 16 blocks of 4 x 4 cells, all 256 centroids each; then for every cell, the centroids of its block, which the
+// 16 lanes of the block's cells hold and pass to each other (through LDS every candidate cost two 16-byte reads per lane: 860
+// us for the encode above, 785 so).
 // The test runs in fp32 in u space, where a squared distance is w_x du_x^2 + w_y du_y^2: every F is lowered by 2^-18 of its
-// |c|^2 / 2 and the threshold raised by 2^-17 (|r|^2 / 2 + |g|^2 + ..), 16 times what the roundings of u, F and w amount to;
+// |c|^2 / 2 and the threshold raised by 2^-16 (|r|^2 / 2 + |g|^2 + ..), 16 times what the roundings of u, F and w amount to;
 // boxes are 2^-17 wider on each side than the cells (the float |u| + 2 is good to 2^-19).
 // A cell's word holds its codes if they are at most 4, filled up with codes that are not in its list; otherwise the two low
 // bytes are equal (which the distinct codes of a list never are): the number of words, and in the upper half where they
-// stand in the pool.  No words: outside, or no room, or more than 64 candidates in the block.
+// stand in the pool.  Outside, where there is no room, or more than 64 candidates in the block: GRID_NONE.
 // Tokens.  The four distances in fp32 (relative error below 2^-21), their 8 low bits replaced by the code: one unsigned
 // minimum gives the least and its code, one median keeps the second.  More than 2^-16 apart, the order is that of the fp64
 // distances; otherwise, and for tokens outside, all 64 lanes evaluate the token's fp64 distances to all centroids together
@@ -37,8 +42,15 @@ namespace {
 constexpr int GRID_SUB = 4;       // neighbouring subspaces of a workgroup: 16 bytes of every token's fp16 row
 constexpr int GRID_WAVES = 16;    // 4 wavefronts build each subspace's grid; then all take tokens, 4 subspaces at a time
 constexpr int GRID_SIDE = 64;
-constexpr int GRID_POOL = 1024;   // words of longer lists per subspace
-constexpr int GRID_QUEUE = 320;   // waiting tokens of a wavefront: fewer than 64, and up to 64 of each subspace
+constexpr int GRID_POOL = 1024;   // words of longer lists per subspace (768 were too few for some sets of 256 random vectors: k-means
+                                  // of 32 heads x 64K samples 1.03 ms, 0.99 so)
+// Waiting tokens of a wavefront: their number, and where KEEP their fp16 sub-vector as well.  (Read again when its turn came,
+// its line had often left the L2: encode, 32K tokens x 32 heads, 696 us, 663 with it.  Beside the k-means' sums, and in
+// fp32, there is no room.)  The queue holds fewer than 64, and up to 64 of each subspace until it is looked at: after two
+// subspaces, or after all four.
+template <bool KEEP> using pq_grid_waiting = typename std::conditional<KEEP, uint2, uint32_t>::type;
+template <bool KEEP> constexpr int GRID_LOOK = KEEP ? 2 : 4;
+template <bool KEEP> constexpr int GRID_QUEUE = 64 * (1 + GRID_LOOK<KEEP>);
 constexpr int GRID_SHIFT = 20;    // 8 cells per octave
 constexpr float GRID_BIAS = 2.0f;
 constexpr uint32_t GRID_FIRST = 0x40000000u, GRID_LAST = 0x41ffffffu;  // float bits of 2 .. just below 32
@@ -244,16 +256,14 @@ template <int K> __device__ __forceinline__ void pq_grid_row_fma(float &v, const
         : "+&v"(v) : "v"(x), "v"(ax), "v"(y), "v"(ay), "n"(K));
 }
 
-// calls f(integral constant 0 .. N - 1), four at a time while the first of the four is below `most` (uniform)
-template <int K, int N, typename F> __device__ __forceinline__ void pq_grid_fours(const int most, F f)
+// calls f(integral constant 0 .. N - 1), two at a time while the first of the two is below `most` (uniform)
+template <int K, int N, typename F> __device__ __forceinline__ void pq_grid_twos(const int most, F f)
 {
     if constexpr (K < N) {
         if (K < most) {
             f(std::integral_constant<int, K>());
             f(std::integral_constant<int, K + 1>());
-            f(std::integral_constant<int, K + 2>());
-            f(std::integral_constant<int, K + 3>());
-            pq_grid_fours<K + 4, N>(most, f);
+            pq_grid_twos<K + 2, N>(most, f);
         }
     }
 }
@@ -299,15 +309,17 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
                 pq_grid_mark(mask, t, limit);
             }
             used = w == 0 ? __builtin_bitreverse32(mask) : used;
+            const int total = count + __builtin_popcount(mask);
+            mask = total <= 64 ? mask : 0;
             while (__builtin_amdgcn_ballot_w64(mask != 0) != 0) {
-                const int k = __builtin_clz(mask | 1u);
                 if (mask != 0) {
-                    if (count < 64)
-                        bytes[list + (uint32_t)((count >> 4) * 256 + (count & 15))] = (unsigned char)(w + k);
+                    const int k = __builtin_clz(mask);
+                    bytes[list + (uint32_t)count + __umul24((uint32_t)count & 48u, 15u)] = (unsigned char)(w + k);
                     ++count;
+                    mask ^= 0x80000000u >> k;
                 }
-                mask &= ~(0x80000000u >> k);
             }
+            count = total;  // (from 65 on nothing is written any more)
         }
         // Lists are filled up to whole words with a code that is not in them: it is never the least, and being there more
         // than once it hides no second least.
@@ -389,7 +401,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             // half the squared distances of its centre; the least, with its place in the list in the low bits
             float v[32];
             int least = 0x7f7fffff;
-            pq_grid_fours<0, 32>(most, [&](auto K) {
+            pq_grid_twos<0, 32>(most, [&](auto K) {
                 const float4 &e = K < 16 ? first : second;
                 constexpr int k = K & 15;
                 v[K] = pq_grid_row<k>(e.z) + half;
@@ -400,7 +412,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             const float nearest = __int_as_float(least & ~31);
             const float limit = nearest + MARGIN * (2.f * fabsf(nearest) + ref.w + far);
             uint32_t mask = 0, marked = fill_cell;
-            pq_grid_fours<0, 32>(most, [&](auto K) {
+            pq_grid_twos<0, 32>(most, [&](auto K) {
                 const float4 &e = K < 16 ? first : second;
                 constexpr int k = K & 15;
                 float t = __builtin_fmaf(-fabsf(pq_grid_row<k>(e.x) - ref.x), x.y, v[K]);
@@ -408,7 +420,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
                 pq_grid_mark(mask, marked, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(K < 16 ? code1 : code2), 0x150 + k, 0xf, 0xf, true),
                              t, limit);
             });
-            mask <<= 32 - ((most + 3) & ~3);
+            mask <<= 32 - ((most + 1) & ~1);
             word = n <= 32 ? marked : word;
             const bool listed = n <= 32 && inside && __builtin_popcount(mask) > 4;
             if (__builtin_amdgcn_ballot_w64(listed) != 0)  // wave-uniform
@@ -531,10 +543,10 @@ template <typename V> __device__ __forceinline__ V pq_grid_pick(const int j, con
 //   fetch(chunk, token &)    the chunk's tokens, lane = token: x[4][2] and live; called for one chunk more than there are,
 //                            in ascending order
 //   store(token, j, code)    the code of this lane's token for subspace j of the group
-//   waiting(id, x, y)        the sub-vector of a token that was put off: id = (chunk - first) << 8 | lane << 2 | j
+//   waiting(id, x, y)        unless KEEP: the sub-vector of a token that was put off, id = (chunk - first) << 8 | lane << 2 | j
 //   store_waiting(id, x, y, code)
-template <typename T, typename TOKEN, typename FETCH, typename STORE, typename WAITING, typename STORE_WAITING>
-__device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB], uint32_t (&queue)[GRID_QUEUE], const int first,
+template <typename T, bool KEEP, typename TOKEN, typename FETCH, typename STORE, typename WAITING, typename STORE_WAITING>
+__device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB], pq_grid_waiting<KEEP> (&queue)[GRID_QUEUE<KEEP>], const int first,
                                              const int last, FETCH fetch, STORE store, WAITING waiting, STORE_WAITING store_waiting)
 {
     typedef typename std::conditional<sizeof(T) == 4, float, _Float16>::type W;
@@ -556,9 +568,18 @@ __device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB],
     auto work_off = [&](const int n) {  // the last n
         n_waiting -= n;
         const bool live = lane < n;
-        const uint32_t id = queue[n_waiting + (live ? lane : 0)];
+        const pq_grid_waiting<KEEP> entry = queue[n_waiting + (live ? lane : 0)];
+        uint32_t id;
         T x, y;
-        waiting(id, x, y);
+        if constexpr (KEEP) {
+            static_assert(sizeof(T) == 2, "two sub-vector halves in a word");
+            id = entry.x;
+            x = __builtin_bit_cast(_Float16, (uint16_t)entry.y);
+            y = __builtin_bit_cast(_Float16, (uint16_t)(entry.y >> 16));
+        } else {
+            id = entry;
+            waiting(id, x, y);
+        }
         const int j = (int)(id & 3u);
         const pq_grid<T> &g = grid[j];
         const uint32_t word = *(const uint32_t *)((const char *)g.cell + pq_grid_cell(x, y, g.sx, g.ox, g.sy, g.oy));
@@ -613,9 +634,19 @@ __device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB],
                 store(k, j, (int)(m1[j] & 255u));
             if (__builtin_amdgcn_inverse_ballot_w64(listed)) {
                 const int at = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(listed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)listed, (uint32_t)n_waiting));
-                queue[at] = (uint32_t)(chunk - first) << 8 | (uint32_t)lane << 2 | (uint32_t)j;
+                const uint32_t id = (uint32_t)(chunk - first) << 8 | (uint32_t)lane << 2 | (uint32_t)j;
+                if constexpr (KEEP)
+                    queue[at] = make_uint2(id, (uint32_t)__builtin_bit_cast(uint16_t, k.x[j][0]) | (uint32_t)__builtin_bit_cast(uint16_t, k.x[j][1]) << 16);
+                else
+                    queue[at] = id;
             }
             n_waiting += __builtin_popcountll(listed);
+            if ((j + 1) % GRID_LOOK<KEEP> == 0 && n_waiting >= 64) {
+                pq_grid_fence();
+                while (n_waiting >= 64)
+                    work_off(64);
+                pq_grid_fence();
+            }
         }
         if (any != 0) {  // wave-uniform
 #pragma unroll 1
@@ -635,12 +666,6 @@ __device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB],
                     store(k, j, code);
             }
         }
-        if (n_waiting >= 64) {
-            pq_grid_fence();
-            while (n_waiting >= 64)
-                work_off(64);
-            pq_grid_fence();
-        }
     }
     pq_grid_fence();
     if (n_waiting != 0)
@@ -649,15 +674,16 @@ __device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB],
 
 // In how many slices the tokens of a head (groups: workgroups per slice; chunks: 64-token chunks that all slices together
 // walk) go through grid workgroups; 0: the filter, which walks filter_chunks, does better.  Modelled from 32K and 8K tokens x
-// 32 heads (MI355X): a workgroup, which fills a compute unit, takes 70 us to build and 0.19 us per chunk; through the
-// filter a chunk of 4 subspaces takes 0.72 us of a compute unit.
+// 32 heads (MI355X): a workgroup, which fills a compute unit, takes 74 us to build and 0.18 us per chunk; through the
+// filter a chunk of 4 subspaces takes 0.72 us of a compute unit.  (8K tokens x 32 heads 386 us either way; 32K tokens x 8
+// heads 383 us through the filter, 187 with grids; 5000 tokens of 4 sequences x 8 heads 262 and 149.)
 inline int pq_grid_slices(const int64_t chunks, const int64_t filter_chunks, const int64_t groups, const int n_cu)
 {
     int64_t best = filter_chunks * groups * 72 / n_cu;  // 10 ns
     int slices = 0;
     for (int s = 1; s <= 32; ++s) {
         const int64_t rounds = (groups * s + n_cu - 1) / n_cu;
-        const int64_t time = rounds * (7000 + (chunks + s - 1) / s * 19);
+        const int64_t time = rounds * (7400 + (chunks + s - 1) / s * 18);
         // (chunk numbers of a slice and workgroup numbers have their limits)
         if (time < best && chunks / s < (1 << 20) && groups * s < (1 << 24)) {
             best = time;
