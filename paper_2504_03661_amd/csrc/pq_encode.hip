@@ -11,7 +11,8 @@
 //
 // Appends of more than a few tokens reach the codes through pq_encode_fast_kernel, where the matrix cores find the
 // few centroids that can be the nearest and the expression above decides among them; a handful of tokens per head
-// through pq_encode_few_kernel, which evaluates the expression for all 256.
+// through pq_encode_few_kernel, which evaluates the expression for all 256; thousands per head at M = 64 through
+// pq_encode_grid_kernel, which looks the candidates up.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -87,7 +88,8 @@ template <> __device__ inline double widen<float>(const void *p, int64_t i)
 // parallel: 355 vector instructions per 64 tokens and subspace counted at M = 64, 16 of them matrix instructions, which
 // fill 82 % of the issue slots at the 2.0 GHz the chip holds (M = 32: 394, 82 %; fp32, M = 64: 407, 78 %); what the
 // wavefronts wait for in the rest is not known.  Prompt of 32K tokens x 32 heads x (K, V), M = 64: 2.75 ms with 4x4x4
-// instructions in two passes (one for the best value, one for the marks), 1.54 ms now.
+// instructions in two passes (one for the best value, one for the marks), 1.54 ms in one; appends of that size go through
+// the grids now (0.66 ms).
 //
 // A workgroup is 4 neighbouring subspaces of the same tokens, one wavefront each: a token's line of 64 subspaces is
 // then fetched from L2 once for four wavefronts (one wavefront per workgroup 2.69 ms, two 2.35, four 1.75, eight 1.73
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
     constexpr int M = 64;
     __shared__ __attribute__((aligned(16))) pq_grid<T> grid[GRID_SUB];
     constexpr bool KEEP = sizeof(T) == 2;
-    __shared__ pq_grid_waiting<KEEP> queue[GRID_WAVES][GRID_QUEUE<KEEP>];
+    __shared__ __attribute__((aligned(16))) pq_grid_scratch<KEEP> scratch;
     __shared__ float2 box[GRID_SIDE];
 
     const int lane = threadIdx.x & 63;
@@ -259,7 +261,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
     const int first = slice * slice_chunks;
     const int last = first + slice_chunks < n_chunks ? first + slice_chunks : n_chunks;
 
-    pq_grid_build(grid, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
+    pq_grid_build(grid, scratch.table, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
 
     const T *x = (const T *)a.x[which] + i0 * 2;
     uint8_t *codes = a.codes[which];
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
         pos = n_old + t;
     };
     pq_grid_scan<T, KEEP, grid_token<T>>(
-        grid, queue[wave], first, last, fetch,
+        grid, scratch.queue[wave], first, last, fetch,
         [&](const grid_token<T> &k, int j, int code) {
             codes[k.block + (uint32_t)pq_grid_pick(j, in_block[0], in_block[1], in_block[2], in_block[3])] = (uint8_t)code;
         },

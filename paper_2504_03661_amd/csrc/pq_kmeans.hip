@@ -19,8 +19,9 @@
 // in LDS (LDS atomics); the sums reach memory with one 64-bit atomic per touched entry and slice.  The 4 wavefronts
 // read neighbouring words of the same rows, so a line of samples leaves L2 once for all of them.  Bound by the issue
 // of vector instructions in the nearest-centroid filter, as the encode; 32 heads x 65536 samples, M = 64: 2.7 ms per
-// iteration with one subspace per workgroup and the two-pass filter, 1.58 ms now (two or four wavefronts per subspace
-// on one set of sums, for more wavefronts per compute unit: 1.6 and 1.8 ms).
+// iteration with one subspace per workgroup and the two-pass filter, 1.58 ms with the one-pass filter (two or four
+// wavefronts per subspace on one set of sums, for more wavefronts per compute unit: 1.6 and 1.8 ms).  As many samples as
+// that take the grids of pq_nearest_grid.h at M = 64 (pq_kmeans_grid_kernel): 0.50 ms.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
 {
     constexpr int M = 64;
     __shared__ __attribute__((aligned(16))) pq_grid<_Float16> grid[GRID_SUB];
-    __shared__ pq_grid_waiting<false> queue[GRID_WAVES][GRID_QUEUE<false>];
+    __shared__ __attribute__((aligned(16))) pq_grid_scratch<false> scratch;
     __shared__ float2 box[GRID_SIDE];
     __shared__ unsigned long long sum[GRID_SUB][512];
     __shared__ unsigned int count[GRID_SUB][256];
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
         ((unsigned long long *)sum)[e] = 0ull;
     for (int e = threadIdx.x; e < GRID_SUB * 256; e += GRID_WAVES * 64)
         ((unsigned int *)count)[e] = 0u;
-    pq_grid_build(grid, box, codebook + ((int64_t)head * M + i0) * 512);
+    pq_grid_build(grid, scratch.table, box, codebook + ((int64_t)head * M + i0) * 512);
 
     constexpr uint64_t BASE = 0x4338000000000000ull;  // the bits of 1.5 2^52
     const _Float16 *x = samples + (int64_t)head * n_samples * PQ_HEAD_DIM + i0 * 2;
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
         atomicAdd(&count[j][code], 1u);
     };
     pq_grid_scan<_Float16, false, pq_sample>(
-        grid, queue[wave], first, last,
+        grid, scratch.queue[wave], first, last,
         [&](int chunk, pq_sample &k) {
             const int s = chunk * 64 + lane;
             k.live = s < n_samples;

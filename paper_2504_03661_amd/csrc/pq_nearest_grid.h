@@ -42,8 +42,11 @@ namespace {
 constexpr int GRID_SUB = 4;       // neighbouring subspaces of a workgroup: 16 bytes of every token's fp16 row
 constexpr int GRID_WAVES = 16;    // 4 wavefronts build each subspace's grid; then all take tokens, 4 subspaces at a time
 constexpr int GRID_SIDE = 64;
-constexpr int GRID_POOL = 1024;   // words of longer lists per subspace (768 were too few for some sets of 256 random vectors: k-means
-                                  // of 32 heads x 64K samples 1.03 ms, 0.99 so)
+// Words of longer lists per subspace.  Random vectors take 400 on average, and up to 1200 where one axis is several times the
+// other: its cells then have many candidates.  Tokens of a cell that found no room are worked on one by one, and a workgroup
+// with one such subspace is what the others wait for (k-means of 32 heads x 64K samples, scales 0.5 .. 4 per channel, 5
+// iterations: 0.68 ms each with 1024 words, 0.66 so, and 0.64 with lists of 33 .. 64 by row broadcast like the shorter ones).
+constexpr int GRID_POOL = 2048;
 // Waiting tokens of a wavefront: their number, and where KEEP their fp16 sub-vector as well.  (Read again when its turn came,
 // its line had often left the L2: encode, 32K tokens x 32 heads, 696 us, 663 with it.  Beside the k-means' sums, and in
 // fp32, there is no room.)  The queue holds fewer than 64, and up to 64 of each subspace until it is looked at: after two
@@ -61,12 +64,18 @@ constexpr uint32_t GRID_SURE = 512;  // keys at least this far apart are in the 
 template <typename T> struct pq_grid {
     uint32_t cell[GRID_SIDE * GRID_SIDE];  // [u_x][u_y]; while building, the 64 bytes of a 4 x 4 block are its list
     unsigned char arow[256 * pq_filter_row_bytes<T>()];
-    float table[256][4];  // a_x, a_y, |c|^2 / 2 lowered, |c|^2 / 2
     T coord[256][2];
     uint32_t pool[GRID_POOL];
     float sx, ox, sy, oy;  // the map
     float scale;           // of the filter
     uint32_t pool_used, unserved, bad;  // bad: 1 no grid, 2 codebook outside the filter's range
+};
+
+// What building a grid needs of its centroids: a_x, a_y, |c|^2 / 2 lowered, |c|^2 / 2.  The waiting tokens take its place.
+typedef float pq_grid_table[256][4];
+template <bool KEEP> union pq_grid_scratch {
+    pq_grid_table table[GRID_SUB];
+    pq_grid_waiting<KEEP> queue[GRID_WAVES][GRID_QUEUE<KEEP>];
 };
 
 // bits 20 .. 25: the cell coordinate, 0 .. 31 upwards from zero, 63 .. 32 downwards
@@ -129,7 +138,7 @@ template <typename T> __device__ __forceinline__ bool pq_grid_unsure(const uint3
 
 // A wavefront's part of a subspace's tables: the map, which all 4 wavefronts work out alike, and the rows and numbers of
 // centroids 64 part .. 64 part + 63.  src: [256][2]
-template <typename T> __device__ inline void pq_grid_tables(pq_grid<T> &g, const T *src, const int part)
+template <typename T> __device__ inline void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, const T *src, const int part)
 {
     const int lane = threadIdx.x & 63;
     float x[4], y[4];
@@ -189,10 +198,10 @@ template <typename T> __device__ inline void pq_grid_tables(pq_grid<T> &g, const
     const float ux = __builtin_fmaf((float)mine[0], sx, ox), uy = __builtin_fmaf((float)mine[1], sy, oy);
     far_out = !(fabsf(ux) < 1.0e6f && fabsf(uy) < 1.0e6f);
     const float ay = wy * uy, n = 0.5f * (ux * ux + uy * ay);
-    g.table[c][0] = ux;
-    g.table[c][1] = ay;
-    g.table[c][2] = n * (1.0f - 3.814697265625e-06f);  // 2^-18
-    g.table[c][3] = n;
+    table[c][0] = ux;
+    table[c][1] = ay;
+    table[c][2] = n * (1.0f - 3.814697265625e-06f);  // 2^-18
+    table[c][3] = n;
     g.coord[c][0] = mine[0];
     g.coord[c][1] = mine[1];
     const uint32_t bad = (__builtin_amdgcn_ballot_w64(far_out) != 0 || !usable ? 1u : 0u) |
@@ -270,7 +279,7 @@ template <int K, int N, typename F> __device__ __forceinline__ void pq_grid_twos
 
 // The lists of one quarter of the grid (cell rows 16 part .. 16 part + 15), by one wavefront.  box: centre and half side of
 // the 64 cell coordinates
-template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const float2 (&box)[GRID_SIDE], const int part)
+template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const pq_grid_table &table, const float2 (&box)[GRID_SIDE], const int part)
 {
     const int lane = threadIdx.x & 63;
     unsigned char *bytes = (unsigned char *)g.cell;
@@ -292,7 +301,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
         const T p[2] = {(T)fminf(fmaxf(px, -end), end), (T)fminf(fmaxf(py, -end), end)};
         typedef typename std::conditional<sizeof(T) == 4, float, _Float16>::type W;
         const int r = pq_filter_code<2, T, W>(g.arow, sizeof(T) == 4 ? (const unsigned char *)g.coord : g.arow, g.scale, false, p, true);
-        const float4 ref = *(const float4 *)g.table[r];
+        const float4 ref = *(const float4 *)table[r];
         const float far_x = fabsf(gx) + hx, far_y = fabsf(gy) + hy;
         const float limit = __builtin_fmaf(-gy, ref.y, __builtin_fmaf(-gx, ref.x, ref.z)) +
                             MARGIN * (ref.w + far_x * far_x + wy * far_y * far_y);
@@ -302,7 +311,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             uint32_t mask = 0;  // candidate w + k in bit 31 - k
 #pragma unroll 8
             for (int k = 0; k < 32; ++k) {
-                const float4 c = *(const float4 *)g.table[w + k];
+                const float4 c = *(const float4 *)table[w + k];
                 float t = __builtin_fmaf(-gy, c.y, __builtin_fmaf(-gx, c.x, c.z));
                 t = __builtin_fmaf(-fabsf(c.x - ref.x), hx, t);
                 t = __builtin_fmaf(-fabsf(c.y - ref.y), hy, t);
@@ -389,13 +398,13 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
         if (__builtin_amdgcn_readlane(n, 0) <= 32) {
             const int most = longest < 32 ? longest : 32;
             const uint32_t code1 = bytes[list + (uint32_t)in_row];
-            float4 first = *(const float4 *)g.table[code1];
+            float4 first = *(const float4 *)table[code1];
             first.z = in_row < n ? first.z : 1.0e30f;  // behind the block's own list: far away
             uint32_t code2 = code1;
             float4 second = first;
             if (most > 16) {
                 code2 = bytes[list + 256u + (uint32_t)in_row];
-                second = *(const float4 *)g.table[code2];
+                second = *(const float4 *)table[code2];
                 second.z = in_row + 16 < n ? second.z : 1.0e30f;
             }
             // half the squared distances of its centre; the least, with its place in the list in the low bits
@@ -408,7 +417,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
                 pq_grid_row_fma<k>(v[K], e.x, minus_gx, e.y, minus_gy);
                 least = min(least, (__float_as_int(v[K]) & ~31) | (int)K);
             });
-            const float4 ref = *(const float4 *)g.table[bytes[list + (uint32_t)(((least >> 4) & 1) * 256 + (least & 15))]];
+            const float4 ref = *(const float4 *)table[bytes[list + (uint32_t)(((least >> 4) & 1) * 256 + (least & 15))]];
             const float nearest = __int_as_float(least & ~31);
             const float limit = nearest + MARGIN * (2.f * fabsf(nearest) + ref.w + far);
             uint32_t mask = 0, marked = fill_cell;
@@ -426,29 +435,42 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             if (__builtin_amdgcn_ballot_w64(listed) != 0)  // wave-uniform
                 write_list(mask, listed);
         }
-        if (longest > 32 && __builtin_amdgcn_ballot_w64(n > 32 && n <= 64) != 0) {  // rare
+        // longer lists (many where one axis is several times the other), the same 16 candidates at a time
+        if (longest > 32 && __builtin_amdgcn_ballot_w64(n > 32 && n <= 64) != 0) {
             const int most = longest < 64 ? longest : 64;
-            float nearest = 3.0e38f;
-            int r = 0;
-#pragma unroll 4
-            for (int k = 0; k < most; ++k) {
-                const int c = bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))];
-                const float v = __builtin_fmaf(g.table[c][1], minus_gy, __builtin_fmaf(g.table[c][0], minus_gx, g.table[c][2] + half));
-                r = v < nearest ? c : r;
-                nearest = fminf(nearest, v);
+            auto sixteen = [&](const int q) {
+                float4 e = *(const float4 *)table[bytes[list + (uint32_t)(q * 256 + in_row)]];
+                e.z = 16 * q + in_row < n ? e.z : 1.0e30f;
+                return e;
+            };
+            int least = 0x7f7fffff;
+#pragma unroll 1
+            for (int q = 0; 16 * q < most; ++q) {
+                const float4 e = sixteen(q);
+                pq_grid_twos<0, 16>(most - 16 * q, [&](auto K) {
+                    float v = pq_grid_row<K>(e.z) + half;
+                    pq_grid_row_fma<K>(v, e.x, minus_gx, e.y, minus_gy);
+                    least = min(least, (__float_as_int(v) & ~63) | (16 * q + (int)K));
+                });
             }
-            const float4 ref = *(const float4 *)g.table[r];
+            const float4 ref = *(const float4 *)table[bytes[list + (uint32_t)(((least >> 4) & 3) * 256 + (least & 15))]];
+            const float nearest = __int_as_float(least & ~63);
             const float limit = nearest + MARGIN * (2.f * fabsf(nearest) + ref.w + far);
-            uint64_t mask = 0;
-#pragma unroll 4
-            for (int k = 0; k < most; ++k) {
-                const int c = bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))];
-                float t = __builtin_fmaf(g.table[c][1], minus_gy, __builtin_fmaf(g.table[c][0], minus_gx, g.table[c][2] + half));
-                t = __builtin_fmaf(-fabsf(g.table[c][0] - ref.x), x.y, t);
-                t = __builtin_fmaf(-fabsf(g.table[c][1] - ref.y), y.y, t);
-                mask |= (uint64_t)(t <= limit ? 1 : 0) << (63 - k);
+            uint64_t mask = 0;  // candidate k in bit 63 - k
+#pragma unroll 1
+            for (int q = 0; 16 * q < most; ++q) {
+                const float4 e = sixteen(q);
+                uint32_t some = 0;
+                pq_grid_twos<0, 16>(most - 16 * q, [&](auto K) {
+                    float t = pq_grid_row<K>(e.z) + half;
+                    pq_grid_row_fma<K>(t, e.x, minus_gx, e.y, minus_gy);
+                    t = __builtin_fmaf(-fabsf(pq_grid_row<K>(e.x) - ref.x), x.y, t);
+                    t = __builtin_fmaf(-fabsf(pq_grid_row<K>(e.y) - ref.y), y.y, t);
+                    pq_grid_mark(some, t, limit);
+                });
+                const int n_marked = most - 16 * q < 16 ? (most - 16 * q + 1) & ~1 : 16;
+                mask |= (uint64_t)(some << (16 - n_marked)) << (48 - 16 * q);
             }
-            mask = n < 64 ? mask & ~(~0ull >> n) : mask;
             const bool own = n > 32 && n <= 64 && inside;
             if (own && __builtin_popcountll(mask) <= 4) {
                 word = fill_cell;
@@ -467,7 +489,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
 }
 
 // Builds the grids of a workgroup's 4 subspaces.  src: the codebook of the first of them, [4][256][2]
-template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GRID_SUB], float2 (&box)[GRID_SIDE], const T *src)
+template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GRID_SUB], pq_grid_table (&table)[GRID_SUB], float2 (&box)[GRID_SIDE], const T *src)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -481,10 +503,10 @@ template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GR
     if (threadIdx.x < GRID_SIDE)
         pq_grid_box((int)threadIdx.x, 1, box[threadIdx.x].x, box[threadIdx.x].y);
     __syncthreads();
-    pq_grid_tables(g, src + (wave >> 2) * 512, part);
+    pq_grid_tables(g, table[wave >> 2], src + (wave >> 2) * 512, part);
     __syncthreads();
     if (g.bad == 0)  // (the same for the 4 wavefronts)
-        pq_grid_lists(g, box, part);
+        pq_grid_lists(g, table[wave >> 2], box, part);
     __syncthreads();
     // The tokens are taken to lie where the centroids do: with more than 24 of 256 in cells without a list the filter does
     // the work
