@@ -13,7 +13,7 @@
 
 prefill: the nearest-centroid encode at prompt shape (Section III-A, "Online Prefill with KV Cache
 Quantization"): vectors per second against the vector-ALU roofline (256 CUs x 64 lanes x 2.4 GHz = 39.3 T
-operations/s) at the instruction count of the fp16 filter kernel, and the time the plain fp64 scan (2 ds + 3
+operations/s) at the instruction count of the grid kernel, and the time the plain fp64 scan (2 ds + 3
 operations per (sub-vector, centroid)) would need at that peak.
 
 async: Section III-B's asynchronous quantization with what this pool allows — two streams of DEFAULT
@@ -22,7 +22,7 @@ two kernels touch disjoint data; the caller publishes the new lengths between st
 
 train: Lloyd iterations of the per-subspace k-means (Section III-A, "Offline PQ Codebook Training") on 65 536
 sampled vectors per head, 32 heads, M = 64: time per iteration against the vector-ALU roofline at the instruction
-count of the assignment (the encode's matrix-core filter), and the time the plain fp64 scan would need at that peak.
+count of the assignment (the encode's grids), and the time the plain fp64 scan would need at that peak.
 
 pq12: the 12-bit setting (M = 32, 4096 centroids, 48 bytes per token and tensor; Section IV-A).  Decode
 against HBM: algorithmic bytes = codes + recent rows + both codebooks once per KV head (2 MiB per head: at 32K
@@ -84,9 +84,9 @@ def prefill():
             app()
         ms = _span_ms(step, 5)
     vectors = 2 * w.batch * w.n_kv_heads * n_new
-    # vector instructions the filter kernel issues per (token, subspace), its 16 matrix instructions per 64 of them
-    # included (rocprofv3 SQ_INSTS_VALU: 355)
-    ops_per_subvector = 355
+    # vector instructions the grid kernel issues per (token, subspace), the building of the grids included (rocprofv3
+    # SQ_INSTS_VALU: 151)
+    ops_per_subvector = 151
     ops = vectors * w.n_subspaces * ops_per_subvector
     achieved = ops / (ms * 1e-3)
     scan_ops = vectors * w.n_subspaces * 256 * (2 * w.sub_dim + 3)
@@ -170,9 +170,9 @@ def train():
 
     ms = _span_ms(run, 3, warmup=1) / iters
     ds = 128 // M
-    # vector instructions of the assignment per (sample, subspace): the encode's matrix-core filter and the member sums
-    # (rocprofv3 SQ_INSTS_VALU: 394)
-    ops = Hkv * M * n * 394
+    # vector instructions of the assignment per (sample, subspace): the grids, the encode's look-up and the member sums
+    # (rocprofv3 SQ_INSTS_VALU: 117, mean of 5 iterations)
+    ops = Hkv * M * n * 117
     scan_ops = Hkv * M * n * 256 * (2 * ds + 3)
     trained = cb.cpu().numpy()
     B.pq_attn_destroy(ctx)
