@@ -235,20 +235,44 @@ __device__ __forceinline__ void pq_grid_box(const int e, const int n, float &g, 
     h = 0.5f * (hi - lo) + 7.62939453125e-06f;  // 2^-17
 }
 
-// appends the bit t <= limit to a mask
-__device__ __forceinline__ void pq_grid_mark(uint32_t &mask, const float t, const float limit)
+// Appending the bit t <= limit to a mask is a comparison and an addition with carry.  What a vector instruction writes to VCC
+// or a scalar register may be read by another from two wait states on; the compiler sees to that, but not inside of asm.  So
+// several candidates are marked at a time, and every read stands behind two other instructions.  (Left to the compiler, an
+// instruction more each: encode of 32K tokens x 32 heads 673 us, 659 so; k-means of 32 heads x 64K samples 1002 and 987.)
+
+// appends the bits t[k] <= limit to a mask, k = 0 .. 3
+__device__ __forceinline__ void pq_grid_mark_four(uint32_t &mask, const float (&t)[4], const float limit)
 {
-    asm("v_cmp_le_f32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(mask) : "v"(t), "v"(limit) : "vcc");
+    uint64_t of0, of1, of2;
+    asm("v_cmp_le_f32_e64 %1, %4, %8\n\t"
+        "v_cmp_le_f32_e64 %2, %5, %8\n\t"
+        "v_cmp_le_f32_e64 %3, %6, %8\n\t"
+        "v_cmp_le_f32_e32 vcc, %7, %8\n\t"
+        "v_addc_co_u32_e64 %0, %1, %0, %0, %1\n\t"
+        "v_addc_co_u32_e64 %0, %2, %0, %0, %2\n\t"
+        "v_addc_co_u32_e64 %0, %3, %0, %0, %3\n\t"
+        "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+        : "+&v"(mask), "=&s"(of0), "=&s"(of1), "=&s"(of2)
+        : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(limit)
+        : "vcc");
 }
 
-// the same, and shifts a code into a word of the last four that were marked
-__device__ __forceinline__ void pq_grid_mark(uint32_t &mask, uint32_t &word, const uint32_t code, const float t, const float limit)
+// the same for two, and shifts the codes of those that are marked into a word
+__device__ __forceinline__ void pq_grid_mark_two(uint32_t &mask, uint32_t &word, const uint32_t code0, const uint32_t code1, const float t0,
+                                                 const float t1, const float limit)
 {
-    const uint32_t next = word << 8 | code;
-    uint64_t carry;
-    asm("v_cmp_le_f32_e32 vcc, %4, %5\n\tv_addc_co_u32_e64 %0, %2, %0, %0, vcc\n\tv_cndmask_b32_e32 %1, %1, %3, vcc"
-        : "+v"(mask), "+v"(word), "=&s"(carry)
-        : "v"(next), "v"(t), "v"(limit)
+    uint64_t of0;
+    uint32_t next;
+    asm("v_cmp_le_f32_e64 %2, %6, %8\n\t"
+        "v_cmp_le_f32_e32 vcc, %7, %8\n\t"
+        "v_lshl_or_b32 %3, %1, 8, %4\n\t"
+        "v_cndmask_b32_e64 %1, %1, %3, %2\n\t"
+        "v_addc_co_u32_e64 %0, %2, %0, %0, %2\n\t"
+        "v_lshl_or_b32 %3, %1, 8, %5\n\t"
+        "v_cndmask_b32_e32 %1, %1, %3, vcc\n\t"
+        "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+        : "+&v"(mask), "+&v"(word), "=&s"(of0), "=&v"(next)
+        : "v"(code0), "v"(code1), "v"(t0), "v"(t1), "v"(limit)
         : "vcc");
 }
 
@@ -265,13 +289,12 @@ template <int K> __device__ __forceinline__ void pq_grid_row_fma(float &v, const
         : "+&v"(v) : "v"(x), "v"(ax), "v"(y), "v"(ay), "n"(K));
 }
 
-// calls f(integral constant 0 .. N - 1), two at a time while the first of the two is below `most` (uniform)
+// calls f(K, K + 1), integral constants, for the even K < N while K is below `most` (uniform)
 template <int K, int N, typename F> __device__ __forceinline__ void pq_grid_twos(const int most, F f)
 {
     if constexpr (K < N) {
         if (K < most) {
-            f(std::integral_constant<int, K>());
-            f(std::integral_constant<int, K + 1>());
+            f(std::integral_constant<int, K>(), std::integral_constant<int, K + 1>());
             pq_grid_twos<K + 2, N>(most, f);
         }
     }
@@ -309,13 +332,17 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
 #pragma unroll 1
         for (int w = 0; w < 256; w += 32) {
             uint32_t mask = 0;  // candidate w + k in bit 31 - k
-#pragma unroll 8
-            for (int k = 0; k < 32; ++k) {
-                const float4 c = *(const float4 *)table[w + k];
-                float t = __builtin_fmaf(-gy, c.y, __builtin_fmaf(-gx, c.x, c.z));
-                t = __builtin_fmaf(-fabsf(c.x - ref.x), hx, t);
-                t = __builtin_fmaf(-fabsf(c.y - ref.y), hy, t);
-                pq_grid_mark(mask, t, limit);
+#pragma unroll 2
+            for (int k = 0; k < 32; k += 4) {
+                float t[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float4 c = *(const float4 *)table[w + k + j];
+                    t[j] = __builtin_fmaf(-gy, c.y, __builtin_fmaf(-gx, c.x, c.z));
+                    t[j] = __builtin_fmaf(-fabsf(c.x - ref.x), hx, t[j]);
+                    t[j] = __builtin_fmaf(-fabsf(c.y - ref.y), hy, t[j]);
+                }
+                pq_grid_mark_four(mask, t, limit);
             }
             used = w == 0 ? __builtin_bitreverse32(mask) : used;
             const int total = count + __builtin_popcount(mask);
@@ -410,24 +437,32 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             // half the squared distances of its centre; the least, with its place in the list in the low bits
             float v[32];
             int least = 0x7f7fffff;
-            pq_grid_twos<0, 32>(most, [&](auto K) {
+            const auto distance = [&](auto K) {
                 const float4 &e = K < 16 ? first : second;
                 constexpr int k = K & 15;
                 v[K] = pq_grid_row<k>(e.z) + half;
                 pq_grid_row_fma<k>(v[K], e.x, minus_gx, e.y, minus_gy);
                 least = min(least, (__float_as_int(v[K]) & ~31) | (int)K);
+            };
+            pq_grid_twos<0, 32>(most, [&](auto K0, auto K1) {
+                distance(K0);
+                distance(K1);
             });
             const float4 ref = *(const float4 *)table[bytes[list + (uint32_t)(((least >> 4) & 1) * 256 + (least & 15))]];
             const float nearest = __int_as_float(least & ~31);
             const float limit = nearest + MARGIN * (2.f * fabsf(nearest) + ref.w + far);
             uint32_t mask = 0, marked = fill_cell;
-            pq_grid_twos<0, 32>(most, [&](auto K) {
-                const float4 &e = K < 16 ? first : second;
-                constexpr int k = K & 15;
-                float t = __builtin_fmaf(-fabsf(pq_grid_row<k>(e.x) - ref.x), x.y, v[K]);
-                t = __builtin_fmaf(-fabsf(pq_grid_row<k>(e.y) - ref.y), y.y, t);
-                pq_grid_mark(mask, marked, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(K < 16 ? code1 : code2), 0x150 + k, 0xf, 0xf, true),
-                             t, limit);
+            pq_grid_twos<0, 32>(most, [&](auto K0, auto K1) {
+                const auto test = [&](auto K, uint32_t &code) {
+                    const float4 &e = K < 16 ? first : second;
+                    constexpr int k = K & 15;
+                    code = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(K < 16 ? code1 : code2), 0x150 + k, 0xf, 0xf, true);
+                    const float t = __builtin_fmaf(-fabsf(pq_grid_row<k>(e.x) - ref.x), x.y, v[K]);
+                    return __builtin_fmaf(-fabsf(pq_grid_row<k>(e.y) - ref.y), y.y, t);
+                };
+                uint32_t code[2];
+                const float t0 = test(K0, code[0]), t1 = test(K1, code[1]);
+                pq_grid_mark_two(mask, marked, code[0], code[1], t0, t1, limit);
             });
             mask <<= 32 - ((most + 1) & ~1);
             word = n <= 32 ? marked : word;
@@ -447,10 +482,14 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
 #pragma unroll 1
             for (int q = 0; 16 * q < most; ++q) {
                 const float4 e = sixteen(q);
-                pq_grid_twos<0, 16>(most - 16 * q, [&](auto K) {
+                const auto distance = [&](auto K) {
                     float v = pq_grid_row<K>(e.z) + half;
                     pq_grid_row_fma<K>(v, e.x, minus_gx, e.y, minus_gy);
                     least = min(least, (__float_as_int(v) & ~63) | (16 * q + (int)K));
+                };
+                pq_grid_twos<0, 16>(most - 16 * q, [&](auto K0, auto K1) {
+                    distance(K0);
+                    distance(K1);
                 });
             }
             const float4 ref = *(const float4 *)table[bytes[list + (uint32_t)(((least >> 4) & 3) * 256 + (least & 15))]];
@@ -461,12 +500,15 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             for (int q = 0; 16 * q < most; ++q) {
                 const float4 e = sixteen(q);
                 uint32_t some = 0;
-                pq_grid_twos<0, 16>(most - 16 * q, [&](auto K) {
+                const auto test = [&](auto K) {
                     float t = pq_grid_row<K>(e.z) + half;
                     pq_grid_row_fma<K>(t, e.x, minus_gx, e.y, minus_gy);
                     t = __builtin_fmaf(-fabsf(pq_grid_row<K>(e.x) - ref.x), x.y, t);
-                    t = __builtin_fmaf(-fabsf(pq_grid_row<K>(e.y) - ref.y), y.y, t);
-                    pq_grid_mark(some, t, limit);
+                    return __builtin_fmaf(-fabsf(pq_grid_row<K>(e.y) - ref.y), y.y, t);
+                };
+                pq_grid_twos<0, 16>(most - 16 * q, [&](auto K0, auto K1) {
+                    const float t0 = test(K0), t1 = test(K1);
+                    some = some * 4 + (t0 <= limit ? 2u : 0u) + (t1 <= limit ? 1u : 0u);
                 });
                 const int n_marked = most - 16 * q < 16 ? (most - 16 * q + 1) & ~1 : 16;
                 mask |= (uint64_t)(some << (16 - n_marked)) << (48 - 16 * q);
