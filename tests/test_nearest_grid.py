@@ -1,6 +1,13 @@
 """The grid that names, for every cell of a subspace's plane, the centroids that can be the nearest of a point in it (long
 appends and large trainings at two dims per subspace).  On the CPU: the cell lists, built in fp32 as the kernel builds them,
 hold the fp64-nearest centroid of every point.  On the GPU: codes and trained codebooks against the oracle."""
+import ctypes
+import functools
+import os
+import re
+import subprocess
+import tempfile
+
 import numpy as np
 import pytest
 import torch
@@ -9,6 +16,7 @@ from oracle import pq_kmeans_oracle as K
 from oracle import pq_oracle as O
 from paper_2504_03661_amd import PQ_CODES_K, PQ_CODES_V
 from paper_2504_03661_amd import binding as B
+from paper_2504_03661_amd import build as lib_build
 from paper_2504_03661_amd.harness import PQSession
 from synth import workloads as W
 from tests.test_gpu_kmeans import gpu_fit, make_ctx
@@ -128,6 +136,47 @@ def test_lists_hold_the_nearest_centroid_of_every_point(kind, dtype):
             assert inside.mean() > 0.98 and (lists[ix, iy].sum(1) > 4)[inside].mean() < 0.15
 
 
+HEADER = open(os.path.join(lib_build.CSRC, "pq_nearest_grid.h")).read()
+
+
+@functools.cache
+def _rule():
+    """The launchers' rule (slices of the tokens for the grid kernels, 0: the filter), compiled from its source."""
+    text = re.search(r"^inline int pq_grid_slices\(.*?^}", HEADER, re.S | re.M).group(0)
+    with tempfile.TemporaryDirectory() as d:
+        with open(os.path.join(d, "rule.cpp"), "w") as f:
+            f.write("#include <cstdint>\n" + text + "\nextern \"C\" int rule(int64_t c, int64_t f, int64_t g, int n) "
+                    "{ return pq_grid_slices(c, f, g, n); }\n")
+        lib = os.path.join(d, "rule.so")
+        subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", lib, f.name], check=True)
+        fn = ctypes.CDLL(lib).rule
+    fn.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
+    return fn
+
+
+def encode_slices(Hkv, B_, n_new, n_cu=256):
+    return _rule()(B_ * ((n_new + 126) >> 6), (B_ * n_new + 63) // 64, 2 * Hkv * 16, n_cu)
+
+
+def train_slices(Hkv, n, n_cu=256):
+    return _rule()((n + 63) // 64, (n + 63) // 64, Hkv * 16, n_cu)
+
+
+LONG_APPENDS = [
+    (2, 1, 68001, np.float16, [0], 68001),
+    (8, 3, 23003, np.float16, [0, 77, 63], 23070),                # K codes by lane quads; the second sequence overflows
+    (2, 2, 34000, np.float32, [5, 64], 40000),
+]
+TRAININGS = [(2, 80003, 1), (5, 45000, 2)]
+
+
+def test_the_sizes_below_take_the_grid():
+    assert all(encode_slices(2, B_, n_new) > 1 for _, B_, n_new, *_ in LONG_APPENDS)
+    assert all(train_slices(Hkv, n) > 1 for Hkv, n, _ in TRAININGS)
+    assert encode_slices(32, 1, 9000) == 1 and encode_slices(32, 1, 8000) == 0 and encode_slices(1, 1, 20000) == 0
+    assert train_slices(32, 9000) == 1 and train_slices(32, 4000) == 0 and train_slices(2, 68003) == 0
+
+
 def _data(Hq, Hkv, B_, n_new, dtype, start):
     w = W.Workload("grid", B_, Hq, Hkv, 128, 64, 64, "f16" if dtype == np.float16 else "f32", n_new=8, seed=n_new)
     data = W.generate(w)
@@ -146,13 +195,14 @@ def _data(Hq, Hkv, B_, n_new, dtype, start):
     return data
 
 
+def _n_cu():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("Hq,B_,n_new,dtype,start,room", [
-    (2, 1, 68001, np.float16, [0], 68001),
-    (8, 3, 23003, np.float16, [0, 77, 63], 23070),                # K codes by lane quads; the second sequence overflows
-    (2, 2, 34000, np.float32, [5, 64], 40000),
-])
+@pytest.mark.parametrize("Hq,B_,n_new,dtype,start,room", LONG_APPENDS)
 def test_long_appends_equal_the_oracle(Hq, B_, n_new, dtype, start, room):
+    assert encode_slices(2, B_, n_new, _n_cu()) > 0
     data = _data(Hq, 2, B_, n_new, dtype, start)
     with PQSession(data, Hq, "f16" if dtype == np.float16 else "f32", max_context=room) as s:
         s.append(torch.from_numpy(data["new_k"]).cuda(), torch.from_numpy(data["new_v"]).cuda())
@@ -168,6 +218,7 @@ def test_long_appends_equal_the_oracle(Hq, B_, n_new, dtype, start, room):
 
 @pytest.mark.gpu
 def test_rows_that_start_off_a_16_byte_address():
+    assert encode_slices(2, 1, 68001, _n_cu()) > 0
     data = _data(2, 2, 1, 68001, np.float16, [0])
     shifted = {}
     for name in ("new_k", "new_v"):
@@ -186,8 +237,9 @@ def test_rows_that_start_off_a_16_byte_address():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("Hkv,n,iters", [(2, 68003, 1), (5, 45000, 2)])
+@pytest.mark.parametrize("Hkv,n,iters", TRAININGS)
 def test_training_on_many_samples_equals_the_oracle(Hkv, n, iters):
+    assert train_slices(Hkv, n, _n_cu()) > 0
     samples = np.empty((Hkv, n, 128), np.float16)
     init = np.empty((Hkv, 64, 256, 2), np.float16)
     for h in range(Hkv):
