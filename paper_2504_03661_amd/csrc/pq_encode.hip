@@ -261,7 +261,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
     const int first = slice * slice_chunks;
     const int last = first + slice_chunks < n_chunks ? first + slice_chunks : n_chunks;
 
-    pq_grid_build(grid, scratch.table, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
+    pq_grid_build(grid, scratch.making, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
 
     const T *x = (const T *)a.x[which] + i0 * 2;
     uint8_t *codes = a.codes[which];
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
         const int n = a.ctx_len[seq];
         return n < 0 ? 0 : n < cap ? n : cap;
     };
-    auto fetch = [&](int, grid_token<T> &k) {
+    auto fetch = [&, b, r](int, grid_token<T> &k) mutable {
         const bool any = b < a.B;
         const int seq = any ? b : a.B - 1;
         const int n_old = length(seq);
@@ -299,15 +299,17 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
             ++b;
         }
     };
+    const int n_old_first = length(0);
     auto place = [&](uint32_t id, int &seq, int &t, int &pos) {
         const uint32_t chunk = (uint32_t)first + (id >> 8);
         seq = a.B == 1 ? 0 : (int)(chunk / (uint32_t)seq_chunks);  // (a division is some 25 instructions)
-        const int block = (int)(chunk - (uint32_t)seq * (uint32_t)seq_chunks), n_old = length(seq);
+        const int block = (int)(chunk - (uint32_t)seq * (uint32_t)seq_chunks);
+        const int n_old = a.B == 1 ? n_old_first : length(seq);  // (no load on the way to a store)
         t = block * 64 + (int)((id >> 2) & 63u) - (n_old & 63);
         pos = n_old + t;
     };
     pq_grid_scan<T, KEEP, grid_token<T>>(
-        grid, scratch.queue[wave], first, last, fetch,
+        grid, scratch.queue, first, last, fetch,
         [&](const grid_token<T> &k, int j, int code) {
             codes[k.block + (uint32_t)pq_grid_pick(j, in_block[0], in_block[1], in_block[2], in_block[3])] = (uint8_t)code;
         },

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
         ((unsigned long long *)sum)[e] = 0ull;
     for (int e = threadIdx.x; e < GRID_SUB * 256; e += GRID_WAVES * 64)
         ((unsigned int *)count)[e] = 0u;
-    pq_grid_build(grid, scratch.table, box, codebook + ((int64_t)head * M + i0) * 512);
+    pq_grid_build(grid, scratch.making, box, codebook + ((int64_t)head * M + i0) * 512);
 
     constexpr uint64_t BASE = 0x4338000000000000ull;  // the bits of 1.5 2^52
     const _Float16 *x = samples + (int64_t)head * n_samples * PQ_HEAD_DIM + i0 * 2;
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
         atomicAdd(&count[j][code], 1u);
     };
     pq_grid_scan<_Float16, false, pq_sample>(
-        grid, scratch.queue[wave], first, last,
+        grid, scratch.queue, first, last,
         [&](int chunk, pq_sample &k) {
             const int s = chunk * 64 + lane;
             k.live = s < n_samples;

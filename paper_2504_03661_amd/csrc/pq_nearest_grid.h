@@ -28,10 +28,14 @@
 // stand in the pool.  Outside, where there is no room, or more than 64 candidates in the block: GRID_NONE.
 // Tokens.  The four distances in fp32 (relative error below 2^-21), their 8 low bits replaced by the code: one unsigned
 // minimum gives the least and its code, one median keeps the second.  More than 2^-16 apart, the order is that of the fp64
-// distances; otherwise, and for tokens outside, all 64 lanes evaluate the token's fp64 distances to all centroids together
-// (four per lane); where a chunk has many such tokens, or the codebook gave no useful grid, the filter takes the chunk.
-// Tokens of cells with longer lists (7 % with a codebook of random vectors, 1 % with a trained one) wait in LDS until 64 are
-// there and are then worked on as one.
+// distances; the others ("unsure": also those outside and in cells without a list) are put off until 64 of a subspace can go
+// through the filter together, and where the codebook gives no useful grid all its tokens go there at once.  Tokens of cells
+// with longer lists (7 % with a codebook of random vectors, 1 % with a trained one) wait in LDS until 64 are there and are then
+// worked on as one.
+// What the data make of it, 32 heads, us, beside the filter alone: encode of 9000 tokens, normal 363 / 440, Laplace's
+// distribution 416 / 442, 2 % of the coordinates times 20 418 / 439; of 32K 633 / 1578, 804 / 1588, 818 / 1598.  A codebook
+// without a useful grid costs the filter's four instead of five wavefronts per SIMD: one dead axis in every subspace 885 / 755
+// and 3060 / 2600, centroids of 16 values in all 2867 / 2489 and 10098 / 8570.
 #pragma once
 
 #include "pq_device_utils.h"
@@ -43,17 +47,15 @@ constexpr int GRID_SUB = 4;       // neighbouring subspaces of a workgroup: 16 b
 constexpr int GRID_WAVES = 16;    // 4 wavefronts build each subspace's grid; then all take tokens, 4 subspaces at a time
 constexpr int GRID_SIDE = 64;
 // Words of longer lists per subspace.  Random vectors take 400 on average, and up to 1200 where one axis is several times the
-// other: its cells then have many candidates.  Tokens of a cell that found no room are worked on one by one, and a workgroup
-// with one such subspace is what the others wait for (k-means of 32 heads x 64K samples, scales 0.5 .. 4 per channel, 5
-// iterations: 0.68 ms each with 1024 words, 0.66 so, and 0.64 with lists of 33 .. 64 by row broadcast like the shorter ones).
+// other: its cells then have many candidates.  Tokens of a cell that found no room go to the filter, and a workgroup with such
+// subspaces is what the others wait for (k-means of 32 heads x 64K samples, scales 0.5 .. 4 per channel, 5 iterations, when
+// these tokens were decided one by one: 0.68 ms each with 1024 words, 0.66 so, and 0.64 with lists of 33 .. 64 by row broadcast).
 constexpr int GRID_POOL = 2048;
 // Waiting tokens of a wavefront: their number, and where KEEP their fp16 sub-vector as well.  (Read again when its turn came,
 // its line had often left the L2: encode, 32K tokens x 32 heads, 696 us, 663 with it.  Beside the k-means' sums, and in
-// fp32, there is no room.)  The queue holds fewer than 64, and up to 64 of each subspace until it is looked at: after two
-// subspaces, or after all four.
+// fp32, there is no room.)  The queue holds fewer than 64 before a chunk, and up to 64 of each subspace more behind it.
 template <bool KEEP> using pq_grid_waiting = typename std::conditional<KEEP, uint2, uint32_t>::type;
-template <bool KEEP> constexpr int GRID_LOOK = KEEP ? 2 : 4;
-template <bool KEEP> constexpr int GRID_QUEUE = 64 * (1 + GRID_LOOK<KEEP>);
+constexpr int GRID_QUEUE = 64 * (1 + GRID_SUB);
 constexpr int GRID_SHIFT = 20;    // 8 cells per octave
 constexpr float GRID_BIAS = 2.0f;
 constexpr uint32_t GRID_FIRST = 0x40000000u, GRID_LAST = 0x41ffffffu;  // float bits of 2 .. just below 32
@@ -65,18 +67,41 @@ template <typename T> struct pq_grid {
     uint32_t cell[GRID_SIDE * GRID_SIDE];  // [u_x][u_y]; while building, the 64 bytes of a 4 x 4 block are its list
     unsigned char arow[256 * pq_filter_row_bytes<T>()];
     T coord[256][2];
-    uint32_t pool[GRID_POOL];
+    __attribute__((aligned(16))) uint32_t pool[GRID_POOL];
     float sx, ox, sy, oy;  // the map
     float scale;           // of the filter
-    uint32_t pool_used, unserved, bad;  // bad: 1 no grid, 2 codebook outside the filter's range
+    uint32_t pool_used, bad;  // bad: 1 no grid, 2 codebook outside the filter's range
+    uint32_t lost, unserved;  // how many centroids the grid does not serve: counted before and after its lists
 };
 
-// What building a grid needs of its centroids: a_x, a_y, |c|^2 / 2 lowered, |c|^2 / 2.  The waiting tokens take its place.
+// The tokens are taken to lie where the centroids do: where many of the 256 are left to the filter (in cells without a list, or
+// with an equal one before them), it does all the work of the subspace.  (For 64 tokens: 86 instructions for the look-ups,
+// some 30 for putting tokens off and for 24 of them 135 in the filter; 355 through the filter alone, and building is saved.)
+constexpr int GRID_LOST = 96;
+template <typename T> __device__ __forceinline__ bool pq_grid_useless(const pq_grid<T> &g) { return g.bad != 0 || g.lost > GRID_LOST || g.unserved > GRID_LOST; }
+
+// What building a grid needs of its centroids: a_x, a_y, |c|^2 / 2 lowered, |c|^2 / 2; how many of them lie in each block of
+// 4 x 4 cells, 16 bits each; and the first of those whose coordinates have the same hash.  The waiting tokens take its place.
 typedef float pq_grid_table[256][4];
-template <bool KEEP> union pq_grid_scratch {
+struct pq_grid_making {
     pq_grid_table table[GRID_SUB];
-    pq_grid_waiting<KEEP> queue[GRID_WAVES][GRID_QUEUE<KEEP>];
+    uint32_t in_block[GRID_SUB][128];
+    uint32_t first_of[GRID_SUB][256];
 };
+template <bool KEEP> union pq_grid_scratch {
+    pq_grid_making making;
+    pq_grid_waiting<KEEP> queue[GRID_WAVES][GRID_QUEUE];
+};
+
+template <typename T> __device__ __forceinline__ uint32_t pq_grid_hash(const T x, const T y)
+{
+    uint32_t h;
+    if constexpr (sizeof(T) == 2)
+        h = (uint32_t)__builtin_bit_cast(uint16_t, x) | (uint32_t)__builtin_bit_cast(uint16_t, y) << 16;
+    else
+        h = __float_as_uint(x) * 0x85ebca6bu ^ __float_as_uint(y);
+    return h * 0x9e3779b1u >> 24;
+}
 
 // bits 20 .. 25: the cell coordinate, 0 .. 31 upwards from zero, 63 .. 32 downwards
 __device__ __forceinline__ uint32_t pq_grid_axis(const float u)
@@ -94,6 +119,9 @@ __device__ __forceinline__ uint32_t pq_grid_cell(const T x, const T y, const flo
     static_assert(GRID_SHIFT == 20 && GRID_SIDE == 64, "the shifts below");
     return ((ex >> 12) & 0x3f00u) | ((ey >> 18) & 0xfcu);
 }
+
+// the block of 4 x 4 cells of a cell's byte offset: [x][y] of 16
+__device__ __forceinline__ uint32_t pq_grid_block(const uint32_t cell) { return (cell >> 6 & 0xf0u) | (cell >> 4 & 15u); }
 
 // lower edge of cell coordinate k = -32 .. 32 (31 and -32: the open ones, given an end)
 __device__ __forceinline__ float pq_grid_edge(const int k)
@@ -137,8 +165,10 @@ template <typename T> __device__ __forceinline__ bool pq_grid_unsure(const uint3
 }
 
 // A wavefront's part of a subspace's tables: the map, which all 4 wavefronts work out alike, and the rows and numbers of
-// centroids 64 part .. 64 part + 63.  src: [256][2]
-template <typename T> __device__ inline void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, const T *src, const int part)
+// centroids 64 part .. 64 part + 63, these centroids counted into their blocks.  src: [256][2]; cell, hash: of centroid 64 part + lane
+template <typename T>
+__device__ inline void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, uint32_t (&in_block)[128], uint32_t (&first_of)[256], const T *src,
+                                      const int part, uint32_t &cell, uint32_t &hash)
 {
     const int lane = threadIdx.x & 63;
     float x[4], y[4];
@@ -204,6 +234,11 @@ template <typename T> __device__ inline void pq_grid_tables(pq_grid<T> &g, pq_gr
     table[c][3] = n;
     g.coord[c][0] = mine[0];
     g.coord[c][1] = mine[1];
+    cell = pq_grid_cell(mine[0], mine[1], sx, ox, sy, oy);
+    hash = pq_grid_hash(mine[0], mine[1]);
+    const uint32_t block = pq_grid_block(cell);
+    atomicAdd(&in_block[block >> 1], 1u << (16 * (block & 1u)));
+    atomicMin(&first_of[hash], (uint32_t)c);
     const uint32_t bad = (__builtin_amdgcn_ballot_w64(far_out) != 0 || !usable ? 1u : 0u) |
                          (__builtin_amdgcn_ballot_w64(cb_bad) != 0 ? 3u : 0u);
     if (lane == 0) {
@@ -530,8 +565,24 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
     }
 }
 
+// How many of the wavefront's 64 centroids the grid will not serve, known before the lists are, which take most of the
+// building: those outside the map, in a block with more than 64 of them, all of which would be in its list (tight clusters), and
+// those that repeat an earlier one (a token there has two nearest ones; a repetition behind a clash of hashes is not seen).
+template <typename T>
+__device__ inline int pq_grid_lost(const pq_grid<T> &g, const uint32_t (&in_block)[128], const uint32_t (&first_of)[256], const int part,
+                                   const uint32_t cell, const uint32_t hash)
+{
+    const int c = 64 * part + (threadIdx.x & 63);
+    const uint32_t ex = cell >> 8, ey = cell >> 2 & 63u, block = pq_grid_block(cell);
+    const bool outside = ex - 31u < 2u || ey - 31u < 2u;
+    const uint32_t n = in_block[block >> 1] >> (16 * (block & 1u)) & 0xffffu;
+    const int other = (int)first_of[hash];
+    const bool again = other != c && g.coord[other][0] == g.coord[c][0] && g.coord[other][1] == g.coord[c][1];
+    return __builtin_popcountll(__builtin_amdgcn_ballot_w64(outside || n > 64 || again));
+}
+
 // Builds the grids of a workgroup's 4 subspaces.  src: the codebook of the first of them, [4][256][2]
-template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GRID_SUB], pq_grid_table (&table)[GRID_SUB], float2 (&box)[GRID_SIDE], const T *src)
+template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GRID_SUB], pq_grid_making &making, float2 (&box)[GRID_SIDE], const T *src)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -539,62 +590,45 @@ template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GR
     const int part = wave & 3;
     if (threadIdx.x < GRID_SUB) {
         grid[threadIdx.x].pool_used = 0;
-        grid[threadIdx.x].unserved = 0;
         grid[threadIdx.x].bad = 0;
+        grid[threadIdx.x].lost = 0;
+        grid[threadIdx.x].unserved = 0;
     }
     if (threadIdx.x < GRID_SIDE)
         pq_grid_box((int)threadIdx.x, 1, box[threadIdx.x].x, box[threadIdx.x].y);
+    if (threadIdx.x < GRID_SUB * 128)
+        ((uint32_t *)making.in_block)[threadIdx.x] = 0;
+    ((uint32_t *)making.first_of)[threadIdx.x] = 255;
     __syncthreads();
-    pq_grid_tables(g, table[wave >> 2], src + (wave >> 2) * 512, part);
+    uint32_t cell, hash;
+    pq_grid_tables(g, making.table[wave >> 2], making.in_block[wave >> 2], making.first_of[wave >> 2], src + (wave >> 2) * 512, part, cell, hash);
     __syncthreads();
-    if (g.bad == 0)  // (the same for the 4 wavefronts)
-        pq_grid_lists(g, table[wave >> 2], box, part);
+    const int n_lost = pq_grid_lost(g, making.in_block[wave >> 2], making.first_of[wave >> 2], part, cell, hash);
+    if (lane == 0)
+        atomicAdd(&g.lost, (uint32_t)n_lost);
     __syncthreads();
-    // The tokens are taken to lie where the centroids do: with more than 24 of 256 in cells without a list the filter does
-    // the work
-    if (g.bad == 0) {
-        const T(&c)[2] = g.coord[64 * part + lane];
-        const uint32_t word = *(const uint32_t *)((const char *)g.cell + pq_grid_cell(c[0], c[1], g.sx, g.ox, g.sy, g.oy));
+    const bool lists = g.bad == 0 && g.lost <= GRID_LOST;  // (the same for the 4 wavefronts)
+    if (lists)
+        pq_grid_lists(g, making.table[wave >> 2], box, part);
+    __syncthreads();
+    if (lists) {
+        const uint32_t word = *(const uint32_t *)((const char *)g.cell + cell);
         const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(word == GRID_NONE));
         if (lane == 0 && n != 0)
             atomicAdd(&g.unserved, (uint32_t)n);
     }
     __syncthreads();
-    if (g.bad != 0 || g.unserved > 24) {
+    if (pq_grid_useless(g)) {
         for (int k = part * 64 + lane; k < GRID_SIDE * GRID_SIDE; k += 256)
             g.cell[k] = GRID_NONE;
+        if constexpr (sizeof(T) == 2) {  // what the filter refines with, in place of the lists
+            const int c = 64 * part + lane;
+            double *wide = (double *)g.pool + 2 * c;
+            wide[0] = (double)((float)g.coord[c][0] * g.scale);
+            wide[1] = (double)((float)g.coord[c][1] * g.scale);
+        }
     }
     __syncthreads();
-}
-
-// The code of the tokens in `lanes`, one after the other, by all lanes together: the defining fp64 distances, four
-// centroids a lane, the lowest index among equal ones.  grid_of_lane: each lane's grid
-template <typename T>
-__device__ inline int pq_grid_exact(const pq_grid<T> (&grid)[GRID_SUB], uint64_t lanes, const int grid_of_lane, const T x, const T y)
-{
-#pragma clang fp contract(off)
-    const int lane = threadIdx.x & 63;
-    int code = 0;
-    while (lanes != 0) {
-        const int l = __builtin_ctzll(lanes);
-        lanes &= lanes - 1;
-        const auto &coord = grid[__builtin_amdgcn_readlane(grid_of_lane, l)].coord;
-        const double px = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int((float)x), l));
-        const double py = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int((float)y), l));
-        double bd = __builtin_huge_val();
-        int bc = lane;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double dx = px - (double)(float)coord[lane + 64 * r][0];
-            const double dy = py - (double)(float)coord[lane + 64 * r][1];
-            const double dist = __builtin_fma(dy, dy, __builtin_fma(dx, dx, 0.0));
-            bc = dist < bd ? lane + 64 * r : bc;
-            bd = __builtin_fmin(bd, dist);
-        }
-        wave_argmin(bd, bc);
-        code = lane == l ? bc : code;
-    }
-    return code;
 }
 
 // the value of subspace j of the group (as values: a choice among array elements would put the array into memory)
@@ -603,19 +637,66 @@ template <typename V> __device__ __forceinline__ V pq_grid_pick(const int j, con
     return j == 0 ? a : j == 1 ? b : j == 2 ? c : d;
 }
 
+// The coordinates that the filter refines with in a subspace without a grid: fp64, which then stand in place of the lists, as
+// in the encode's own filter kernel; fp32 as they are.
+template <typename T> using pq_grid_wide = typename std::conditional<sizeof(T) == 4, float, double>::type;
+
+// The chunks of a workgroup through the filter, for the subspaces in the mask `useless`
+template <typename T, typename TOKEN, typename FETCH, typename STORE>
+__device__ __forceinline__ void pq_grid_filter_scan(const pq_grid<T> (&grid)[GRID_SUB], const uint32_t useless, const int first, const int last,
+                                                    FETCH fetch, STORE store)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    TOKEN next;
+    fetch(first + wave, next);
+#pragma unroll 1
+    for (int chunk = first + wave; chunk < last; chunk += GRID_WAVES) {
+        const TOKEN k = next;
+        fetch(chunk + GRID_WAVES, next);
+#pragma unroll 1
+        for (int j = 0; j < GRID_SUB; ++j) {
+            if (((useless >> j) & 1u) == 0)
+                continue;
+            const pq_grid<T> &g = grid[j];
+            const T x[2] = {pq_grid_pick(j, k.x[0][0], k.x[1][0], k.x[2][0], k.x[3][0]),
+                            pq_grid_pick(j, k.x[0][1], k.x[1][1], k.x[2][1], k.x[3][1])};
+            const int code = pq_filter_code<2, T, pq_grid_wide<T>>(g.arow, sizeof(T) == 4 ? (const unsigned char *)g.coord : (const unsigned char *)g.pool,
+                                                                   g.scale, (g.bad & 2u) != 0, x, k.live);
+            if (k.live)
+                store(k, j, code);
+        }
+    }
+}
+
 // All tokens of a workgroup, 64 at a time, chunks first + wave, first + wave + 16, .. below last.
 //   fetch(chunk, token &)    the chunk's tokens, lane = token: x[4][2] and live; called for one chunk more than there are,
-//                            in ascending order
+//                            in ascending order; copied for another walk over the chunks
 //   store(token, j, code)    the code of this lane's token for subspace j of the group
-//   waiting(id, x, y)        unless KEEP: the sub-vector of a token that was put off, id = (chunk - first) << 8 | lane << 2 | j
-//   store_waiting(id, x, y, code)
-template <typename T, bool KEEP, typename TOKEN, typename FETCH, typename STORE, typename WAITING, typename STORE_WAITING>
-__device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB], pq_grid_waiting<KEEP> (&queue)[GRID_QUEUE<KEEP>], const int first,
-                                             const int last, FETCH fetch, STORE store, WAITING waiting, STORE_WAITING store_waiting)
+//   again(id, x, y)          the sub-vector of a token that was put off, id = (chunk - first) << 8 | lane << 2 | j
+//   store_late(id, x, y, code)
+// Two kinds of tokens are put off until 64 of them can be worked on as one:
+//   waiting  in a cell with a list: in LDS, all four subspaces together
+//   unsure   per subspace, in a register that holds their ids lane by lane (fp16: another their sub-vectors); the filter takes
+//            64 for 355 instructions.  (All lanes on one token's fp64 distances take 80, and 3 to 4 % of the tokens lie outside
+//            where the coordinates have heavy tails: encode of 32 heads x 9000 tokens, Laplace's distribution, 682 us one at a
+//            time, 416 so.)  What the 16 wavefronts have left over in the end is decided together: 457 us by each for itself.
+template <typename T, bool KEEP, typename TOKEN, typename FETCH, typename STORE, typename AGAIN, typename STORE_LATE>
+__device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_grid_waiting<KEEP> (&queue)[GRID_WAVES][GRID_QUEUE], const int first,
+                                             const int last, FETCH fetch, STORE store, AGAIN again, STORE_LATE store_late)
 {
     typedef typename std::conditional<sizeof(T) == 4, float, _Float16>::type W;
+    constexpr bool WITH = sizeof(T) == 2;  // unsure tokens keep their sub-vectors
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t useless = 0;
+#pragma unroll
+    for (int j = 0; j < GRID_SUB; ++j)
+        useless |= (uint32_t)__builtin_amdgcn_readfirstlane(pq_grid_useless(grid[j]) ? 1 << j : 0);
+    if (useless != 0) {
+        pq_grid_filter_scan<T, TOKEN>(grid, useless, first, last, fetch, store);
+        if (useless == (1u << GRID_SUB) - 1u)
+            return;
+    }
     float sx[GRID_SUB], ox[GRID_SUB], sy[GRID_SUB], oy[GRID_SUB];
 #pragma unroll
     for (int j = 0; j < GRID_SUB; ++j) {
@@ -628,112 +709,196 @@ __device__ __forceinline__ void pq_grid_scan(const pq_grid<T> (&grid)[GRID_SUB],
     float minus_one = -1.0f;
     asm volatile("" : "+s"(minus_one));  // (a difference of two halves in one instruction, not two conversions more)
 
-    int n_waiting = 0;
-    auto work_off = [&](const int n) {  // the last n
-        n_waiting -= n;
-        const bool live = lane < n;
-        const pq_grid_waiting<KEEP> entry = queue[n_waiting + (live ? lane : 0)];
-        uint32_t id;
-        T x, y;
-        if constexpr (KEEP) {
-            static_assert(sizeof(T) == 2, "two sub-vector halves in a word");
-            id = entry.x;
-            x = __builtin_bit_cast(_Float16, (uint16_t)entry.y);
-            y = __builtin_bit_cast(_Float16, (uint16_t)(entry.y >> 16));
-        } else {
-            id = entry;
-            waiting(id, x, y);
-        }
-        const int j = (int)(id & 3u);
-        const pq_grid<T> &g = grid[j];
-        const uint32_t word = *(const uint32_t *)((const char *)g.cell + pq_grid_cell(x, y, g.sx, g.ox, g.sy, g.oy));
-        const uint32_t words = word & 255u, at = word >> 16;
-        uint32_t m1 = 0xffffffffu, m2 = 0xffffffffu;
-        for (uint32_t k = 0; __builtin_amdgcn_ballot_w64(k < words) != 0; ++k) {
-            if (k < words) {
-                const uint32_t four = g.pool[at + k];
-                pq_grid_take(m1, m2, pq_grid_key<0>(g.coord, four, x, y, minus_one));
-                pq_grid_take(m1, m2, pq_grid_key<1>(g.coord, four, x, y, minus_one));
-                pq_grid_take(m1, m2, pq_grid_key<2>(g.coord, four, x, y, minus_one));
-                pq_grid_take(m1, m2, pq_grid_key<3>(g.coord, four, x, y, minus_one));
-            }
-        }
-        int code = (int)(m1 & 255u);
-        const uint64_t hard = __builtin_amdgcn_ballot_w64(live && pq_grid_unsure<T>(m1, m2));
-        if (hard != 0) {
-            const int exact = pq_grid_exact(grid, hard, j, x, y);
-            code = __builtin_amdgcn_inverse_ballot_w64(hard) ? exact : code;
-        }
-        if (live)
-            store_waiting(id, x, y, code);
+    const auto word_of = [](const T x, const T y) {
+        return WITH ? (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x) | (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)y) << 16 : 0u;
     };
+    const auto of_word = [](const uint32_t xy, T &x, T &y) {
+        x = (T)__builtin_bit_cast(_Float16, (uint16_t)xy);
+        y = (T)__builtin_bit_cast(_Float16, (uint16_t)(xy >> 16));
+    };
+    // the codes of 64 unsure tokens of subspace j; a lane that is not live passes the id of a token too
+    const auto decide = [&](const int j, const uint32_t id, const uint32_t xy, const bool live) {
+        T x[2];
+        if constexpr (WITH)
+            of_word(xy, x[0], x[1]);
+        else
+            again(id, x[0], x[1]);
+        const int code = pq_filter_code<2, T, W>(grid[j].arow, sizeof(T) == 4 ? (const unsigned char *)grid[j].coord : grid[j].arow, grid[j].scale,
+                                                 (grid[j].bad & 2u) != 0, x, live);
+        if (live)
+            store_late(id, x[0], x[1], code);
+    };
+    int n_waiting = 0;
+    uint32_t n_unsure = 0;  // of subspace j in byte j; below 64
+    uint32_t unsure_id[GRID_SUB] = {}, unsure_xy[GRID_SUB] = {};
 
     TOKEN next;
-    fetch(first + wave, next);
-#pragma unroll 1
-    for (int chunk = first + wave; chunk < last; chunk += GRID_WAVES) {
-        const TOKEN k = next;
-        fetch(chunk + GRID_WAVES, next);  // in flight while this chunk is worked on
-        uint32_t word[GRID_SUB], m1[GRID_SUB], m2[GRID_SUB];
+    int chunk = first + wave;
+    fetch(chunk, next);
+    for (;;) {
+        uint64_t hard[GRID_SUB] = {};  // the lanes whose tokens this step leaves unsure: `id`, of subspace j `xy[j]`
+        uint32_t id = 0, xy[GRID_SUB] = {};
+        if (n_waiting < 64 && chunk < last) {
+            const TOKEN k = next;
+            fetch(chunk + GRID_WAVES, next);  // in flight while this chunk is worked on
+            id = (uint32_t)(chunk - first) << 8 | (uint32_t)lane << 2;
+            uint32_t word[GRID_SUB], m1[GRID_SUB], m2[GRID_SUB];
 #pragma unroll
-        for (int j = 0; j < GRID_SUB; ++j)
-            word[j] = *(const uint32_t *)((const char *)grid[j].cell + pq_grid_cell(k.x[j][0], k.x[j][1], sx[j], ox[j], sy[j], oy[j]));
+            for (int j = 0; j < GRID_SUB; ++j)
+                word[j] = *(const uint32_t *)((const char *)grid[j].cell + pq_grid_cell(k.x[j][0], k.x[j][1], sx[j], ox[j], sy[j], oy[j]));
 #pragma unroll
-        for (int j = 0; j < GRID_SUB; ++j) {
-            const uint32_t k0 = pq_grid_key<0>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one);
-            const uint32_t k1 = pq_grid_key<1>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one);
-            m1[j] = min(k0, k1);
-            m2[j] = max(k0, k1);
-            pq_grid_take(m1[j], m2[j], pq_grid_key<2>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one));
-            pq_grid_take(m1[j], m2[j], pq_grid_key<3>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one));
-        }
-        uint64_t hard[GRID_SUB], any = 0;
-        const uint64_t live = __builtin_amdgcn_ballot_w64(k.live);
-#pragma unroll
-        for (int j = 0; j < GRID_SUB; ++j) {
-            const uint64_t listed = __builtin_amdgcn_ballot_w64(((word[j] ^ (word[j] >> 8)) & 255u) == 0) & live;
-            hard[j] = __builtin_amdgcn_ballot_w64(pq_grid_unsure<T>(m1[j], m2[j])) & live & ~listed;
-            any |= hard[j];
-            if (__builtin_amdgcn_inverse_ballot_w64(live & ~(hard[j] | listed)))
-                store(k, j, (int)(m1[j] & 255u));
-            if (__builtin_amdgcn_inverse_ballot_w64(listed)) {
-                const int at = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(listed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)listed, (uint32_t)n_waiting));
-                const uint32_t id = (uint32_t)(chunk - first) << 8 | (uint32_t)lane << 2 | (uint32_t)j;
-                if constexpr (KEEP)
-                    queue[at] = make_uint2(id, (uint32_t)__builtin_bit_cast(uint16_t, k.x[j][0]) | (uint32_t)__builtin_bit_cast(uint16_t, k.x[j][1]) << 16);
-                else
-                    queue[at] = id;
-            }
-            n_waiting += __builtin_popcountll(listed);
-            if ((j + 1) % GRID_LOOK<KEEP> == 0 && n_waiting >= 64) {
-                pq_grid_fence();
-                while (n_waiting >= 64)
-                    work_off(64);
-                pq_grid_fence();
-            }
-        }
-        if (any != 0) {  // wave-uniform
-#pragma unroll 1
             for (int j = 0; j < GRID_SUB; ++j) {
-                const uint64_t lanes = pq_grid_pick(j, hard[0], hard[1], hard[2], hard[3]);
-                if (lanes == 0)
-                    continue;
-                const T x[2] = {pq_grid_pick(j, k.x[0][0], k.x[1][0], k.x[2][0], k.x[3][0]),
-                                pq_grid_pick(j, k.x[0][1], k.x[1][1], k.x[2][1], k.x[3][1])};
-                int code;
-                if (__builtin_popcountll(lanes) <= 5)  // 80 instructions each
-                    code = pq_grid_exact(grid, lanes, j, x[0], x[1]);
-                else
-                    code = pq_filter_code<2, T, W>(grid[j].arow, sizeof(T) == 4 ? (const unsigned char *)grid[j].coord : grid[j].arow,
-                                                   grid[j].scale, (grid[j].bad & 2u) != 0, x, k.live);
-                if (__builtin_amdgcn_inverse_ballot_w64(lanes))
-                    store(k, j, code);
+                const uint32_t k0 = pq_grid_key<0>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one);
+                const uint32_t k1 = pq_grid_key<1>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one);
+                m1[j] = min(k0, k1);
+                m2[j] = max(k0, k1);
+                pq_grid_take(m1[j], m2[j], pq_grid_key<2>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one));
+                pq_grid_take(m1[j], m2[j], pq_grid_key<3>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one));
             }
+            const uint64_t live = __builtin_amdgcn_ballot_w64(k.live);
+#pragma unroll
+            for (int j = 0; j < GRID_SUB; ++j) {
+                const uint64_t listed = __builtin_amdgcn_ballot_w64(((word[j] ^ (word[j] >> 8)) & 255u) == 0) & live;
+                hard[j] = __builtin_amdgcn_ballot_w64(pq_grid_unsure<T>(m1[j], m2[j])) & live & ~listed;
+                if (__builtin_amdgcn_inverse_ballot_w64(live & ~(hard[j] | listed)))
+                    store(k, j, (int)(m1[j] & 255u));
+                if (__builtin_amdgcn_inverse_ballot_w64(listed)) {
+                    const int at = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(listed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)listed, (uint32_t)n_waiting));
+                    if constexpr (KEEP)
+                        queue[wave][at] = make_uint2(id | (uint32_t)j, word_of(k.x[j][0], k.x[j][1]));
+                    else
+                        queue[wave][at] = id | (uint32_t)j;
+                }
+                n_waiting += __builtin_popcountll(listed);
+            }
+            chunk += GRID_WAVES;
+            if ((hard[0] | hard[1] | hard[2] | hard[3]) == 0)  // wave-uniform
+                continue;
+#pragma unroll
+            for (int j = 0; j < GRID_SUB; ++j)
+                xy[j] = word_of(k.x[j][0], k.x[j][1]);
+        } else if (n_waiting > 0) {  // the last 64 of those that wait
+            const int n = n_waiting < 64 ? n_waiting : 64;
+            n_waiting -= n;
+            const bool live = lane < n;
+            pq_grid_fence();
+            const pq_grid_waiting<KEEP> entry = queue[wave][n_waiting + (live ? lane : 0)];
+            T x, y;
+            if constexpr (KEEP) {
+                id = entry.x;
+                of_word(entry.y, x, y);
+            } else {
+                id = entry;
+                again(id, x, y);
+            }
+            pq_grid_fence();
+            const int j = (int)(id & 3u);
+            id &= ~3u;
+            const pq_grid<T> &g = grid[j];
+            const uint32_t word = *(const uint32_t *)((const char *)g.cell + pq_grid_cell(x, y, g.sx, g.ox, g.sy, g.oy));
+            const uint32_t words = word & 255u, at = word >> 16;
+            uint32_t m1 = 0xffffffffu, m2 = 0xffffffffu;
+            for (uint32_t k = 0; __builtin_amdgcn_ballot_w64(k < words) != 0; ++k) {
+                if (k < words) {
+                    const uint32_t four = g.pool[at + k];
+                    pq_grid_take(m1, m2, pq_grid_key<0>(g.coord, four, x, y, minus_one));
+                    pq_grid_take(m1, m2, pq_grid_key<1>(g.coord, four, x, y, minus_one));
+                    pq_grid_take(m1, m2, pq_grid_key<2>(g.coord, four, x, y, minus_one));
+                    pq_grid_take(m1, m2, pq_grid_key<3>(g.coord, four, x, y, minus_one));
+                }
+            }
+            const uint64_t unsure = __builtin_amdgcn_ballot_w64(live && pq_grid_unsure<T>(m1, m2));
+            if (live && !__builtin_amdgcn_inverse_ballot_w64(unsure))
+                store_late(id | (uint32_t)j, x, y, (int)(m1 & 255u));
+            if (unsure == 0)  // wave-uniform
+                continue;
+#pragma unroll
+            for (int s = 0; s < GRID_SUB; ++s) {
+                hard[s] = unsure & __builtin_amdgcn_ballot_w64(j == s);
+                xy[s] = word_of(x, y);
+            }
+        } else {
+            break;
+        }
+#pragma unroll 1
+        for (int j = 0; j < GRID_SUB; ++j) {
+            const uint64_t lanes = (useless >> j) & 1u ? 0 : pq_grid_pick(j, hard[0], hard[1], hard[2], hard[3]);
+            if (lanes == 0)
+                continue;
+            const int n = (int)((n_unsure >> (8 * j)) & 255u), total = n + __builtin_popcountll(lanes);
+            // The new ones move to the lanes from n on, cyclically, and the other lanes' values to the rest.
+            const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u));
+            const int to = 4 * (63 & (__builtin_amdgcn_inverse_ballot_w64(lanes) ? n + below : total + lane - below));
+            const uint32_t old_id = pq_grid_pick(j, unsure_id[0], unsure_id[1], unsure_id[2], unsure_id[3]);
+            const uint32_t new_id = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)id);
+            uint32_t old_xy = 0, new_xy = 0;
+            if constexpr (WITH) {
+                old_xy = pq_grid_pick(j, unsure_xy[0], unsure_xy[1], unsure_xy[2], unsure_xy[3]);
+                new_xy = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)pq_grid_pick(j, xy[0], xy[1], xy[2], xy[3]));
+            }
+            // together; 64 are decided, and the rest of the new ones then stands in lanes 0 .. total - 65
+            const uint32_t now_id = lane < n ? old_id : new_id, now_xy = lane < n ? old_xy : new_xy;
+            const bool full = total >= 64;
+            const uint32_t kept_id = full ? new_id : now_id, kept_xy = full ? new_xy : now_xy;
+            n_unsure = (n_unsure & ~(255u << (8 * j))) | (uint32_t)(full ? total - 64 : total) << (8 * j);
+#pragma unroll
+            for (int s = 0; s < GRID_SUB; ++s) {
+                unsure_id[s] = j == s ? kept_id : unsure_id[s];
+                if constexpr (WITH)
+                    unsure_xy[s] = j == s ? kept_xy : unsure_xy[s];
+            }
+            if (full)
+                decide(j, now_id | (uint32_t)j, now_xy, true);
         }
     }
-    pq_grid_fence();
-    if (n_waiting != 0)
-        work_off(n_waiting);
+
+    // What is left of the unsure tokens, the 16 wavefronts' together, in the place of the lists: every wavefront has 64 entries
+    // of each subspace's pool, which nothing reads any more.
+    static_assert(GRID_POOL * 4 >= GRID_WAVES * 64 * 8, "the place of the lists");
+    typedef typename std::conditional<WITH, uint2, uint32_t>::type left_over;
+    uint32_t *const counts = (uint32_t *)&queue[0];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < GRID_SUB; ++j) {
+        left_over &entry = ((left_over *)grid[j].pool)[64 * wave + lane];
+        if constexpr (WITH)
+            entry = make_uint2(unsure_id[j], unsure_xy[j]);
+        else
+            entry = unsure_id[j];
+    }
+    if (lane == 0)
+        counts[wave] = n_unsure;
+    __syncthreads();
+    // lane 16 j + w: how many of subspace j wavefronts 0 .. w have
+    int end = (int)(counts[lane & (GRID_WAVES - 1)] >> (8 * (lane >> 4)) & 255u);
+    static_assert(GRID_WAVES == 16 && GRID_SUB == 4, "a row of 16 lanes per subspace");
+    end += __builtin_amdgcn_update_dpp(0, end, 0x111, 0xf, 0xf, true);  // (row_shr: 0 from outside of the row)
+    end += __builtin_amdgcn_update_dpp(0, end, 0x112, 0xf, 0xf, true);
+    end += __builtin_amdgcn_update_dpp(0, end, 0x114, 0xf, 0xf, true);
+    end += __builtin_amdgcn_update_dpp(0, end, 0x118, 0xf, 0xf, true);
+    int batch = wave;  // of 64, over the subspaces in turn
+#pragma unroll 1
+    for (int j = 0; j < GRID_SUB; ++j) {
+        const int total = __builtin_amdgcn_readlane(end, 16 * j + GRID_WAVES - 1);
+        for (; 64 * batch < total; batch += GRID_WAVES) {
+            const int t = 64 * batch + lane;
+            const bool live = t < total;
+            const int k = live ? t : 64 * batch;
+            int of = 0, start = 0;
+#pragma unroll
+            for (int w = 0; w < GRID_WAVES - 1; ++w) {
+                const int e = __builtin_amdgcn_readlane(end, 16 * j + w);
+                of += k >= e ? 1 : 0;
+                start = k >= e ? e : start;
+            }
+            const left_over entry = ((const left_over *)grid[j].pool)[64 * of + k - start];
+            if constexpr (WITH)
+                decide(j, entry.x | (uint32_t)j, entry.y, live);
+            else
+                decide(j, entry | (uint32_t)j, 0u, live);
+        }
+        batch -= (total + 63) >> 6;
+    }
 }
 
 // In how many slices the tokens of a head (groups: workgroups per slice; chunks: 64-token chunks that all slices together
