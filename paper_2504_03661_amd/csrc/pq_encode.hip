@@ -420,21 +420,33 @@ hipError_t pq_launch_bump_len(int32_t *ctx_len, int B, int n_new, int max_contex
     return hipGetLastError();
 }
 
+// How many of a head's chunks a wavefront takes in a row; rows: subspaces of all heads, keys and values.  Up to 32, so that
+// there are 8192 wavefronts or more, and all about the same number (63 chunks of 32 heads as 31 + 31 + 1: 222 us, as 3 x 21: 198).
+// Up to 16384 chunks in all go to about 4096 wavefronts, since setting up a codebook costs about a chunk (2 x 96 tokens x 32
+// heads, fp32, M = 64: 23.7 -> 21.3 us; 8 x 16 tokens, fp16: 16.0 -> 14.8), if these get nearly equal shares: workgroups go to the
+// XCDs in turn, and where the last of 2 or 4 per head is short, it is short on the same XCDs every time (192 tokens x 32 heads, M =
+// 32, fp32: 18.6 us as 2 + 1 chunks, 16.6 as three; 448 tokens as 4 + 3 26.6, as seven 30.1).  Far fewer than 4096 are too few
+// (576 tokens x 8 heads, M = 32, fp16: 13.9 us as 4 x 2 + 1, 13.1 as nine).
+inline int64_t pq_encode_rounds(int64_t n_chunks, int64_t rows)
+{
+    const int64_t waves = rows * n_chunks;
+    int64_t rounds = waves <= 16384 ? (waves + 4095) / 4096 : waves / 8192 > 32 ? 32 : waves / 8192;
+    int64_t jobs = (n_chunks + rounds - 1) / rounds;
+    while (waves <= 16384 && rounds > 1 && ((jobs * rounds - n_chunks) * 7 > n_chunks || rows * jobs < 3072)) {
+        --rounds;
+        jobs = (n_chunks + rounds - 1) / rounds;
+    }
+    return (n_chunks + jobs - 1) / jobs;
+}
+
 template <int M, int DS, typename T>
 void launch_fast(const pq_encode_args &a, hipStream_t s)
 {
-    // Whole 64-token chunks of each sequence unless that leaves more than an eighth of the lanes without a token.  A
-    // wavefront takes up to 32 chunks in a row, so that there are 8192 wavefronts or more, and all about the same number (63
-    // chunks of 32 heads as 31 + 31 + 1: 222 us, as 3 x 21: 198).  Up to 16384 chunks in all go to 4096 wavefronts, which
-    // are resident at once: setting up a codebook costs about a chunk (2 x 96 tokens x 32 heads, fp32: 23.7 -> 21.3 us; 8 x 16
-    // tokens x 32 heads, fp16: 16.0 -> 14.8; at 32768 chunks 8192 wavefronts are as good or better).
+    // whole 64-token chunks of each sequence unless that leaves more than an eighth of the lanes without a token
     const int64_t seq_chunks = ((int64_t)a.n_new + 63) / 64;
     const bool per_seq = seq_chunks * 512 <= (int64_t)a.n_new * 9 || a.B == 1;
     const int64_t n_chunks = per_seq ? a.B * seq_chunks : ((int64_t)a.B * a.n_new + 63) / 64;
-    const int64_t waves = a.Hkv * n_chunks * M * 2;
-    int64_t rounds = waves <= 16384 ? (waves + 4095) / 4096 : waves / 8192 > 32 ? 32 : waves / 8192;
-    const int64_t jobs = (n_chunks + rounds - 1) / rounds;
-    rounds = (n_chunks + jobs - 1) / jobs;
+    const int64_t rounds = pq_encode_rounds(n_chunks, (int64_t)a.Hkv * M * 2);
     dim3 grid((unsigned)(a.Hkv * ((n_chunks + rounds - 1) / rounds)), M / FAST_WAVES, 2);
     if (per_seq)
         hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, true>), grid, dim3(64 * FAST_WAVES), 0, s, a, (int)rounds);
