@@ -59,7 +59,12 @@ constexpr int GRID_QUEUE = 64 * (1 + GRID_SUB);
 constexpr int GRID_SHIFT = 20;    // 8 cells per octave
 constexpr float GRID_BIAS = 2.0f;
 constexpr uint32_t GRID_FIRST = 0x40000000u, GRID_LAST = 0x41ffffffu;  // float bits of 2 .. just below 32
-constexpr float GRID_COVER = 28.0f;  // where the outermost cell starts, less the bias
+constexpr float GRID_COVER = 28.0f;  // where the outermost cell starts, less the bias, ..
+constexpr float GRID_DEVIATIONS = 5.0f;  // .. for coordinates this many mean deviations from the mean (normal ones: 3.75 sigma)
+constexpr float GRID_LOWERED = 3.814697265625e-06f;   // 2^-18: shares of |c|^2 / 2 that F is lowered by, ..
+constexpr float GRID_MARGIN = 1.52587890625e-05f;     // 2^-16: .. that the threshold is raised by,
+constexpr float GRID_WIDER = 7.62939453125e-06f;      // 2^-17: and what boxes have more on each side than their cells
+constexpr int GRID_LONGEST = 64;  // candidates of a block (a bit each in a 64-bit mask)
 constexpr uint32_t GRID_NONE = 0x01000100u;  // a cell without a list: two codes, twice, so that the least has an equal
 constexpr uint32_t GRID_SURE = 512;  // keys at least this far apart are in the right order
 
@@ -216,8 +221,7 @@ __device__ inline void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, uint3
         ex = 3.0f * dx;
         ey = 3.0f * dy;
     }
-    // 5 of these mean deviations are 3.75 standard deviations of normal coordinates
-    const float sx = GRID_COVER / (5.0f * dx), sy = GRID_COVER / (5.0f * dy);
+    const float sx = GRID_COVER / (GRID_DEVIATIONS * dx), sy = GRID_COVER / (GRID_DEVIATIONS * dy);
     const float ox = -mx * sx, oy = -my * sy;
     // squared distances in units of 1 / s_x^2
     const float ratio = sx / sy, wy = ratio * ratio;
@@ -230,7 +234,7 @@ __device__ inline void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, uint3
     const float ay = wy * uy, n = 0.5f * (ux * ux + uy * ay);
     table[c][0] = ux;
     table[c][1] = ay;
-    table[c][2] = n * (1.0f - 3.814697265625e-06f);  // 2^-18
+    table[c][2] = n * (1.0f - GRID_LOWERED);
     table[c][3] = n;
     g.coord[c][0] = mine[0];
     g.coord[c][1] = mine[1];
@@ -267,7 +271,7 @@ __device__ __forceinline__ void pq_grid_box(const int e, const int n, float &g, 
     const int k = e < 32 ? e : e - 64;
     const float lo = pq_grid_edge(k), hi = pq_grid_edge(k + n);
     g = 0.5f * (lo + hi);
-    h = 0.5f * (hi - lo) + 7.62939453125e-06f;  // 2^-17
+    h = 0.5f * (hi - lo) + GRID_WIDER;
 }
 
 // Appending the bit t <= limit to a mask is a comparison and an addition with carry.  What a vector instruction writes to VCC
@@ -343,7 +347,6 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
     unsigned char *bytes = (unsigned char *)g.cell;
     const float sx = g.sx, ox = g.ox, sy = g.sy, oy = g.oy;
     const float ratio = sx / sy, wy = ratio * ratio;
-    constexpr float MARGIN = 1.52587890625e-05f;  // 2^-16
 
     // ---- lane = block of 4 x 4 cells, all centroids
     int count = 0;
@@ -362,7 +365,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
         const float4 ref = *(const float4 *)table[r];
         const float far_x = fabsf(gx) + hx, far_y = fabsf(gy) + hy;
         const float limit = __builtin_fmaf(-gy, ref.y, __builtin_fmaf(-gx, ref.x, ref.z)) +
-                            MARGIN * (ref.w + far_x * far_x + wy * far_y * far_y);
+                            GRID_MARGIN * (ref.w + far_x * far_x + wy * far_y * far_y);
         uint32_t used = 0;  // which of codes 0 .. 31 are in the list
 #pragma unroll 1
         for (int w = 0; w < 256; w += 32) {
@@ -381,7 +384,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             }
             used = w == 0 ? __builtin_bitreverse32(mask) : used;
             const int total = count + __builtin_popcount(mask);
-            mask = total <= 64 ? mask : 0;
+            mask = total <= GRID_LONGEST ? mask : 0;
             while (__builtin_amdgcn_ballot_w64(mask != 0) != 0) {
                 if (mask != 0) {
                     const int k = __builtin_clz(mask);
@@ -390,14 +393,14 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
                     mask ^= 0x80000000u >> k;
                 }
             }
-            count = total;  // (from 65 on nothing is written any more)
+            count = total;  // (beyond GRID_LONGEST nothing is written any more)
         }
         // Lists are filled up to whole words with a code that is not in them: it is never the least, and being there more
         // than once it hides no second least.
         fill = (uint32_t)__builtin_ctz(~used | 0x80000000u);
-        for (int k = count; (k & 3) != 0 && k < 64; ++k)
+        for (int k = count; (k & 3) != 0 && k < GRID_LONGEST; ++k)
             bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))] = (unsigned char)fill;
-        count = used == 0xffffffffu ? 65 : count;  // (none to fill up with: no list)
+        count = used == 0xffffffffu ? GRID_LONGEST + 1 : count;  // (none to fill up with: no list)
     }
     pq_grid_fence();
 
@@ -485,7 +488,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             });
             const float4 ref = *(const float4 *)table[bytes[list + (uint32_t)(((least >> 4) & 1) * 256 + (least & 15))]];
             const float nearest = __int_as_float(least & ~31);
-            const float limit = nearest + MARGIN * (2.f * fabsf(nearest) + ref.w + far);
+            const float limit = nearest + GRID_MARGIN * (2.f * fabsf(nearest) + ref.w + far);
             uint32_t mask = 0, marked = fill_cell;
             pq_grid_twos<0, 32>(most, [&](auto K0, auto K1) {
                 const auto test = [&](auto K, uint32_t &code) {
@@ -506,8 +509,8 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
                 write_list(mask, listed);
         }
         // longer lists (many where one axis is several times the other), the same 16 candidates at a time
-        if (longest > 32 && __builtin_amdgcn_ballot_w64(n > 32 && n <= 64) != 0) {
-            const int most = longest < 64 ? longest : 64;
+        if (longest > 32 && __builtin_amdgcn_ballot_w64(n > 32 && n <= GRID_LONGEST) != 0) {
+            const int most = longest < GRID_LONGEST ? longest : GRID_LONGEST;
             auto sixteen = [&](const int q) {
                 float4 e = *(const float4 *)table[bytes[list + (uint32_t)(q * 256 + in_row)]];
                 e.z = 16 * q + in_row < n ? e.z : 1.0e30f;
@@ -529,7 +532,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             }
             const float4 ref = *(const float4 *)table[bytes[list + (uint32_t)(((least >> 4) & 3) * 256 + (least & 15))]];
             const float nearest = __int_as_float(least & ~63);
-            const float limit = nearest + MARGIN * (2.f * fabsf(nearest) + ref.w + far);
+            const float limit = nearest + GRID_MARGIN * (2.f * fabsf(nearest) + ref.w + far);
             uint64_t mask = 0;  // candidate k in bit 63 - k
 #pragma unroll 1
             for (int q = 0; 16 * q < most; ++q) {
@@ -548,7 +551,7 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
                 const int n_marked = most - 16 * q < 16 ? (most - 16 * q + 1) & ~1 : 16;
                 mask |= (uint64_t)(some << (16 - n_marked)) << (48 - 16 * q);
             }
-            const bool own = n > 32 && n <= 64 && inside;
+            const bool own = n > 32 && n <= GRID_LONGEST && inside;
             if (own && __builtin_popcountll(mask) <= 4) {
                 word = fill_cell;
                 for (uint64_t left = mask; left != 0;) {
@@ -561,12 +564,12 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
             if (__builtin_amdgcn_ballot_w64(listed) != 0)
                 write_list(mask, listed);
         }
-        g.cell[cell_x * GRID_SIDE + cell_y] = inside && n <= 64 ? word : GRID_NONE;
+        g.cell[cell_x * GRID_SIDE + cell_y] = inside && n <= GRID_LONGEST ? word : GRID_NONE;
     }
 }
 
 // How many of the wavefront's 64 centroids the grid will not serve, known before the lists are, which take most of the
-// building: those outside the map, in a block with more than 64 of them, all of which would be in its list (tight clusters), and
+// building: those outside the map, in a block with more than GRID_LONGEST of them, all of which would be in its list (tight clusters), and
 // those that repeat an earlier one (a token there has two nearest ones; a repetition behind a clash of hashes is not seen).
 template <typename T>
 __device__ inline int pq_grid_lost(const pq_grid<T> &g, const uint32_t (&in_block)[128], const uint32_t (&first_of)[256], const int part,
@@ -578,7 +581,7 @@ __device__ inline int pq_grid_lost(const pq_grid<T> &g, const uint32_t (&in_bloc
     const uint32_t n = in_block[block >> 1] >> (16 * (block & 1u)) & 0xffffu;
     const int other = (int)first_of[hash];
     const bool again = other != c && g.coord[other][0] == g.coord[c][0] && g.coord[other][1] == g.coord[c][1];
-    return __builtin_popcountll(__builtin_amdgcn_ballot_w64(outside || n > 64 || again));
+    return __builtin_popcountll(__builtin_amdgcn_ballot_w64(outside || n > GRID_LONGEST || again));
 }
 
 // Builds the grids of a workgroup's 4 subspaces.  src: the codebook of the first of them, [4][256][2]

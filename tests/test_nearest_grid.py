@@ -66,21 +66,47 @@ def codebook_and_points(kind, n, seed, dtype=np.float16):
     return c, rng.permutation(x).astype(dtype)
 
 
+HEADER = open(os.path.join(lib_build.CSRC, "pq_nearest_grid.h")).read()
+
+
+def _constant(name):
+    """A number the kernels are compiled with, from their header."""
+    m = re.search(r"\bconstexpr (?:float|int) " + name + r" = ([0-9.e+-]+)f?;", HEADER)
+    assert m, name
+    return F(m.group(1))
+
+
+COVER, DEVIATIONS, LOWERED, MARGIN, WIDER = (_constant("GRID_" + n) for n in ("COVER", "DEVIATIONS", "LOWERED", "MARGIN", "WIDER"))
+LONGEST = int(_constant("GRID_LONGEST"))
+
+
+def _fma(a, b, c):
+    return (np.asarray(a, np.float64) * b + c).astype(F)
+
+
 def _edge(k):
     e = (np.uint32(0x40000000) + (np.abs(k).astype(np.uint32) << np.uint32(20))).astype(np.uint32).view(F) - F(2)
     return np.where(k < 0, -e, e)
 
 
 def _cells(x, s, o):
-    u = (x.astype(np.float64) * s + o).astype(F)                # one rounding, as the fused multiply-add
+    u = _fma(x, s, o)
     b = np.minimum((np.abs(u) + F(2)).astype(F).view(np.uint32), np.uint32(0x41ffffff))
     e = ((b >> np.uint32(20)) & np.uint32(63)).astype(np.int64)
     return np.where(np.signbit(u), 63 - e, e)
 
 
+def _box(e, n):
+    """Centre and half side of cell coordinates e .. e + n - 1."""
+    k = np.where(e < 32, e, e - 64)
+    lo, hi = _edge(k), _edge(k + n)
+    return F(0.5) * (lo + hi), F(0.5) * (hi - lo) + WIDER
+
+
 def _lists(c):
-    """(s, o, [64, 64, 256] bool) in fp32, as pq_grid_tables and pq_grid_lists; None: no grid for this codebook."""
-    c = c.astype(F)
+    """The steps of pq_grid_tables and pq_grid_lists in fp32 -> (s, o, candidates [64, 64, 256] bool, which cells have a
+    list, fill code of every cell); None: no grid for this codebook."""
+    dtype, exact, c = c.dtype, c.astype(np.float64), c.astype(F)
     mean, end = np.zeros(2, F), np.full(2, 3e38, F)
     for _ in range(2):
         near = np.abs(c - mean) <= end
@@ -90,31 +116,51 @@ def _lists(c):
         mean, end = new, F(3) * dev
     if not (dev > 1e-30).all():
         return None
-    s = F(28) / (F(5) * dev)
+    s = COVER / (DEVIATIONS * dev)
     o = -mean * s
     w = F(s[0] / s[1]) ** 2
-    u = (c.astype(np.float64) * s + o).astype(F)
+    u = _fma(c, s, o)
     if not (np.abs(u) < 1e6).all() or not 1e-9 < w < 1e9:
         return None
-    a = np.stack([u[:, 0], w * u[:, 1]], 1)
-    norm = F(0.5) * (u * a).sum(1, dtype=F)
-    low = norm * F(1 - 2.0 ** -18)
-
-    def candidates(size):                                       # of boxes of size x size cells
-        e = np.arange(0, 64, size)
-        k = np.where(e < 32, e, e - 64)
-        lo, hi = _edge(k), _edge(k + size)
-        g, h = (F(0.5) * (lo + hi)).astype(F), (F(0.5) * (hi - lo) + F(2.0 ** -17)).astype(F)
-        gx, gy, hx, hy = g[:, None, None], g[None, :, None], h[:, None, None], h[None, :, None]
-        v = low - gx * a[:, 0] - gy * a[:, 1]
-        r = v.argmin(2)
-        far = (np.abs(gx) + hx) ** 2 + w * (np.abs(gy) + hy) ** 2
-        limit = v.min(2)[..., None] + F(2.0 ** -16) * (norm[r][..., None] + far)
-        t = v - np.abs(a[:, 0] - a[r, 0][..., None]) * hx - np.abs(a[:, 1] - a[r, 1][..., None]) * hy
-        return t <= limit
-
-    block = candidates(4)
-    return s, o, candidates(1) & block.repeat(4, 0).repeat(4, 1)
+    ax, ay = u[:, 0], w * u[:, 1]
+    norm = F(0.5) * (u[:, 0] * ax + u[:, 1] * ay)
+    low = norm * (F(1) - LOWERED)
+    lists, listed, fills = np.zeros((64, 64, 256), bool), np.zeros((64, 64), bool), np.zeros((64, 64), np.int64)
+    lowest, largest = (-60000, 60000) if dtype == np.float16 else (-3e37, 3e37)
+    for bx in range(16):
+        for by in range(16):
+            # the block's list: all centroids against the one nearest to its centre
+            (gx, hx), (gy, hy) = _box(np.int64(4 * bx), 4), _box(np.int64(4 * by), 4)
+            p = np.clip([(gx - o[0]) / s[0], (gy - o[1]) / s[1]], lowest, largest).astype(dtype).astype(np.float64)
+            r = int(((exact - p) ** 2).sum(1).argmin())
+            value = lambda k: _fma(-gy, ay[k], _fma(-gx, ax[k], low[k]))
+            far_x, far_y = np.abs(gx) + hx, np.abs(gy) + hy
+            limit = value(r) + MARGIN * (norm[r] + far_x * far_x + w * far_y * far_y)
+            t = _fma(-np.abs(ay - ay[r]), hy, _fma(-np.abs(ax - ax[r]), hx, value(slice(None))))
+            k = np.nonzero(t <= limit)[0]
+            free = np.setdiff1d(np.arange(32), k)
+            if len(k) > LONGEST or len(free) == 0:
+                continue
+            # its cells' lists: the block's candidates against the one nearest to the cell's centre, found in numbers whose
+            # low bits hold the place in the list
+            e = np.arange(4)
+            (gx, hx), (gy, hy) = _box(4 * bx + e, 1), _box(4 * by + e, 1)
+            gx, hx, gy, hy = (np.repeat(gx, 4), np.repeat(hx, 4), np.tile(gy, 4), np.tile(hy, 4))
+            half = F(0.5) * (gx * gx + w * gy * gy)
+            v = _fma(ay[k], -gy[:, None], _fma(ax[k], -gx[:, None], low[k] + half[:, None]))
+            cut = v.view(np.int32) & ~(31 if len(k) <= 32 else 63)
+            first = cut.argmin(1)
+            ref, nearest = k[first], cut[np.arange(16), first].view(F)
+            far = (np.abs(gx) + hx) ** 2 + w * (np.abs(gy) + hy) ** 2
+            limit = nearest + MARGIN * (F(2) * np.abs(nearest) + norm[ref] + far)
+            t = _fma(-np.abs(ax[k] - ax[ref][:, None]), hx[:, None], v)
+            t = _fma(-np.abs(ay[k] - ay[ref][:, None]), hy[:, None], t)
+            rows, cols = 4 * bx + np.repeat(e, 4), 4 * by + np.tile(e, 4)
+            mask = np.zeros((16, 256), bool)
+            mask[:, k] = t <= limit[:, None]
+            lists[rows, cols], listed[rows, cols], fills[rows, cols] = mask, True, free[0]
+    listed[31:33] = listed[:, 31:33] = False
+    return s, o, lists, listed, fills
 
 
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
@@ -126,17 +172,15 @@ def test_lists_hold_the_nearest_centroid_of_every_point(kind, dtype):
         if grid is None:
             assert kind in ("line", "equal")
             continue
-        s, o, lists = grid
+        s, o, lists, listed, fills = grid
         ix, iy = _cells(x[:, 0], s[0], o[0]), _cells(x[:, 1], s[1], o[1])
-        inside = ~(np.isin(ix, (31, 32)) | np.isin(iy, (31, 32)))
+        inside = listed[ix, iy]
         d = ((x.astype(np.float64)[:, None] - c.astype(np.float64)[None]) ** 2).sum(-1)
         nearest = d == d.min(1)[:, None]                         # with all ties
         assert not (nearest & ~lists[ix, iy])[inside].any()
+        assert not nearest[np.arange(len(x)), fills[ix, iy]][inside].any()
         if kind == "normal":
             assert inside.mean() > 0.98 and (lists[ix, iy].sum(1) > 4)[inside].mean() < 0.15
-
-
-HEADER = open(os.path.join(lib_build.CSRC, "pq_nearest_grid.h")).read()
 
 
 @functools.cache
