@@ -6,9 +6,9 @@
 // dimensions the plane can be cut up once per codebook instead, and a token then looks at the 2 or 3 centroids of its cell:
 // 86 instructions with codebooks of random vectors, whose cells have long lists more often than trained ones'.  Building a
 // grid takes 34 000, as many as 100 chunks of 64 tokens through the filter, so the grid serves appends and trainings of
-// thousands of tokens per head (pq_grid_slices below).  Encode (K and V), 32 heads x 32K tokens: 1549 -> 660 us, of which
-// 295 us are the grids (vector issue 76 % busy, the rest latencies between barriers) and 365 us the tokens (87 %).  k-means,
-// 32 heads x 64K samples, 2 iterations: 3148 -> 1000 us.
+// thousands of tokens per head (pq_grid_slices below).  Encode (K and V), 32 heads x 32K tokens: 1549 -> 631 us, of which
+// some 265 us are the grids (latencies between barriers beside vector issue) and 365 us the tokens.  k-means, 32 heads x 64K
+// samples, 2 iterations: 3148 -> 990 us.
 //
 // Map.  Per axis u = s x + o, fp32, chosen from the codebook (mean and mean deviation of its coordinates without outliers):
 // |u| <= 28 holds what lies within some 4 standard deviations.  The cell coordinate is five bits of the float |u| + 2 — 8
@@ -32,10 +32,10 @@
 // through the filter together, and where the codebook gives no useful grid all its tokens go there at once.  Tokens of cells
 // with longer lists (7 % with a codebook of random vectors, 1 % with a trained one) wait in LDS until 64 are there and are then
 // worked on as one.
-// What the data make of it, 32 heads, us, beside the filter alone: encode of 9000 tokens, normal 363 / 440, Laplace's
-// distribution 416 / 442, 2 % of the coordinates times 20 418 / 439; of 32K 633 / 1578, 804 / 1588, 818 / 1598.  A codebook
-// without a useful grid costs the filter's four instead of five wavefronts per SIMD: one dead axis in every subspace 885 / 755
-// and 3060 / 2600, centroids of 16 values in all 2867 / 2489 and 10098 / 8570.
+// What the data make of it, 32 heads, us, beside the filter alone: encode of 9000 tokens, normal 364 / 440, Laplace's
+// distribution 411 / 441, 2 % of the coordinates times 20 414 / 446; of 32K 631 / 1590, 803 / 1596, 816 / 1610.  A codebook
+// without a useful grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every subspace 882 / 757
+// and 3047 / 2611, centroids of 16 values in all 2873 / 2496 and 10149 / 8583.
 #pragma once
 
 #include "pq_device_utils.h"
@@ -682,7 +682,7 @@ __device__ __forceinline__ void pq_grid_filter_scan(const pq_grid<T> (&grid)[GRI
 //   unsure   per subspace, in a register that holds their ids lane by lane (fp16: another their sub-vectors); the filter takes
 //            64 for 355 instructions.  (All lanes on one token's fp64 distances take 80, and 3 to 4 % of the tokens lie outside
 //            where the coordinates have heavy tails: encode of 32 heads x 9000 tokens, Laplace's distribution, 682 us one at a
-//            time, 416 so.)  What the 16 wavefronts have left over in the end is decided together: 457 us by each for itself.
+//            time, 411 so.)  What the 16 wavefronts have left over in the end is decided together: 457 us by each for itself.
 template <typename T, bool KEEP, typename TOKEN, typename FETCH, typename STORE, typename AGAIN, typename STORE_LATE>
 __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_grid_waiting<KEEP> (&queue)[GRID_WAVES][GRID_QUEUE], const int first,
                                              const int last, FETCH fetch, STORE store, AGAIN again, STORE_LATE store_late)
@@ -905,10 +905,12 @@ __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_gr
 }
 
 // In how many slices the tokens of a head (groups: workgroups per slice; chunks: 64-token chunks that all slices together
-// walk) go through grid workgroups; 0: the filter, which walks filter_chunks, does better.  Modelled from 32K and 8K tokens x
-// 32 heads (MI355X): a workgroup, which fills a compute unit, takes 74 us to build and 0.18 us per chunk; through the
-// filter a chunk of 4 subspaces takes 0.72 us of a compute unit.  (8K tokens x 32 heads 386 us either way; 32K tokens x 8
-// heads 383 us through the filter, 187 with grids; 5000 tokens of 4 sequences x 8 heads 262 and 149.)
+// walk) go through grid workgroups; 0: the filter, which walks filter_chunks, does better.  Modelled: a workgroup, which fills
+// a compute unit, takes 74 us to build and 0.18 us per chunk; through the filter a chunk of 4 subspaces takes 0.72 us of a
+// compute unit.  Measured on normal data, 256 compute units: fp16 encode 66 and 0.18, filter 0.78; fp32 encode 65 and 0.27,
+// 0.94; k-means 76 and 0.15, 0.85.  So the model is on the filter's side for all three, and data that the grids serve less well
+// still gain at the line (32 heads x 9000 tokens or samples, us, grids / filter, the three in turn: normal 364 / 440, 410 /
+// 530, 198 / 267; Laplace's distribution 411 / 441, 437 / 526, 219 / 266; channel scales 0.5 .. 4 444 / 458 and 248 / 275).
 inline int pq_grid_slices(const int64_t chunks, const int64_t filter_chunks, const int64_t groups, const int n_cu)
 {
     int64_t best = filter_chunks * groups * 72 / n_cu;  // 10 ns
