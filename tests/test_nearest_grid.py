@@ -183,6 +183,25 @@ def test_lists_hold_the_nearest_centroid_of_every_point(kind, dtype):
             assert inside.mean() > 0.98 and (lists[ix, iy].sum(1) > 4)[inside].mean() < 0.15
 
 
+def test_the_kinds_reach_every_form_of_list():
+    """Blocks of up to 32, of 33 to 64 and of more candidates; cells of up to 4, of more, and of more than 32; a pool that is too
+    small: what the kernel treats in different ways, in the codebooks that the GPU tests use as well."""
+    seen = set()
+    for kind in KINDS:
+        grid = _lists(codebook_and_points(kind, 8000, 0)[0])
+        if grid is None:
+            seen.add("no grid")
+            continue
+        _, _, lists, listed, _ = grid
+        n = lists.sum(2)[listed]
+        seen |= {"cells " + size for size, any_ in (("<= 4", (n <= 4).any()), ("> 4", ((n > 4) & (n <= 32)).any()), ("> 32", (n > 32).any())) if any_}
+        if listed.sum() < 62 * 62:
+            seen.add("blocks > 64")
+        if ((n + 3) // 4)[n > 4].sum() > _constant("GRID_POOL"):
+            seen.add("pool too small")
+    assert seen == {"no grid", "cells <= 4", "cells > 4", "cells > 32", "blocks > 64", "pool too small"}
+
+
 @functools.cache
 def _rule():
     """The launchers' rule (slices of the tokens for the grid kernels, 0: the filter), compiled from its source."""
