@@ -11,7 +11,7 @@
 //
 // Appends of more than a few tokens reach the codes through pq_encode_fast_kernel, where the matrix cores find the
 // few centroids that can be the nearest and the expression above decides among them; a handful of tokens per head
-// through pq_encode_few_kernel, which evaluates the expression for all 256; thousands per head at M = 64 through
+// through pq_encode_few_kernel, where the fp32 distances to all 256 do; thousands per head at M = 64 through
 // pq_encode_grid_kernel, which looks the candidates up.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -24,16 +24,6 @@
 #include "pq_nearest_grid.h"
 
 namespace {
-
-template <typename T> __device__ inline double widen(const void *p, int64_t i);
-template <> __device__ inline double widen<__half>(const void *p, int64_t i)
-{
-    return (double)__half2float(((const __half *)p)[i]);  // fp16 -> fp32 -> fp64, both exact
-}
-template <> __device__ inline double widen<float>(const void *p, int64_t i)
-{
-    return (double)((const float *)p)[i];
-}
 
 // ---------------------------------------------------------------------------------
 // The codes of many tokens, found with the matrix cores as a filter (pq_nearest_filter.h); fp16 inputs first.
@@ -330,66 +320,109 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
 }
 
 // ---------------------------------------------------------------------------------
-// A handful of tokens per KV head (one decoding step of a small batch): lane = CENTROID.  With one token per
-// lane a wavefront would walk 256 centroids for a few live lanes; here every lane holds 4 centroids in
-// registers, evaluates the defining fp64 distances of the token at hand to its 4 (ascending, strict "<") and
-// the wavefront takes the lexicographic minimum of (distance, index) — the lowest index among equal distances,
-// as in the scan.  One wavefront per (K or V, KV head, subspace) loops over the head's tokens of all sequences.
-constexpr int FEW_TOKENS = 6;
+// A handful of tokens per KV head (one decoding step of a small batch): lane = four CENTROIDS.  With one token per
+// lane a wavefront would walk 256 centroids for a few live lanes; here every lane holds 4 neighbouring centroids in
+// registers and the wavefront takes one token after the other, its sub-vector in scalar registers.
+// The fp32 distances name the candidates: their relative error is at most 6 x 2^-24 (ds = 4: a difference twice, a product,
+// three sums), so the nearest centroid's is within 12 x 2^-24 of the least, and all within 16 steps of the least
+// distance's bits — at least 2^-20 of it — are kept.  One candidate, nearly always: it is the code, and naming it is scalar
+// work.  Several (ties, near-ties), none, or fp32 squares below 2^-100, which are not that good: the defining fp64 distances
+// of all 256, ascending, and the lexicographic minimum of (distance, index), the lowest index among equal distances.
+// 30 vector instructions per token and subspace at ds = 2 where the fp64 distances and their minimum over the wavefront
+// took 80.
+constexpr int FEW_WAVES = 4;  // neighbouring subspaces of a workgroup: they share the lines of the tokens
 
+__device__ __forceinline__ uint32_t few_wave_min(uint32_t x)
+{
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true));   // quad_perm [2,3,0,1]
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, true));  // row_half_mirror
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xf, 0xf, true));  // row_mirror
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 0), r1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 16);
+    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 32), r3 = (uint32_t)__builtin_amdgcn_readlane((int)x, 48);
+    return min(min(r0, r1), min(r2, r3));
+}
+
+// per_wave: tokens of a wavefront, at most 64; by_n_new: pq_divisor(n_new)
 template <int M, int DS, typename T>
-__global__ __launch_bounds__(64) void pq_encode_few_kernel(const pq_encode_args a)
+__global__ __launch_bounds__(FEW_WAVES * 64) void pq_encode_few_kernel(const pq_encode_args a, const int per_wave, const uint32_t by_n_new)
 {
 #pragma clang fp contract(off)
-    const int lane = threadIdx.x;
-    const int which = blockIdx.z;
-    const int i = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int which = blockIdx.z & 1;
+    const int i = blockIdx.y * FEW_WAVES + wave;
     const int hkv = blockIdx.x;
-    const int n_tok = a.B * a.n_new;  // <= FEW_TOKENS
+    const int first = (int)(blockIdx.z >> 1) * per_wave, left = a.B * a.n_new - first;
+    const int n_tok = left < per_wave ? left : per_wave;
 
-    const int64_t cb_base = ((int64_t)hkv * M + i) * 256 * DS;
-    double c[4][DS];
+    // lane u < n_tok fetches token first + u: its sub-vector, sequence and position
+    const uint32_t u_mine = (uint32_t)(first + (lane < n_tok ? lane : 0));
+    const int b_mine = (int)divided(u_mine, by_n_new);
+    const int t_mine = (int)u_mine - b_mine * a.n_new;
+    const T *xp = (const T *)a.x[which] + (((int64_t)b_mine * a.Hkv + hkv) * a.n_new + t_mine) * PQ_HEAD_DIM + i * DS;
+    float x_mine[DS];
+#pragma unroll
+    for (int j = 0; j < DS; ++j)
+        x_mine[j] = (float)xp[j];
+    const int n_old = a.ctx_len[b_mine];
+
+    // centroids 4 lane .. 4 lane + 3
+    typedef T quad __attribute__((ext_vector_type(4 * DS)));
+    const quad cq = *((const quad *)((const T *)a.codebook[which] + ((int64_t)hkv * M + i) * 256 * DS) + lane);
+    float c[4][DS];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int j = 0; j < DS; ++j)
-            c[r][j] = widen<T>(a.codebook[which], cb_base + (int64_t)(lane + 64 * r) * DS + j);
-
-    // lane u < n_tok fetches token u: its sub-vector, sequence and position
-    const int u_mine = lane < n_tok ? lane : 0;
-    const int b_mine = u_mine / a.n_new;
-    const int t_mine = u_mine - b_mine * a.n_new;
-    double x_mine[DS];
-#pragma unroll
-    for (int j = 0; j < DS; ++j)
-        x_mine[j] = widen<T>(a.x[which], (((int64_t)b_mine * a.Hkv + hkv) * a.n_new + t_mine) * PQ_HEAD_DIM + i * DS + j);
-    int n_old = a.ctx_len[b_mine];
-    n_old = n_old < 0 ? 0 : n_old;
+            c[r][j] = (float)cq[r * DS + j];
 
     int code_mine = 0;
     for (int u = 0; u < n_tok; ++u) {
-        double x[DS];
+        float x[DS];
 #pragma unroll
         for (int j = 0; j < DS; ++j)
-            x[j] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x_mine[j]), u),
-                                    __builtin_amdgcn_readlane(__double2loint(x_mine[j]), u));
-        double bd = __builtin_huge_val();
-        int bc = lane;
+            x[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x_mine[j]), u));
+        uint32_t d[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            double dist = 0.0;
+            float dist = 0.f;
 #pragma unroll
             for (int j = 0; j < DS; ++j) {
-                const double diff = x[j] - c[r][j];
-                dist = __builtin_fma(diff, diff, dist);
+                const float diff = x[j] - c[r][j];
+                dist = j == 0 ? diff * diff : __builtin_fmaf(diff, diff, dist);
             }
-            bc = dist < bd ? lane + 64 * r : bc;  // ascending index inside the lane, strict "<"
-            bd = __builtin_fmin(bd, dist);
+            d[r] = __float_as_uint(dist);  // (positive floats order like their bits)
         }
-        wave_argmin(bd, bc);
-        code_mine = lane == u ? bc : code_mine;
+        const uint32_t least = few_wave_min(min(min(min(d[0], d[1]), d[2]), d[3]));
+        uint64_t near[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            near[r] = __builtin_amdgcn_ballot_w64(d[r] <= least + 16u);
+        const int n_near = __builtin_popcountll(near[0]) + __builtin_popcountll(near[1]) + __builtin_popcountll(near[2]) +
+                           __builtin_popcountll(near[3]);
+        int code = 4 * __builtin_ctzll(near[0] | near[1] | near[2] | near[3] | 1ull << 63) +
+                   (near[1] != 0 ? 1 : near[2] != 0 ? 2 : near[3] != 0 ? 3 : 0);
+        if (n_near != 1 || (sizeof(T) == 4 && least < 0x0d800000u)) {  // wave-uniform, rare
+            double bd = __builtin_huge_val();
+            int bc = 4 * lane;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                double dist = 0.0;
+#pragma unroll
+                for (int j = 0; j < DS; ++j) {
+                    const double diff = (double)x[j] - (double)c[r][j];
+                    dist = __builtin_fma(diff, diff, dist);
+                }
+                bc = dist < bd ? 4 * lane + r : bc;  // ascending index inside the lane, strict "<"
+                bd = __builtin_fmin(bd, dist);
+            }
+            wave_argmin(bd, bc);
+            code = __builtin_amdgcn_readfirstlane(bc);
+        }
+        code_mine = lane == u ? code : code_mine;
     }
-    const int64_t pos = (int64_t)n_old + t_mine;
+    const int64_t pos = (int64_t)(n_old < 0 ? 0 : n_old) + t_mine;
     if (lane < n_tok && pos < a.max_context) {
         uint8_t *dst = a.codes[which] + ((int64_t)b_mine * a.Hkv + hkv) * a.head_stride;
         const int64_t off = which == 0 ? pq_k_code_offset(pos, i, M, a.k_skew) : pq_v_code_offset(pos, i, M);
@@ -454,6 +487,32 @@ void launch_fast(const pq_encode_args &a, hipStream_t s)
         hipLaunchKernelGGL((pq_encode_fast_kernel<M, DS, T, false>), grid, dim3(64 * FAST_WAVES), 0, s, a, (int)rounds);
 }
 
+// Tokens of a wavefront of the few-token kernel, from a head's tokens and the subspaces of all heads, keys and values; 0: the
+// filter does better.  The few-token kernel takes some 2.5 us and 0.11 us for every 1024 (token, subspace) pairs, the filter 5
+// to 8 us for any of these sizes, more for more subspaces, whose codebooks it sets up (whole calls with the length reset,
+// us, few-token kernel / filter, fp16: M = 64, 32 heads, 8 tokens 8.5 / 11.2, 12 9.7 / 11.2, 16 10.7 / 11.3, 24 13.0 / 11.3; 8
+// heads, 8 tokens 6.3 / 8.3, 24 7.7 / 8.2, 32 8.3 / 8.3, 64 10.6 / 8.7; 4 heads, 45 tokens 8.5 / 9.2, 128 11.2 / 8.8; M = 32, 32
+// heads, 12 tokens 8.6 / 9.6, 16 9.3 / 9.5, 24 11.4 / 9.4; 8 heads, 32 tokens 7.9 / 8.5, 64 9.7 / 8.7; fp32, where the filter
+// has twice the terms: M = 64, 32 heads, 16 tokens 10.4 / 13.1, 24 13.0 / 13.1).
+// Some 6000 wavefronts are the best division: 8192 cost 0.1 .. 1 us more, and what a wavefront takes in a row shows from a
+// dozen tokens on (8 heads, M = 64, 16 tokens: 1 each 8.1 us, 3 6.9, 8 7.3, 16 8.6).
+inline int pq_encode_few_per_wave(int64_t tokens, int64_t rows, int M)
+{
+    const int64_t pairs = tokens * rows;
+    if (pairs > (M == 64 ? 24576 : 16384) + 8 * rows)
+        return 0;
+    const int64_t per_wave = (pairs + 6143) / 6144, most = per_wave < 64 ? per_wave : 64;
+    const int64_t groups = (tokens + most - 1) / most;
+    return (int)((tokens + groups - 1) / groups);
+}
+
+template <int M, int DS, typename T> void launch_few(const pq_encode_args &a, int per_wave, hipStream_t s)
+{
+    const int groups = (a.B * a.n_new + per_wave - 1) / per_wave;
+    hipLaunchKernelGGL((pq_encode_few_kernel<M, DS, T>), dim3(a.Hkv, M / FEW_WAVES, 2 * groups), dim3(64 * FEW_WAVES), 0, s, a, per_wave,
+                       pq_divisor(a.n_new));
+}
+
 template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, int slices, hipStream_t s)
 {
     const int n_chunks = a.B * seq_chunks;
@@ -467,19 +526,14 @@ hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int
                             hipStream_t s)
 {
     const bool f16 = ctx->cfg.dtype == PQ_F16;
-    // from 7 tokens per head the filter kernel is the faster one (fp16, 32 heads, one new token per sequence: 4
-    // sequences 7.4 us, 8 sequences 10.7 us, 16 sequences 17.9 us here against 10.1 us there; fp32, 16 sequences, with
-    // the length reset and the launches: 19.8 against 13.1 us)
-    if ((int64_t)a.B * a.n_new <= FEW_TOKENS) {
-        const dim3 grid(a.Hkv, ctx->cfg.n_subspaces, 2);
+    const int few = pq_encode_few_per_wave((int64_t)a.B * a.n_new, (int64_t)a.Hkv * ctx->cfg.n_subspaces * 2, ctx->cfg.n_subspaces);
+    if (few > 0) {
         if (ctx->cfg.n_subspaces == 64) {
-            if (f16) hipLaunchKernelGGL((pq_encode_few_kernel<64, 2, __half>), grid, dim3(64), 0, s, a);
-            else hipLaunchKernelGGL((pq_encode_few_kernel<64, 2, float>), grid, dim3(64), 0, s, a);
+            if (f16) launch_few<64, 2, _Float16>(a, few, s); else launch_few<64, 2, float>(a, few, s);
         } else {
-            if (f16) hipLaunchKernelGGL((pq_encode_few_kernel<32, 4, __half>), grid, dim3(64), 0, s, a);
-            else hipLaunchKernelGGL((pq_encode_few_kernel<32, 4, float>), grid, dim3(64), 0, s, a);
+            if (f16) launch_few<32, 4, _Float16>(a, few, s); else launch_few<32, 4, float>(a, few, s);
         }
-        hipError_t e = hipGetLastError();
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
         return pq_launch_bump_len(ctx_len, a.B, a.n_new, a.max_context, dev_err, s);
