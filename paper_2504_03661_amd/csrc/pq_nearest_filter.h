@@ -92,6 +92,13 @@ __device__ inline void pq_filter_build_row(const T (&c)[DS], const float scale, 
     __builtin_memcpy(arow_c, row, pq_filter_row_bytes<T>());
 }
 
+// Takes a centroid out: all its values are infinite, so it is never marked.  For one that repeats an earlier centroid.
+template <int DS, typename T> __device__ __forceinline__ void pq_filter_hide_row(unsigned char *arow_c)
+{
+    constexpr int N_AT = sizeof(T) == 2 ? DS : 3 * DS;  // (h, as above)
+    ((_Float16 *)arow_c)[N_AT] = (_Float16)__builtin_inff();
+}
+
 // What the matrix instruction and the refinement need of this lane's token
 template <int DS, typename T> struct pq_filter_token {
     static constexpr bool F16 = sizeof(T) == 2;

@@ -33,9 +33,9 @@
 // with longer lists (7 % with a codebook of random vectors, 1 % with a trained one) wait in LDS until 64 are there and are then
 // worked on as one.
 // What the data make of it, 32 heads, us, beside the filter alone: encode of 9000 tokens, normal 364 / 440, Laplace's
-// distribution 411 / 441, 2 % of the coordinates times 20 414 / 446; of 32K 631 / 1590, 803 / 1596, 816 / 1610.  A codebook
-// without a useful grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every subspace 882 / 757
-// and 3047 / 2611, centroids of 16 values in all 2873 / 2496 and 10149 / 8583.
+// distribution 411 / 441, 2 % of the coordinates times 20 414 / 446; of 32K 631 / 1590, 803 / 1596, 816 / 1610.  Centroids that
+// repeat others are taken out: k-means of 32 heads x 64K samples rounded to quarters 18.5 -> 8.1 ms.  A codebook without a useful
+// grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every subspace 882 / 757 and 3047 / 2611.
 #pragma once
 
 #include "pq_device_utils.h"
@@ -70,23 +70,25 @@ constexpr uint32_t GRID_SURE = 512;  // keys at least this far apart are in the 
 
 template <typename T> struct pq_grid {
     uint32_t cell[GRID_SIDE * GRID_SIDE];  // [u_x][u_y]; while building, the 64 bytes of a 4 x 4 block are its list
-    unsigned char arow[256 * pq_filter_row_bytes<T>()];
     T coord[256][2];
-    __attribute__((aligned(16))) uint32_t pool[GRID_POOL];
     float sx, ox, sy, oy;  // the map
     float scale;           // of the filter
     uint32_t pool_used, bad;  // bad: 1 no grid, 2 codebook outside the filter's range
     uint32_t lost, unserved;  // how many centroids the grid does not serve: counted before and after its lists
+    uint32_t again[8];     // a bit per centroid: equal to one before it
+    __attribute__((aligned(16))) uint32_t pool[GRID_POOL];
+    unsigned char arow[256 * pq_filter_row_bytes<T>()];
 };
 
-// The tokens are taken to lie where the centroids do: where many of the 256 are left to the filter (in cells without a list, or
-// with an equal one before them), it does all the work of the subspace.  (For 64 tokens: 86 instructions for the look-ups,
+// The tokens are taken to lie where the centroids do: where many of the 256 are left to the filter (in cells without a list), it
+// does all the work of the subspace.  (For 64 tokens: 86 instructions for the look-ups,
 // some 30 for putting tokens off and for 24 of them 135 in the filter; 355 through the filter alone, and building is saved.)
 constexpr int GRID_LOST = 96;
 template <typename T> __device__ __forceinline__ bool pq_grid_useless(const pq_grid<T> &g) { return g.bad != 0 || g.lost > GRID_LOST || g.unserved > GRID_LOST; }
 
 // What building a grid needs of its centroids: a_x, a_y, |c|^2 / 2 lowered, |c|^2 / 2; how many of them lie in each block of
-// 4 x 4 cells, 16 bits each; and the first of those whose coordinates have the same hash.  The waiting tokens take its place.
+// 4 x 4 cells, 16 bits each (repeated ones not counted); and the first of those whose coordinates have the same hash.  The
+// waiting tokens take its place.
 typedef float pq_grid_table[256][4];
 struct pq_grid_making {
     pq_grid_table table[GRID_SUB];
@@ -170,10 +172,10 @@ template <typename T> __device__ __forceinline__ bool pq_grid_unsure(const uint3
 }
 
 // A wavefront's part of a subspace's tables: the map, which all 4 wavefronts work out alike, and the rows and numbers of
-// centroids 64 part .. 64 part + 63, these centroids counted into their blocks.  src: [256][2]; cell, hash: of centroid 64 part + lane
+// centroids 64 part .. 64 part + 63.  src: [256][2]; cell, hash: of centroid 64 part + lane
 template <typename T>
-__device__ inline void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, uint32_t (&in_block)[128], uint32_t (&first_of)[256], const T *src,
-                                      const int part, uint32_t &cell, uint32_t &hash)
+__device__ __forceinline__ void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, uint32_t (&first_of)[256], const T *src, const int part,
+                                      uint32_t &cell, uint32_t &hash)
 {
     const int lane = threadIdx.x & 63;
     float x[4], y[4];
@@ -240,8 +242,6 @@ __device__ inline void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, uint3
     g.coord[c][1] = mine[1];
     cell = pq_grid_cell(mine[0], mine[1], sx, ox, sy, oy);
     hash = pq_grid_hash(mine[0], mine[1]);
-    const uint32_t block = pq_grid_block(cell);
-    atomicAdd(&in_block[block >> 1], 1u << (16 * (block & 1u)));
     atomicMin(&first_of[hash], (uint32_t)c);
     const uint32_t bad = (__builtin_amdgcn_ballot_w64(far_out) != 0 || !usable ? 1u : 0u) |
                          (__builtin_amdgcn_ballot_w64(cb_bad) != 0 ? 3u : 0u);
@@ -341,7 +341,7 @@ template <int K, int N, typename F> __device__ __forceinline__ void pq_grid_twos
 
 // The lists of one quarter of the grid (cell rows 16 part .. 16 part + 15), by one wavefront.  box: centre and half side of
 // the 64 cell coordinates
-template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const pq_grid_table &table, const float2 (&box)[GRID_SIDE], const int part)
+template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &g, const pq_grid_table &table, const float2 (&box)[GRID_SIDE], const int part)
 {
     const int lane = threadIdx.x & 63;
     unsigned char *bytes = (unsigned char *)g.cell;
@@ -397,10 +397,11 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
         }
         // Lists are filled up to whole words with a code that is not in them: it is never the least, and being there more
         // than once it hides no second least.
-        fill = (uint32_t)__builtin_ctz(~used | 0x80000000u);
+        const uint32_t others = used | g.again[0];  // (a repetition of a listed one would be as near as that)
+        fill = (uint32_t)__builtin_ctz(~others | 0x80000000u);
         for (int k = count; (k & 3) != 0 && k < GRID_LONGEST; ++k)
             bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))] = (unsigned char)fill;
-        count = used == 0xffffffffu ? GRID_LONGEST + 1 : count;  // (none to fill up with: no list)
+        count = others == 0xffffffffu ? GRID_LONGEST + 1 : count;  // (none to fill up with: no list)
     }
     pq_grid_fence();
 
@@ -568,24 +569,42 @@ template <typename T> __device__ inline void pq_grid_lists(pq_grid<T> &g, const 
     }
 }
 
-// How many of the wavefront's 64 centroids the grid will not serve, known before the lists are, which take most of the
-// building: those outside the map, in a block with more than GRID_LONGEST of them, all of which would be in its list (tight clusters), and
-// those that repeat an earlier one (a token there has two nearest ones; a repetition behind a clash of hashes is not seen).
+// A centroid that repeats an earlier one is never a code: it is taken out of the filter's rows and of all lists, so that its
+// tokens have one nearest centroid (left in, a token there was unsure, and a codebook of some 100 values no case for a
+// grid).  A repetition behind a clash of hashes is not seen, and costs time only.
 template <typename T>
-__device__ inline int pq_grid_lost(const pq_grid<T> &g, const uint32_t (&in_block)[128], const uint32_t (&first_of)[256], const int part,
-                                   const uint32_t cell, const uint32_t hash)
+__device__ __forceinline__ bool pq_grid_take_out(pq_grid<T> &g, pq_grid_table &table, uint32_t (&in_block)[128], const uint32_t (&first_of)[256],
+                                                 const int part, const uint32_t cell, const uint32_t hash)
 {
-    const int c = 64 * part + (threadIdx.x & 63);
+    const int lane = threadIdx.x & 63, c = 64 * part + lane;
+    const int other = (int)first_of[hash];
+    const bool again = other < c && g.coord[other][0] == g.coord[c][0] && g.coord[other][1] == g.coord[c][1];
+    const uint64_t of = __builtin_amdgcn_ballot_w64(again);
+    if (lane < 2)
+        g.again[2 * part + lane] = (uint32_t)(of >> (32 * lane));
+    const uint32_t block = pq_grid_block(cell);
+    if (again) {
+        pq_filter_hide_row<2, T>(g.arow + c * pq_filter_row_bytes<T>());
+        table[c][2] = 1.0e30f;  // far from everywhere
+    } else {
+        atomicAdd(&in_block[block >> 1], 1u << (16 * (block & 1u)));
+    }
+    return again;
+}
+
+// How many of the wavefront's 64 centroids the grid will not serve, known before the lists are, which take most of the
+// building: those outside the map or in a block with more than GRID_LONGEST of them, all of which would be in its list (tight
+// clusters).
+__device__ __forceinline__ int pq_grid_lost(const uint32_t (&in_block)[128], const uint32_t cell, const bool again)
+{
     const uint32_t ex = cell >> 8, ey = cell >> 2 & 63u, block = pq_grid_block(cell);
     const bool outside = ex - 31u < 2u || ey - 31u < 2u;
     const uint32_t n = in_block[block >> 1] >> (16 * (block & 1u)) & 0xffffu;
-    const int other = (int)first_of[hash];
-    const bool again = other != c && g.coord[other][0] == g.coord[c][0] && g.coord[other][1] == g.coord[c][1];
-    return __builtin_popcountll(__builtin_amdgcn_ballot_w64(outside || n > GRID_LONGEST || again));
+    return __builtin_popcountll(__builtin_amdgcn_ballot_w64(!again && (outside || n > GRID_LONGEST)));
 }
 
 // Builds the grids of a workgroup's 4 subspaces.  src: the codebook of the first of them, [4][256][2]
-template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GRID_SUB], pq_grid_making &making, float2 (&box)[GRID_SIDE], const T *src)
+template <typename T> __device__ __forceinline__ void pq_grid_build(pq_grid<T> (&grid)[GRID_SUB], pq_grid_making &making, float2 (&box)[GRID_SIDE], const T *src)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -604,9 +623,11 @@ template <typename T> __device__ inline void pq_grid_build(pq_grid<T> (&grid)[GR
     ((uint32_t *)making.first_of)[threadIdx.x] = 255;
     __syncthreads();
     uint32_t cell, hash;
-    pq_grid_tables(g, making.table[wave >> 2], making.in_block[wave >> 2], making.first_of[wave >> 2], src + (wave >> 2) * 512, part, cell, hash);
+    pq_grid_tables(g, making.table[wave >> 2], making.first_of[wave >> 2], src + (wave >> 2) * 512, part, cell, hash);
     __syncthreads();
-    const int n_lost = pq_grid_lost(g, making.in_block[wave >> 2], making.first_of[wave >> 2], part, cell, hash);
+    const bool again = pq_grid_take_out(g, making.table[wave >> 2], making.in_block[wave >> 2], making.first_of[wave >> 2], part, cell, hash);
+    __syncthreads();
+    const int n_lost = pq_grid_lost(making.in_block[wave >> 2], cell, again);
     if (lane == 0)
         atomicAdd(&g.lost, (uint32_t)n_lost);
     __syncthreads();
