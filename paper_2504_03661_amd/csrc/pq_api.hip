@@ -172,7 +172,8 @@ int choose_jobs(const pq_attn_config *c, int n_cu)
 // Codebook pointers passed to an entry point are registered there and then: the context copies them on the
 // stream (its own natural-layout copy for the encode kernels, the centroid-major image for the decode
 // kernels) and never looks at the caller's tensors again.  NULL, NULL means "the registered ones".
-int ensure_codebooks(pq_attn_ctx *ctx, const void *k, const void *v, hipStream_t s)
+// once: a registration for the calls to come, not by one of them
+int ensure_codebooks(pq_attn_ctx *ctx, const void *k, const void *v, hipStream_t s, bool once = false)
 {
     if (k == nullptr && v == nullptr)
         return ctx->registered ? PQ_OK : PQ_ERR_NULL;
@@ -185,12 +186,15 @@ int ensure_codebooks(pq_attn_ctx *ctx, const void *k, const void *v, hipStream_t
             pq_launch_copy16(v, ctx->vcb_packed, bytes, s) != hipSuccess)
             return PQ_ERR_HIP;
     } else {
-        if (pq_launch_pack_codebook(ctx, k, ctx->kcb_packed, ctx->kcb_natural, s) != hipSuccess)
+        unsigned int *const of_k = ctx->grid_state, *const of_v = of_k ? of_k + pq_grid_groups(&ctx->cfg) / 2 : nullptr;
+        if (pq_launch_pack_codebook(ctx, k, ctx->kcb_packed, ctx->kcb_natural, of_k, s) != hipSuccess)
             return PQ_ERR_HIP;
-        if (pq_launch_pack_codebook(ctx, v, ctx->vcb_packed, ctx->vcb_natural, s) != hipSuccess)
+        if (pq_launch_pack_codebook(ctx, v, ctx->vcb_packed, ctx->vcb_natural, of_v, s) != hipSuccess)
             return PQ_ERR_HIP;
     }
     ctx->registered = true;
+    ctx->grids_kept = false;
+    ctx->grid_chunks = once ? 0 : -1;
     return PQ_OK;
 }
 
@@ -250,6 +254,7 @@ void free_ctx(pq_attn_ctx *ctx)
     if (ctx->vcb_packed) (void)hipFree(ctx->vcb_packed);
     if (ctx->kcb_natural && ctx->kcb_natural != ctx->kcb_packed) (void)hipFree(ctx->kcb_natural);
     if (ctx->vcb_natural && ctx->vcb_natural != ctx->vcb_packed) (void)hipFree(ctx->vcb_natural);
+    if (ctx->grids) (void)hipFree(ctx->grids);
     if (ctx->partials) (void)hipFree(ctx->partials);
     if (ctx->tickets) (void)hipFree(ctx->tickets);
     if (ctx->dev_err) (void)hipFree(ctx->dev_err);
@@ -350,7 +355,14 @@ int pq_attn_create(const pq_attn_config *cfg, pq_attn_ctx **out)
         free_ctx(ctx);
         return PQ_ERR_ALLOC;
     }
+    // the grids of long appends are an image of what their workgroups otherwise build: nobody depends on there being one
+    const int64_t grid_bytes = pq_grid_images_bytes(cfg, ctx->n_cu);
+    if (grid_bytes > 0 && hipMalloc(&ctx->grids, (size_t)grid_bytes + pq_grid_groups(cfg) * sizeof(unsigned int)) == hipSuccess)
+        ctx->grid_state = (unsigned int *)((char *)ctx->grids + grid_bytes);
+    else
+        (void)hipGetLastError();
     ok = hipMemset(ctx->tickets, 0, n_bh * sizeof(unsigned int)) == hipSuccess;
+    ok = ok && (ctx->grids == nullptr || hipMemset(ctx->grid_state, 0, pq_grid_groups(cfg) * sizeof(unsigned int)) == hipSuccess);
     ok = ok && hipMemset(ctx->dev_err, 0, 2 * sizeof(unsigned int)) == hipSuccess;
     ok = ok && hipMemset(ctx->partials, 0, part_bytes) == hipSuccess;
     ok = ok && hipDeviceSynchronize() == hipSuccess;
@@ -393,7 +405,7 @@ int pq_attn_set_codebooks(pq_attn_ctx *ctx, const void *k_codebook, const void *
     device_guard guard(ctx->cfg.device);
     if (!guard.ok)
         return PQ_ERR_HIP;
-    return ensure_codebooks(ctx, k_codebook, v_codebook, (hipStream_t)hip_stream);
+    return ensure_codebooks(ctx, k_codebook, v_codebook, (hipStream_t)hip_stream, true);
 }
 
 int pq_attn_decode(pq_attn_ctx *ctx, const void *q, const uint8_t *k_codes, const uint8_t *v_codes,
@@ -470,8 +482,8 @@ int pq_attn_decode_noalloc(const pq_attn_config *cfg, const void *q, const uint8
     ctx.partials = (float *)(dev.ptr + PQ_NOALLOC_PARTIALS_OFF);
     ctx.tickets = (unsigned int *)(dev.ptr + PQ_NOALLOC_TICKETS_OFF);
     hipStream_t s = (hipStream_t)hip_stream;
-    if (pq_launch_pack_codebook(&ctx, k_codebook, ctx.kcb_packed, nullptr, s) != hipSuccess ||
-        pq_launch_pack_codebook(&ctx, v_codebook, ctx.vcb_packed, nullptr, s) != hipSuccess)
+    if (pq_launch_pack_codebook(&ctx, k_codebook, ctx.kcb_packed, nullptr, nullptr, s) != hipSuccess ||
+        pq_launch_pack_codebook(&ctx, v_codebook, ctx.vcb_packed, nullptr, nullptr, s) != hipSuccess)
         return PQ_ERR_HIP;
     // the tickets must start at zero; the array keeps whatever the last call on this GPU left (a fill kernel,
     // not a memset: this call may be recorded into a HIP graph)
@@ -511,6 +523,8 @@ int pq_encode_append(pq_attn_ctx *ctx, const void *new_k, const void *new_v, int
     a.max_context = ctx->cfg.max_context;
     a.k_skew = ctx->k_skew;
     a.head_stride = ctx->cap_padded * token_bytes(&ctx->cfg);
+    a.grids = ctx->grids;
+    a.grid_state = ctx->grid_state;
     if (pq_config_is_12bit(&ctx->cfg)) {
         // codes are staged token-major (uint16) and packed by a second kernel; the staging buffers were sized at
         // creation, a longer append goes through them in chunks (each chunk: encode, pack, advance the lengths)

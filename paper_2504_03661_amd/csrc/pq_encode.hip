@@ -227,6 +227,76 @@ template <typename T> struct grid_token {
     int64_t block;  // byte offset of the chunk's block of codes
 };
 
+// The grids of registered codebooks are the same in every append, so a context keeps them, once its appends have paid for
+// building them (pq_launch_encode), and a workgroup fetches the 80 KiB or so that are used of its four (fp16) instead of
+// building for 66 us: 32 heads x 32K tokens 641 -> 412 us, and from some 1000 tokens on appends do better with kept grids than
+// through the filter, where before 9000 had to pay for building them (32 heads x 4000 tokens 200 -> 85 us).  An image takes
+// 25 KiB per subspace (32 heads, K and V: 105 MB of memory).
+// A word per 4 subspaces says whether the image there is that of the codebooks in force.  It is on the device, so that
+// stream order and what a captured graph replays decide, not the host: registering codebooks puts it to GRID_ABSENT, and a
+// workgroup that finds that builds for itself and waits for nobody.  Images are written and read by agent-scope accesses, the
+// word behind the image (the exchange of pq_device_utils.h): an append on another stream finds a whole image or none.
+enum : uint32_t { GRID_ABSENT = 0, GRID_THERE = 1 };
+
+// words of a grid's image behind the cells that are used
+template <typename T> __device__ __forceinline__ int grid_image_words(const pq_grid<T> &g)
+{
+    const int pool = pq_grid_useless(g) || g.pool_used > GRID_POOL ? GRID_POOL : (int)g.pool_used;  // (useless: the wide coordinates)
+    return (int)(offsetof(pq_grid<T>, pool) / 4) + pool;
+}
+
+// image -> grids in LDS: 256 threads per subspace, 8 bytes each.  Requested together are the cells and, for most grids, all
+// that is used behind them: the coordinates, the map and the first 748 words of the pool (fp32: 492).  The filter's rows are
+// made anew, a thread each.
+template <typename T> __device__ __forceinline__ void grid_fetch(pq_grid<T> (&grid)[GRID_SUB], const char *images)
+{
+    constexpr int TURNS = GRID_SIDE * GRID_SIDE / 512 + 2;
+    const int j = threadIdx.x >> 8, c = threadIdx.x & 255;
+    pq_grid<T> &g = grid[j];
+    const float *image = (const float *)(images + j * pq_grid_image_bytes<T>());
+    float2 t[TURNS];
+#pragma unroll
+    for (int k = 0; k < TURNS; ++k)
+        t[k] = fetch(image + 2 * (k * 256 + c));
+#pragma unroll
+    for (int k = 0; k < TURNS; ++k)
+        ((float2 *)&g)[k * 256 + c] = t[k];
+    __syncthreads();
+    bool bad = false;
+    const T mine[2] = {g.coord[c][0], g.coord[c][1]};
+    pq_filter_build_row<2>(mine, g.scale, g.arow + c * pq_filter_row_bytes<T>(), bad);
+    if ((g.again[c >> 5] >> (c & 31)) & 1u)
+        pq_filter_hide_row<2, T>(g.arow + c * pq_filter_row_bytes<T>());
+    const int words = grid_image_words(g);
+    for (int at = TURNS * 256 + c; 2 * at < words; at += 256)
+        ((float2 *)&g)[at] = fetch(image + 2 * at);
+    __syncthreads();
+}
+
+// A workgroup: 4 subspaces, as the encode's workgroups, in the order of the images.
+template <typename T>
+__global__ __launch_bounds__(GRID_WAVES * 64) void pq_grid_image_kernel(const T *codebook_k, const T *codebook_v, const int groups_k, void *images,
+                                                                        unsigned int *grid_state)
+{
+    __shared__ __attribute__((aligned(16))) pq_grid<T> grid[GRID_SUB];
+    __shared__ __attribute__((aligned(16))) pq_grid_scratch<false> scratch;
+    __shared__ float2 box[GRID_SIDE];
+
+    const int group = blockIdx.x;
+    const T *src = group < groups_k ? codebook_k + (int64_t)group * (GRID_SUB * 512) : codebook_v + (int64_t)(group - groups_k) * (GRID_SUB * 512);
+    pq_grid_build(grid, scratch.making, box, src);
+    const int j = threadIdx.x >> 8;
+    const float2 *from = (const float2 *)&grid[j];
+    float *image = (float *)((char *)images + ((int64_t)group * GRID_SUB + j) * pq_grid_image_bytes<T>());
+    const int words = grid_image_words(grid[j]);
+    for (int at = threadIdx.x & 255; 2 * at < words; at += 256)
+        publish(image + 2 * at, from[at].x, from[at].y);
+    publish_wait();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(grid_state + group, (unsigned int)GRID_THERE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <typename T>
 __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const pq_encode_args a, const int seq_chunks, const int slices,
                                                                          const int slice_chunks)
@@ -236,6 +306,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
     constexpr bool KEEP = sizeof(T) == 2;
     __shared__ __attribute__((aligned(16))) pq_grid_scratch<KEEP> scratch;
     __shared__ float2 box[GRID_SIDE];
+    __shared__ unsigned int there;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -251,7 +322,14 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
     const int first = slice * slice_chunks;
     const int last = first + slice_chunks < n_chunks ? first + slice_chunks : n_chunks;
 
-    pq_grid_build(grid, scratch.making, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
+    const int group = head * (M / GRID_SUB) + i0 / GRID_SUB;
+    if (threadIdx.x == 0)  // one look for all: the word may change
+        there = a.grids != nullptr ? __hip_atomic_load(a.grid_state + group, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (unsigned int)GRID_ABSENT;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane((int)there) == (int)GRID_THERE)
+        grid_fetch<T>(grid, (const char *)a.grids + (int64_t)group * (GRID_SUB * pq_grid_image_bytes<T>()));
+    else
+        pq_grid_build(grid, scratch.making, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
 
     const T *x = (const T *)a.x[which] + i0 * 2;
     uint8_t *codes = a.codes[which];
@@ -522,7 +600,33 @@ template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, 
                        slice_chunks);
 }
 
-hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,
+// Builds the grids into the context's images when this append and those since the codebooks were registered, chunks of 64 tokens
+// per head, would together have paid for it: a single long append at once, so that no append takes longer than by building its
+// own, and a context that never appends much never builds any.  (What is counted decides about time alone: threads that append at
+// once may count less, one of them builds.)  Not while a graph is recorded, which would build again with every replay, and not
+// for codebooks that were handed to a call, which may be handed to the next one again.
+static hipError_t keep_grids(pq_attn_ctx *ctx, int64_t filter_chunks, int64_t groups, hipStream_t s)
+{
+    if (ctx->grids_kept.load(std::memory_order_relaxed) || ctx->grid_chunks.load(std::memory_order_relaxed) < 0)
+        return hipSuccess;
+    const int64_t so_far = ctx->grid_chunks.fetch_add(filter_chunks, std::memory_order_relaxed) + filter_chunks;
+    if (pq_grid_slices(so_far, so_far, groups, ctx->n_cu) == 0)
+        return hipSuccess;
+    hipStreamCaptureStatus recording = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &recording) != hipSuccess)
+        (void)hipGetLastError();
+    if (recording != hipStreamCaptureStatusNone || ctx->grids_kept.exchange(true, std::memory_order_relaxed))
+        return hipSuccess;
+    if (ctx->cfg.dtype == PQ_F16)
+        hipLaunchKernelGGL(pq_grid_image_kernel<_Float16>, dim3((unsigned)groups), dim3(GRID_WAVES * 64), 0, s, (const _Float16 *)ctx->kcb_natural,
+                           (const _Float16 *)ctx->vcb_natural, (int)groups / 2, ctx->grids, ctx->grid_state);
+    else
+        hipLaunchKernelGGL(pq_grid_image_kernel<float>, dim3((unsigned)groups), dim3(GRID_WAVES * 64), 0, s, (const float *)ctx->kcb_natural,
+                           (const float *)ctx->vcb_natural, (int)groups / 2, ctx->grids, ctx->grid_state);
+    return hipGetLastError();
+}
+
+hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,
                             hipStream_t s)
 {
     const bool f16 = ctx->cfg.dtype == PQ_F16;
@@ -542,7 +646,16 @@ hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int
     // its 16-byte loads ask for rows that start at such an address
     const bool grid_can = ctx->cfg.n_subspaces == 64 && (((uintptr_t)a.x[0] | (uintptr_t)a.x[1]) & 15) == 0 &&
                           (int64_t)a.B * seq_chunks < (1 << 30);
-    const int slices = grid_can ? pq_grid_slices((int64_t)a.B * seq_chunks, ((int64_t)a.B * a.n_new + 63) / 64, (int64_t)2 * a.Hkv * 16, ctx->n_cu) : 0;
+    const int64_t chunks = (int64_t)a.B * seq_chunks, filter_chunks = ((int64_t)a.B * a.n_new + 63) / 64, groups = (int64_t)2 * a.Hkv * 16;
+    int slices = grid_can ? pq_grid_slices(chunks, filter_chunks, groups, ctx->n_cu) : 0;
+    const int with_kept = grid_can && ctx->grids != nullptr ? pq_grid_slices(chunks, filter_chunks, groups, ctx->n_cu, true) : 0;
+    if (with_kept > 0) {
+        const hipError_t e = keep_grids(ctx, filter_chunks, groups, s);
+        if (e != hipSuccess)
+            return e;
+        if (ctx->grids_kept.load(std::memory_order_relaxed))
+            slices = with_kept;
+    }
     if (slices > 0) {
         if (f16) launch_grid<_Float16>(a, seq_chunks, slices, s); else launch_grid<float>(a, seq_chunks, slices, s);
     } else if (ctx->cfg.n_subspaces == 64) {
@@ -555,4 +668,19 @@ hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int
         return e;
     // lengths move only after every encode workgroup has read the old ones (stream order)
     return pq_launch_bump_len(ctx_len, a.B, a.n_new, a.max_context, dev_err, s);
+}
+
+int64_t pq_grid_groups(const pq_attn_config *cfg) { return (int64_t)2 * cfg->n_kv_heads * (cfg->n_subspaces / GRID_SUB); }
+
+int64_t pq_grid_images_bytes(const pq_attn_config *cfg, int n_cu)
+{
+    // (sequences below 1024 tokens are never appended to by thousands)
+    if (pq_config_is_12bit(cfg) || cfg->n_subspaces != 64 || cfg->max_context < 1024)
+        return 0;
+    // the longest append that fits: the launcher's rule for it (which has no upper end that the capacities reach)
+    const int64_t seq_chunks = ((int64_t)cfg->max_context + 126) >> 6;
+    const int64_t chunks = ((int64_t)cfg->batch * cfg->max_context + 63) / 64;
+    if (pq_grid_slices(cfg->batch * seq_chunks, chunks, pq_grid_groups(cfg), n_cu, true) == 0)
+        return 0;
+    return pq_grid_groups(cfg) * GRID_SUB * (cfg->dtype == PQ_F16 ? pq_grid_image_bytes<_Float16>() : pq_grid_image_bytes<float>());
 }

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "pq_attn.h"
 
 // ---------------------------------------------------------------------------------
@@ -102,6 +104,14 @@ struct pq_attn_ctx {
     void *kcb_natural;    // the context's own copy of the registered codebooks in the caller's layout
     void *vcb_natural;    // [Hkv][M][C][ds] (what the encode kernels read); 12-bit contexts: = *_packed
     bool registered;      // codebooks have been registered (the copies above hold them)
+    // 8-bit contexts of 64 subspaces with room for long appends: the grids of the registered codebooks
+    // (pq_encode_grid_kernel), an image of a workgroup's LDS for every 4 subspaces of a KV head (K's, then V's), and a word
+    // for each of them: whether it is there.  NULL: no such appends, or no memory for it
+    void *grids;
+    unsigned int *grid_state;
+    std::atomic<bool> grids_kept;        // they have been built (the launcher's rule asks; what the kernel does follows the words)
+    std::atomic<int64_t> grid_chunks;    // 64-token chunks that appends could have used them for since pq_attn_set_codebooks;
+                                         // below zero: a call registered the codebooks
     float *partials;      // [B*Hq][n_splits][PQ_PART_STRIDE]; jobs > B: [Hq][jobs][PQ_PART_STRIDE]
     unsigned int *tickets;  // [B*Hq], zero between calls
     unsigned int *dev_err;  // sticky error word
@@ -163,6 +173,8 @@ struct pq_encode_args {
     int B, Hkv, n_new, max_context;
     int k_skew;
     int64_t head_stride;
+    void *grids;              // pq_attn_ctx::grids, grid_state
+    unsigned int *grid_state;
 };
 
 // launchers (each returns hipGetLastError() after its launches)
@@ -174,12 +186,18 @@ hipError_t pq_launch_decode_grouped(const pq_attn_ctx *ctx, const pq_decode_args
 bool pq_config_uses_grouped_kernel(const pq_attn_config *cfg);
 int pq_grouped_sub_groups(int g);
 int pq_grouped_heads_per_workgroup(int g);
-hipError_t pq_launch_encode(const pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,
+hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,
                             hipStream_t s);
 // lengths += n_new, saturating at max_context (sets the overflow flag)
 hipError_t pq_launch_bump_len(int32_t *ctx_len, int B, int n_new, int max_context, unsigned int *dev_err, hipStream_t s);
-// src [Hkv][M][256][ds] (caller memory) -> packed [Hkv][256][M][ds] and a plain copy in the source layout
-hipError_t pq_launch_pack_codebook(const pq_attn_ctx *ctx, const void *src, void *packed, void *natural, hipStream_t s);
+// src [Hkv][M][256][ds] (caller memory) -> packed [Hkv][256][M][ds] and a plain copy in the source layout; the words of
+// grid_state (those of K's or V's codebooks, or NULL) say that there are no grids of these yet
+hipError_t pq_launch_pack_codebook(const pq_attn_ctx *ctx, const void *src, void *packed, void *natural, unsigned int *grid_state,
+                                   hipStream_t s);
+// grids of a context (pq_attn_ctx::grids): words of grid_state, and bytes of all images — 0 where no append that fits the
+// context takes the grids
+int64_t pq_grid_groups(const pq_attn_config *cfg);
+int64_t pq_grid_images_bytes(const pq_attn_config *cfg, int n_cu);
 hipError_t pq_launch_pack_codes(const pq_attn_ctx *ctx, int kind, const uint8_t *token_major, int n_tokens,
                                 uint8_t *packed, bool unpack, hipStream_t s);
 hipError_t pq_launch_stream_read(const void *src, int64_t bytes, uint32_t *sink, hipStream_t s);

@@ -9,12 +9,15 @@
 namespace {
 
 // [Hkv][M][256][ds] -> [Hkv][256][M][ds]; one thread per (head, centroid, subspace)
-// (also writes `nat`, unless NULL: a plain copy of src, the context's own codebooks for the encode kernels)
+// (also writes `nat`, unless NULL: a plain copy of src, the context's own codebooks for the encode kernels; and zeroes the
+// words of grid_state, one per 4 subspaces, unless NULL)
 template <typename E>
-__global__ void pq_pack_codebook_kernel(const E *src, E *dst, E *nat, int Hkv, int M, int ds)
+__global__ void pq_pack_codebook_kernel(const E *src, E *dst, E *nat, unsigned int *grid_state, int Hkv, int M, int ds)
 {
     const int64_t n = (int64_t)Hkv * 256 * M;
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (grid_state != nullptr && x < Hkv * (M / 4))
+        grid_state[x] = 0;
     if (x >= n)
         return;
     const int i = (int)(x % M);
@@ -72,17 +75,18 @@ __global__ __launch_bounds__(1024) void pq_stream_read_kernel(const u32x4 *p, in
 
 }  // namespace
 
-hipError_t pq_launch_pack_codebook(const pq_attn_ctx *ctx, const void *src, void *dst, void *natural, hipStream_t s)
+hipError_t pq_launch_pack_codebook(const pq_attn_ctx *ctx, const void *src, void *dst, void *natural, unsigned int *grid_state,
+                                   hipStream_t s)
 {
     const int Hkv = ctx->cfg.n_kv_heads, M = ctx->cfg.n_subspaces, ds = ctx->ds;
     const int64_t n = (int64_t)Hkv * 256 * M;
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
     if (ctx->cfg.dtype == PQ_F16)
         hipLaunchKernelGGL(pq_pack_codebook_kernel<uint16_t>, grid, block, 0, s, (const uint16_t *)src,
-                           (uint16_t *)dst, (uint16_t *)natural, Hkv, M, ds);
+                           (uint16_t *)dst, (uint16_t *)natural, grid_state, Hkv, M, ds);
     else
         hipLaunchKernelGGL(pq_pack_codebook_kernel<uint32_t>, grid, block, 0, s, (const uint32_t *)src,
-                           (uint32_t *)dst, (uint32_t *)natural, Hkv, M, ds);
+                           (uint32_t *)dst, (uint32_t *)natural, grid_state, Hkv, M, ds);
     return hipGetLastError();
 }
 

@@ -32,11 +32,15 @@
 // through the filter together, and where the codebook gives no useful grid all its tokens go there at once.  Tokens of cells
 // with longer lists (7 % with a codebook of random vectors, 1 % with a trained one) wait in LDS until 64 are there and are then
 // worked on as one.
-// What the data make of it, 32 heads, us, beside the filter alone: encode of 9000 tokens, normal 364 / 440, Laplace's
-// distribution 411 / 441, 2 % of the coordinates times 20 414 / 446; of 32K 631 / 1590, 803 / 1596, 816 / 1610.  Centroids that
-// repeat others are taken out: k-means of 32 heads x 64K samples rounded to quarters 18.5 -> 8.1 ms.  A codebook without a useful
-// grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every subspace 882 / 757 and 3047 / 2611.
+// What the data make of it, 32 heads, us, grids built / kept from an earlier append / the filter alone: encode of 9000 tokens,
+// normal 364 / 140 / 440, Laplace's distribution 411 / 185 / 441, 2 % of the coordinates times 20 414 / 191 / 446; of 32K 631 / 410
+// / 1590, 803 / 575 / 1596, 816 / 594 / 1610.  Centroids that repeat others are taken out: 16 values in all 1480 kept, 2496 by the
+// filter (9000 tokens; 2850 when a repeated centroid made its tokens unsure), k-means of 64K samples rounded to quarters 18.5 ->
+// 8.1 ms.  A codebook without a useful grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every
+// subspace 863 / 757 and 3000 / 2611.
 #pragma once
+
+#include <stddef.h>
 
 #include "pq_device_utils.h"
 #include "pq_nearest_filter.h"
@@ -69,6 +73,7 @@ constexpr uint32_t GRID_NONE = 0x01000100u;  // a cell without a list: two codes
 constexpr uint32_t GRID_SURE = 512;  // keys at least this far apart are in the right order
 
 template <typename T> struct pq_grid {
+    // (what stands in front of arow is a grid's image in memory, its pool as far as it is used)
     uint32_t cell[GRID_SIDE * GRID_SIDE];  // [u_x][u_y]; while building, the 64 bytes of a 4 x 4 block are its list
     T coord[256][2];
     float sx, ox, sy, oy;  // the map
@@ -79,6 +84,7 @@ template <typename T> struct pq_grid {
     __attribute__((aligned(16))) uint32_t pool[GRID_POOL];
     unsigned char arow[256 * pq_filter_row_bytes<T>()];
 };
+template <typename T> constexpr int pq_grid_image_bytes() { return (int)offsetof(pq_grid<T>, arow); }
 
 // The tokens are taken to lie where the centroids do: where many of the 256 are left to the filter (in cells without a list), it
 // does all the work of the subspace.  (For 64 tokens: 86 instructions for the look-ups,
@@ -932,13 +938,17 @@ __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_gr
 // 0.94; k-means 76 and 0.15, 0.85.  So the model is on the filter's side for all three, and data that the grids serve less well
 // still gain at the line (32 heads x 9000 tokens or samples, us, grids / filter, the three in turn: normal 364 / 440, 410 /
 // 530, 198 / 267; Laplace's distribution 411 / 441, 437 / 526, 219 / 266; channel scales 0.5 .. 4 444 / 458 and 248 / 275).
-inline int pq_grid_slices(const int64_t chunks, const int64_t filter_chunks, const int64_t groups, const int n_cu)
+// kept: the grids are there (pq_encode_grid_kernel), a workgroup takes some 9 us to start, fetch them and end.  Grids / filter,
+// fp16, whole appends with the length reset: 32 heads, 500 tokens 45 / 37 us, 1000 52 / 61, 2000 63 / 109, 8000 127 / 383; 8
+// heads, 500 tokens 14.8 / 15.3, 1000 15.6 / 22.7, 4000 24 / 60; 4 heads in two slices, 1000 tokens 14.3 / 15.2, 4000 18.8 / 36.5;
+// fp32, 32 heads, 500 tokens 48 / 45, 1000 55 / 70, 4000 93 / 230.
+inline int pq_grid_slices(const int64_t chunks, const int64_t filter_chunks, const int64_t groups, const int n_cu, const bool kept = false)
 {
     int64_t best = filter_chunks * groups * 72 / n_cu;  // 10 ns
     int slices = 0;
     for (int s = 1; s <= 32; ++s) {
         const int64_t rounds = (groups * s + n_cu - 1) / n_cu;
-        const int64_t time = rounds * (7400 + (chunks + s - 1) / s * 18);
+        const int64_t time = rounds * ((kept ? 900 : 7400) + (chunks + s - 1) / s * 18);
         // (chunk numbers of a slice and workgroup numbers have their limits)
         if (time < best && chunks / s < (1 << 20) && groups * s < (1 << 24)) {
             best = time;
