@@ -229,8 +229,8 @@ template <typename T> struct grid_token {
 
 // The grids of registered codebooks are the same in every append, so a context keeps them, once its appends have paid for
 // building them (pq_launch_encode), and a workgroup fetches the 80 KiB or so that are used of its four (fp16) instead of
-// building for 66 us: 32 heads x 32K tokens 641 -> 412 us, and from some 1000 tokens on appends do better with kept grids than
-// through the filter, where before 9000 had to pay for building them (32 heads x 4000 tokens 200 -> 85 us).  An image takes
+// building for 66 us: 32 heads x 32K tokens 641 -> 392 us, and from some 1000 tokens on appends do better with kept grids than
+// through the filter, where before 9000 had to pay for building them (32 heads x 4000 tokens 200 -> 84 us).  An image takes
 // 25 KiB per subspace (32 heads, K and V: 105 MB of memory).
 // A word per 4 subspaces says whether the image there is that of the codebooks in force.  It is on the device, so that
 // stream order and what a captured graph replays decide, not the host: registering codebooks puts it to GRID_ABSENT, and a
@@ -238,38 +238,44 @@ template <typename T> struct grid_token {
 // word behind the image (the exchange of pq_device_utils.h): an append on another stream finds a whole image or none.
 enum : uint32_t { GRID_ABSENT = 0, GRID_THERE = 1 };
 
-// words of a grid's image behind the cells that are used
-template <typename T> __device__ __forceinline__ int grid_image_words(const pq_grid<T> &g)
+// words of a subspace's pool that are used
+__device__ __forceinline__ int grid_pool_words(const pq_grid_map &m)
 {
-    const int pool = pq_grid_useless(g) || g.pool_used > GRID_POOL ? GRID_POOL : (int)g.pool_used;  // (useless: the wide coordinates)
-    return (int)(offsetof(pq_grid<T>, pool) / 4) + pool;
+    return pq_grid_useless(m) || m.pool_used > GRID_POOL ? GRID_POOL : (int)m.pool_used;  // (useless: the wide coordinates)
 }
 
-// image -> grids in LDS: 256 threads per subspace, 8 bytes each.  Requested together are the cells and, for most grids, all
-// that is used behind them: the coordinates, the map and the first 748 words of the pool (fp32: 492).  The filter's rows are
-// made anew, a thread each.
-template <typename T> __device__ __forceinline__ void grid_fetch(pq_grid<T> (&grid)[GRID_SUB], const char *images)
+// image -> grids in LDS, 8 bytes a thread and turn.  Requested together are coordinates, cells and maps and the first 512 words of
+// every pool, which is all that most grids use of theirs.  The filter's rows are made anew, a thread each.
+template <typename T> __device__ __forceinline__ void grid_fetch(pq_grids<T> &grids, const char *image)
 {
-    constexpr int TURNS = GRID_SIDE * GRID_SIDE / 512 + 2;
+    constexpr int THREADS = GRID_WAVES * 64, FRONT = (int)offsetof(pq_grids<T>, pool) / 8, TURNS = (FRONT + THREADS - 1) / THREADS;
+    static_assert(THREADS == GRID_SUB * 256 && sizeof(pq_grid_map) % 16 == 0, "256 threads per pool, whole vectors");
     const int j = threadIdx.x >> 8, c = threadIdx.x & 255;
-    pq_grid<T> &g = grid[j];
-    const float *image = (const float *)(images + j * pq_grid_image_bytes<T>());
-    float2 t[TURNS];
+    const float *pool_from = (const float *)(image + offsetof(pq_grids<T>, pool) + j * (GRID_POOL * 4));
+    float2 t[TURNS + 1];
 #pragma unroll
-    for (int k = 0; k < TURNS; ++k)
-        t[k] = fetch(image + 2 * (k * 256 + c));
+    for (int k = 0; k < TURNS; ++k) {
+        const int at = k * THREADS + (int)threadIdx.x;
+        t[k] = fetch((const float *)image + 2 * (at < FRONT ? at : FRONT - 1));
+    }
+    t[TURNS] = fetch(pool_from + 2 * c);
 #pragma unroll
-    for (int k = 0; k < TURNS; ++k)
-        ((float2 *)&g)[k * 256 + c] = t[k];
+    for (int k = 0; k < TURNS; ++k) {
+        const int at = k * THREADS + (int)threadIdx.x;
+        if (at < FRONT)
+            ((float2 *)&grids)[at] = t[k];
+    }
+    ((float2 *)grids.pool[j])[c] = t[TURNS];
     __syncthreads();
     bool bad = false;
-    const T mine[2] = {g.coord[c][0], g.coord[c][1]};
-    pq_filter_build_row<2>(mine, g.scale, g.arow + c * pq_filter_row_bytes<T>(), bad);
-    if ((g.again[c >> 5] >> (c & 31)) & 1u)
-        pq_filter_hide_row<2, T>(g.arow + c * pq_filter_row_bytes<T>());
-    const int words = grid_image_words(g);
-    for (int at = TURNS * 256 + c; 2 * at < words; at += 256)
-        ((float2 *)&g)[at] = fetch(image + 2 * at);
+    const T mine[2] = {grids.coord[j][c][0], grids.coord[j][c][1]};
+    const pq_grid_map &m = grids.map[j];
+    pq_filter_build_row<2>(mine, m.scale, grids.arow[j] + c * pq_filter_row_bytes<T>(), bad);
+    if ((m.again[c >> 5] >> (c & 31)) & 1u)
+        pq_filter_hide_row<2, T>(grids.arow[j] + c * pq_filter_row_bytes<T>());
+    const int words = grid_pool_words(m);
+    for (int at = 256 + c; 2 * at < words; at += 256)
+        ((float2 *)grids.pool[j])[at] = fetch(pool_from + 2 * at);
     __syncthreads();
 }
 
@@ -278,19 +284,23 @@ template <typename T>
 __global__ __launch_bounds__(GRID_WAVES * 64) void pq_grid_image_kernel(const T *codebook_k, const T *codebook_v, const int groups_k, void *images,
                                                                         unsigned int *grid_state)
 {
-    __shared__ __attribute__((aligned(16))) pq_grid<T> grid[GRID_SUB];
+    __shared__ __attribute__((aligned(16))) pq_grids<T> grids;
     __shared__ __attribute__((aligned(16))) pq_grid_scratch<false> scratch;
     __shared__ float2 box[GRID_SIDE];
 
     const int group = blockIdx.x;
     const T *src = group < groups_k ? codebook_k + (int64_t)group * (GRID_SUB * 512) : codebook_v + (int64_t)(group - groups_k) * (GRID_SUB * 512);
-    pq_grid_build(grid, scratch.making, box, src);
+    pq_grid_build(grids, scratch.making, box, src);
+    char *const image = (char *)images + (int64_t)group * pq_grid_image_bytes<T>();
+    const auto write = [&](const int from, const int bytes, const int first, const int step) {
+        for (int at = first * 8; at < bytes; at += step * 8) {
+            const float2 v = *(const float2 *)((const char *)&grids + from + at);
+            publish((float *)(image + from + at), v.x, v.y);
+        }
+    };
+    write(0, (int)offsetof(pq_grids<T>, pool), threadIdx.x, GRID_WAVES * 64);
     const int j = threadIdx.x >> 8;
-    const float2 *from = (const float2 *)&grid[j];
-    float *image = (float *)((char *)images + ((int64_t)group * GRID_SUB + j) * pq_grid_image_bytes<T>());
-    const int words = grid_image_words(grid[j]);
-    for (int at = threadIdx.x & 255; 2 * at < words; at += 256)
-        publish(image + 2 * at, from[at].x, from[at].y);
+    write((int)offsetof(pq_grids<T>, pool) + j * (GRID_POOL * 4), 4 * grid_pool_words(grids.map[j]), threadIdx.x & 255, 256);
     publish_wait();
     __syncthreads();
     if (threadIdx.x == 0)
@@ -302,7 +312,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
                                                                          const int slice_chunks)
 {
     constexpr int M = 64;
-    __shared__ __attribute__((aligned(16))) pq_grid<T> grid[GRID_SUB];
+    __shared__ __attribute__((aligned(16))) pq_grids<T> grids;
     constexpr bool KEEP = sizeof(T) == 2;
     __shared__ __attribute__((aligned(16))) pq_grid_scratch<KEEP> scratch;
     __shared__ float2 box[GRID_SIDE];
@@ -327,9 +337,9 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
         there = a.grids != nullptr ? __hip_atomic_load(a.grid_state + group, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (unsigned int)GRID_ABSENT;
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane((int)there) == (int)GRID_THERE)
-        grid_fetch<T>(grid, (const char *)a.grids + (int64_t)group * (GRID_SUB * pq_grid_image_bytes<T>()));
+        grid_fetch<T>(grids, (const char *)a.grids + (int64_t)group * pq_grid_image_bytes<T>());
     else
-        pq_grid_build(grid, scratch.making, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
+        pq_grid_build(grids, scratch.making, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
 
     const T *x = (const T *)a.x[which] + i0 * 2;
     uint8_t *codes = a.codes[which];
@@ -345,10 +355,11 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
         const int n = a.ctx_len[seq];
         return n < 0 ? 0 : n < cap ? n : cap;
     };
-    auto fetch = [&, b, r](int, grid_token<T> &k) mutable {
+    // (a sequence's length is loaded when its chunks begin, a chunk ahead: in front of every chunk's rows it was waited for,
+    // and for the codes on their way to memory with it)
+    auto fetch = [&, b, r, n_old = length(b < a.B ? b : a.B - 1)](int, grid_token<T> &k) mutable {
         const bool any = b < a.B;
         const int seq = any ? b : a.B - 1;
-        const int n_old = length(seq);
         const int t = r * 64 + lane - (n_old & 63);  // position among the new tokens
         const int pos = (n_old & ~63) + r * 64 + lane;
         k.live = any && t >= 0 && t < n_new && pos < cap;
@@ -362,9 +373,12 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
         __builtin_memcpy(k.x, part, sizeof(k.x));
         k.block = ((int64_t)seq * a.Hkv + hkv) * a.head_stride + (int64_t)((n_old >> 6) + r) * (64 * M);
         r += GRID_WAVES;
-        while (r >= seq_chunks && b < a.B) {
-            r -= seq_chunks;
-            ++b;
+        if (r >= seq_chunks && any) {
+            do {
+                r -= seq_chunks;
+                ++b;
+            } while (r >= seq_chunks && b < a.B);
+            n_old = length(b < a.B ? b : a.B - 1);
         }
     };
     const int n_old_first = length(0);
@@ -377,9 +391,21 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
         pos = n_old + t;
     };
     pq_grid_scan<T, KEEP, grid_token<T>>(
-        grid, scratch.queue, first, last, fetch,
-        [&](const grid_token<T> &k, int j, int code) {
-            codes[k.block + (uint32_t)pq_grid_pick(j, in_block[0], in_block[1], in_block[2], in_block[3])] = (uint8_t)code;
+        grids, scratch.queue, first, last, fetch,
+        [&](const grid_token<T> &k, int j, int code, bool decided) {
+            const int off = pq_grid_pick(j, in_block[0], in_block[1], in_block[2], in_block[3]);
+            if constexpr (sizeof(T) == 4) {  // (the other way 198 -> 202 us for 9000 tokens of 32 heads)
+                if (decided)
+                    codes[k.block + (uint32_t)off] = (uint8_t)code;
+                return;
+            }
+            // A store for every lane, those beyond the block's bytes dropped: with stores in branches the compiler does not know how
+            // many are on their way behind the next chunk's rows, and waits for all of them.
+            const uint64_t at = (uint64_t)codes + (uint64_t)k.block;
+            const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at) |
+                                  (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32;
+            const auto block = __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, 64 * M, 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code, block, decided ? off : -1, 0, 0);
         },
         [&](uint32_t id, T &x0, T &x1) {
             int seq, t, pos;
@@ -682,5 +708,5 @@ int64_t pq_grid_images_bytes(const pq_attn_config *cfg, int n_cu)
     const int64_t chunks = ((int64_t)cfg->batch * cfg->max_context + 63) / 64;
     if (pq_grid_slices(cfg->batch * seq_chunks, chunks, pq_grid_groups(cfg), n_cu, true) == 0)
         return 0;
-    return pq_grid_groups(cfg) * GRID_SUB * (cfg->dtype == PQ_F16 ? pq_grid_image_bytes<_Float16>() : pq_grid_image_bytes<float>());
+    return pq_grid_groups(cfg) * (cfg->dtype == PQ_F16 ? pq_grid_image_bytes<_Float16>() : pq_grid_image_bytes<float>());
 }

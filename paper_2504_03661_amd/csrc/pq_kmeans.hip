@@ -137,7 +137,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
                                                                          const int n_samples, const int slices, const int slice_chunks)
 {
     constexpr int M = 64;
-    __shared__ __attribute__((aligned(16))) pq_grid<_Float16> grid[GRID_SUB];
+    __shared__ __attribute__((aligned(16))) pq_grids<_Float16> grids;
     __shared__ __attribute__((aligned(16))) pq_grid_scratch<false> scratch;
     __shared__ float2 box[GRID_SIDE];
     __shared__ unsigned long long sum[GRID_SUB][512];
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
         ((unsigned long long *)sum)[e] = 0ull;
     for (int e = threadIdx.x; e < GRID_SUB * 256; e += GRID_WAVES * 64)
         ((unsigned int *)count)[e] = 0u;
-    pq_grid_build(grid, scratch.making, box, codebook + ((int64_t)head * M + i0) * 512);
+    pq_grid_build(grids, scratch.making, box, codebook + ((int64_t)head * M + i0) * 512);
 
     constexpr uint64_t BASE = 0x4338000000000000ull;  // the bits of 1.5 2^52
     const _Float16 *x = samples + (int64_t)head * n_samples * PQ_HEAD_DIM + i0 * 2;
@@ -170,15 +170,16 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
         atomicAdd(&count[j][code], 1u);
     };
     pq_grid_scan<_Float16, false, pq_sample>(
-        grid, scratch.queue, first, last,
+        grids, scratch.queue, first, last,
         [&](int chunk, pq_sample &k) {
             const int s = chunk * 64 + lane;
             k.live = s < n_samples;
             const f16x8 row = *(const f16x8 *)(x + (int64_t)(k.live ? s : n_samples - 1) * PQ_HEAD_DIM);
             __builtin_memcpy(k.x, &row, sizeof(k.x));
         },
-        [&](const pq_sample &k, int j, int code) {
-            add(j, code, pq_grid_pick(j, k.x[0][0], k.x[1][0], k.x[2][0], k.x[3][0]), pq_grid_pick(j, k.x[0][1], k.x[1][1], k.x[2][1], k.x[3][1]));
+        [&](const pq_sample &k, int j, int code, bool decided) {
+            if (decided)
+                add(j, code, pq_grid_pick(j, k.x[0][0], k.x[1][0], k.x[2][0], k.x[3][0]), pq_grid_pick(j, k.x[0][1], k.x[1][1], k.x[2][1], k.x[3][1]));
         },
         [&](uint32_t id, _Float16 &x0, _Float16 &x1) {
             const _Float16 *xp = x + ((int64_t)(first + (int)(id >> 8)) * 64 + (id >> 2 & 63u)) * PQ_HEAD_DIM + (id & 3u) * 2;

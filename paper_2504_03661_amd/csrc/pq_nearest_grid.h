@@ -4,13 +4,14 @@
 //
 // The filter of pq_nearest_filter.h looks at all 256 values of every token: 355 vector instructions per 64 tokens.  In two
 // dimensions the plane can be cut up once per codebook instead, and a token then looks at the 2 or 3 centroids of its cell:
-// 86 instructions with codebooks of random vectors, whose cells have long lists more often than trained ones'.  Building a
+// 68 instructions with codebooks of random vectors, whose cells have long lists more often than trained ones'.  Building a
 // grid takes 34 000, as many as 100 chunks of 64 tokens through the filter, so the grid serves appends and trainings of
-// thousands of tokens per head (pq_grid_slices below).  Encode (K and V), 32 heads x 32K tokens: 1549 -> 631 us, of which
-// some 265 us are the grids (latencies between barriers beside vector issue) and 365 us the tokens.  k-means, 32 heads x 64K
-// samples, 2 iterations: 3148 -> 990 us.
+// thousands of tokens per head (pq_grid_slices below).  Encode (K and V), 32 heads x 32K tokens, kept grids: 392 us, of which 36
+// us are workgroups' starts, image loads and ends, 184 the tokens' main path, which vector issue bounds (220 instructions per 64
+// tokens and 4 subspaces), and, each left out by itself: 63 the stores of the codes, a byte per token and subspace, 61 the tokens that
+// wait, 34 the rows from memory (1549 us through the filter).  k-means, 32 heads x 64K samples, 2 iterations: 3148 -> 975 us.
 //
-// Map.  Per axis u = s x + o, fp32, chosen from the codebook (mean and mean deviation of its coordinates without outliers):
+// Map.  Per axis u = s x + o, chosen from the codebook (mean and mean deviation of its coordinates without outliers):
 // |u| <= 28 holds what lies within some 4 standard deviations.  The cell coordinate is five bits of the float |u| + 2 — 8
 // cells in each of the four octaves [2, 4) .. [16, 32), fine in the middle and coarse outside, for an addition and a shift —
 // and the sign.  64 x 64 cells of 4 bytes.  The last cell on each side takes everything beyond: no list, "outside".
@@ -23,18 +24,18 @@
 // The test runs in fp32 in u space, where a squared distance is w_x du_x^2 + w_y du_y^2: every F is lowered by 2^-18 of its
 // |c|^2 / 2 and the threshold raised by 2^-16 (|r|^2 / 2 + |g|^2 + ..), 16 times what the roundings of u, F and w amount to;
 // boxes are 2^-17 wider on each side than the cells (the float |u| + 2 is good to 2^-19).
-// A cell's word holds its codes if they are at most 4, filled up with codes that are not in its list; otherwise the two low
-// bytes are equal (which the distinct codes of a list never are): the number of words, and in the upper half where they
-// stand in the pool.  Outside, where there is no room, or more than 64 candidates in the block: GRID_NONE.
+// A cell's word holds its codes if they are at most 4, filled up with codes that are not in its list; otherwise its halves
+// are equal (which those of a list never are): where its words stand in the pool, and how many they are.  Outside, where there is
+// no room, or more than 64 candidates in the block: GRID_NONE.
 // Tokens.  The four distances in fp32 (relative error below 2^-21), their 8 low bits replaced by the code: one unsigned
 // minimum gives the least and its code, one median keeps the second.  More than 2^-16 apart, the order is that of the fp64
-// distances; the others ("unsure": also those outside and in cells without a list) are put off until 64 of a subspace can go
-// through the filter together, and where the codebook gives no useful grid all its tokens go there at once.  Tokens of cells
-// with longer lists (7 % with a codebook of random vectors, 1 % with a trained one) wait in LDS until 64 are there and are then
-// worked on as one.
+// distances.  The others wait in LDS until 64 are there and are then worked on as one: tokens of cells with longer lists (7 % with a
+// codebook of random vectors, 1 % with a trained one), whose word gives the least distance twice, in the same way.  What these
+// leave undecided ("unsure": near-ties, outside, cells without a list) is put off until 64 of a subspace can go through the filter
+// together, and where the codebook gives no useful grid all its tokens go there at once.
 // What the data make of it, 32 heads, us, grids built / kept from an earlier append / the filter alone: encode of 9000 tokens,
-// normal 364 / 140 / 440, Laplace's distribution 411 / 185 / 441, 2 % of the coordinates times 20 414 / 191 / 446; of 32K 631 / 410
-// / 1590, 803 / 575 / 1596, 816 / 594 / 1610.  Centroids that repeat others are taken out: 16 values in all 1480 kept, 2496 by the
+// normal 360 / 136 / 440, Laplace's distribution 390 / 158 / 441, 2 % of the coordinates times 20 395 / 165 / 446; of 32K 630 / 392
+// / 1590, 710 / 477 / 1596, 730 / 499 / 1610.  Centroids that repeat others are taken out: 16 values in all 1480 kept, 2496 by the
 // filter (9000 tokens; 2850 when a repeated centroid made its tokens unsure), k-means of 64K samples rounded to quarters 18.5 ->
 // 8.1 ms.  A codebook without a useful grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every
 // subspace 863 / 757 and 3000 / 2611.
@@ -69,28 +70,42 @@ constexpr float GRID_LOWERED = 3.814697265625e-06f;   // 2^-18: shares of |c|^2 
 constexpr float GRID_MARGIN = 1.52587890625e-05f;     // 2^-16: .. that the threshold is raised by,
 constexpr float GRID_WIDER = 7.62939453125e-06f;      // 2^-17: and what boxes have more on each side than their cells
 constexpr int GRID_LONGEST = 64;  // candidates of a block (a bit each in a 64-bit mask)
-constexpr uint32_t GRID_NONE = 0x01000100u;  // a cell without a list: two codes, twice, so that the least has an equal
+constexpr uint32_t GRID_NONE = 0;  // a cell without a list: a list of no words
 constexpr uint32_t GRID_SURE = 512;  // keys at least this far apart are in the right order
 
-template <typename T> struct pq_grid {
-    // (what stands in front of arow is a grid's image in memory, its pool as far as it is used)
-    uint32_t cell[GRID_SIDE * GRID_SIDE];  // [u_x][u_y]; while building, the 64 bytes of a 4 x 4 block are its list
-    T coord[256][2];
-    float sx, ox, sy, oy;  // the map
+// The map of a subspace and what is known of its grid.  fp16: the factors are fp16 numbers, and a token's cell is found in fp16,
+// both axes at once: 8 instructions instead of the 14 of fp32.  A rounding of 2^-11 of |u| and one of |u| + 2 then move a token
+// by 2^-10 (|u| + 2) at most, which the boxes allow for (GRID_WIDER_F16).
+struct pq_grid_map {
+    float sx, ox, sy, oy;
+    uint32_t s16, o16;     // (fp16: x in the low half)
     float scale;           // of the filter
     uint32_t pool_used, bad;  // bad: 1 no grid, 2 codebook outside the filter's range
     uint32_t lost, unserved;  // how many centroids the grid does not serve: counted before and after its lists
     uint32_t again[8];     // a bit per centroid: equal to one before it
-    __attribute__((aligned(16))) uint32_t pool[GRID_POOL];
-    unsigned char arow[256 * pq_filter_row_bytes<T>()];
+    uint32_t unused;
 };
-template <typename T> constexpr int pq_grid_image_bytes() { return (int)offsetof(pq_grid<T>, arow); }
+constexpr float GRID_WIDER_F16 = 1.1e-3f;  // of |u| + 2 (2^-10 is 0.98e-3)
+
+// The grids of a workgroup.  Coordinates and cells stand where the 16 bits of an LDS instruction's offset reach those of all
+// four (bases apart cost an addition for every look-up); the cells of the four are interleaved, so that the two bytes of a token's
+// cell are its address as they are.
+template <typename T> struct pq_grids {
+    // (what stands in front of arow is the image in memory that a context keeps, the pools as far as they are used)
+    T coord[GRID_SUB][256][2];
+    uint32_t cell[GRID_SIDE][GRID_SUB][GRID_SIDE];  // [u_x][][u_y]; while building, the 64 bytes of a 4 x 4 block are its list
+    pq_grid_map map[GRID_SUB];
+    __attribute__((aligned(16))) uint32_t pool[GRID_SUB][GRID_POOL];
+    __attribute__((aligned(16))) unsigned char arow[GRID_SUB][256 * pq_filter_row_bytes<T>()];
+};
+constexpr int GRID_ROW = 4 * GRID_SUB * GRID_SIDE;  // bytes from one u_x to the next
+template <typename T> constexpr int pq_grid_image_bytes() { return (int)offsetof(pq_grids<T>, arow); }
 
 // The tokens are taken to lie where the centroids do: where many of the 256 are left to the filter (in cells without a list), it
 // does all the work of the subspace.  (For 64 tokens: 86 instructions for the look-ups,
 // some 30 for putting tokens off and for 24 of them 135 in the filter; 355 through the filter alone, and building is saved.)
 constexpr int GRID_LOST = 96;
-template <typename T> __device__ __forceinline__ bool pq_grid_useless(const pq_grid<T> &g) { return g.bad != 0 || g.lost > GRID_LOST || g.unserved > GRID_LOST; }
+__device__ __forceinline__ bool pq_grid_useless(const pq_grid_map &m) { return m.bad != 0 || m.lost > GRID_LOST || m.unserved > GRID_LOST; }
 
 // What building a grid needs of its centroids: a_x, a_y, |c|^2 / 2 lowered, |c|^2 / 2; how many of them lie in each block of
 // 4 x 4 cells, 16 bits each (repeated ones not counted); and the first of those whose coordinates have the same hash.  The
@@ -123,18 +138,45 @@ __device__ __forceinline__ uint32_t pq_grid_axis(const float u)
     return b ^ (uint32_t)(__float_as_int(u) >> 31);
 }
 
-// byte offset of the cell of a point
-template <typename T>
-__device__ __forceinline__ uint32_t pq_grid_cell(const T x, const T y, const float sx, const float ox, const float sy, const float oy)
+// byte offset of the cell of a point among those of subspace 0, s, o: pq_grid_map's
+__device__ __forceinline__ uint32_t pq_grid_cell(const float x, const float y, const float sx, const float ox, const float sy, const float oy)
 {
-    const uint32_t ex = pq_grid_axis(__builtin_fmaf((float)x, sx, ox));
-    const uint32_t ey = pq_grid_axis(__builtin_fmaf((float)y, sy, oy));
-    static_assert(GRID_SHIFT == 20 && GRID_SIDE == 64, "the shifts below");
-    return ((ex >> 12) & 0x3f00u) | ((ey >> 18) & 0xfcu);
+    const uint32_t ex = pq_grid_axis(__builtin_fmaf(x, sx, ox));
+    const uint32_t ey = pq_grid_axis(__builtin_fmaf(y, sy, oy));
+    static_assert(GRID_SHIFT == 20 && GRID_SIDE == 64 && GRID_ROW == 1024, "the shifts below");
+    return ((ex >> 10) & 0xfc00u) | ((ey >> 18) & 0xfcu);
+}
+
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+
+// the same in fp16; xy: the point as it stands in memory
+__device__ __forceinline__ uint32_t pq_grid_cell_f16(const uint32_t xy, const uint32_t s16, const uint32_t o16)
+{
+    const f16x2 u = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, xy), __builtin_bit_cast(f16x2, s16), __builtin_bit_cast(f16x2, o16));
+    const uint32_t bits = __builtin_bit_cast(uint32_t, u);
+    f16x2 w = __builtin_bit_cast(f16x2, bits & 0x7fff7fffu) + (f16x2){(_Float16)GRID_BIAS, (_Float16)GRID_BIAS};
+    const _Float16 last = __builtin_bit_cast(_Float16, (uint16_t)0x4fff);  // just below 32
+    w = __builtin_elementwise_min(w, (f16x2){last, last});
+    // bits 7 .. 12 of each half are its cell coordinate, complemented where u is negative
+    const uint32_t five = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, w) >> (u16x2){5, 5});
+    const uint32_t sign = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2, bits) >> (i16x2){15, 15});
+    const uint32_t e = (five ^ sign) & 0x00fc00fcu;
+    return __builtin_amdgcn_perm(e, e, 0x0c0c0002u);
+}
+
+// the cell of a point of a subspace with a map in memory
+template <typename T> __device__ __forceinline__ uint32_t pq_grid_cell_of(const T x, const T y, const pq_grid_map &m)
+{
+    if constexpr (sizeof(T) == 2)
+        return pq_grid_cell_f16((uint32_t)__builtin_bit_cast(uint16_t, x) | (uint32_t)__builtin_bit_cast(uint16_t, y) << 16, m.s16, m.o16);
+    else
+        return pq_grid_cell(x, y, m.sx, m.ox, m.sy, m.oy);
 }
 
 // the block of 4 x 4 cells of a cell's byte offset: [x][y] of 16
-__device__ __forceinline__ uint32_t pq_grid_block(const uint32_t cell) { return (cell >> 6 & 0xf0u) | (cell >> 4 & 15u); }
+__device__ __forceinline__ uint32_t pq_grid_block(const uint32_t cell) { return (cell >> 8 & 0xf0u) | (cell >> 4 & 15u); }
 
 // lower edge of cell coordinate k = -32 .. 32 (31 and -32: the open ones, given an end)
 __device__ __forceinline__ float pq_grid_edge(const int k)
@@ -180,9 +222,10 @@ template <typename T> __device__ __forceinline__ bool pq_grid_unsure(const uint3
 // A wavefront's part of a subspace's tables: the map, which all 4 wavefronts work out alike, and the rows and numbers of
 // centroids 64 part .. 64 part + 63.  src: [256][2]; cell, hash: of centroid 64 part + lane
 template <typename T>
-__device__ __forceinline__ void pq_grid_tables(pq_grid<T> &g, pq_grid_table &table, uint32_t (&first_of)[256], const T *src, const int part,
-                                      uint32_t &cell, uint32_t &hash)
+__device__ __forceinline__ void pq_grid_tables(pq_grids<T> &grids, const int sub, pq_grid_table &table, uint32_t (&first_of)[256], const T *src,
+                                               const int part, uint32_t &cell, uint32_t &hash)
 {
+    pq_grid_map &m = grids.map[sub];
     const int lane = threadIdx.x & 63;
     float x[4], y[4];
     T mine[2] = {};
@@ -229,14 +272,25 @@ __device__ __forceinline__ void pq_grid_tables(pq_grid<T> &g, pq_grid_table &tab
         ex = 3.0f * dx;
         ey = 3.0f * dy;
     }
-    const float sx = GRID_COVER / (GRID_DEVIATIONS * dx), sy = GRID_COVER / (GRID_DEVIATIONS * dy);
-    const float ox = -mx * sx, oy = -my * sy;
+    float sx = GRID_COVER / (GRID_DEVIATIONS * dx), sy = GRID_COVER / (GRID_DEVIATIONS * dy);
+    float ox = -mx * sx, oy = -my * sy;
+    bool usable = dx > 1.0e-30f && dy > 1.0e-30f && c_max < 1.0e30f;
+    if constexpr (sizeof(T) == 2) {
+        // (deviations below 1e-4: coarser cells; an offset this large would move the middle by its rounding)
+        sx = (float)(_Float16)fminf(sx, 60000.f);
+        sy = (float)(_Float16)fminf(sy, 60000.f);
+        ox = -mx * sx;
+        oy = -my * sy;
+        usable = usable && sx > 1.0e-4f && sy > 1.0e-4f && fabsf(ox) < 4096.f && fabsf(oy) < 4096.f;
+        ox = (float)(_Float16)ox;
+        oy = (float)(_Float16)oy;
+    }
     // squared distances in units of 1 / s_x^2
     const float ratio = sx / sy, wy = ratio * ratio;
-    bool usable = dx > 1.0e-30f && dy > 1.0e-30f && c_max < 1.0e30f && wy > 1.0e-9f && wy < 1.0e9f;
+    usable = usable && wy > 1.0e-9f && wy < 1.0e9f;
     bool far_out = false, cb_bad = false;
     const int c = 64 * part + lane;
-    pq_filter_build_row<2>(mine, scale, g.arow + c * pq_filter_row_bytes<T>(), cb_bad);
+    pq_filter_build_row<2>(mine, scale, grids.arow[sub] + c * pq_filter_row_bytes<T>(), cb_bad);
     const float ux = __builtin_fmaf((float)mine[0], sx, ox), uy = __builtin_fmaf((float)mine[1], sy, oy);
     far_out = !(fabsf(ux) < 1.0e6f && fabsf(uy) < 1.0e6f);
     const float ay = wy * uy, n = 0.5f * (ux * ux + uy * ay);
@@ -244,23 +298,29 @@ __device__ __forceinline__ void pq_grid_tables(pq_grid<T> &g, pq_grid_table &tab
     table[c][1] = ay;
     table[c][2] = n * (1.0f - GRID_LOWERED);
     table[c][3] = n;
-    g.coord[c][0] = mine[0];
-    g.coord[c][1] = mine[1];
-    cell = pq_grid_cell(mine[0], mine[1], sx, ox, sy, oy);
+    grids.coord[sub][c][0] = mine[0];
+    grids.coord[sub][c][1] = mine[1];
+    const auto both = [](float lo, float hi) {
+        return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)lo) | (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)hi) << 16;
+    };
+    const pq_grid_map here = {sx, ox, sy, oy, both(sx, sy), both(ox, oy)};
+    cell = pq_grid_cell_of(mine[0], mine[1], here);
     hash = pq_grid_hash(mine[0], mine[1]);
     atomicMin(&first_of[hash], (uint32_t)c);
     const uint32_t bad = (__builtin_amdgcn_ballot_w64(far_out) != 0 || !usable ? 1u : 0u) |
                          (__builtin_amdgcn_ballot_w64(cb_bad) != 0 ? 3u : 0u);
     if (lane == 0) {
         if (part == 0) {
-            g.sx = sx;
-            g.ox = ox;
-            g.sy = sy;
-            g.oy = oy;
-            g.scale = scale;
+            m.sx = sx;
+            m.ox = ox;
+            m.sy = sy;
+            m.oy = oy;
+            m.s16 = here.s16;
+            m.o16 = here.o16;
+            m.scale = scale;
         }
         if (bad)
-            atomicOr(&g.bad, bad);
+            atomicOr(&m.bad, bad);
     }
 }
 
@@ -272,12 +332,14 @@ __device__ __forceinline__ void pq_grid_fence()
 }
 
 // centre and half side of cell coordinates e .. e + n - 1 (e as in pq_grid_axis)
-__device__ __forceinline__ void pq_grid_box(const int e, const int n, float &g, float &h)
+template <typename T> __device__ __forceinline__ void pq_grid_box(const int e, const int n, float &g, float &h)
 {
     const int k = e < 32 ? e : e - 64;
     const float lo = pq_grid_edge(k), hi = pq_grid_edge(k + n);
     g = 0.5f * (lo + hi);
     h = 0.5f * (hi - lo) + GRID_WIDER;
+    if constexpr (sizeof(T) == 2)
+        h = __builtin_fmaf(fmaxf(-lo, hi) + GRID_BIAS, GRID_WIDER_F16, h);
 }
 
 // Appending the bit t <= limit to a mask is a comparison and an addition with carry.  What a vector instruction writes to VCC
@@ -334,6 +396,13 @@ template <int K> __device__ __forceinline__ void pq_grid_row_fma(float &v, const
         : "+&v"(v) : "v"(x), "v"(ax), "v"(y), "v"(ay), "n"(K));
 }
 
+// the word of a cell with a longer list: both halves say where its words stand in the pool and how many they are
+__device__ __forceinline__ uint32_t pq_grid_list_word(const uint32_t at, const uint32_t words)
+{
+    static_assert(GRID_POOL <= 2048 && GRID_LONGEST / 4 < 32, "11 and 5 bits");
+    return (at | words << 11) * 0x10001u;
+}
+
 // calls f(K, K + 1), integral constants, for the even K < N while K is below `most` (uniform)
 template <int K, int N, typename F> __device__ __forceinline__ void pq_grid_twos(const int most, F f)
 {
@@ -347,11 +416,16 @@ template <int K, int N, typename F> __device__ __forceinline__ void pq_grid_twos
 
 // The lists of one quarter of the grid (cell rows 16 part .. 16 part + 15), by one wavefront.  box: centre and half side of
 // the 64 cell coordinates
-template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &g, const pq_grid_table &table, const float2 (&box)[GRID_SIDE], const int part)
+template <typename T>
+__device__ __forceinline__ void pq_grid_lists(pq_grids<T> &grids, const int sub, const pq_grid_table &table, const float2 (&box)[GRID_SIDE],
+                                              const int part)
 {
     const int lane = threadIdx.x & 63;
-    unsigned char *bytes = (unsigned char *)g.cell;
-    const float sx = g.sx, ox = g.ox, sy = g.sy, oy = g.oy;
+    pq_grid_map &m = grids.map[sub];
+    unsigned char *bytes = (unsigned char *)grids.cell[0][sub];
+    // where candidate k of a block's list stands behind its first byte: 16 in each of the block's rows of cells
+    const auto place = [](const uint32_t k) { return k + __umul24(k & 48u, GRID_ROW / 16 - 1); };
+    const float sx = m.sx, ox = m.ox, sy = m.sy, oy = m.oy;
     const float ratio = sx / sy, wy = ratio * ratio;
 
     // ---- lane = block of 4 x 4 cells, all centroids
@@ -359,15 +433,16 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
     uint32_t fill = 0;  // a code that is not in the block's list
     {
         const int bx = part * 4 + (lane >> 4), by = lane & 15;
-        const uint32_t list = (uint32_t)(bx * 1024 + by * 16);  // its bytes: 16 at each of list + 256 k
+        const uint32_t list = (uint32_t)(bx * 4 * GRID_ROW + by * 16);
         float gx, hx, gy, hy;
-        pq_grid_box(4 * bx, 4, gx, hx);
-        pq_grid_box(4 * by, 4, gy, hy);
+        pq_grid_box<T>(4 * bx, 4, gx, hx);
+        pq_grid_box<T>(4 * by, 4, gy, hy);
         const float px = (gx - ox) / sx, py = (gy - oy) / sy;
         const float end = sizeof(T) == 2 ? 60000.f : 3.0e37f;
         const T p[2] = {(T)fminf(fmaxf(px, -end), end), (T)fminf(fmaxf(py, -end), end)};
         typedef typename std::conditional<sizeof(T) == 4, float, _Float16>::type W;
-        const int r = pq_filter_code<2, T, W>(g.arow, sizeof(T) == 4 ? (const unsigned char *)g.coord : g.arow, g.scale, false, p, true);
+        const int r = pq_filter_code<2, T, W>(grids.arow[sub], sizeof(T) == 4 ? (const unsigned char *)grids.coord[sub] : grids.arow[sub],
+                                                   m.scale, false, p, true);
         const float4 ref = *(const float4 *)table[r];
         const float far_x = fabsf(gx) + hx, far_y = fabsf(gy) + hy;
         const float limit = __builtin_fmaf(-gy, ref.y, __builtin_fmaf(-gx, ref.x, ref.z)) +
@@ -394,7 +469,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
             while (__builtin_amdgcn_ballot_w64(mask != 0) != 0) {
                 if (mask != 0) {
                     const int k = __builtin_clz(mask);
-                    bytes[list + (uint32_t)count + __umul24((uint32_t)count & 48u, 15u)] = (unsigned char)(w + k);
+                    bytes[list + place((uint32_t)count)] = (unsigned char)(w + k);
                     ++count;
                     mask ^= 0x80000000u >> k;
                 }
@@ -403,10 +478,10 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
         }
         // Lists are filled up to whole words with a code that is not in them: it is never the least, and being there more
         // than once it hides no second least.
-        const uint32_t others = used | g.again[0];  // (a repetition of a listed one would be as near as that)
+        const uint32_t others = used | m.again[0];  // (a repetition of a listed one would be as near as that)
         fill = (uint32_t)__builtin_ctz(~others | 0x80000000u);
         for (int k = count; (k & 3) != 0 && k < GRID_LONGEST; ++k)
-            bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))] = (unsigned char)fill;
+            bytes[list + place((uint32_t)k)] = (unsigned char)fill;
         count = others == 0xffffffffu ? GRID_LONGEST + 1 : count;  // (none to fill up with: no list)
     }
     pq_grid_fence();
@@ -430,7 +505,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
         const int n = __shfl(count, block);
         const int cell_x = 4 * (part * 4 + (block >> 4)) + (in_row >> 2);
         const int cell_y = 4 * (block & 15) + (in_row & 3);
-        const uint32_t list = (uint32_t)((part * 4 + (block >> 4)) * 1024 + (block & 15) * 16);
+        const uint32_t list = (uint32_t)((part * 4 + (block >> 4)) * (4 * GRID_ROW) + (block & 15) * 16);
         const int longest = __builtin_amdgcn_readlane(n, 63);  // of the 4 blocks: the last
         uint32_t word = 0;
         const bool inside = cell_x != 31 && cell_x != 32 && cell_y != 31 && cell_y != 32;
@@ -448,7 +523,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
             const uint32_t words = (uint32_t)(total + 3) >> 2;
             uint32_t at = GRID_POOL;
             if (listed)
-                at = atomicAdd(&g.pool_used, words);
+                at = atomicAdd(&m.pool_used, words);
             const bool fits = listed && at + words <= GRID_POOL;
             mask = fits ? mask : 0;
             for (uint32_t w = 0; __builtin_amdgcn_ballot_w64(mask != 0) != 0; ++w) {
@@ -457,15 +532,15 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int k = LONG ? __builtin_clzll(mask | 1u) : __builtin_clz((uint32_t)mask | 1u);
-                    const uint32_t c = bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))];
+                    const uint32_t c = bytes[list + place((uint32_t)k)];
                     four = mask != 0 ? __builtin_amdgcn_perm(c, four, 0x03020100u + ((4u - (uint32_t)j) << (8 * j))) : four;
                     mask &= ~((decltype(mask))1 << (LONG ? 63 - k : 31 - k));
                 }
                 if (any)
-                    g.pool[at + w] = four;
+                    grids.pool[sub][at + w] = four;
             }
             if (listed)
-                word = fits ? words | words << 8 | at << 16 : GRID_NONE;
+                word = fits ? pq_grid_list_word(at, words) : GRID_NONE;
         };
         if (__builtin_amdgcn_readlane(n, 0) <= 32) {
             const int most = longest < 32 ? longest : 32;
@@ -475,7 +550,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
             uint32_t code2 = code1;
             float4 second = first;
             if (most > 16) {
-                code2 = bytes[list + 256u + (uint32_t)in_row];
+                code2 = bytes[list + GRID_ROW + (uint32_t)in_row];
                 second = *(const float4 *)table[code2];
                 second.z = in_row + 16 < n ? second.z : 1.0e30f;
             }
@@ -493,7 +568,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
                 distance(K0);
                 distance(K1);
             });
-            const float4 ref = *(const float4 *)table[bytes[list + (uint32_t)(((least >> 4) & 1) * 256 + (least & 15))]];
+            const float4 ref = *(const float4 *)table[bytes[list + place((uint32_t)least & 31u)]];
             const float nearest = __int_as_float(least & ~31);
             const float limit = nearest + GRID_MARGIN * (2.f * fabsf(nearest) + ref.w + far);
             uint32_t mask = 0, marked = fill_cell;
@@ -519,7 +594,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
         if (longest > 32 && __builtin_amdgcn_ballot_w64(n > 32 && n <= GRID_LONGEST) != 0) {
             const int most = longest < GRID_LONGEST ? longest : GRID_LONGEST;
             auto sixteen = [&](const int q) {
-                float4 e = *(const float4 *)table[bytes[list + (uint32_t)(q * 256 + in_row)]];
+                float4 e = *(const float4 *)table[bytes[list + (uint32_t)(q * GRID_ROW + in_row)]];
                 e.z = 16 * q + in_row < n ? e.z : 1.0e30f;
                 return e;
             };
@@ -537,7 +612,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
                     distance(K1);
                 });
             }
-            const float4 ref = *(const float4 *)table[bytes[list + (uint32_t)(((least >> 4) & 3) * 256 + (least & 15))]];
+            const float4 ref = *(const float4 *)table[bytes[list + place((uint32_t)least & 63u)]];
             const float nearest = __int_as_float(least & ~63);
             const float limit = nearest + GRID_MARGIN * (2.f * fabsf(nearest) + ref.w + far);
             uint64_t mask = 0;  // candidate k in bit 63 - k
@@ -563,7 +638,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
                 word = fill_cell;
                 for (uint64_t left = mask; left != 0;) {
                     const int k = __builtin_clzll(left);
-                    word = word << 8 | bytes[list + (uint32_t)((k >> 4) * 256 + (k & 15))];
+                    word = word << 8 | bytes[list + place((uint32_t)k)];
                     left &= ~(1ull << (63 - k));
                 }
             }
@@ -571,7 +646,7 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
             if (__builtin_amdgcn_ballot_w64(listed) != 0)
                 write_list(mask, listed);
         }
-        g.cell[cell_x * GRID_SIDE + cell_y] = inside && n <= GRID_LONGEST ? word : GRID_NONE;
+        grids.cell[cell_x][sub][cell_y] = inside && n <= GRID_LONGEST ? word : GRID_NONE;
     }
 }
 
@@ -579,18 +654,19 @@ template <typename T> __device__ __forceinline__ void pq_grid_lists(pq_grid<T> &
 // tokens have one nearest centroid (left in, a token there was unsure, and a codebook of some 100 values no case for a
 // grid).  A repetition behind a clash of hashes is not seen, and costs time only.
 template <typename T>
-__device__ __forceinline__ bool pq_grid_take_out(pq_grid<T> &g, pq_grid_table &table, uint32_t (&in_block)[128], const uint32_t (&first_of)[256],
-                                                 const int part, const uint32_t cell, const uint32_t hash)
+__device__ __forceinline__ bool pq_grid_take_out(pq_grids<T> &grids, const int sub, pq_grid_table &table, uint32_t (&in_block)[128],
+                                                 const uint32_t (&first_of)[256], const int part, const uint32_t cell, const uint32_t hash)
 {
     const int lane = threadIdx.x & 63, c = 64 * part + lane;
     const int other = (int)first_of[hash];
-    const bool again = other < c && g.coord[other][0] == g.coord[c][0] && g.coord[other][1] == g.coord[c][1];
+    const T(&coord)[256][2] = grids.coord[sub];
+    const bool again = other < c && coord[other][0] == coord[c][0] && coord[other][1] == coord[c][1];
     const uint64_t of = __builtin_amdgcn_ballot_w64(again);
     if (lane < 2)
-        g.again[2 * part + lane] = (uint32_t)(of >> (32 * lane));
+        grids.map[sub].again[2 * part + lane] = (uint32_t)(of >> (32 * lane));
     const uint32_t block = pq_grid_block(cell);
     if (again) {
-        pq_filter_hide_row<2, T>(g.arow + c * pq_filter_row_bytes<T>());
+        pq_filter_hide_row<2, T>(grids.arow[sub] + c * pq_filter_row_bytes<T>());
         table[c][2] = 1.0e30f;  // far from everywhere
     } else {
         atomicAdd(&in_block[block >> 1], 1u << (16 * (block & 1u)));
@@ -603,59 +679,59 @@ __device__ __forceinline__ bool pq_grid_take_out(pq_grid<T> &g, pq_grid_table &t
 // clusters).
 __device__ __forceinline__ int pq_grid_lost(const uint32_t (&in_block)[128], const uint32_t cell, const bool again)
 {
-    const uint32_t ex = cell >> 8, ey = cell >> 2 & 63u, block = pq_grid_block(cell);
+    const uint32_t ex = cell >> 10, ey = cell >> 2 & 63u, block = pq_grid_block(cell);
     const bool outside = ex - 31u < 2u || ey - 31u < 2u;
     const uint32_t n = in_block[block >> 1] >> (16 * (block & 1u)) & 0xffffu;
     return __builtin_popcountll(__builtin_amdgcn_ballot_w64(!again && (outside || n > GRID_LONGEST)));
 }
 
 // Builds the grids of a workgroup's 4 subspaces.  src: the codebook of the first of them, [4][256][2]
-template <typename T> __device__ __forceinline__ void pq_grid_build(pq_grid<T> (&grid)[GRID_SUB], pq_grid_making &making, float2 (&box)[GRID_SIDE], const T *src)
+template <typename T> __device__ __forceinline__ void pq_grid_build(pq_grids<T> &grids, pq_grid_making &making, float2 (&box)[GRID_SIDE], const T *src)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    pq_grid<T> &g = grid[wave >> 2];
-    const int part = wave & 3;
+    const int sub = wave >> 2, part = wave & 3;
+    pq_grid_map &m = grids.map[sub];
     if (threadIdx.x < GRID_SUB) {
-        grid[threadIdx.x].pool_used = 0;
-        grid[threadIdx.x].bad = 0;
-        grid[threadIdx.x].lost = 0;
-        grid[threadIdx.x].unserved = 0;
+        grids.map[threadIdx.x].pool_used = 0;
+        grids.map[threadIdx.x].bad = 0;
+        grids.map[threadIdx.x].lost = 0;
+        grids.map[threadIdx.x].unserved = 0;
     }
     if (threadIdx.x < GRID_SIDE)
-        pq_grid_box((int)threadIdx.x, 1, box[threadIdx.x].x, box[threadIdx.x].y);
+        pq_grid_box<T>((int)threadIdx.x, 1, box[threadIdx.x].x, box[threadIdx.x].y);
     if (threadIdx.x < GRID_SUB * 128)
         ((uint32_t *)making.in_block)[threadIdx.x] = 0;
     ((uint32_t *)making.first_of)[threadIdx.x] = 255;
     __syncthreads();
     uint32_t cell, hash;
-    pq_grid_tables(g, making.table[wave >> 2], making.first_of[wave >> 2], src + (wave >> 2) * 512, part, cell, hash);
+    pq_grid_tables(grids, sub, making.table[sub], making.first_of[sub], src + sub * 512, part, cell, hash);
     __syncthreads();
-    const bool again = pq_grid_take_out(g, making.table[wave >> 2], making.in_block[wave >> 2], making.first_of[wave >> 2], part, cell, hash);
+    const bool again = pq_grid_take_out(grids, sub, making.table[sub], making.in_block[sub], making.first_of[sub], part, cell, hash);
     __syncthreads();
-    const int n_lost = pq_grid_lost(making.in_block[wave >> 2], cell, again);
+    const int n_lost = pq_grid_lost(making.in_block[sub], cell, again);
     if (lane == 0)
-        atomicAdd(&g.lost, (uint32_t)n_lost);
+        atomicAdd(&m.lost, (uint32_t)n_lost);
     __syncthreads();
-    const bool lists = g.bad == 0 && g.lost <= GRID_LOST;  // (the same for the 4 wavefronts)
+    const bool lists = m.bad == 0 && m.lost <= GRID_LOST;  // (the same for the 4 wavefronts)
     if (lists)
-        pq_grid_lists(g, making.table[wave >> 2], box, part);
+        pq_grid_lists(grids, sub, making.table[sub], box, part);
     __syncthreads();
     if (lists) {
-        const uint32_t word = *(const uint32_t *)((const char *)g.cell + cell);
+        const uint32_t word = *(const uint32_t *)((const char *)grids.cell[0][sub] + cell);
         const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(word == GRID_NONE));
         if (lane == 0 && n != 0)
-            atomicAdd(&g.unserved, (uint32_t)n);
+            atomicAdd(&m.unserved, (uint32_t)n);
     }
     __syncthreads();
-    if (pq_grid_useless(g)) {
-        for (int k = part * 64 + lane; k < GRID_SIDE * GRID_SIDE; k += 256)
-            g.cell[k] = GRID_NONE;
+    if (pq_grid_useless(m)) {
+        for (int k = part; k < GRID_SIDE; k += 4)
+            grids.cell[k][sub][lane] = GRID_NONE;
         if constexpr (sizeof(T) == 2) {  // what the filter refines with, in place of the lists
             const int c = 64 * part + lane;
-            double *wide = (double *)g.pool + 2 * c;
-            wide[0] = (double)((float)g.coord[c][0] * g.scale);
-            wide[1] = (double)((float)g.coord[c][1] * g.scale);
+            double *wide = (double *)grids.pool[sub] + 2 * c;
+            wide[0] = (double)((float)grids.coord[sub][c][0] * m.scale);
+            wide[1] = (double)((float)grids.coord[sub][c][1] * m.scale);
         }
     }
     __syncthreads();
@@ -673,7 +749,7 @@ template <typename T> using pq_grid_wide = typename std::conditional<sizeof(T) =
 
 // The chunks of a workgroup through the filter, for the subspaces in the mask `useless`
 template <typename T, typename TOKEN, typename FETCH, typename STORE>
-__device__ __forceinline__ void pq_grid_filter_scan(const pq_grid<T> (&grid)[GRID_SUB], const uint32_t useless, const int first, const int last,
+__device__ __forceinline__ void pq_grid_filter_scan(const pq_grids<T> &grids, const uint32_t useless, const int first, const int last,
                                                     FETCH fetch, STORE store)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -687,31 +763,42 @@ __device__ __forceinline__ void pq_grid_filter_scan(const pq_grid<T> (&grid)[GRI
         for (int j = 0; j < GRID_SUB; ++j) {
             if (((useless >> j) & 1u) == 0)
                 continue;
-            const pq_grid<T> &g = grid[j];
             const T x[2] = {pq_grid_pick(j, k.x[0][0], k.x[1][0], k.x[2][0], k.x[3][0]),
                             pq_grid_pick(j, k.x[0][1], k.x[1][1], k.x[2][1], k.x[3][1])};
-            const int code = pq_filter_code<2, T, pq_grid_wide<T>>(g.arow, sizeof(T) == 4 ? (const unsigned char *)g.coord : (const unsigned char *)g.pool,
-                                                                   g.scale, (g.bad & 2u) != 0, x, k.live);
-            if (k.live)
-                store(k, j, code);
+            const int code = pq_filter_code<2, T, pq_grid_wide<T>>(
+                grids.arow[j], sizeof(T) == 4 ? (const unsigned char *)grids.coord[j] : (const unsigned char *)grids.pool[j], grids.map[j].scale,
+                (grids.map[j].bad & 2u) != 0, x, k.live);
+            store(k, j, code, k.live);
         }
     }
+}
+
+// The values are here, in registers of their own, from here on: without it the copy from the registers that the next chunk's rows
+// are loaded into stands at the end of the loop, and waits for them there.
+template <typename T> __device__ __forceinline__ void pq_grid_hold(T (&x)[GRID_SUB][2])
+{
+    uint32_t w[sizeof(x) / 4];
+    __builtin_memcpy(w, x, sizeof(x));
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(x) / 4); ++i)
+        asm volatile("" : "+v"(w[i]));
+    __builtin_memcpy(x, w, sizeof(x));
 }
 
 // All tokens of a workgroup, 64 at a time, chunks first + wave, first + wave + 16, .. below last.
 //   fetch(chunk, token &)    the chunk's tokens, lane = token: x[4][2] and live; called for one chunk more than there are,
 //                            in ascending order; copied for another walk over the chunks
-//   store(token, j, code)    the code of this lane's token for subspace j of the group
+//   store(token, j, code, decided)  the code of this lane's token for subspace j of the group, if it is decided
 //   again(id, x, y)          the sub-vector of a token that was put off, id = (chunk - first) << 8 | lane << 2 | j
 //   store_late(id, x, y, code)
 // Two kinds of tokens are put off until 64 of them can be worked on as one:
-//   waiting  in a cell with a list: in LDS, all four subspaces together
-//   unsure   per subspace, in a register that holds their ids lane by lane (fp16: another their sub-vectors); the filter takes
+//   waiting  not decided by the distances of a cell's word: in LDS, all four subspaces together
+//   unsure   nor by those of its list: per subspace, in a register that holds their ids lane by lane (fp16: another their sub-vectors); the filter takes
 //            64 for 355 instructions.  (All lanes on one token's fp64 distances take 80, and 3 to 4 % of the tokens lie outside
 //            where the coordinates have heavy tails: encode of 32 heads x 9000 tokens, Laplace's distribution, 682 us one at a
 //            time, 411 so.)  What the 16 wavefronts have left over in the end is decided together: 457 us by each for itself.
 template <typename T, bool KEEP, typename TOKEN, typename FETCH, typename STORE, typename AGAIN, typename STORE_LATE>
-__device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_grid_waiting<KEEP> (&queue)[GRID_WAVES][GRID_QUEUE], const int first,
+__device__ __forceinline__ void pq_grid_scan(pq_grids<T> &grids, pq_grid_waiting<KEEP> (&queue)[GRID_WAVES][GRID_QUEUE], const int first,
                                              const int last, FETCH fetch, STORE store, AGAIN again, STORE_LATE store_late)
 {
     typedef typename std::conditional<sizeof(T) == 4, float, _Float16>::type W;
@@ -721,20 +808,22 @@ __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_gr
     uint32_t useless = 0;
 #pragma unroll
     for (int j = 0; j < GRID_SUB; ++j)
-        useless |= (uint32_t)__builtin_amdgcn_readfirstlane(pq_grid_useless(grid[j]) ? 1 << j : 0);
+        useless |= (uint32_t)__builtin_amdgcn_readfirstlane(pq_grid_useless(grids.map[j]) ? 1 << j : 0);
     if (useless != 0) {
-        pq_grid_filter_scan<T, TOKEN>(grid, useless, first, last, fetch, store);
+        pq_grid_filter_scan<T, TOKEN>(grids, useless, first, last, fetch, store);
         if (useless == (1u << GRID_SUB) - 1u)
             return;
     }
-    float sx[GRID_SUB], ox[GRID_SUB], sy[GRID_SUB], oy[GRID_SUB];
+    pq_grid_map map[GRID_SUB];  // (in registers, as far as it is used)
 #pragma unroll
     for (int j = 0; j < GRID_SUB; ++j) {
         const auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
-        sx[j] = uniform(grid[j].sx);
-        sy[j] = uniform(grid[j].sy);
-        ox[j] = grid[j].ox;
-        oy[j] = grid[j].oy;
+        map[j].s16 = (uint32_t)__builtin_amdgcn_readfirstlane((int)grids.map[j].s16);
+        map[j].o16 = grids.map[j].o16;
+        map[j].sx = uniform(grids.map[j].sx);
+        map[j].sy = uniform(grids.map[j].sy);
+        map[j].ox = grids.map[j].ox;
+        map[j].oy = grids.map[j].oy;
     }
     float minus_one = -1.0f;
     asm volatile("" : "+s"(minus_one));  // (a difference of two halves in one instruction, not two conversions more)
@@ -753,8 +842,8 @@ __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_gr
             of_word(xy, x[0], x[1]);
         else
             again(id, x[0], x[1]);
-        const int code = pq_filter_code<2, T, W>(grid[j].arow, sizeof(T) == 4 ? (const unsigned char *)grid[j].coord : grid[j].arow, grid[j].scale,
-                                                 (grid[j].bad & 2u) != 0, x, live);
+        const int code = pq_filter_code<2, T, W>(grids.arow[j], sizeof(T) == 4 ? (const unsigned char *)grids.coord[j] : grids.arow[j],
+                                                 grids.map[j].scale, (grids.map[j].bad & 2u) != 0, x, live);
         if (live)
             store_late(id, x[0], x[1], code);
     };
@@ -765,48 +854,52 @@ __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_gr
     TOKEN next;
     int chunk = first + wave;
     fetch(chunk, next);
+    // (as many stores behind the rows as in the loop, so that there is one number to wait for; nothing is stored)
+    if constexpr (WITH) {
+#pragma unroll
+        for (int s = 0; s < GRID_SUB; ++s)
+            store(next, s, s, false);
+    }
     for (;;) {
-        uint64_t hard[GRID_SUB] = {};  // the lanes whose tokens this step leaves unsure: `id`, of subspace j `xy[j]`
-        uint32_t id = 0, xy[GRID_SUB] = {};
+        uint64_t unsure;  // the lanes whose tokens this step leaves unsure, of subspace `j`
+        uint32_t id, xy;
+        int j;
         if (n_waiting < 64 && chunk < last) {
-            const TOKEN k = next;
+            TOKEN k = next;
+            if constexpr (sizeof(T) == 2)
+                pq_grid_hold(k.x);
             fetch(chunk + GRID_WAVES, next);  // in flight while this chunk is worked on
-            id = (uint32_t)(chunk - first) << 8 | (uint32_t)lane << 2;
+            const uint32_t at = (uint32_t)(chunk - first) << 8 | (uint32_t)lane << 2;
             uint32_t word[GRID_SUB], m1[GRID_SUB], m2[GRID_SUB];
 #pragma unroll
-            for (int j = 0; j < GRID_SUB; ++j)
-                word[j] = *(const uint32_t *)((const char *)grid[j].cell + pq_grid_cell(k.x[j][0], k.x[j][1], sx[j], ox[j], sy[j], oy[j]));
+            for (int s = 0; s < GRID_SUB; ++s)
+                word[s] = *(const uint32_t *)((const char *)grids.cell[0][s] + pq_grid_cell_of(k.x[s][0], k.x[s][1], map[s]));
 #pragma unroll
-            for (int j = 0; j < GRID_SUB; ++j) {
-                const uint32_t k0 = pq_grid_key<0>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one);
-                const uint32_t k1 = pq_grid_key<1>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one);
-                m1[j] = min(k0, k1);
-                m2[j] = max(k0, k1);
-                pq_grid_take(m1[j], m2[j], pq_grid_key<2>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one));
-                pq_grid_take(m1[j], m2[j], pq_grid_key<3>(grid[j].coord, word[j], k.x[j][0], k.x[j][1], minus_one));
+            for (int s = 0; s < GRID_SUB; ++s) {
+                const uint32_t k0 = pq_grid_key<0>(grids.coord[s], word[s], k.x[s][0], k.x[s][1], minus_one);
+                const uint32_t k1 = pq_grid_key<1>(grids.coord[s], word[s], k.x[s][0], k.x[s][1], minus_one);
+                m1[s] = min(k0, k1);
+                m2[s] = max(k0, k1);
+                pq_grid_take(m1[s], m2[s], pq_grid_key<2>(grids.coord[s], word[s], k.x[s][0], k.x[s][1], minus_one));
+                pq_grid_take(m1[s], m2[s], pq_grid_key<3>(grids.coord[s], word[s], k.x[s][0], k.x[s][1], minus_one));
             }
             const uint64_t live = __builtin_amdgcn_ballot_w64(k.live);
 #pragma unroll
-            for (int j = 0; j < GRID_SUB; ++j) {
-                const uint64_t listed = __builtin_amdgcn_ballot_w64(((word[j] ^ (word[j] >> 8)) & 255u) == 0) & live;
-                hard[j] = __builtin_amdgcn_ballot_w64(pq_grid_unsure<T>(m1[j], m2[j])) & live & ~listed;
-                if (__builtin_amdgcn_inverse_ballot_w64(live & ~(hard[j] | listed)))
-                    store(k, j, (int)(m1[j] & 255u));
-                if (__builtin_amdgcn_inverse_ballot_w64(listed)) {
-                    const int at = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(listed >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)listed, (uint32_t)n_waiting));
+            for (int s = 0; s < GRID_SUB; ++s) {
+                const uint64_t mine = (useless >> s) & 1u ? 0 : live;
+                const uint64_t waits = __builtin_amdgcn_ballot_w64(pq_grid_unsure<T>(m1[s], m2[s])) & mine;
+                store(k, s, (int)(m1[s] & 255u), __builtin_amdgcn_inverse_ballot_w64(mine & ~waits));
+                if (__builtin_amdgcn_inverse_ballot_w64(waits)) {
+                    const int to = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(waits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)waits, (uint32_t)n_waiting));
                     if constexpr (KEEP)
-                        queue[wave][at] = make_uint2(id | (uint32_t)j, word_of(k.x[j][0], k.x[j][1]));
+                        queue[wave][to] = make_uint2(at | (uint32_t)s, word_of(k.x[s][0], k.x[s][1]));
                     else
-                        queue[wave][at] = id | (uint32_t)j;
+                        queue[wave][to] = at | (uint32_t)s;
                 }
-                n_waiting += __builtin_popcountll(listed);
+                n_waiting += __builtin_popcountll(waits);
             }
             chunk += GRID_WAVES;
-            if ((hard[0] | hard[1] | hard[2] | hard[3]) == 0)  // wave-uniform
-                continue;
-#pragma unroll
-            for (int j = 0; j < GRID_SUB; ++j)
-                xy[j] = word_of(k.x[j][0], k.x[j][1]);
+            continue;
         } else if (n_waiting > 0) {  // the last 64 of those that wait
             const int n = n_waiting < 64 ? n_waiting : 64;
             n_waiting -= n;
@@ -822,63 +915,59 @@ __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_gr
                 again(id, x, y);
             }
             pq_grid_fence();
-            const int j = (int)(id & 3u);
+            j = (int)(id & 3u);
             id &= ~3u;
-            const pq_grid<T> &g = grid[j];
-            const uint32_t word = *(const uint32_t *)((const char *)g.cell + pq_grid_cell(x, y, g.sx, g.ox, g.sy, g.oy));
-            const uint32_t words = word & 255u, at = word >> 16;
+            const uint32_t word = *(const uint32_t *)((const char *)grids.cell[0][j] + pq_grid_cell_of(x, y, grids.map[j]));
+            // (a token whose cell has no list keeps two equal distances)
+            const uint32_t words = word >> 16 == (word & 0xffffu) ? word >> 27 : 0u, at = word & 2047u;
             uint32_t m1 = 0xffffffffu, m2 = 0xffffffffu;
             for (uint32_t k = 0; __builtin_amdgcn_ballot_w64(k < words) != 0; ++k) {
                 if (k < words) {
-                    const uint32_t four = g.pool[at + k];
-                    pq_grid_take(m1, m2, pq_grid_key<0>(g.coord, four, x, y, minus_one));
-                    pq_grid_take(m1, m2, pq_grid_key<1>(g.coord, four, x, y, minus_one));
-                    pq_grid_take(m1, m2, pq_grid_key<2>(g.coord, four, x, y, minus_one));
-                    pq_grid_take(m1, m2, pq_grid_key<3>(g.coord, four, x, y, minus_one));
+                    const uint32_t four = grids.pool[j][at + k];
+                    pq_grid_take(m1, m2, pq_grid_key<0>(grids.coord[j], four, x, y, minus_one));
+                    pq_grid_take(m1, m2, pq_grid_key<1>(grids.coord[j], four, x, y, minus_one));
+                    pq_grid_take(m1, m2, pq_grid_key<2>(grids.coord[j], four, x, y, minus_one));
+                    pq_grid_take(m1, m2, pq_grid_key<3>(grids.coord[j], four, x, y, minus_one));
                 }
             }
-            const uint64_t unsure = __builtin_amdgcn_ballot_w64(live && pq_grid_unsure<T>(m1, m2));
+            unsure = __builtin_amdgcn_ballot_w64(live && pq_grid_unsure<T>(m1, m2));
             if (live && !__builtin_amdgcn_inverse_ballot_w64(unsure))
                 store_late(id | (uint32_t)j, x, y, (int)(m1 & 255u));
             if (unsure == 0)  // wave-uniform
                 continue;
-#pragma unroll
-            for (int s = 0; s < GRID_SUB; ++s) {
-                hard[s] = unsure & __builtin_amdgcn_ballot_w64(j == s);
-                xy[s] = word_of(x, y);
-            }
+            xy = word_of(x, y);
         } else {
             break;
         }
 #pragma unroll 1
-        for (int j = 0; j < GRID_SUB; ++j) {
-            const uint64_t lanes = (useless >> j) & 1u ? 0 : pq_grid_pick(j, hard[0], hard[1], hard[2], hard[3]);
+        for (int s = 0; s < GRID_SUB; ++s) {
+            const uint64_t lanes = unsure & __builtin_amdgcn_ballot_w64(j == s);
             if (lanes == 0)
                 continue;
-            const int n = (int)((n_unsure >> (8 * j)) & 255u), total = n + __builtin_popcountll(lanes);
+            const int n = (int)((n_unsure >> (8 * s)) & 255u), total = n + __builtin_popcountll(lanes);
             // The new ones move to the lanes from n on, cyclically, and the other lanes' values to the rest.
             const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u));
             const int to = 4 * (63 & (__builtin_amdgcn_inverse_ballot_w64(lanes) ? n + below : total + lane - below));
-            const uint32_t old_id = pq_grid_pick(j, unsure_id[0], unsure_id[1], unsure_id[2], unsure_id[3]);
+            const uint32_t old_id = pq_grid_pick(s, unsure_id[0], unsure_id[1], unsure_id[2], unsure_id[3]);
             const uint32_t new_id = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)id);
             uint32_t old_xy = 0, new_xy = 0;
             if constexpr (WITH) {
-                old_xy = pq_grid_pick(j, unsure_xy[0], unsure_xy[1], unsure_xy[2], unsure_xy[3]);
-                new_xy = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)pq_grid_pick(j, xy[0], xy[1], xy[2], xy[3]));
+                old_xy = pq_grid_pick(s, unsure_xy[0], unsure_xy[1], unsure_xy[2], unsure_xy[3]);
+                new_xy = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)xy);
             }
             // together; 64 are decided, and the rest of the new ones then stands in lanes 0 .. total - 65
             const uint32_t now_id = lane < n ? old_id : new_id, now_xy = lane < n ? old_xy : new_xy;
             const bool full = total >= 64;
             const uint32_t kept_id = full ? new_id : now_id, kept_xy = full ? new_xy : now_xy;
-            n_unsure = (n_unsure & ~(255u << (8 * j))) | (uint32_t)(full ? total - 64 : total) << (8 * j);
+            n_unsure = (n_unsure & ~(255u << (8 * s))) | (uint32_t)(full ? total - 64 : total) << (8 * s);
 #pragma unroll
-            for (int s = 0; s < GRID_SUB; ++s) {
-                unsure_id[s] = j == s ? kept_id : unsure_id[s];
+            for (int r = 0; r < GRID_SUB; ++r) {
+                unsure_id[r] = s == r ? kept_id : unsure_id[r];
                 if constexpr (WITH)
-                    unsure_xy[s] = j == s ? kept_xy : unsure_xy[s];
+                    unsure_xy[r] = s == r ? kept_xy : unsure_xy[r];
             }
             if (full)
-                decide(j, now_id | (uint32_t)j, now_xy, true);
+                decide(s, now_id | (uint32_t)s, now_xy, true);
         }
     }
 
@@ -890,7 +979,7 @@ __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_gr
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < GRID_SUB; ++j) {
-        left_over &entry = ((left_over *)grid[j].pool)[64 * wave + lane];
+        left_over &entry = ((left_over *)grids.pool[j])[64 * wave + lane];
         if constexpr (WITH)
             entry = make_uint2(unsure_id[j], unsure_xy[j]);
         else
@@ -921,7 +1010,7 @@ __device__ __forceinline__ void pq_grid_scan(pq_grid<T> (&grid)[GRID_SUB], pq_gr
                 of += k >= e ? 1 : 0;
                 start = k >= e ? e : start;
             }
-            const left_over entry = ((const left_over *)grid[j].pool)[64 * of + k - start];
+            const left_over entry = ((const left_over *)grids.pool[j])[64 * of + k - start];
             if constexpr (WITH)
                 decide(j, entry.x | (uint32_t)j, entry.y, live);
             else
