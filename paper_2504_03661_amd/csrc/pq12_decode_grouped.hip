@@ -319,22 +319,33 @@ __global__ __launch_bounds__(GN * 64) void pq12_decode_grouped_kernel(const pq_d
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     qb[j] = __builtin_bit_cast(f16x4, *(lds_u32x2 *)(lbase + G12_Q + row * 256 + (8 * g + 4 * hf + j) * 8));
-#pragma unroll
-                for (int jj = 0; jj < WAVE_VB; ++jj) {
-                    request_part(jj, next_slice);
-                    if (jj >= n_jj)
-                        continue;  // wave-uniform; `continue`, not `break`: the loop must unroll (registers are indexed by jj)
+                // a block's gathers go out in front of the matrix instructions of the block before it
+                u32x2 cvs[2][2][4];
+                auto gather = [&](const int jj) {
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         uint32_t c[8];
                         unpack8g(ku[2 * jj + h][0], ku[2 * jj + h][1], ku[2 * jj + h][2], c);
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const u32x2 cv = *(lds_u32x2 *)(lbase + G12_TAB + j * (PQ12_CENTROIDS * 8) + c[4 * hf + j] * 8);
-                            score[2 * jj + h] =
-                                __builtin_amdgcn_mfma_f32_4x4x4f16(f16x4_of(cv.x, cv.y), qb[j], score[2 * jj + h], 0, 0, 0);
-                        }
+                        for (int j = 0; j < 4; ++j)
+                            cvs[jj & 1][h][j] = *(lds_u32x2 *)(lbase + G12_TAB + j * (PQ12_CENTROIDS * 8) + c[4 * hf + j] * 8);
                     }
+                };
+                gather(0);
+#pragma unroll
+                for (int jj = 0; jj < WAVE_VB; ++jj) {
+                    request_part(jj, next_slice);
+                    if (jj >= n_jj)
+                        continue;  // wave-uniform; `continue`, not `break`: the loop must unroll (registers are indexed by jj)
+                    if (jj + 1 < WAVE_VB)
+                        gather(jj + 1);  // (beyond the wavefront's blocks: a valid block's codes, not used)
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            score[2 * jj + h] = __builtin_amdgcn_mfma_f32_4x4x4f16(f16x4_of(cvs[jj & 1][h][j].x, cvs[jj & 1][h][j].y), qb[j],
+                                                                                   score[2 * jj + h], 0, 0, 0);
                 }
                 if (hf == 0) {
                     __builtin_amdgcn_sched_barrier(0);
@@ -395,6 +406,8 @@ __global__ __launch_bounds__(GN * 64) void pq12_decode_grouped_kernel(const pq_d
             const f16x4 vh = {hi[0], hi[1], hi[2], hi[3]}, vl = {lo[0], lo[1], lo[2], lo[3]};
             const u32x2 bh = __builtin_bit_cast(u32x2, vh), bl = __builtin_bit_cast(u32x2, vl);
             wt[e] = u32x4{bh.x, bh.y, bl.x, bl.y};
+            // (added here and now: left to itself the compiler keeps all weights until the round's end, in 32 registers)
+            asm volatile("" : "+v"(l_lane));
         }
 
         // ---------------- value passes: 4 pairs of groups of 4 subspaces
@@ -420,19 +433,26 @@ __global__ __launch_bounds__(GN * 64) void pq12_decode_grouped_kernel(const pq_d
 #pragma unroll
                 for (int d = 0; d < 4; ++d)
                     acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+                u32x2 cvs[2][2][4];  // tokens quad + 16 k of a half block, k = 0..3: dims (0, 1) and (2, 3)
+                auto gather = [&](const int jj) {
+                    uint32_t c[8];
+                    unpack8g(vu[2 * jj + x2][0], vu[2 * jj + x2][1], vu[2 * jj + x2][2], c);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        cvs[jj & 1][k >> 2][k & 3] = *(lds_u32x2 *)(lbase + v_tab + c[k] * 8);
+                };
+                gather(0);
 #pragma unroll
                 for (int jj = 0; jj < WAVE_VB; ++jj) {
                     request_part(jj, next_slice);
                     if (jj >= n_jj)
                         continue;
-                    uint32_t c[8];
-                    unpack8g(vu[2 * jj + x2][0], vu[2 * jj + x2][1], vu[2 * jj + x2][2], c);
+                    if (jj + 1 < WAVE_VB)
+                        gather(jj + 1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        u32x2 cv[4];  // tokens quad + 16 k of the half block, k = 0..3: dims (0, 1) and (2, 3)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            cv[k] = *(lds_u32x2 *)(lbase + v_tab + c[4 * h + k] * 8);
+                        const u32x2(&cv)[4] = cvs[jj & 1][h];
                         f16x4 B[4];  // per dim: the 4 tokens' values
                         B[0] = f16x4_of(__builtin_amdgcn_perm(cv[1].x, cv[0].x, 0x05040100u),
                                         __builtin_amdgcn_perm(cv[3].x, cv[2].x, 0x05040100u));
