@@ -79,7 +79,7 @@ namespace {
 // fill 82 % of the issue slots at the 2.0 GHz the chip holds (M = 32: 394, 82 %; fp32, M = 64: 407, 78 %); what the
 // wavefronts wait for in the rest is not known.  Prompt of 32K tokens x 32 heads x (K, V), M = 64: 2.75 ms with 4x4x4
 // instructions in two passes (one for the best value, one for the marks), 1.54 ms in one; appends of that size go through
-// the grids now (0.63 ms).
+// the grids now (0.39 ms).
 //
 // A workgroup is 4 neighbouring subspaces of the same tokens, one wavefront each: a token's line of 64 subspaces is
 // then fetched from L2 once for four wavefronts (one wavefront per workgroup 2.69 ms, two 2.35, four 1.75, eight 1.73

@@ -21,7 +21,7 @@
 // of vector instructions in the nearest-centroid filter, as the encode; 32 heads x 65536 samples, M = 64: 2.7 ms per
 // iteration with one subspace per workgroup and the two-pass filter, 1.58 ms with the one-pass filter (two or four
 // wavefronts per subspace on one set of sums, for more wavefronts per compute unit: 1.6 and 1.8 ms).  As many samples as
-// that take the grids of pq_nearest_grid.h at M = 64 (pq_kmeans_grid_kernel): 0.50 ms.
+// that take the grids of pq_nearest_grid.h at M = 64 (pq_kmeans_grid_kernel): 0.44 ms.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 

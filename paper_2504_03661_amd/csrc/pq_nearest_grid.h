@@ -9,7 +9,7 @@
 // thousands of tokens per head (pq_grid_slices below).  Encode (K and V), 32 heads x 32K tokens, kept grids: 392 us, of which 36
 // us are workgroups' starts, image loads and ends, 184 the tokens' main path, which vector issue bounds (220 instructions per 64
 // tokens and 4 subspaces), and, each left out by itself: 63 the stores of the codes, a byte per token and subspace, 61 the tokens that
-// wait, 34 the rows from memory (1549 us through the filter).  k-means, 32 heads x 64K samples, 2 iterations: 3148 -> 975 us.
+// wait, 34 the rows from memory (1549 us through the filter).  k-means, 32 heads x 64K samples, 2 iterations: 3148 -> 872 us.
 //
 // Map.  Per axis u = s x + o, chosen from the codebook (mean and mean deviation of its coordinates without outliers):
 // |u| <= 28 holds what lies within some 4 standard deviations.  The cell coordinate is five bits of the float |u| + 2 — 8
@@ -102,7 +102,7 @@ constexpr int GRID_ROW = 4 * GRID_SUB * GRID_SIDE;  // bytes from one u_x to the
 template <typename T> constexpr int pq_grid_image_bytes() { return (int)offsetof(pq_grids<T>, arow); }
 
 // The tokens are taken to lie where the centroids do: where many of the 256 are left to the filter (in cells without a list), it
-// does all the work of the subspace.  (For 64 tokens: 86 instructions for the look-ups,
+// does all the work of the subspace.  (For 64 tokens: 68 instructions for the look-ups,
 // some 30 for putting tokens off and for 24 of them 135 in the filter; 355 through the filter alone, and building is saved.)
 constexpr int GRID_LOST = 96;
 __device__ __forceinline__ bool pq_grid_useless(const pq_grid_map &m) { return m.bad != 0 || m.lost > GRID_LOST || m.unserved > GRID_LOST; }
@@ -1024,7 +1024,7 @@ __device__ __forceinline__ void pq_grid_scan(pq_grids<T> &grids, pq_grid_waiting
 // walk) go through grid workgroups; 0: the filter, which walks filter_chunks, does better.  Modelled: a workgroup, which fills
 // a compute unit, takes 74 us to build and 0.18 us per chunk; through the filter a chunk of 4 subspaces takes 0.72 us of a
 // compute unit.  Measured on normal data, 256 compute units: fp16 encode 66 and 0.18, filter 0.78; fp32 encode 65 and 0.27,
-// 0.94; k-means 76 and 0.15, 0.85.  So the model is on the filter's side for all three, and data that the grids serve less well
+// 0.94; k-means 78 and 0.14, 0.85.  So the model is on the filter's side for all three, and data that the grids serve less well
 // still gain at the line (32 heads x 9000 tokens or samples, us, grids / filter, the three in turn: normal 364 / 440, 410 /
 // 530, 198 / 267; Laplace's distribution 411 / 441, 437 / 526, 219 / 266; channel scales 0.5 .. 4 444 / 458 and 248 / 275).
 // kept: the grids are there (pq_encode_grid_kernel), a workgroup takes some 9 us to start, fetch them and end.  Grids / filter,
