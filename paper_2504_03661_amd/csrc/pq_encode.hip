@@ -79,7 +79,7 @@ namespace {
 // fill 82 % of the issue slots at the 2.0 GHz the chip holds (M = 32: 394, 82 %; fp32, M = 64: 407, 78 %); what the
 // wavefronts wait for in the rest is not known.  Prompt of 32K tokens x 32 heads x (K, V), M = 64: 2.75 ms with 4x4x4
 // instructions in two passes (one for the best value, one for the marks), 1.54 ms in one; appends of that size go through
-// the grids now (0.39 ms).
+// the grids now (0.37 ms).
 //
 // A workgroup is 4 neighbouring subspaces of the same tokens, one wavefront each: a token's line of 64 subspaces is
 // then fetched from L2 once for four wavefronts (one wavefront per workgroup 2.69 ms, two 2.35, four 1.75, eight 1.73
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_grid_image_kernel(const T 
         __hip_atomic_store(grid_state + group, (unsigned int)GRID_THERE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <typename T>
+template <typename T, bool WIDE>
 __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const pq_encode_args a, const int seq_chunks, const int slices,
                                                                          const int slice_chunks)
 {
@@ -390,37 +390,73 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
         t = block * 64 + (int)((id >> 2) & 63u) - (n_old & 63);
         pos = n_old + t;
     };
-    pq_grid_scan<T, KEEP, grid_token<T>>(
-        grids, scratch.queue, first, last, fetch,
-        [&](const grid_token<T> &k, int j, int code, bool decided) {
-            const int off = pq_grid_pick(j, in_block[0], in_block[1], in_block[2], in_block[3]);
-            if constexpr (sizeof(T) == 4) {  // (the other way 198 -> 202 us for 9000 tokens of 32 heads)
-                if (decided)
-                    codes[k.block + (uint32_t)off] = (uint8_t)code;
-                return;
-            }
-            // A store for every lane, those beyond the block's bytes dropped: with stores in branches the compiler does not know how
-            // many are on their way behind the next chunk's rows, and waits for all of them.
-            const uint64_t at = (uint64_t)codes + (uint64_t)k.block;
-            const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at) |
-                                  (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32;
-            const auto block = __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, 64 * M, 0x00020000);
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code, block, decided ? off : -1, 0, 0);
-        },
-        [&](uint32_t id, T &x0, T &x1) {
-            int seq, t, pos;
-            place(id, seq, t, pos);
-            const T *xp = x + (((int64_t)seq * a.Hkv + hkv) * n_new + t) * PQ_HEAD_DIM + (id & 3u) * 2;
-            x0 = xp[0];
-            x1 = xp[1];
-        },
-        [&](uint32_t id, T, T, int code) {
-            int seq, t, pos;
-            place(id, seq, t, pos);
-            const int i = i0 + (int)(id & 3u);
-            const uint32_t off = which == 0 ? pq_k_code_offset((uint32_t)pos, i, M, a.k_skew) : pq_v_code_offset((uint32_t)pos, i, M);
-            codes[((int64_t)seq * a.Hkv + hkv) * a.head_stride + off] = (uint8_t)code;
-        });
+    const auto block_of = [&](const grid_token<T> &k) {
+        const uint64_t at = (uint64_t)codes + (uint64_t)k.block;
+        const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at) |
+                              (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32;
+        return __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, 64 * M, 0x00020000);
+    };
+    // WIDE: 4 bytes a store.  Of V, four tokens' codes of a subspace stand together, and a transposition within four lanes
+    // makes them so.  Of K, a token's codes of four subspaces do: at a multiple of 4 where the skew goes by quads of lanes, else
+    // anywhere, and in 12 of the 64 lanes on both sides of a turn to the lane's next 16 bytes, 1 KiB on: three stores more.
+    const bool is_k = which == 0;
+    const bool apart = is_k && in_block[3] != in_block[0] + 3;
+    const int in_front = in_block[1] != in_block[0] + 1 ? 1 : in_block[2] != in_block[1] + 1 ? 2 : 3;  // of the turn
+    const int two_at = !apart ? -1 : in_front == 1 ? in_block[1] : in_block[0];
+    const int one_at = !apart ? -1 : in_front == 1 ? in_block[0] : in_block[2];
+    const int last_at = !apart ? -1 : in_block[3];
+    const uint32_t two_of = apart && in_front == 1 ? 8u : 0u, one_of = apart && in_front == 1 ? 0u : 16u;
+    const int four_at = apart ? -1 : is_k ? in_block[0] : (int)pq_v_code_offset((uint32_t)(lane & ~3), i0 + (lane & 3), M);
+    const uint32_t turn_1 = (lane & 1) == 0 ? 0x06020400u : 0x03070105u, turn_2 = (lane & 2) == 0 ? 0x05040100u : 0x03020706u;
+    const auto scan = [&](auto FOUR) {
+        pq_grid_scan<T, KEEP, decltype(FOUR)::value, grid_token<T>>(
+            grids, scratch.queue, first, last, fetch,
+            [&](const grid_token<T> &k, int j, int code, bool decided) {
+                const int off = pq_grid_pick(j, in_block[0], in_block[1], in_block[2], in_block[3]);
+                if constexpr (sizeof(T) == 4) {  // (the other way 198 -> 202 us for 9000 tokens of 32 heads)
+                    if (decided)
+                        codes[k.block + (uint32_t)off] = (uint8_t)code;
+                    return;
+                }
+                // A store for every lane, those beyond the block's bytes dropped: with stores in branches the compiler does not know how
+                // many are on their way behind the next chunk's rows, and waits for all of them.
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code, block_of(k), decided ? off : -1, 0, 0);
+            },
+            [&](const grid_token<T> &k, uint32_t w) {
+                if (decltype(FOUR)::value == 1 && !is_k) {  // lane l of four: the four tokens' codes of subspace l
+                    w = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xf, 0xf, true), w, turn_1);
+                    w = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xf, 0xf, true), w, turn_2);
+                }
+                __builtin_amdgcn_raw_buffer_store_b32(w, block_of(k), four_at, 0, 0);
+                if constexpr (decltype(FOUR)::value == 4) {
+                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(w >> two_of), block_of(k), two_at, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(w >> one_of), block_of(k), one_at, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(w >> 24), block_of(k), last_at, 0, 0);
+                }
+            },
+            [&](uint32_t id, T &x0, T &x1) {
+                int seq, t, pos;
+                place(id, seq, t, pos);
+                const T *xp = x + (((int64_t)seq * a.Hkv + hkv) * n_new + t) * PQ_HEAD_DIM + (id & 3u) * 2;
+                x0 = xp[0];
+                x1 = xp[1];
+            },
+            [&](uint32_t id, T, T, int code) {
+                int seq, t, pos;
+                place(id, seq, t, pos);
+                const int i = i0 + (int)(id & 3u);
+                const uint32_t off = which == 0 ? pq_k_code_offset((uint32_t)pos, i, M, a.k_skew) : pq_v_code_offset((uint32_t)pos, i, M);
+                codes[((int64_t)seq * a.Hkv + hkv) * a.head_stride + off] = (uint8_t)code;
+            });
+    };
+    if (!WIDE || pq_grid_useless_of(grids) != 0)
+        scan(std::integral_constant<int, 0>());
+    else if constexpr (WIDE) {
+        if (is_k && a.k_skew == PQ_K_SKEW_LANE)
+            scan(std::integral_constant<int, 4>());
+        else
+            scan(std::integral_constant<int, 1>());
+    }
 }
 
 // ---------------------------------------------------------------------------------
@@ -617,13 +653,28 @@ template <int M, int DS, typename T> void launch_few(const pq_encode_args &a, in
                        pq_divisor(a.n_new));
 }
 
-template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, int slices, hipStream_t s)
+// Whether a grid workgroup stores the codes of a chunk together, from its chunks of 64 tokens and the number of workgroups: it
+// needs a second copy of the loop over the tokens, fetching that costs 1 us, and what is gained shows where the stores of
+// several rounds of workgroups queue.  us, single / wide codes: 32 heads x 32K 392 / 366 (normal data), 477 / 458 (Laplace's), 436 /
+// 426 (channel scales), over 128 query heads 386 / 350; 16 heads x 33 000 201 / 189, x 20 000 121 / 119; 32 x 9000 135.7 / 134.9 and
+// 146.1 / 147.3 (scales), 8 x 32 x 1100, many chunks not full, 143.0 / 145.5; 8 heads, a workgroup per compute unit, 30 000
+// tokens 87.7 / 88.1.
+inline bool pq_grid_stores_wide(int64_t slice_chunks, int64_t n_new, int64_t workgroups, int n_cu)
+{
+    return slice_chunks >= 256 && n_new >= 2048 && workgroups >= 2 * (int64_t)n_cu;
+}
+
+template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, int slices, int n_cu, hipStream_t s)
 {
     const int n_chunks = a.B * seq_chunks;
     const int slice_chunks = (n_chunks + slices - 1) / slices;
     const int units = 2 * a.Hkv * slices;
-    hipLaunchKernelGGL((pq_encode_grid_kernel<T>), dim3((unsigned)((units + 7) / 8 * 128)), dim3(64 * GRID_WAVES), 0, s, a, seq_chunks, slices,
-                       slice_chunks);
+    const dim3 grid((unsigned)((units + 7) / 8 * 128));
+    // (fp32: no registers for it)
+    if (sizeof(T) == 2 && pq_grid_stores_wide(slice_chunks, a.n_new, (int64_t)units * 16, n_cu))
+        hipLaunchKernelGGL((pq_encode_grid_kernel<T, sizeof(T) == 2>), grid, dim3(64 * GRID_WAVES), 0, s, a, seq_chunks, slices, slice_chunks);
+    else
+        hipLaunchKernelGGL((pq_encode_grid_kernel<T, false>), grid, dim3(64 * GRID_WAVES), 0, s, a, seq_chunks, slices, slice_chunks);
 }
 
 // Builds the grids into the context's images when this append and those since the codebooks were registered, chunks of 64 tokens
@@ -683,7 +734,7 @@ hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *
             slices = with_kept;
     }
     if (slices > 0) {
-        if (f16) launch_grid<_Float16>(a, seq_chunks, slices, s); else launch_grid<float>(a, seq_chunks, slices, s);
+        if (f16) launch_grid<_Float16>(a, seq_chunks, slices, ctx->n_cu, s); else launch_grid<float>(a, seq_chunks, slices, ctx->n_cu, s);
     } else if (ctx->cfg.n_subspaces == 64) {
         if (f16) launch_fast<64, 2, _Float16>(a, s); else launch_fast<64, 2, float>(a, s);
     } else {

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
         atomicAdd(&sum[j][256 + code], (unsigned long long)__double_as_longlong(__builtin_fma((double)(float)x1, 16777216.0, 6755399441055744.0)));
         atomicAdd(&count[j][code], 1u);
     };
-    pq_grid_scan<_Float16, false, pq_sample>(
+    pq_grid_scan<_Float16, false, 0, pq_sample>(
         grids, scratch.queue, first, last,
         [&](int chunk, pq_sample &k) {
             const int s = chunk * 64 + lane;
@@ -183,6 +183,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_kmeans_grid_kernel(const _
             if (decided)
                 add(j, code, pq_grid_pick(j, k.x[0][0], k.x[1][0], k.x[2][0], k.x[3][0]), pq_grid_pick(j, k.x[0][1], k.x[1][1], k.x[2][1], k.x[3][1]));
         },
+        [](const pq_sample &, uint32_t) {},
         [&](uint32_t id, _Float16 &x0, _Float16 &x1) {
             const _Float16 *xp = x + ((int64_t)(first + (int)(id >> 8)) * 64 + (id >> 2 & 63u)) * PQ_HEAD_DIM + (id & 3u) * 2;
             x0 = xp[0];

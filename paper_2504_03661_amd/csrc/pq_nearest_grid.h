@@ -8,7 +8,7 @@
 // grid takes 34 000, as many as 100 chunks of 64 tokens through the filter, so the grid serves appends and trainings of
 // thousands of tokens per head (pq_grid_slices below).  Encode (K and V), 32 heads x 32K tokens, kept grids: 392 us, of which 36
 // us are workgroups' starts, image loads and ends, 184 the tokens' main path, which vector issue bounds (220 instructions per 64
-// tokens and 4 subspaces), and, each left out by itself: 63 the stores of the codes, a byte per token and subspace, 61 the tokens that
+// tokens and 4 subspaces), and, each left out by itself: 63 the stores of the codes, a byte per token and subspace (stored together 367 us in all: pq_grid_stores_wide), 61 the tokens that
 // wait, 34 the rows from memory (1549 us through the filter).  k-means, 32 heads x 64K samples, 2 iterations: 3148 -> 872 us.
 //
 // Map.  Per axis u = s x + o, chosen from the codebook (mean and mean deviation of its coordinates without outliers):
@@ -34,8 +34,8 @@
 // leave undecided ("unsure": near-ties, outside, cells without a list) is put off until 64 of a subspace can go through the filter
 // together, and where the codebook gives no useful grid all its tokens go there at once.
 // What the data make of it, 32 heads, us, grids built / kept from an earlier append / the filter alone: encode of 9000 tokens,
-// normal 360 / 136 / 440, Laplace's distribution 390 / 158 / 441, 2 % of the coordinates times 20 395 / 165 / 446; of 32K 630 / 392
-// / 1590, 710 / 477 / 1596, 730 / 499 / 1610.  Centroids that repeat others are taken out: 16 values in all 1480 kept, 2496 by the
+// normal 360 / 136 / 440, Laplace's distribution 390 / 158 / 441, 2 % of the coordinates times 20 395 / 165 / 446; of 32K 630 / 367
+// / 1590, 710 / 462 / 1596.  Centroids that repeat others are taken out: 16 values in all 1480 kept, 2496 by the
 // filter (9000 tokens; 2850 when a repeated centroid made its tokens unsure), k-means of 64K samples rounded to quarters 18.5 ->
 // 8.1 ms.  A codebook without a useful grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every
 // subspace 863 / 757 and 3000 / 2611.
@@ -785,10 +785,23 @@ template <typename T> __device__ __forceinline__ void pq_grid_hold(T (&x)[GRID_S
     __builtin_memcpy(x, w, sizeof(x));
 }
 
+// the subspaces that are the filter's alone, a bit each
+template <typename T> __device__ __forceinline__ uint32_t pq_grid_useless_of(const pq_grids<T> &grids)
+{
+    uint32_t useless = 0;
+#pragma unroll
+    for (int j = 0; j < GRID_SUB; ++j)
+        useless |= (uint32_t)__builtin_amdgcn_readfirstlane(pq_grid_useless(grids.map[j]) ? 1 << j : 0);
+    return useless;
+}
+
 // All tokens of a workgroup, 64 at a time, chunks first + wave, first + wave + 16, .. below last.
 //   fetch(chunk, token &)    the chunk's tokens, lane = token: x[4][2] and live; called for one chunk more than there are,
 //                            in ascending order; copied for another walk over the chunks
 //   store(token, j, code, decided)  the code of this lane's token for subspace j of the group, if it is decided
+//   store_four(token, codes)  FOUR, the number of its stores, is not 0: the codes of this lane's token, one a byte, for chunks with a
+//                            token in every lane.  Those not decided are stored with the others, and again by store_late: by the
+//                            same wavefront, whose stores stay in order, or behind a wait.  No subspace is the filter's alone
 //   again(id, x, y)          the sub-vector of a token that was put off, id = (chunk - first) << 8 | lane << 2 | j
 //   store_late(id, x, y, code)
 // Two kinds of tokens are put off until 64 of them can be worked on as one:
@@ -797,18 +810,15 @@ template <typename T> __device__ __forceinline__ void pq_grid_hold(T (&x)[GRID_S
 //            64 for 355 instructions.  (All lanes on one token's fp64 distances take 80, and 3 to 4 % of the tokens lie outside
 //            where the coordinates have heavy tails: encode of 32 heads x 9000 tokens, Laplace's distribution, 682 us one at a
 //            time, 411 so.)  What the 16 wavefronts have left over in the end is decided together: 457 us by each for itself.
-template <typename T, bool KEEP, typename TOKEN, typename FETCH, typename STORE, typename AGAIN, typename STORE_LATE>
+template <typename T, bool KEEP, int FOUR, typename TOKEN, typename FETCH, typename STORE, typename STORE_FOUR, typename AGAIN, typename STORE_LATE>
 __device__ __forceinline__ void pq_grid_scan(pq_grids<T> &grids, pq_grid_waiting<KEEP> (&queue)[GRID_WAVES][GRID_QUEUE], const int first,
-                                             const int last, FETCH fetch, STORE store, AGAIN again, STORE_LATE store_late)
+                                             const int last, FETCH fetch, STORE store, STORE_FOUR store_four, AGAIN again, STORE_LATE store_late)
 {
     typedef typename std::conditional<sizeof(T) == 4, float, _Float16>::type W;
     constexpr bool WITH = sizeof(T) == 2;  // unsure tokens keep their sub-vectors
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint32_t useless = 0;
-#pragma unroll
-    for (int j = 0; j < GRID_SUB; ++j)
-        useless |= (uint32_t)__builtin_amdgcn_readfirstlane(pq_grid_useless(grids.map[j]) ? 1 << j : 0);
+    const uint32_t useless = FOUR != 0 ? 0u : pq_grid_useless_of(grids);
     if (useless != 0) {
         pq_grid_filter_scan<T, TOKEN>(grids, useless, first, last, fetch, store);
         if (useless == (1u << GRID_SUB) - 1u)
@@ -857,7 +867,7 @@ __device__ __forceinline__ void pq_grid_scan(pq_grids<T> &grids, pq_grid_waiting
     // (as many stores behind the rows as in the loop, so that there is one number to wait for; nothing is stored)
     if constexpr (WITH) {
 #pragma unroll
-        for (int s = 0; s < GRID_SUB; ++s)
+        for (int s = 0; s < (FOUR != 0 ? FOUR : GRID_SUB); ++s)
             store(next, s, s, false);
     }
     for (;;) {
@@ -884,11 +894,15 @@ __device__ __forceinline__ void pq_grid_scan(pq_grids<T> &grids, pq_grid_waiting
                 pq_grid_take(m1[s], m2[s], pq_grid_key<3>(grids.coord[s], word[s], k.x[s][0], k.x[s][1], minus_one));
             }
             const uint64_t live = __builtin_amdgcn_ballot_w64(k.live);
+            const bool whole = FOUR != 0 && ~live == 0;
+            if (whole)
+                store_four(k, __builtin_amdgcn_perm(m1[1], m1[0], 0x0c0c0400u) | __builtin_amdgcn_perm(m1[3], m1[2], 0x04000c0cu));
 #pragma unroll
             for (int s = 0; s < GRID_SUB; ++s) {
                 const uint64_t mine = (useless >> s) & 1u ? 0 : live;
                 const uint64_t waits = __builtin_amdgcn_ballot_w64(pq_grid_unsure<T>(m1[s], m2[s])) & mine;
-                store(k, s, (int)(m1[s] & 255u), __builtin_amdgcn_inverse_ballot_w64(mine & ~waits));
+                if (!whole)
+                    store(k, s, (int)(m1[s] & 255u), __builtin_amdgcn_inverse_ballot_w64(mine & ~waits));
                 if (__builtin_amdgcn_inverse_ballot_w64(waits)) {
                     const int to = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(waits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)waits, (uint32_t)n_waiting));
                     if constexpr (KEEP)
@@ -976,6 +990,8 @@ __device__ __forceinline__ void pq_grid_scan(pq_grids<T> &grids, pq_grid_waiting
     static_assert(GRID_POOL * 4 >= GRID_WAVES * 64 * 8, "the place of the lists");
     typedef typename std::conditional<WITH, uint2, uint32_t>::type left_over;
     uint32_t *const counts = (uint32_t *)&queue[0];
+    if constexpr (FOUR != 0)  // other wavefronts store some of this one's codes again
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < GRID_SUB; ++j) {
