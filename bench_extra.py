@@ -84,9 +84,9 @@ def prefill():
             app()
         ms = _span_ms(step, 5)
     vectors = 2 * w.batch * w.n_kv_heads * n_new
-    # vector instructions the grid kernel issues per (token, subspace), the building of the grids included (rocprofv3
-    # SQ_INSTS_VALU: 147)
-    ops_per_subvector = 147
+    # vector instructions the grid kernel issues per 64 tokens and subspace, with the context's kept grids (rocprofv3
+    # SQ_INSTS_VALU: 78)
+    ops_per_subvector = 78
     ops = vectors * w.n_subspaces * ops_per_subvector
     achieved = ops / (ms * 1e-3)
     scan_ops = vectors * w.n_subspaces * 256 * (2 * w.sub_dim + 3)
@@ -171,8 +171,8 @@ def train():
     ms = _span_ms(run, 3, warmup=1) / iters
     ds = 128 // M
     # vector instructions of the assignment per (sample, subspace): the grids, the encode's look-up and the member sums
-    # (rocprofv3 SQ_INSTS_VALU: 116, mean of 5 iterations)
-    ops = Hkv * M * n * 116
+    # (rocprofv3 SQ_INSTS_VALU: 106, mean of 5 iterations)
+    ops = Hkv * M * n * 106
     scan_ops = Hkv * M * n * 256 * (2 * ds + 3)
     trained = cb.cpu().numpy()
     B.pq_attn_destroy(ctx)

@@ -35,7 +35,7 @@
 // together, and where the codebook gives no useful grid all its tokens go there at once.
 // What the data make of it, 32 heads, us, grids built / kept from an earlier append / the filter alone: encode of 9000 tokens,
 // normal 360 / 136 / 440, Laplace's distribution 390 / 158 / 441, 2 % of the coordinates times 20 395 / 165 / 446; of 32K 630 / 367
-// / 1590, 710 / 462 / 1596.  Centroids that repeat others are taken out: 16 values in all 1480 kept, 2496 by the
+// / 1590, 710 / 462 / 1596, 730 / 483 / 1610.  Centroids that repeat others are taken out: 16 values in all 1480 kept, 2496 by the
 // filter (9000 tokens; 2850 when a repeated centroid made its tokens unsure), k-means of 64K samples rounded to quarters 18.5 ->
 // 8.1 ms.  A codebook without a useful grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every
 // subspace 863 / 757 and 3000 / 2611.
