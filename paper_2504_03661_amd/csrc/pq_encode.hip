@@ -466,7 +466,8 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
 // The fp32 distances name the candidates: their relative error is at most 6 x 2^-24 (ds = 4: a difference twice, a product,
 // three sums), so the nearest centroid's is within 12 x 2^-24 of the least, and all within 16 steps of the least
 // distance's bits — at least 2^-20 of it — are kept.  One candidate, nearly always: it is the code, and naming it is scalar
-// work.  Several (ties, near-ties), none, or fp32 squares below 2^-100, which are not that good: the defining fp64 distances
+// work.  Several (ties, near-ties), none, fp32 squares below 2^-100, which are not that good, or no finite one (an infinite token
+// may have a single distance that is not NaN, and it is no less than infinity): the defining fp64 distances
 // of all 256, ascending, and the lexicographic minimum of (distance, index), the lowest index among equal distances.
 // 30 vector instructions per token and subspace at ds = 2 where the fp64 distances and their minimum over the wavefront
 // took 80.
@@ -543,7 +544,7 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void pq_encode_few_kernel(const pq_
                            __builtin_popcountll(near[3]);
         int code = 4 * __builtin_ctzll(near[0] | near[1] | near[2] | near[3] | 1ull << 63) +
                    (near[1] != 0 ? 1 : near[2] != 0 ? 2 : near[3] != 0 ? 3 : 0);
-        if (n_near != 1 || (sizeof(T) == 4 && least < 0x0d800000u)) {  // wave-uniform, rare
+        if (n_near != 1 || least >= 0x7f800000u || (sizeof(T) == 4 && least < 0x0d800000u)) {  // wave-uniform, rare
             double bd = __builtin_huge_val();
             int bc = 4 * lane;
 #pragma unroll

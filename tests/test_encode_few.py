@@ -86,3 +86,32 @@ def test_codes_of_few_tokens(per_wave, M, B_, Hkv, n_new, share, dtype):
         for b, n in enumerate(w.ctx_lens):
             np.testing.assert_array_equal(codes[b, :, n:n + n_new], want[b, :, :cap - n])
             np.testing.assert_array_equal(codes[b, :, :n], old[b, :, :n])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("M,B_,n_new,few", [(64, 1, 1, True), (64, 3, 5, True), (32, 2, 7, True), (64, 3, 300, False), (32, 3, 300, False)])
+def test_codes_of_infinities_and_nans(per_wave, M, B_, n_new, few, dtype):
+    """No distance of such a token is below infinity, so its code is 0, also where a single one is not NaN; and centroids at
+    infinity are never a finite token's.  The filter of longer appends on the same data."""
+    assert (per_wave(B_ * n_new, 2 * M * 2, M) > 0) == few
+    ds = 128 // M
+    w = W.Workload("not finite", B_, 2, 2, 128, M, n_new, dtype, n_new=n_new, seed=M + n_new)
+    data = W.generate(w)
+    for cb, x in ((data["k_codebook"], data["new_k"]), (data["v_codebook"], data["new_v"])):
+        cb[:, 0, :, 0] = np.inf
+        cb[:, 0, 37, 0] = 0.5                              # infinite tokens: infinitely far, NaN to all others
+        cb[:, 1, ::3, 1] = -np.inf
+        cb[:, 2, 5:, ds - 1] = np.inf
+        for i, v in ((0, np.inf), (1, -np.inf), (2, np.inf), (3, np.inf), (4, -np.inf), (5, np.nan)):
+            x[:, :, ::2, i * ds + (ds - 1 if i == 2 else i & 1)] = v
+        x[:, :, ::2, 6 * ds:7 * ds] = np.inf
+    with PQSession(data, 2, dtype) as s:
+        s.ctx_len.zero_()
+        s.append(torch.from_numpy(data["new_k"]).cuda(), torch.from_numpy(data["new_v"]).cuda())
+        torch.cuda.synchronize()
+        got = s.unpack(PQ_CODES_K, n_new), s.unpack(PQ_CODES_V, n_new)
+    for codes, x, cb in ((got[0], data["new_k"], data["k_codebook"]), (got[1], data["new_v"], data["v_codebook"])):
+        want = O.encode(x, cb)
+        assert (want[:, :, ::2, :7] == 0).all()
+        np.testing.assert_array_equal(codes, want)
