@@ -73,12 +73,15 @@ constexpr int GRID_LONGEST = 64;  // candidates of a block (a bit each in a 64-b
 constexpr uint32_t GRID_NONE = 0;  // a cell without a list: a list of no words
 constexpr uint32_t GRID_SURE = 512;  // keys at least this far apart are in the right order
 
-// The map of a subspace and what is known of its grid.  fp16: the factors are fp16 numbers, and a token's cell is found in fp16,
-// both axes at once: 8 instructions instead of the 14 of fp32.  A rounding of 2^-11 of |u| and one of |u| + 2 then move a token
-// by 2^-10 (|u| + 2) at most, which the boxes allow for (GRID_WIDER_F16).
+// The map of a subspace and what is known of its grid.  fp16: a token's cell is found in fp16, both axes at once: 8 instructions
+// instead of the 14 of fp32.  Factors, u and |u| + 2 are held there in units of 2^8, whose cells have the same bits: factors then
+// reach from deviations of 4e-7 (the smallest fp16 number is 6e-8; in units of 1 they ended at 9e-5, and codebooks of 1e-5 were
+// left to the filter: encode of 9000 tokens x 32 heads 585 us) to the largest.  A rounding of 2^-11 of |u| (2^-17 where u is
+// subnormal) and one of |u| + 2 move a token by 2^-10 (|u| + 2) at most, which the boxes allow for (GRID_WIDER_F16).
+constexpr float GRID_F16_UNIT = 256.0f;
 struct pq_grid_map {
     float sx, ox, sy, oy;
-    uint32_t s16, o16;     // (fp16: x in the low half)
+    uint32_t s16, o16;     // (fp16: in units of GRID_F16_UNIT, x in the low half)
     float scale;           // of the filter
     uint32_t pool_used, bad;  // bad: 1 no grid, 2 codebook outside the filter's range
     uint32_t lost, unserved;  // how many centroids the grid does not serve: counted before and after its lists
@@ -156,8 +159,10 @@ __device__ __forceinline__ uint32_t pq_grid_cell_f16(const uint32_t xy, const ui
 {
     const f16x2 u = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, xy), __builtin_bit_cast(f16x2, s16), __builtin_bit_cast(f16x2, o16));
     const uint32_t bits = __builtin_bit_cast(uint32_t, u);
-    f16x2 w = __builtin_bit_cast(f16x2, bits & 0x7fff7fffu) + (f16x2){(_Float16)GRID_BIAS, (_Float16)GRID_BIAS};
-    const _Float16 last = __builtin_bit_cast(_Float16, (uint16_t)0x4fff);  // just below 32
+    const _Float16 bias = (_Float16)(GRID_BIAS / GRID_F16_UNIT);
+    f16x2 w = __builtin_bit_cast(f16x2, bits & 0x7fff7fffu) + (f16x2){bias, bias};
+    const _Float16 last = __builtin_bit_cast(_Float16, (uint16_t)0x2fff);  // just below 32 units
+    static_assert(GRID_F16_UNIT == 256.0f, "the number above, and three bits of the exponent");
     w = __builtin_elementwise_min(w, (f16x2){last, last});
     // bits 7 .. 12 of each half are its cell coordinate, complemented where u is negative
     const uint32_t five = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, w) >> (u16x2){5, 5});
@@ -276,14 +281,16 @@ __device__ __forceinline__ void pq_grid_tables(pq_grids<T> &grids, const int sub
     float ox = -mx * sx, oy = -my * sy;
     bool usable = dx > 1.0e-30f && dy > 1.0e-30f && c_max < 1.0e30f;
     if constexpr (sizeof(T) == 2) {
-        // (deviations below 1e-4: coarser cells; an offset this large would move the middle by its rounding)
-        sx = (float)(_Float16)fminf(sx, 60000.f);
-        sy = (float)(_Float16)fminf(sy, 60000.f);
+        // (an offset of 16384 is rounded to 4 of the 28 on either side of the middle: the mean is then some 3000 mean deviations from
+        // zero; 32 heads x 9000 tokens 700 standard deviations from it 2843 us with 4096 for a limit, 644 so)
+        const auto rounded = [](float v) { return GRID_F16_UNIT * (float)(_Float16)(v * (1.0f / GRID_F16_UNIT)); };
+        sx = rounded(fminf(sx, 60000.f * GRID_F16_UNIT));
+        sy = rounded(fminf(sy, 60000.f * GRID_F16_UNIT));
         ox = -mx * sx;
         oy = -my * sy;
-        usable = usable && sx > 1.0e-4f && sy > 1.0e-4f && fabsf(ox) < 4096.f && fabsf(oy) < 4096.f;
-        ox = (float)(_Float16)ox;
-        oy = (float)(_Float16)oy;
+        usable = usable && sx > 1.0e-4f && sy > 1.0e-4f && fabsf(ox) < 16384.f && fabsf(oy) < 16384.f;
+        ox = rounded(ox);
+        oy = rounded(oy);
     }
     // squared distances in units of 1 / s_x^2
     const float ratio = sx / sy, wy = ratio * ratio;
@@ -301,7 +308,8 @@ __device__ __forceinline__ void pq_grid_tables(pq_grids<T> &grids, const int sub
     grids.coord[sub][c][0] = mine[0];
     grids.coord[sub][c][1] = mine[1];
     const auto both = [](float lo, float hi) {
-        return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)lo) | (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)hi) << 16;
+        return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(lo * (1.0f / GRID_F16_UNIT))) |
+               (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(hi * (1.0f / GRID_F16_UNIT))) << 16;
     };
     const pq_grid_map here = {sx, ox, sy, oy, both(sx, sy), both(ox, oy)};
     cell = pq_grid_cell_of(mine[0], mine[1], here);

@@ -16,19 +16,20 @@ def _constant(name):
     return float(re.search(r"\bconstexpr float " + name + r" = ([0-9.e+-]+)f?;", HEADER).group(1))
 
 
-BIAS, WIDER, WIDER_F16 = (_constant("GRID_" + n) for n in ("BIAS", "WIDER", "WIDER_F16"))
+BIAS, WIDER, WIDER_F16, UNIT = (_constant("GRID_" + n) for n in ("BIAS", "WIDER", "WIDER_F16", "F16_UNIT"))
 X = np.arange(65536, dtype=np.uint16).view(H)
 X = X[np.isfinite(X)]
 
 
 def _cells(s, o):
-    """pq_grid_cell_f16, one axis: a fused multiply-add, an addition and a minimum in fp16, then bits"""
+    """pq_grid_cell_f16, one axis, s and o in units of UNIT: a fused multiply-add, an addition and a minimum in fp16, then
+    bits -> cells, and u in units of 1"""
     exact = X.astype(np.float64) * float(s) + float(o)                  # (a product of two halves and a sum: exact in a double
     with np.errstate(over="ignore"):                                    # unless it leaves the map by far)
         u = exact.astype(H)
-        w = np.minimum((np.abs(u) + H(BIAS)).astype(H), np.uint16(0x4fff).view(H))
+        w = np.minimum((np.abs(u) + H(BIAS / UNIT)).astype(H), np.uint16(0x2fff).view(H))
     bits = (w.view(np.uint16) >> 5) ^ np.where(np.signbit(u), 0xffff, 0).astype(np.uint16)
-    return ((bits & 0xfc) >> 2).astype(np.int64), exact
+    return ((bits & 0xfc) >> 2).astype(np.int64), exact * UNIT
 
 
 def _box(e):
@@ -40,10 +41,10 @@ def _box(e):
     return 0.5 * (lo + hi), half
 
 
-@pytest.mark.parametrize("scale", [1.1e-4, 0.003, 0.11, 1.0, 5.59, 47.3, 913.0, 60000.0])
-@pytest.mark.parametrize("offset", [0.0, 0.37, -1.93, 27.9, -311.0, 4093.0])
+@pytest.mark.parametrize("scale", [1.1e-4, 0.003, 0.11, 1.0, 5.59, 47.3, 913.0, 60000.0, 7.1e5, 60000.0 * 256])
+@pytest.mark.parametrize("offset", [0.0, 0.37, -1.93, 27.9, -311.0, 4093.0, -16383.0])
 def test_every_point_lies_in_the_box_of_its_cell(scale, offset):
-    s, o = H(scale), H(offset)
+    s, o = H(scale / UNIT), H(offset / UNIT)
     cell, u = _cells(s, o)
     inside = (cell != 31) & (cell != 32)
     centre, half = _box(cell[inside])
