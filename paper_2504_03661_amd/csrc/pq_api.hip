@@ -186,14 +186,14 @@ int ensure_codebooks(pq_attn_ctx *ctx, const void *k, const void *v, hipStream_t
             pq_launch_copy16(v, ctx->vcb_packed, bytes, s) != hipSuccess)
             return PQ_ERR_HIP;
     } else {
-        unsigned int *const of_k = ctx->grid_state, *const of_v = of_k ? of_k + pq_grid_groups(&ctx->cfg) / 2 : nullptr;
+        uint64_t *const of_k = ctx->grid_state, *const of_v = of_k ? of_k + pq_grid_groups(&ctx->cfg) / 2 : nullptr;
         if (pq_launch_pack_codebook(ctx, k, ctx->kcb_packed, ctx->kcb_natural, of_k, s) != hipSuccess)
             return PQ_ERR_HIP;
         if (pq_launch_pack_codebook(ctx, v, ctx->vcb_packed, ctx->vcb_natural, of_v, s) != hipSuccess)
             return PQ_ERR_HIP;
     }
     ctx->registered = true;
-    ctx->grids_kept = false;
+    ctx->grid_phase = GRIDS_NONE;
     ctx->grid_chunks = once ? 0 : -1;
     return PQ_OK;
 }
@@ -332,11 +332,15 @@ int pq_attn_create(const pq_attn_config *cfg, pq_attn_ctx **out)
     // job — a job has one sequence (63 sequences x 4 heads, 64 jobs each: 132 KiB, 8.3 MiB with a slot per row and job)
     const size_t slots = ctx->jobs > cfg->batch ? (size_t)cfg->n_q_heads * ctx->jobs : n_bh * ctx->n_splits;
     const size_t part_bytes = slots * PQ_PART_STRIDE * sizeof(float);
+    ctx->grid_bytes = pq_grid_images_bytes(cfg, ctx->n_cu);
+    const size_t err_bytes = 2 * sizeof(unsigned int) + (ctx->grid_bytes > 0 ? pq_grid_groups(cfg) * sizeof(uint64_t) : 0);
     bool ok = hipMalloc(&ctx->kcb_packed, cb_bytes) == hipSuccess;
     ok = ok && hipMalloc(&ctx->vcb_packed, cb_bytes) == hipSuccess;
     ok = ok && hipMalloc((void **)&ctx->partials, part_bytes) == hipSuccess;
     ok = ok && hipMalloc((void **)&ctx->tickets, n_bh * sizeof(unsigned int)) == hipSuccess;
-    ok = ok && hipMalloc((void **)&ctx->dev_err, 2 * sizeof(unsigned int)) == hipSuccess;  // [1]: probe sink
+    ok = ok && hipMalloc((void **)&ctx->dev_err, err_bytes) == hipSuccess;  // [1]: probe sink
+    if (ok && ctx->grid_bytes > 0)
+        ctx->grid_state = (uint64_t *)(ctx->dev_err + 2);
     if (two_pass)  // partial scores [B*Hq][4 groups][capacity]
         ok = ok && hipMalloc((void **)&ctx->scores12, n_bh * 4 * (size_t)ctx->cap_padded * sizeof(float)) == hipSuccess;
     if (pq_config_is_12bit(cfg)) {
@@ -355,15 +359,8 @@ int pq_attn_create(const pq_attn_config *cfg, pq_attn_ctx **out)
         free_ctx(ctx);
         return PQ_ERR_ALLOC;
     }
-    // the grids of long appends are an image of what their workgroups otherwise build: nobody depends on there being one
-    const int64_t grid_bytes = pq_grid_images_bytes(cfg, ctx->n_cu);
-    if (grid_bytes > 0 && hipMalloc(&ctx->grids, (size_t)grid_bytes + pq_grid_groups(cfg) * sizeof(unsigned int)) == hipSuccess)
-        ctx->grid_state = (unsigned int *)((char *)ctx->grids + grid_bytes);
-    else
-        (void)hipGetLastError();
     ok = hipMemset(ctx->tickets, 0, n_bh * sizeof(unsigned int)) == hipSuccess;
-    ok = ok && (ctx->grids == nullptr || hipMemset(ctx->grid_state, 0, pq_grid_groups(cfg) * sizeof(unsigned int)) == hipSuccess);
-    ok = ok && hipMemset(ctx->dev_err, 0, 2 * sizeof(unsigned int)) == hipSuccess;
+    ok = ok && hipMemset(ctx->dev_err, 0, err_bytes) == hipSuccess;
     ok = ok && hipMemset(ctx->partials, 0, part_bytes) == hipSuccess;
     ok = ok && hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
@@ -523,7 +520,6 @@ int pq_encode_append(pq_attn_ctx *ctx, const void *new_k, const void *new_v, int
     a.max_context = ctx->cfg.max_context;
     a.k_skew = ctx->k_skew;
     a.head_stride = ctx->cap_padded * token_bytes(&ctx->cfg);
-    a.grids = ctx->grids;
     a.grid_state = ctx->grid_state;
     if (pq_config_is_12bit(&ctx->cfg)) {
         // codes are staged token-major (uint16) and packed by a second kernel; the staging buffers were sized at

@@ -232,11 +232,10 @@ template <typename T> struct grid_token {
 // building for 66 us: 32 heads x 32K tokens 641 -> 392 us, and from some 1000 tokens on appends do better with kept grids than
 // through the filter, where before 9000 had to pay for building them (32 heads x 4000 tokens 200 -> 84 us).  An image takes
 // 25 KiB per subspace (32 heads, K and V: 105 MB of memory).
-// A word per 4 subspaces says whether the image there is that of the codebooks in force.  It is on the device, so that
-// stream order and what a captured graph replays decide, not the host: registering codebooks puts it to GRID_ABSENT, and a
+// A word per 4 subspaces holds the address of their image if it is that of the codebooks in force.  It is on the device, so that
+// stream order and what a captured graph replays decide, not the host: registering codebooks puts it to 0, and a
 // workgroup that finds that builds for itself and waits for nobody.  Images are written and read by agent-scope accesses, the
 // word behind the image (the exchange of pq_device_utils.h): an append on another stream finds a whole image or none.
-enum : uint32_t { GRID_ABSENT = 0, GRID_THERE = 1 };
 
 // words of a subspace's pool that are used
 __device__ __forceinline__ int grid_pool_words(const pq_grid_map &m)
@@ -282,7 +281,7 @@ template <typename T> __device__ __forceinline__ void grid_fetch(pq_grids<T> &gr
 // A workgroup: 4 subspaces, as the encode's workgroups, in the order of the images.
 template <typename T>
 __global__ __launch_bounds__(GRID_WAVES * 64) void pq_grid_image_kernel(const T *codebook_k, const T *codebook_v, const int groups_k, void *images,
-                                                                        unsigned int *grid_state)
+                                                                        uint64_t *grid_state)
 {
     __shared__ __attribute__((aligned(16))) pq_grids<T> grids;
     __shared__ __attribute__((aligned(16))) pq_grid_scratch<false> scratch;
@@ -304,7 +303,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_grid_image_kernel(const T 
     publish_wait();
     __syncthreads();
     if (threadIdx.x == 0)
-        __hip_atomic_store(grid_state + group, (unsigned int)GRID_THERE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(grid_state + group, (uint64_t)image, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <typename T, bool WIDE>
@@ -316,7 +315,7 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
     constexpr bool KEEP = sizeof(T) == 2;
     __shared__ __attribute__((aligned(16))) pq_grid_scratch<KEEP> scratch;
     __shared__ float2 box[GRID_SIDE];
-    __shared__ unsigned int there;
+    __shared__ uint64_t there;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -334,10 +333,12 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_encode_grid_kernel(const p
 
     const int group = head * (M / GRID_SUB) + i0 / GRID_SUB;
     if (threadIdx.x == 0)  // one look for all: the word may change
-        there = a.grids != nullptr ? __hip_atomic_load(a.grid_state + group, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (unsigned int)GRID_ABSENT;
+        there = a.grid_state != nullptr ? __hip_atomic_load(a.grid_state + group, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane((int)there) == (int)GRID_THERE)
-        grid_fetch<T>(grids, (const char *)a.grids + (int64_t)group * pq_grid_image_bytes<T>());
+    const uint64_t image = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)there) |
+                           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(there >> 32)) << 32;
+    if (image != 0)
+        grid_fetch<T>(grids, (const char *)image);
     else
         pq_grid_build(grids, scratch.making, box, (const T *)a.codebook[which] + ((int64_t)hkv * M + i0) * 512);
 
@@ -682,10 +683,12 @@ template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, 
 // per head, would together have paid for it: a single long append at once, so that no append takes longer than by building its
 // own, and a context that never appends much never builds any.  (What is counted decides about time alone: threads that append at
 // once may count less, one of them builds.)  Not while a graph is recorded, which would build again with every replay, and not
-// for codebooks that were handed to a call, which may be handed to the next one again.
+// for codebooks that were handed to a call, which may be handed to the next one again.  The first to build allocates (105 MB for
+// 32 heads, 35 to 90 us): at creation every context with room for a long append had them, three times the codes of 4096 tokens.
+// Without the memory appends go on building for themselves.
 static hipError_t keep_grids(pq_attn_ctx *ctx, int64_t filter_chunks, int64_t groups, hipStream_t s)
 {
-    if (ctx->grids_kept.load(std::memory_order_relaxed) || ctx->grid_chunks.load(std::memory_order_relaxed) < 0)
+    if (ctx->grid_phase.load(std::memory_order_relaxed) != GRIDS_NONE || ctx->grid_chunks.load(std::memory_order_relaxed) < 0)
         return hipSuccess;
     const int64_t so_far = ctx->grid_chunks.fetch_add(filter_chunks, std::memory_order_relaxed) + filter_chunks;
     if (pq_grid_slices(so_far, so_far, groups, ctx->n_cu) == 0)
@@ -693,15 +696,31 @@ static hipError_t keep_grids(pq_attn_ctx *ctx, int64_t filter_chunks, int64_t gr
     hipStreamCaptureStatus recording = hipStreamCaptureStatusActive;
     if (hipStreamIsCapturing(s, &recording) != hipSuccess)
         (void)hipGetLastError();
-    if (recording != hipStreamCaptureStatusNone || ctx->grids_kept.exchange(true, std::memory_order_relaxed))
+    int none = GRIDS_NONE;
+    if (recording != hipStreamCaptureStatusNone || !ctx->grid_phase.compare_exchange_strong(none, GRIDS_CLAIMED))
         return hipSuccess;
+    if (ctx->grids == nullptr) {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another stream may be recording; it is none of its business)
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        const bool ok = hipMalloc(&ctx->grids, (size_t)ctx->grid_bytes) == hipSuccess;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!ok) {
+            (void)hipGetLastError();
+            ctx->grids = nullptr;
+            ctx->grid_chunks = -1;
+            ctx->grid_phase = GRIDS_NONE;
+            return hipSuccess;
+        }
+    }
     if (ctx->cfg.dtype == PQ_F16)
         hipLaunchKernelGGL(pq_grid_image_kernel<_Float16>, dim3((unsigned)groups), dim3(GRID_WAVES * 64), 0, s, (const _Float16 *)ctx->kcb_natural,
                            (const _Float16 *)ctx->vcb_natural, (int)groups / 2, ctx->grids, ctx->grid_state);
     else
         hipLaunchKernelGGL(pq_grid_image_kernel<float>, dim3((unsigned)groups), dim3(GRID_WAVES * 64), 0, s, (const float *)ctx->kcb_natural,
                            (const float *)ctx->vcb_natural, (int)groups / 2, ctx->grids, ctx->grid_state);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    ctx->grid_phase = e == hipSuccess ? GRIDS_KEPT : GRIDS_NONE;
+    return e;
 }
 
 hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,
@@ -726,12 +745,12 @@ hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *
                           (int64_t)a.B * seq_chunks < (1 << 30);
     const int64_t chunks = (int64_t)a.B * seq_chunks, filter_chunks = ((int64_t)a.B * a.n_new + 63) / 64, groups = (int64_t)2 * a.Hkv * 16;
     int slices = grid_can ? pq_grid_slices(chunks, filter_chunks, groups, ctx->n_cu) : 0;
-    const int with_kept = grid_can && ctx->grids != nullptr ? pq_grid_slices(chunks, filter_chunks, groups, ctx->n_cu, true) : 0;
+    const int with_kept = grid_can && ctx->grid_state != nullptr ? pq_grid_slices(chunks, filter_chunks, groups, ctx->n_cu, true) : 0;
     if (with_kept > 0) {
         const hipError_t e = keep_grids(ctx, filter_chunks, groups, s);
         if (e != hipSuccess)
             return e;
-        if (ctx->grids_kept.load(std::memory_order_relaxed))
+        if (ctx->grid_phase.load(std::memory_order_relaxed) == GRIDS_KEPT)
             slices = with_kept;
     }
     if (slices > 0) {

@@ -91,6 +91,8 @@ __host__ __device__ inline int64_t pq12_v_unit(int64_t t, int i, int *slot)
 #define PQ_NOALLOC_CODEBOOK_BYTES (2 << 20)
 #define PQ_NOALLOC_MAX_ROWS 1024
 
+enum { GRIDS_NONE, GRIDS_CLAIMED, GRIDS_KEPT };  // not there; an append is at it; built by work on a stream
+
 struct pq_attn_ctx {
     pq_attn_config cfg;
     int ds;               // sub-vector width
@@ -105,11 +107,12 @@ struct pq_attn_ctx {
     void *vcb_natural;    // [Hkv][M][C][ds] (what the encode kernels read); 12-bit contexts: = *_packed
     bool registered;      // codebooks have been registered (the copies above hold them)
     // 8-bit contexts of 64 subspaces with room for long appends: the grids of the registered codebooks
-    // (pq_encode_grid_kernel), an image of a workgroup's LDS for every 4 subspaces of a KV head (K's, then V's), and a word
-    // for each of them: whether it is there.  NULL: no such appends, or no memory for it
+    // (pq_encode_grid_kernel), an image of a workgroup's LDS for every 4 subspaces of a KV head (K's, then V's).  The append
+    // that first builds them allocates them, so that a context without such appends has none; destroying the context frees them
+    int64_t grid_bytes;   // of all images; 0: no such appends
     void *grids;
-    unsigned int *grid_state;
-    std::atomic<bool> grids_kept;        // they have been built (the launcher's rule asks; what the kernel does follows the words)
+    uint64_t *grid_state;  // (behind dev_err) per image its address, 0 while it is not there; NULL: no such appends
+    std::atomic<int> grid_phase;         // GRIDS_*: the launcher's rule asks; what the kernel does follows the words
     std::atomic<int64_t> grid_chunks;    // 64-token chunks that appends could have used them for since pq_attn_set_codebooks;
                                          // below zero: a call registered the codebooks
     float *partials;      // [B*Hq][n_splits][PQ_PART_STRIDE]; jobs > B: [Hq][jobs][PQ_PART_STRIDE]
@@ -173,8 +176,7 @@ struct pq_encode_args {
     int B, Hkv, n_new, max_context;
     int k_skew;
     int64_t head_stride;
-    void *grids;              // pq_attn_ctx::grids, grid_state
-    unsigned int *grid_state;
+    const uint64_t *grid_state;  // pq_attn_ctx::grid_state
 };
 
 // launchers (each returns hipGetLastError() after its launches)
@@ -192,7 +194,7 @@ hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *
 hipError_t pq_launch_bump_len(int32_t *ctx_len, int B, int n_new, int max_context, unsigned int *dev_err, hipStream_t s);
 // src [Hkv][M][256][ds] (caller memory) -> packed [Hkv][256][M][ds] and a plain copy in the source layout; the words of
 // grid_state (those of K's or V's codebooks, or NULL) say that there are no grids of these yet
-hipError_t pq_launch_pack_codebook(const pq_attn_ctx *ctx, const void *src, void *packed, void *natural, unsigned int *grid_state,
+hipError_t pq_launch_pack_codebook(const pq_attn_ctx *ctx, const void *src, void *packed, void *natural, uint64_t *grid_state,
                                    hipStream_t s);
 // grids of a context (pq_attn_ctx::grids): words of grid_state, and bytes of all images — 0 where no append that fits the
 // context takes the grids

@@ -12,7 +12,7 @@ namespace {
 // (also writes `nat`, unless NULL: a plain copy of src, the context's own codebooks for the encode kernels; and zeroes the
 // words of grid_state, one per 4 subspaces, unless NULL)
 template <typename E>
-__global__ void pq_pack_codebook_kernel(const E *src, E *dst, E *nat, unsigned int *grid_state, int Hkv, int M, int ds)
+__global__ void pq_pack_codebook_kernel(const E *src, E *dst, E *nat, uint64_t *grid_state, int Hkv, int M, int ds)
 {
     const int64_t n = (int64_t)Hkv * 256 * M;
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(1024) void pq_stream_read_kernel(const u32x4 *p, in
 
 }  // namespace
 
-hipError_t pq_launch_pack_codebook(const pq_attn_ctx *ctx, const void *src, void *dst, void *natural, unsigned int *grid_state,
+hipError_t pq_launch_pack_codebook(const pq_attn_ctx *ctx, const void *src, void *dst, void *natural, uint64_t *grid_state,
                                    hipStream_t s)
 {
     const int Hkv = ctx->cfg.n_kv_heads, M = ctx->cfg.n_subspaces, ds = ctx->ds;
