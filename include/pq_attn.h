@@ -113,8 +113,8 @@ int pq_attn_heads_per_workgroup(const pq_attn_ctx *ctx);
  * pointers are registered by that call, on its stream, before its kernels (the
  * copy costs a few microseconds per call — register once and pass NULL in a
  * decoding loop).  A codebook changed in place has to be registered again.
- * Contexts of 64 subspaces keep what long appends look codes up in, from the append on that has paid for building
- * it, for codebooks registered by this call, not by the other two: 3.3 MB of device memory per KV head (3.4 MB in
+ * Contexts of 64 subspaces keep what long appends look codes up in, from the first append on before which others
+ * have paid for building it, for codebooks registered by this call, not by the other two: 3.3 MB of device memory per KV head (3.4 MB in
  * fp32), allocated by the first such append (never while a graph is recorded), freed with the context.
  * Registration must be stream-ordered with every other call on the context that
  * uses the codebooks: with two streams (asynchronous quantization), register

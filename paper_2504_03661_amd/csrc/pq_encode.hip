@@ -228,7 +228,7 @@ template <typename T> struct grid_token {
 };
 
 // The grids of registered codebooks are the same in every append, so a context keeps them, once its appends have paid for
-// building them (pq_launch_encode), and a workgroup fetches the 80 KiB or so that are used of its four (fp16) instead of
+// building them (keep_grids), and a workgroup fetches the 80 KiB or so that are used of its four (fp16) instead of
 // building for 66 us: 32 heads x 32K tokens 641 -> 392 us, and from some 1000 tokens on appends do better with kept grids than
 // through the filter, where before 9000 had to pay for building them (32 heads x 4000 tokens 200 -> 84 us).  An image takes
 // 25 KiB per subspace (32 heads, K and V: 105 MB of memory).
@@ -679,9 +679,10 @@ template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, 
         hipLaunchKernelGGL((pq_encode_grid_kernel<T, false>), grid, dim3(64 * GRID_WAVES), 0, s, a, seq_chunks, slices, slice_chunks);
 }
 
-// Builds the grids into the context's images when this append and those since the codebooks were registered, chunks of 64 tokens
-// per head, would together have paid for it: a single long append at once, so that no append takes longer than by building its
-// own, and a context that never appends much never builds any.  (What is counted decides about time alone: threads that append at
+// Builds the grids into the context's images when the appends before this one since the codebooks were registered, chunks of 64
+// tokens per head, would together have paid for it: the second of two long ones, so that the first takes no longer than by
+// building its own (32 heads x 32K tokens 692 us with the images against 672, 9000 tokens 439 against 410), and a context that
+// never appends much, or a prompt once, never builds any.  (What is counted decides about time alone: threads that append at
 // once may count less, one of them builds.)  Not while a graph is recorded, which would build again with every replay, and not
 // for codebooks that were handed to a call, which may be handed to the next one again.  The first to build allocates (105 MB for
 // 32 heads, 35 to 90 us): at creation every context with room for a long append had them, three times the codes of 4096 tokens.
@@ -690,14 +691,14 @@ static hipError_t keep_grids(pq_attn_ctx *ctx, int64_t filter_chunks, int64_t gr
 {
     if (ctx->grid_phase.load(std::memory_order_relaxed) != GRIDS_NONE || ctx->grid_chunks.load(std::memory_order_relaxed) < 0)
         return hipSuccess;
-    const int64_t so_far = ctx->grid_chunks.fetch_add(filter_chunks, std::memory_order_relaxed) + filter_chunks;
-    if (pq_grid_slices(so_far, so_far, groups, ctx->n_cu) == 0)
-        return hipSuccess;
     hipStreamCaptureStatus recording = hipStreamCaptureStatusActive;
     if (hipStreamIsCapturing(s, &recording) != hipSuccess)
         (void)hipGetLastError();
+    if (recording != hipStreamCaptureStatusNone)
+        return hipSuccess;
+    const int64_t before = ctx->grid_chunks.fetch_add(filter_chunks, std::memory_order_relaxed);
     int none = GRIDS_NONE;
-    if (recording != hipStreamCaptureStatusNone || !ctx->grid_phase.compare_exchange_strong(none, GRIDS_CLAIMED))
+    if (pq_grid_slices(before, before, groups, ctx->n_cu) == 0 || !ctx->grid_phase.compare_exchange_strong(none, GRIDS_CLAIMED))
         return hipSuccess;
     if (ctx->grids == nullptr) {
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another stream may be recording; it is none of its business)

@@ -22,7 +22,8 @@ def _appended(s, n_new, **kw):
 
 @pytest.mark.parametrize("dtype,B_,n_new", [(np.float16, 2, 34007), (np.float32, 2, 34007), (np.float16, 1, 9003)])
 def test_appends_with_kept_grids_equal_the_oracle(dtype, B_, n_new):
-    """One append of 2 x 34007 tokens pays for the grids, it takes several of 9003, which go through the filter until then."""
+    """One append of 2 x 34007 tokens pays for the grids, it takes several of 9003, which go through the filter until then; the
+    next one builds them."""
     first = next(n for n in range(1, 100) if _rule()(*[n * (B_ * n_new + 63) // 64] * 2, 64, _n_cu()) > 0)
     assert (first == 1) == (encode_slices(2, B_, n_new, _n_cu()) > 0) == (n_new > 10000)
     kind = "f16" if dtype == np.float16 else "f32"
@@ -35,10 +36,10 @@ def test_appends_with_kept_grids_equal_the_oracle(dtype, B_, n_new):
             for got, ref in zip(_appended(s, n_new, **kw), want[books]):
                 np.testing.assert_array_equal(got, ref)
 
-        for _ in range(first + 2):
+        for _ in range(first + 3):
             check("kv")
         pq_attn_set_codebooks(s.ctx, s.v_codebook, s.k_codebook)
-        for _ in range(first + 1):
+        for _ in range(first + 2):
             check("vk")
         check("kv", pass_codebooks=True)                        # none are kept of these
         check("kv")
@@ -57,6 +58,7 @@ def test_a_recorded_append_follows_the_registration_in_force():
         torch.cuda.synchronize()
         g = torch.cuda.CUDAGraph()
         _appended(s, n_new)                                     # (pays for the grids)
+        _appended(s, n_new)                                     # (builds them)
         torch.cuda.synchronize()
         with torch.cuda.graph(g, stream=side):
             s.ctx_len.zero_()
@@ -110,7 +112,9 @@ def test_only_contexts_that_append_long_hold_images():
         a.append(a.books)                                   # (of codebooks handed over none are kept)
     assert _used(before) < 50 << 20
     a.register()
-    for _ in range(3):
+    a.append()                                              # (one long append pays for building, the next one builds)
+    assert _used(before) < 50 << 20
+    for _ in range(2):
         a.append()
     assert 100 << 20 < _used(before) < 160 << 20
     a.register()                                            # the same memory again
