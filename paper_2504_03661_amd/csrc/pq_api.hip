@@ -193,8 +193,15 @@ int ensure_codebooks(pq_attn_ctx *ctx, const void *k, const void *v, hipStream_t
             return PQ_ERR_HIP;
     }
     ctx->registered = true;
+    if (ctx->grid_state != nullptr && !ctx->registers_in_graph) {
+        hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &recording) != hipSuccess)
+            (void)hipGetLastError();
+        if (recording != hipStreamCaptureStatusNone)
+            ctx->registers_in_graph = true;
+    }
     ctx->grid_phase = GRIDS_NONE;
-    ctx->grid_chunks = once ? 0 : -1;
+    ctx->grid_chunks = once && !ctx->registers_in_graph ? 0 : -1;
     return PQ_OK;
 }
 

@@ -684,7 +684,9 @@ template <typename T> void launch_grid(const pq_encode_args &a, int seq_chunks, 
 // building its own (32 heads x 32K tokens 692 us with the images against 672, 9000 tokens 439 against 410), and a context that
 // never appends much, or a prompt once, never builds any.  (What is counted decides about time alone: threads that append at
 // once may count less, one of them builds.)  Not while a graph is recorded, which would build again with every replay, and not
-// for codebooks that were handed to a call, which may be handed to the next one again.  The first to build allocates (105 MB for
+// for codebooks that were handed to a call, which may be handed to the next one again, nor in a context with a recorded
+// registration: every replay of it takes the images away, and appends that count on them then build for themselves, in all four
+// rounds of workgroups (32 heads x 2000 tokens 307 us, 123 through the filter).  The first to build allocates (105 MB for
 // 32 heads, 35 to 90 us): at creation every context with room for a long append had them, three times the codes of 4096 tokens.
 // Without the memory appends go on building for themselves.
 static hipError_t keep_grids(pq_attn_ctx *ctx, int64_t filter_chunks, int64_t groups, hipStream_t s)

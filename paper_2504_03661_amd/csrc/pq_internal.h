@@ -114,7 +114,8 @@ struct pq_attn_ctx {
     uint64_t *grid_state;  // (behind dev_err) per image its address, 0 while it is not there; NULL: no such appends
     std::atomic<int> grid_phase;         // GRIDS_*: the launcher's rule asks; what the kernel does follows the words
     std::atomic<int64_t> grid_chunks;    // 64-token chunks of the appends that could have used them since pq_attn_set_codebooks;
-                                         // below zero: a call registered the codebooks
+                                         // below zero: a call registered the codebooks, or
+    std::atomic<bool> registers_in_graph;  // .. a registration has been recorded: a replay takes the images away unseen by the host
     float *partials;      // [B*Hq][n_splits][PQ_PART_STRIDE]; jobs > B: [Hq][jobs][PQ_PART_STRIDE]
     unsigned int *tickets;  // [B*Hq], zero between calls
     unsigned int *dev_err;  // sticky error word
