@@ -201,6 +201,7 @@ int ensure_codebooks(pq_attn_ctx *ctx, const void *k, const void *v, hipStream_t
             ctx->registers_in_graph = true;
     }
     ctx->grid_phase = GRIDS_NONE;
+    ++ctx->grid_generation;
     ctx->grid_chunks = once && !ctx->registers_in_graph ? 0 : -1;
     return PQ_OK;
 }
@@ -262,6 +263,7 @@ void free_ctx(pq_attn_ctx *ctx)
     if (ctx->kcb_natural && ctx->kcb_natural != ctx->kcb_packed) (void)hipFree(ctx->kcb_natural);
     if (ctx->vcb_natural && ctx->vcb_natural != ctx->vcb_packed) (void)hipFree(ctx->vcb_natural);
     if (ctx->grids) (void)hipFree(ctx->grids);
+    if (ctx->grid_found) (void)hipHostFree(ctx->grid_found);
     if (ctx->partials) (void)hipFree(ctx->partials);
     if (ctx->tickets) (void)hipFree(ctx->tickets);
     if (ctx->dev_err) (void)hipFree(ctx->dev_err);

@@ -15,6 +15,7 @@
 // pq_encode_grid_kernel, which looks the candidates up.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
+#include <string.h>
 
 #include <type_traits>
 
@@ -281,7 +282,7 @@ template <typename T> __device__ __forceinline__ void grid_fetch(pq_grids<T> &gr
 // A workgroup: 4 subspaces, as the encode's workgroups, in the order of the images.
 template <typename T>
 __global__ __launch_bounds__(GRID_WAVES * 64) void pq_grid_image_kernel(const T *codebook_k, const T *codebook_v, const int groups_k, void *images,
-                                                                        uint64_t *grid_state)
+                                                                        uint64_t *grid_state, uint64_t *found, const uint32_t generation)
 {
     __shared__ __attribute__((aligned(16))) pq_grids<T> grids;
     __shared__ __attribute__((aligned(16))) pq_grid_scratch<false> scratch;
@@ -304,6 +305,15 @@ __global__ __launch_bounds__(GRID_WAVES * 64) void pq_grid_image_kernel(const T 
     __syncthreads();
     if (threadIdx.x == 0)
         __hip_atomic_store(grid_state + group, (uint64_t)image, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 64 && found != nullptr) {
+        pq_grid_price sum = {0, 0};
+        for (int k = 0; k < GRID_SUB; ++k) {
+            const pq_grid_price price = pq_grid_price_of(grids.map[k]);
+            sum.grid += price.grid;
+            sum.filter += price.filter;
+        }
+        __hip_atomic_store(found + group, (uint64_t)generation << 32 | sum.grid << 16 | sum.filter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 template <typename T, bool WIDE>
@@ -706,24 +716,52 @@ static hipError_t keep_grids(pq_attn_ctx *ctx, int64_t filter_chunks, int64_t gr
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another stream may be recording; it is none of its business)
         (void)hipThreadExchangeStreamCaptureMode(&mode);
         const bool ok = hipMalloc(&ctx->grids, (size_t)ctx->grid_bytes) == hipSuccess;
+        if (ok && hipHostMalloc((void **)&ctx->grid_found, (size_t)groups * sizeof(uint64_t), 0) == hipSuccess)
+            memset(ctx->grid_found, 0, (size_t)groups * sizeof(uint64_t));
+        else
+            ctx->grid_found = nullptr;
         (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (!ok) {
+        if (ctx->grid_found == nullptr)
             (void)hipGetLastError();
+        if (!ok) {
             ctx->grids = nullptr;
             ctx->grid_chunks = -1;
             ctx->grid_phase = GRIDS_NONE;
             return hipSuccess;
         }
     }
+    const uint32_t generation = ctx->grid_generation.load(std::memory_order_relaxed);
     if (ctx->cfg.dtype == PQ_F16)
         hipLaunchKernelGGL(pq_grid_image_kernel<_Float16>, dim3((unsigned)groups), dim3(GRID_WAVES * 64), 0, s, (const _Float16 *)ctx->kcb_natural,
-                           (const _Float16 *)ctx->vcb_natural, (int)groups / 2, ctx->grids, ctx->grid_state);
+                           (const _Float16 *)ctx->vcb_natural, (int)groups / 2, ctx->grids, ctx->grid_state, ctx->grid_found, generation);
     else
         hipLaunchKernelGGL(pq_grid_image_kernel<float>, dim3((unsigned)groups), dim3(GRID_WAVES * 64), 0, s, (const float *)ctx->kcb_natural,
-                           (const float *)ctx->vcb_natural, (int)groups / 2, ctx->grids, ctx->grid_state);
+                           (const float *)ctx->vcb_natural, (int)groups / 2, ctx->grids, ctx->grid_state, ctx->grid_found, generation);
     const hipError_t e = hipGetLastError();
     ctx->grid_phase = e == hipSuccess ? GRIDS_KEPT : GRIDS_NONE;
     return e;
+}
+
+// What a chunk costs with the codebooks in force: the rule's own figures until every image's workgroup has said what it found.  Waits
+// for nothing; the appends until then go by codebooks that the grids serve.
+static pq_grid_price grid_price(pq_attn_ctx *ctx, int64_t groups)
+{
+    const uint32_t generation = ctx->grid_generation.load(std::memory_order_relaxed);
+    const uint64_t known = ctx->grid_cost.load(std::memory_order_relaxed);
+    if ((uint32_t)(known >> 32) == generation)
+        return {(uint32_t)known >> 16, (uint32_t)known & 0xffffu};
+    uint64_t grid = 0, filter = 0;
+    for (int64_t k = 0; k < groups; ++k) {
+        const uint64_t found = ctx->grid_found != nullptr ? __atomic_load_n(ctx->grid_found + k, __ATOMIC_RELAXED) : 0u;
+        if ((uint32_t)(found >> 32) != generation || (uint32_t)found == 0)
+            return {18, 72};
+        grid += found >> 16 & 0xffffu;
+        filter += found & 0xffffu;
+    }
+    const uint64_t n = (uint64_t)groups * GRID_SUB;
+    const pq_grid_price mean = {(uint32_t)((grid + n / 2) / n), (uint32_t)((filter + n / 2) / n)};
+    ctx->grid_cost.store((uint64_t)generation << 32 | mean.grid << 16 | mean.filter, std::memory_order_relaxed);
+    return mean;
 }
 
 hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *ctx_len, unsigned int *dev_err,
@@ -754,7 +792,7 @@ hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *
         if (e != hipSuccess)
             return e;
         if (ctx->grid_phase.load(std::memory_order_relaxed) == GRIDS_KEPT)
-            slices = with_kept;
+            slices = pq_grid_slices(chunks, filter_chunks, groups, ctx->n_cu, true, grid_price(ctx, groups));
     }
     if (slices > 0) {
         if (f16) launch_grid<_Float16>(a, seq_chunks, slices, ctx->n_cu, s); else launch_grid<float>(a, seq_chunks, slices, ctx->n_cu, s);

@@ -112,6 +112,11 @@ struct pq_attn_ctx {
     int64_t grid_bytes;   // of all images; 0: no such appends
     void *grids;
     uint64_t *grid_state;  // (behind dev_err) per image its address, 0 while it is not there; NULL: no such appends
+    // in host memory, allocated with the images: per image generation << 32 | pq_grid_price of its 4 subspaces, 16 bits each,
+    // written by the kernel that builds it; and their mean, once all are there
+    uint64_t *grid_found;
+    std::atomic<uint32_t> grid_generation;  // registrations
+    std::atomic<uint64_t> grid_cost;
     std::atomic<int> grid_phase;         // GRIDS_*: the launcher's rule asks; what the kernel does follows the words
     std::atomic<int64_t> grid_chunks;    // 64-token chunks of the appends that could have used them since pq_attn_set_codebooks;
                                          // below zero: a call registered the codebooks, or

@@ -110,6 +110,32 @@ template <typename T> constexpr int pq_grid_image_bytes() { return (int)offsetof
 constexpr int GRID_LOST = 96;
 __device__ __forceinline__ bool pq_grid_useless(const pq_grid_map &m) { return m.bad != 0 || m.lost > GRID_LOST || m.unserved > GRID_LOST; }
 
+// What a chunk of a subspace's tokens costs a grid workgroup and the filter by itself (10 ns for four such subspaces), for a rule that
+// would else take all codebooks to be served by their grids.  A grid that leaves a third of its centroids, so a third of the tokens,
+// to the filter takes 233 of its 355 instructions.  A useless one has the filter's work at four wavefronts per SIMD instead of
+// five, on codebooks that are the slower ones to the filter as well: 32 heads x 4000 tokens, one dead axis in every subspace 405 us,
+// 350 through the filter (200 for normal data); one in four subspaces 176 and 255; centroids beyond the filter's range (bad & 2), all
+// distances in fp64, 2494 and 2117 for 9000 tokens with 6 of 10 codebooks so.  Where many centroids repeat others, the filter
+// by itself finds all of them and walks over their quads, which these rows do not have (centroids of 16 values 690 and 1118 for
+// 4000 tokens, rounded to quarters 566 and 1133).
+struct pq_grid_price {
+    uint32_t grid, filter;
+};
+__device__ __forceinline__ pq_grid_price pq_grid_price_of(const pq_grid_map &m)
+{
+    int repeated = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        repeated += __builtin_popcount(m.again[k]);
+    if (m.bad & 2u)
+        return {610u, 520u};
+    if (repeated >= 64)
+        return {240u, 400u};
+    if (pq_grid_useless(m))
+        return {152u, 130u};
+    return {18u + 78u * m.unserved / 256u, 72u};
+}
+
 // What building a grid needs of its centroids: a_x, a_y, |c|^2 / 2 lowered, |c|^2 / 2; how many of them lie in each block of
 // 4 x 4 cells, 16 bits each (repeated ones not counted); and the first of those whose coordinates have the same hash.  The
 // waiting tokens take its place.
@@ -1054,14 +1080,16 @@ __device__ __forceinline__ void pq_grid_scan(pq_grids<T> &grids, pq_grid_waiting
 // kept: the grids are there (pq_encode_grid_kernel), a workgroup takes some 9 us to start, fetch them and end.  Grids / filter,
 // fp16, whole appends with the length reset: 32 heads, 500 tokens 45 / 37 us, 1000 52 / 61, 2000 63 / 109, 8000 127 / 383; 8
 // heads, 500 tokens 14.8 / 15.3, 1000 15.6 / 22.7, 4000 24 / 60; 4 heads in two slices, 1000 tokens 14.3 / 15.2, 4000 18.8 / 36.5;
-// fp32, 32 heads, 500 tokens 48 / 45, 1000 55 / 70, 4000 93 / 230.
-inline int pq_grid_slices(const int64_t chunks, const int64_t filter_chunks, const int64_t groups, const int n_cu, const bool kept = false)
+// fp32, 32 heads, 500 tokens 48 / 45, 1000 55 / 70, 4000 93 / 230.  price: the mean
+// pq_grid_price_of of the codebooks, once it is known.
+inline int pq_grid_slices(const int64_t chunks, const int64_t filter_chunks, const int64_t groups, const int n_cu, const bool kept = false,
+                          const pq_grid_price price = {18, 72})
 {
-    int64_t best = filter_chunks * groups * 72 / n_cu;  // 10 ns
+    int64_t best = filter_chunks * groups * price.filter / n_cu;  // 10 ns
     int slices = 0;
     for (int s = 1; s <= 32; ++s) {
         const int64_t rounds = (groups * s + n_cu - 1) / n_cu;
-        const int64_t time = rounds * ((kept ? 900 : 7400) + (chunks + s - 1) / s * 18);
+        const int64_t time = rounds * ((kept ? 900 : 7400) + (chunks + s - 1) / s * price.grid);
         // (chunk numbers of a slice and workgroup numbers have their limits)
         if (time < best && chunks / s < (1 << 20) && groups * s < (1 << 24)) {
             best = time;

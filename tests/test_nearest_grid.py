@@ -205,16 +205,16 @@ def test_the_kinds_reach_every_form_of_list():
 @functools.cache
 def _rule():
     """The launchers' rule (slices of the tokens for the grid kernels, 0: the filter), compiled from its source."""
-    text = re.search(r"^inline int pq_grid_slices\(.*?^}", HEADER, re.S | re.M).group(0)
+    text = "".join(re.search(what, HEADER, re.S | re.M).group(0) for what in (r"^struct pq_grid_price {.*?^};", r"^inline int pq_grid_slices\(.*?^}"))
     with tempfile.TemporaryDirectory() as d:
         with open(os.path.join(d, "rule.cpp"), "w") as f:
-            f.write("#include <cstdint>\n" + text + "\nextern \"C\" int rule(int64_t c, int64_t f, int64_t g, int n) "
-                    "{ return pq_grid_slices(c, f, g, n); }\n")
+            f.write("#include <cstdint>\n" + text + "\nextern \"C\" int rule(int64_t c, int64_t f, int64_t g, int n, int kept, uint32_t price) "
+                    "{ return pq_grid_slices(c, f, g, n, kept, {price >> 16, price & 65535}); }\n")
         lib = os.path.join(d, "rule.so")
         subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", lib, f.name], check=True)
         fn = ctypes.CDLL(lib).rule
-    fn.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
-    return fn
+    fn.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2 + [ctypes.c_uint32]
+    return lambda chunks, filter_chunks, groups, n_cu, kept=False, price=18 << 16 | 72: fn(chunks, filter_chunks, groups, n_cu, kept, price)
 
 
 def encode_slices(Hkv, B_, n_new, n_cu=256):
@@ -231,6 +231,16 @@ LONG_APPENDS = [
     (2, 2, 34000, np.float32, [5, 64], 40000),
 ]
 TRAININGS = [(2, 80003, 1), (5, 45000, 2)]
+
+
+def test_codebooks_that_the_grids_do_not_serve_are_left_to_the_filter():
+    """The rule for kept grids, told that none of the subspaces are the filter's, one of four, all."""
+    useless = [int(v) for v in re.search(r"if \(pq_grid_useless\(m\)\)\s+return {(\d+)u, (\d+)u};", HEADER).groups()]
+    none, some, all_ = (((4 - k) * 18 + k * useless[0]) // 4 << 16 | ((4 - k) * 72 + k * useless[1]) // 4 for k in (0, 1, 4))
+    sizes = [(32, 1, n) for n in (1200, 2000, 4000, 9000, 32768)] + [(8, 1, 4000), (8, 3, 30000), (4, 64, 2000)]
+    kept = lambda H, b, n, c: _rule()(b * ((n + 126) >> 6), (b * n + 63) // 64, 2 * H * 16, 256, True, c)
+    assert all(kept(*s, none) > 0 and kept(*s, all_) == 0 for s in sizes)
+    assert all(kept(*s, some) > 0 for s in sizes[1:])
 
 
 def test_the_sizes_below_take_the_grid():
