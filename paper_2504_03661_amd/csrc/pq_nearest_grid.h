@@ -1086,10 +1086,14 @@ inline int pq_grid_slices(const int64_t chunks, const int64_t filter_chunks, con
                           const pq_grid_price price = {18, 72})
 {
     int64_t best = filter_chunks * groups * price.filter / n_cu;  // 10 ns
+    const int64_t fixed = kept ? 900 : 7400;
     int slices = 0;
+    // (no number of slices takes less than this: appends of some tens of tokens are spared the walk below, 0.1 us)
+    if (best <= (groups + n_cu - 1) / n_cu * (fixed + price.grid))
+        return 0;
     for (int s = 1; s <= 32; ++s) {
         const int64_t rounds = (groups * s + n_cu - 1) / n_cu;
-        const int64_t time = rounds * ((kept ? 900 : 7400) + (chunks + s - 1) / s * price.grid);
+        const int64_t time = rounds * (fixed + (chunks + s - 1) / s * price.grid);
         // (chunk numbers of a slice and workgroup numbers have their limits)
         if (time < best && chunks / s < (1 << 20) && groups * s < (1 << 24)) {
             best = time;

@@ -233,6 +233,22 @@ LONG_APPENDS = [
 TRAININGS = [(2, 80003, 1), (5, 45000, 2)]
 
 
+def test_the_rule_takes_the_cheapest_of_all_divisions():
+    """What the launchers' rule gives without a walk over them for appends too short to gain."""
+    rng = np.random.default_rng(0)
+    seen = set()
+    for _ in range(3000):
+        n, b, heads, n_cu = (int(np.exp(rng.uniform(0, top))) for top in (11, 4, 5, 6.3))
+        kept, price = bool(rng.integers(2)), (18, 72) if rng.random() < 0.5 else (int(rng.integers(18, 600)), int(rng.integers(72, 500)))
+        chunks, through_filter, groups = b * ((n + 126) >> 6), (b * n + 63) // 64, heads * 32
+        times = {s: -(-groups * s // n_cu) * ((900 if kept else 7400) + -(-chunks // s) * price[0]) for s in range(1, 33)}
+        best = min(times, key=times.get)
+        want = best if times[best] < through_filter * groups * price[1] // n_cu else 0
+        assert _rule()(chunks, through_filter, groups, n_cu, kept, price[0] << 16 | price[1]) == want
+        seen.add(min(want, 2))
+    assert seen == {0, 1, 2}
+
+
 def test_codebooks_that_the_grids_do_not_serve_are_left_to_the_filter():
     """The rule for kept grids, told that none of the subspaces are the filter's, one of four, all."""
     useless = [int(v) for v in re.search(r"if \(pq_grid_useless\(m\)\)\s+return {(\d+)u, (\d+)u};", HEADER).groups()]
