@@ -1,9 +1,11 @@
 """Appends of a few tokens per KV head (one wavefront per subspace and group of tokens): the launcher's rule, compiled from
 its source, and the codes against the oracle, exact, where fp32 distances decide and where they do not."""
 import ctypes
+import functools
 import os
 import re
 import subprocess
+import tempfile
 
 import numpy as np
 import pytest
@@ -16,17 +18,29 @@ from paper_2504_03661_amd.harness import PQSession
 from synth import workloads as W
 
 
-@pytest.fixture(scope="module")
-def per_wave(tmp_path_factory):
+@functools.cache
+def _per_wave():
     text = open(os.path.join(lib_build.CSRC, "pq_encode.hip")).read()
     text = re.search(r"^inline int pq_encode_few_per_wave\(.*?^}", text, re.S | re.M).group(0)
-    d = tmp_path_factory.mktemp("few")
-    (d / "rule.cpp").write_text("#include <cstdint>\n" + text +
-                                '\nextern "C" int rule(int64_t t, int64_t r, int M) { return pq_encode_few_per_wave(t, r, M); }\n')
-    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", str(d / "rule.so"), str(d / "rule.cpp")], check=True)
-    fn = ctypes.CDLL(str(d / "rule.so")).rule
+    with tempfile.TemporaryDirectory() as d:
+        with open(os.path.join(d, "rule.cpp"), "w") as f:
+            f.write("#include <cstdint>\n" + text + '\nextern "C" int rule(int64_t t, int64_t r, int M) { return pq_encode_few_per_wave(t, r, M); }\n')
+        lib = os.path.join(d, "rule.so")
+        subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", lib, f.name], check=True)
+        fn = ctypes.CDLL(lib).rule
     fn.argtypes, fn.restype = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int], ctypes.c_int
     return fn
+
+
+def takes_the_few_token_kernel(Hkv, tokens, M):
+    """Whether the launcher gives an append of so many tokens per head (of all sequences) to the few-token kernel: the other tests
+    of the filter ask, so that their sizes reach it."""
+    return _per_wave()(tokens, Hkv * M * 2, M) > 0
+
+
+@pytest.fixture
+def per_wave():
+    return _per_wave()
 
 
 @pytest.mark.parametrize("M", [32, 64])

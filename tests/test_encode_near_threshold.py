@@ -10,6 +10,7 @@ from oracle import pq_oracle as O
 from paper_2504_03661_amd import PQ_CODES_K, PQ_CODES_V
 from paper_2504_03661_amd.harness import PQSession
 from synth import workloads as W
+from tests.test_encode_few import takes_the_few_token_kernel
 from tests.test_filter_bound_cpu import K_ABS, X2F, _constant
 
 NEAR, NEAR_F32 = float(_constant("PQ_FILTER_TAU_NEAR")), float(_constant("PQ_FILTER_TAU_NEAR_F32"))
@@ -121,12 +122,14 @@ def test_fp32_codes_over_magnitudes_and_near_ties(M):
 @pytest.mark.parametrize("dtype", ["f16", "f32"])
 @pytest.mark.parametrize("M", [64, 32])
 @pytest.mark.parametrize("B_,n_new", [(3, 56), (3, 57), (2, 63), (2, 64), (2, 65), (3, 113), (3, 114), (1, 70), (40, 7),
-                                      (1, 6), (6, 1), (1, 7), (7, 1), (2, 3), (4, 2)])
+                                      (1, 6), (6, 1), (1, 7), (7, 1), (2, 3), (4, 2), (1, 56), (2, 28), (1, 57), (3, 19), (1, 72),
+                                      (8, 9), (1, 73), (73, 1)])
 def test_codes_at_the_edges_of_the_mapping_and_of_the_offset(M, B_, n_new, dtype):
     """Token counts on both sides of the rule that gives every sequence its own 64-token chunks (57 and 114 are the first
-    to have them) and of the one between the per-token kernel (up to 6 tokens per head) and the filter, remainders;
-    sub-vectors up to the largest fp16 (beyond a length of 345 the offset moves to its second slot, beyond 6e4 the chunk
+    to have them) and of the one between the few-token kernel and the filter (4 heads: up to 56 tokens per head at M = 64, 72 at
+    M = 32), remainders; sub-vectors up to the largest fp16 (beyond a length of 345 the offset moves to its second slot, beyond 6e4 the chunk
     takes the full scan)."""
+    assert takes_the_few_token_kernel(4, B_ * n_new, M) == (B_ * n_new <= (56 if M == 64 else 72))
     ds = 128 // M
     lens = tuple(int(v) for v in np.random.default_rng(B_).integers(0, 90, B_))
     w = W.Workload("edge", B_, 4, 4, 128, M, 90 + n_new, dtype, n_new=n_new, seed=70 + M + n_new, ctx_lens=lens)

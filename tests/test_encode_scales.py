@@ -11,6 +11,7 @@ from oracle import pq_oracle as O
 from paper_2504_03661_amd import PQ_CODES_K, PQ_CODES_V
 from paper_2504_03661_amd.harness import PQSession
 from synth import workloads as W
+from tests.test_encode_few import takes_the_few_token_kernel
 from tests.test_encode_near_threshold import EPS, NEAR
 from tests.test_filter_bound_cpu import K_ABS, X2F
 from tests.test_gpu_kmeans import gpu_fit, make_ctx
@@ -57,10 +58,12 @@ def test_the_filter_is_safe_and_selective_at_every_scale(ds, scale):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,C,B_,n_new", [(64, 256, 1, 200), (32, 256, 3, 40), (32, 4096, 1, 100), (32, 4096, 1, 300)])
+@pytest.mark.parametrize("M,C,B_,n_new", [(64, 256, 1, 200), (32, 256, 3, 40), (32, 256, 4, 40), (32, 256, 2, 150),
+                                            (32, 4096, 1, 100), (32, 4096, 1, 300)])
 def test_codes_at_every_scale(M, C, B_, n_new):
     """Every subspace has its own scale, from subnormal codebooks to 30, tokens of the codebook's scale, far larger ones and
-    zeros, an infinite centroid in a codebook of small and in one of large numbers."""
+    zeros, an infinite centroid in a codebook of small and in one of large numbers.  (3 x 40 tokens are the few-token kernel's.)"""
+    assert C == 4096 or takes_the_few_token_kernel(2, B_ * n_new, M) == ((B_, n_new) == (3, 40))
     ds = 128 // M
     w = W.Workload("scales", B_, 2, 2, 128, M, n_new, "f16", n_new=n_new, seed=9 + M + n_new, n_centroids=C)
     data = W.generate(w)
@@ -143,7 +146,8 @@ def test_a_codebook_of_equal_centroids_takes_one_scan():
 def test_tokens_as_near_to_many_quads(M, dtype):
     """1 to 64 quads with the token's nearest centroid, several times inside some: an even and an odd number, 40 and 41, in one
     lane half or both; the lowest index of all is the code."""
-    ds, n_new = 128 // M, 130
+    ds, n_new = 128 // M, 150
+    assert not takes_the_few_token_kernel(2, n_new, M)
     w = W.Workload("quads", 1, 2, 2, 128, M, n_new, dtype, n_new=n_new, seed=M)
     data = W.generate(w)
     rng = np.random.default_rng(M)

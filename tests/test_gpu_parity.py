@@ -11,6 +11,7 @@ from oracle import pq_oracle as O
 from paper_2504_03661_amd import PQ_CODES_K, PQ_CODES_V, PQAttnError, binding
 from paper_2504_03661_amd.harness import PQSession
 from synth import workloads as W
+from tests.test_encode_few import takes_the_few_token_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -374,16 +375,20 @@ def test_bulk_encode_with_several_chunks_per_wavefront(M, n_new):
 
 
 @pytest.mark.parametrize("M", [64, 32])
-@pytest.mark.parametrize("B_,n_new", [(1, 1), (3, 20), (2, 50), (2, 200), (5, 333), (1, 64), (1, 65), (2, 64), (1, 129), (1, 256),
-                                       (1, 257), (16, 1), (1, 16), (2, 5), (1, 17)])
-def test_encode_filter_paths_are_bit_exact(M, B_, n_new):
+@pytest.mark.parametrize("Hkv,B_,n_new", [(2, 1, 1), (2, 3, 20), (2, 2, 50), (2, 2, 200), (2, 5, 333), (2, 1, 64), (2, 1, 65), (2, 2, 64),
+                                           (2, 1, 129), (2, 1, 256), (2, 1, 257), (2, 16, 1), (2, 1, 16), (2, 2, 5), (2, 1, 17),
+                                           (16, 3, 20), (16, 2, 50), (16, 1, 64), (16, 1, 65), (16, 2, 64), (16, 1, 129),
+                                           (40, 16, 1), (40, 1, 16), (40, 1, 17)])
+def test_encode_filter_paths_are_bit_exact(M, Hkv, B_, n_new):
     """fp16 encode = matrix-core filter + fp64 decision: every way through it gives the oracle's codes — ties inside
     one quad of centroids, across two quads, across three and more (a walk over them), clusters of near-ties far
     below the filter's resolution, subnormal and zero inputs, a codebook whose norms leave the fp16 range (full
     scan), tokens that are far outliers; token counts per head of one chunk and of several, with chunks of each
-    sequence and with all sequences' tokens in a row, and (6 tokens or fewer) the centroid-per-lane kernel."""
+    sequence and with all sequences' tokens in a row.  Two heads with up to 104 tokens (M = 32: 136) take the few-token kernel,
+    which has its own way through the same data; the larger numbers of heads bring these token counts to the filter."""
+    assert takes_the_few_token_kernel(Hkv, B_ * n_new, M) == (Hkv == 2 and B_ * n_new <= (104 if M == 64 else 136))
     ds = 128 // M
-    w = W.Workload("filt", B_, 4, 2, 128, M, n_new + 3, "f16", n_new=n_new, seed=900 + M + n_new)
+    w = W.Workload("filt", B_, 2 * Hkv, Hkv, 128, M, n_new + 3, "f16", n_new=n_new, seed=900 + M + n_new)
     data = W.generate(w)
     rng = np.random.default_rng(17 + M + n_new)
     for cb in (data["k_codebook"], data["v_codebook"]):
@@ -416,7 +421,7 @@ def test_encode_filter_paths_are_bit_exact(M, B_, n_new):
         mid = 0.5 * (cb8[hk, pair] + cb8[hk, pair + 128])
         jit = rng.integers(-2, 3, size=mid.shape).astype(np.float32) * np.abs(np.spacing(mid.astype(np.float16))).astype(np.float32)
         x[..., 8 * ds:9 * ds] = (mid + jit).astype(np.float16)
-    with PQSession(data, 4, "f16") as s:
+    with PQSession(data, 2 * Hkv, "f16") as s:
         s.ctx_len.zero_()
         s.append(torch.from_numpy(data["new_k"]).cuda(), torch.from_numpy(data["new_v"]).cuda())
         torch.cuda.synchronize()
