@@ -21,15 +21,14 @@ X = np.arange(65536, dtype=np.uint16).view(H)
 X = X[np.isfinite(X)]
 
 
-def _cells(s, o):
-    """pq_grid_cell_f16, one axis, s and o in units of UNIT: a fused multiply-add, an addition and a minimum in fp16, then
-    bits -> cells, and u in units of 1"""
-    exact = X.astype(np.float64) * float(s) + float(o)                  # (a product of two halves and a sum: exact in a double
+def cells(x, s, o):
+    """pq_grid_cell_f16, one axis, s and o in units of UNIT: a fused multiply-add, an addition and a minimum in fp16, then bits"""
+    exact = x.astype(np.float64) * float(s) + float(o)                  # (a product of two halves and a sum: exact in a double
     with np.errstate(over="ignore"):                                    # unless it leaves the map by far)
         u = exact.astype(H)
         w = np.minimum((np.abs(u) + H(BIAS / UNIT)).astype(H), np.uint16(0x2fff).view(H))
     bits = (w.view(np.uint16) >> 5) ^ np.where(np.signbit(u), 0xffff, 0).astype(np.uint16)
-    return ((bits & 0xfc) >> 2).astype(np.int64), exact * UNIT
+    return ((bits & 0xfc) >> 2).astype(np.int64)
 
 
 def _box(e):
@@ -45,7 +44,7 @@ def _box(e):
 @pytest.mark.parametrize("offset", [0.0, 0.37, -1.93, 27.9, -311.0, 4093.0, -16383.0])
 def test_every_point_lies_in_the_box_of_its_cell(scale, offset):
     s, o = H(scale / UNIT), H(offset / UNIT)
-    cell, u = _cells(s, o)
+    cell, u = cells(X, s, o), (X.astype(np.float64) * float(s) + float(o)) * UNIT
     inside = (cell != 31) & (cell != 32)
     centre, half = _box(cell[inside])
     assert (np.abs(u[inside] - centre) <= half).all()

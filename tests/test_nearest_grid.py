@@ -1,6 +1,6 @@
 """The grid that names, for every cell of a subspace's plane, the centroids that can be the nearest of a point in it (long
-appends and large trainings at two dims per subspace).  On the CPU: the cell lists, built in fp32 as the kernel builds them,
-hold the fp64-nearest centroid of every point.  On the GPU: codes and trained codebooks against the oracle."""
+appends and large trainings at two dims per subspace).  On the CPU: the cell lists, built as the kernel builds them for fp16 and
+for fp32 codebooks, hold the fp64-nearest centroid of every point.  On the GPU: codes and trained codebooks against the oracle."""
 import ctypes
 import functools
 import os
@@ -19,6 +19,7 @@ from paper_2504_03661_amd import binding as B
 from paper_2504_03661_amd import build as lib_build
 from paper_2504_03661_amd.harness import PQSession
 from synth import workloads as W
+from tests import test_grid_map as map16
 from tests.test_gpu_kmeans import gpu_fit, make_ctx
 
 F = np.float32
@@ -45,6 +46,8 @@ def codebook_and_points(kind, n, seed, dtype=np.float16):
         "heavy tails": lambda m: np.clip(rng.standard_cauchy((m, 2)), -3e4, 3e4),
         "equal": lambda m: normal(m) * 0 + 0.75,
         "sixteen values": lambda m: rng.integers(0, 4, (m, 2)) * 0.5,
+        "smallest": lambda m: normal(m) * 1e-5,
+        "far and narrow": lambda m: normal(m) * [0.1, 0.01] + [70, -7],
     }[kind]
     c = draw(256)
     if kind == "lattice":
@@ -76,7 +79,8 @@ def _constant(name):
     return F(m.group(1))
 
 
-COVER, DEVIATIONS, LOWERED, MARGIN, WIDER = (_constant("GRID_" + n) for n in ("COVER", "DEVIATIONS", "LOWERED", "MARGIN", "WIDER"))
+COVER, DEVIATIONS, LOWERED, MARGIN, WIDER, WIDER_F16, UNIT = (
+    _constant("GRID_" + n) for n in ("COVER", "DEVIATIONS", "LOWERED", "MARGIN", "WIDER", "WIDER_F16", "F16_UNIT"))
 LONGEST = int(_constant("GRID_LONGEST"))
 
 
@@ -89,24 +93,43 @@ def _edge(k):
     return np.where(k < 0, -e, e)
 
 
+def _rounded(v):
+    """A factor of the fp16 map: an fp16 number in units of UNIT."""
+    return (v / UNIT).astype(np.float16).astype(F) * UNIT
+
+
 def _cells(x, s, o):
+    if x.dtype == np.float16:
+        return map16.cells(x, s / UNIT, o / UNIT)
     u = _fma(x, s, o)
     b = np.minimum((np.abs(u) + F(2)).astype(F).view(np.uint32), np.uint32(0x41ffffff))
     e = ((b >> np.uint32(20)) & np.uint32(63)).astype(np.int64)
     return np.where(np.signbit(u), 63 - e, e)
 
 
-def _box(e, n):
+def _box(e, n, dtype):
     """Centre and half side of cell coordinates e .. e + n - 1."""
     k = np.where(e < 32, e, e - 64)
     lo, hi = _edge(k), _edge(k + n)
-    return F(0.5) * (lo + hi), F(0.5) * (hi - lo) + WIDER
+    half = F(0.5) * (hi - lo) + WIDER
+    if dtype == np.float16:
+        half = _fma(np.maximum(-lo, hi) + F(2), WIDER_F16, half)
+    return F(0.5) * (lo + hi), half
+
+
+def _repeats(c):
+    """The centroids that pq_grid_take_out finds to be equal to one before them: the first with their hash."""
+    bits = c.view(np.uint16 if c.dtype == np.float16 else np.uint32).astype(np.uint64)
+    h = bits[:, 0] | bits[:, 1] << np.uint64(16) if c.dtype == np.float16 else bits[:, 0] * np.uint64(0x85ebca6b) & np.uint64(0xffffffff) ^ bits[:, 1]
+    h = (h * np.uint64(0x9e3779b1) & np.uint64(0xffffffff)) >> np.uint64(24)
+    first = np.array([np.nonzero(h == v)[0][0] for v in h])
+    return (first < np.arange(256)) & (c[first] == c).all(1)
 
 
 def _lists(c):
-    """The steps of pq_grid_tables and pq_grid_lists in fp32 -> (s, o, candidates [64, 64, 256] bool, which cells have a
+    """The steps of pq_grid_tables, pq_grid_take_out and pq_grid_lists -> (s, o, candidates [64, 64, 256] bool, which cells have a
     list, fill code of every cell); None: no grid for this codebook."""
-    dtype, exact, c = c.dtype, c.astype(np.float64), c.astype(F)
+    dtype, exact, again, c = c.dtype, c.astype(np.float64), _repeats(c), c.astype(F)
     mean, end = np.zeros(2, F), np.full(2, 3e38, F)
     for _ in range(2):
         near = np.abs(c - mean) <= end
@@ -117,20 +140,27 @@ def _lists(c):
     if not (dev > 1e-30).all():
         return None
     s = COVER / (DEVIATIONS * dev)
+    if dtype == np.float16:
+        s = _rounded(np.minimum(s, F(60000) * UNIT))
+        if not ((s > 1e-4).all() and (np.abs(mean * s) < 16384).all()):
+            return None
     o = -mean * s
+    if dtype == np.float16:
+        o = _rounded(o)
     w = F(s[0] / s[1]) ** 2
     u = _fma(c, s, o)
     if not (np.abs(u) < 1e6).all() or not 1e-9 < w < 1e9:
         return None
     ax, ay = u[:, 0], w * u[:, 1]
     norm = F(0.5) * (u[:, 0] * ax + u[:, 1] * ay)
-    low = norm * (F(1) - LOWERED)
+    low = np.where(again, F(1e30), norm * (F(1) - LOWERED))
+    exact = np.where(again[:, None], np.inf, exact)
     lists, listed, fills = np.zeros((64, 64, 256), bool), np.zeros((64, 64), bool), np.zeros((64, 64), np.int64)
     lowest, largest = (-60000, 60000) if dtype == np.float16 else (-3e37, 3e37)
     for bx in range(16):
         for by in range(16):
             # the block's list: all centroids against the one nearest to its centre
-            (gx, hx), (gy, hy) = _box(np.int64(4 * bx), 4), _box(np.int64(4 * by), 4)
+            (gx, hx), (gy, hy) = _box(np.int64(4 * bx), 4, dtype), _box(np.int64(4 * by), 4, dtype)
             p = np.clip([(gx - o[0]) / s[0], (gy - o[1]) / s[1]], lowest, largest).astype(dtype).astype(np.float64)
             r = int(((exact - p) ** 2).sum(1).argmin())
             value = lambda k: _fma(-gy, ay[k], _fma(-gx, ax[k], low[k]))
@@ -138,13 +168,13 @@ def _lists(c):
             limit = value(r) + MARGIN * (norm[r] + far_x * far_x + w * far_y * far_y)
             t = _fma(-np.abs(ay - ay[r]), hy, _fma(-np.abs(ax - ax[r]), hx, value(slice(None))))
             k = np.nonzero(t <= limit)[0]
-            free = np.setdiff1d(np.arange(32), k)
+            free = np.setdiff1d(np.arange(32), np.concatenate([k, np.nonzero(again)[0]]))
             if len(k) > LONGEST or len(free) == 0:
                 continue
             # its cells' lists: the block's candidates against the one nearest to the cell's centre, found in numbers whose
             # low bits hold the place in the list
             e = np.arange(4)
-            (gx, hx), (gy, hy) = _box(4 * bx + e, 1), _box(4 * by + e, 1)
+            (gx, hx), (gy, hy) = _box(4 * bx + e, 1, dtype), _box(4 * by + e, 1, dtype)
             gx, hx, gy, hy = (np.repeat(gx, 4), np.repeat(hx, 4), np.tile(gy, 4), np.tile(hy, 4))
             half = F(0.5) * (gx * gx + w * gy * gy)
             v = _fma(ay[k], -gy[:, None], _fma(ax[k], -gx[:, None], low[k] + half[:, None]))
@@ -164,8 +194,9 @@ def _lists(c):
 
 
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
-@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("kind", KINDS + ["smallest", "far and narrow"])
 def test_lists_hold_the_nearest_centroid_of_every_point(kind, dtype):
+    """With all ties but the centroids that repeat one before them, which are no codes."""
     for seed in range(3):
         c, x = codebook_and_points(kind, 8000, seed, dtype)
         grid = _lists(c)
@@ -176,10 +207,13 @@ def test_lists_hold_the_nearest_centroid_of_every_point(kind, dtype):
         ix, iy = _cells(x[:, 0], s[0], o[0]), _cells(x[:, 1], s[1], o[1])
         inside = listed[ix, iy]
         d = ((x.astype(np.float64)[:, None] - c.astype(np.float64)[None]) ** 2).sum(-1)
-        nearest = d == d.min(1)[:, None]                         # with all ties
-        assert not (nearest & ~lists[ix, iy])[inside].any()
+        nearest = d == d.min(1)[:, None]
+        again = _repeats(c)
+        assert not again[d.argmin(1)].any()
+        assert not (nearest & ~again & ~lists[ix, iy])[inside].any()
+        assert not lists[:, :, again].any()
         assert not nearest[np.arange(len(x)), fills[ix, iy]][inside].any()
-        if kind == "normal":
+        if kind in ("normal", "tiny") or (kind == "smallest" and dtype == np.float32):
             assert inside.mean() > 0.98 and (lists[ix, iy].sum(1) > 4)[inside].mean() < 0.15
 
 
