@@ -429,13 +429,13 @@ def _rows(kind, shape, gen):
     return x.half()
 
 
-# What the data make of the grids, beside the same call through the filter, which takes rows that start off a 16-byte address.
-# Heavy tails: 0.95 and 0.83 measured, 1.55 and 1.35 with the tokens outside the map one by one.  A codebook without a useful
-# grid has the filter's work on four wavefronts per SIMD instead of five (1.25 where all of it is waiting): 1.2 and 0.95
-# measured, 2.3 and 1.9 with its tokens one by one.
+# What the data make of the grids, beside the same call through the filter, which takes rows that start off a 16-byte address:
+# appends with kept grids, appends and trainings that build them in place.
+# Heavy tails: 0.38, 0.91 and 0.78 measured; 1.55 in place and 1.35 in training with the tokens outside the map one by one.  Few
+# values, ties all over: 0.51, 0.63 and 0.49; 2.3 and 1.9 with their tokens one by one, 1.2 and 0.95 with repeated centroids left in.
 @pytest.mark.gpu
-@pytest.mark.parametrize("kind,most", [("laplace", 1.15), ("2 % times 20", 1.15), ("few values", 1.45)])
-def test_data_that_the_grids_do_not_serve_cost_little(kind, most):
+@pytest.mark.parametrize("kind,most_kept,most", [("laplace", 0.5, 1.15), ("2 % times 20", 0.5, 1.15), ("few values", 0.7, 0.85)])
+def test_data_that_the_grids_do_not_serve_cost_little(kind, most_kept, most):
     n, H, gen = 9000, 32, torch.Generator(device="cuda").manual_seed(1)
     assert encode_slices(H, 1, n, _n_cu()) > 0 and train_slices(H, n, _n_cu()) > 0
     cfg = B.PQAttnConfig(batch=1, n_q_heads=H, n_kv_heads=H, n_subspaces=64, max_context=n)
@@ -448,9 +448,9 @@ def test_data_that_the_grids_do_not_serve_cost_little(kind, most):
     nbytes = B.pq_kmeans_workspace_bytes(ctx)
     workspace, book = torch.empty(nbytes, dtype=torch.uint8, device="cuda"), books[0].clone()
 
-    def encode(k, v):
+    def encode(k, v, own=(None, None)):
         length.zero_()
-        B.pq_encode_append(ctx, k, v, n, None, None, codes[0], codes[1], length)
+        B.pq_encode_append(ctx, k, v, n, *own, codes[0], codes[1], length)
 
     def train(k):
         book.copy_(books[0])
@@ -461,9 +461,13 @@ def test_data_that_the_grids_do_not_serve_cost_little(kind, most):
         flat = torch.empty(t.numel() + 2, dtype=t.dtype, device="cuda")
         off.append(flat[2:].view(t.shape))
         off[-1].copy_(t)
-    times = [_span_us(lambda: encode(*x)), _span_us(lambda: encode(*off)), _span_us(lambda: train(x[0])), _span_us(lambda: train(off[0]))]
+    kept, through_filter = _span_us(lambda: encode(*x)), _span_us(lambda: encode(*off))
+    in_place, again = _span_us(lambda: encode(*x, books)), _span_us(lambda: encode(*off, books))    # (none are kept of these)
+    trained, trained_by_filter = _span_us(lambda: train(x[0])), _span_us(lambda: train(off[0]))
     B.pq_attn_destroy(ctx)
-    assert times[0] <= most * times[1] and times[2] <= most * times[3], times
+    print(f"{kind}: kept {kept / through_filter:.2f}, in place {in_place / again:.2f}, training {trained / trained_by_filter:.2f}")
+    assert kept <= most_kept * through_filter and in_place <= most * again, (kept, through_filter, in_place, again)
+    assert trained <= most * trained_by_filter, (trained, trained_by_filter)
 
 
 @pytest.mark.gpu
