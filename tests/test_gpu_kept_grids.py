@@ -184,3 +184,54 @@ def test_kept_grids_are_used_where_they_serve(n, H, kind, most):
     through_filter, kept = a.us(a.off()), a.us()
     pq_attn_destroy(a.ctx)
     assert kept <= most * through_filter, (kept, through_filter)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+def test_an_append_on_another_stream_while_images_are_built(dtype):
+    """The second of two long appends builds the images; one on another stream at the same time, into tensors of its own, finds a
+    whole image or none, group by group.  Registered anew three times, so that there are images of other codebooks to be mistaken."""
+    n_new = 34007
+    data = _data(2, 2, 2, n_new, dtype, [0, 0])
+    want = {books: [O.encode(data["new_" + n], data[m + "_codebook"]) for n, m in zip("kv", books)] for books in ("kv", "vk")}
+    with PQSession(data, 2, "f16" if dtype == np.float16 else "f32", max_context=n_new) as s:
+        s.new = [torch.from_numpy(data["new_" + n]).cuda() for n in "kv"]
+        main, side = torch.cuda.current_stream(), torch.cuda.Stream()
+        other, length = [torch.zeros_like(t) for t in (s.k_codes[0], s.v_codes[0])], torch.zeros_like(s.ctx_len)
+        for books in ("kv", "vk", "kv"):
+            pq_attn_set_codebooks(s.ctx, *((s.k_codebook, s.v_codebook) if books == "kv" else (s.v_codebook, s.k_codebook)))
+            _appended(s, n_new)                             # (pays for them)
+            for t in (*other, length, s.ctx_len, s.k_codes[0], s.v_codes[0]):
+                t.zero_()
+            side.wait_stream(main)
+            s.append(s.new[0], s.new[1])                    # builds them ..
+            with torch.cuda.stream(side):                   # .. while this one starts
+                pq_encode_append(s.ctx, *s.new, n_new, None, None, *other, length)
+            main.wait_stream(side)
+            torch.cuda.synchronize()
+            assert length.tolist() == s.ctx_len.tolist() == [n_new, n_new]
+            for kind, mine, theirs, ref in zip((PQ_CODES_K, PQ_CODES_V), (s.k_codes[0], s.v_codes[0]), other, want[books]):
+                assert torch.equal(mine, theirs)
+                np.testing.assert_array_equal(s.unpack(kind, n_new), ref)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+def test_infinities_and_nans_in_long_appends(dtype):
+    """Their distances are below no other: code 0, by grids built in place, kept, and by the filter."""
+    n_new = 34007
+    data = _data(2, 2, 2, n_new, dtype, [0, 0], ["normal", "outliers", "duplicates", "line"])
+    data["k_codebook"][:, 8, :, 0] = np.inf
+    data["k_codebook"][:, 8, 37, 0] = 0.5
+    for x in (data["new_k"], data["new_v"]):
+        x[:, :, ::5, 0::2] = np.inf
+        x[:, :, 1::5, 1::2] = -np.inf
+        x[:, :, 2::5, 0::4] = np.nan
+    want = [O.encode(data["new_" + n], data[n + "_codebook"]) for n in "kv"]
+    assert all((w[:, :, :2] == 0).all() for w in want)
+    with PQSession(data, 2, "f16" if dtype == np.float16 else "f32", max_context=n_new) as s:
+        s.new = [torch.from_numpy(data["new_" + n]).cuda() for n in "kv"]
+        for _ in range(3):
+            for got, ref in zip(_appended(s, n_new), want):
+                np.testing.assert_array_equal(got, ref)
+        s.new = [torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape).copy_(t) for t in s.new]
+        for got, ref in zip(_appended(s, n_new), want):
+            np.testing.assert_array_equal(got, ref)
