@@ -85,8 +85,8 @@ def prefill():
         ms = _span_ms(step, 5)
     vectors = 2 * w.batch * w.n_kv_heads * n_new
     # vector instructions the grid kernel issues per 64 tokens and subspace, with the context's kept grids (rocprofv3
-    # SQ_INSTS_VALU: 78)
-    ops_per_subvector = 78
+    # SQ_INSTS_VALU: 79)
+    ops_per_subvector = 79
     ops = vectors * w.n_subspaces * ops_per_subvector
     achieved = ops / (ms * 1e-3)
     scan_ops = vectors * w.n_subspaces * 256 * (2 * w.sub_dim + 3)

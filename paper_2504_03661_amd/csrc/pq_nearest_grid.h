@@ -5,11 +5,12 @@
 // The filter of pq_nearest_filter.h looks at all 256 values of every token: 355 vector instructions per 64 tokens.  In two
 // dimensions the plane can be cut up once per codebook instead, and a token then looks at the 2 or 3 centroids of its cell:
 // 68 instructions with codebooks of random vectors, whose cells have long lists more often than trained ones'.  Building a
-// grid takes 34 000, as many as 100 chunks of 64 tokens through the filter, so the grid serves appends and trainings of
+// grid takes 32 200, as many as 91 chunks of 64 tokens through the filter, so the grid serves appends and trainings of
 // thousands of tokens per head (pq_grid_slices below).  Encode (K and V), 32 heads x 32K tokens, kept grids: 392 us, of which 36
 // us are workgroups' starts, image loads and ends, 184 the tokens' main path, which vector issue bounds (220 instructions per 64
 // tokens and 4 subspaces), and, each left out by itself: 63 the stores of the codes, a byte per token and subspace (stored together 367 us in all: pq_grid_stores_wide), 61 the tokens that
-// wait, 34 the rows from memory (1549 us through the filter).  k-means, 32 heads x 64K samples, 2 iterations: 3148 -> 872 us.
+// wait, 34 the rows from memory (1549 us through the filter).  k-means, 32 heads x 64K samples, 2 iterations: 3148 -> 872 us
+// (normal data; 940 where the channels' scales go from 1/2 to 2).
 //
 // Map.  Per axis u = s x + o, chosen from the codebook (mean and mean deviation of its coordinates without outliers):
 // |u| <= 28 holds what lies within some 4 standard deviations.  The cell coordinate is five bits of the float |u| + 2 — 8
@@ -34,11 +35,11 @@
 // leave undecided ("unsure": near-ties, outside, cells without a list) is put off until 64 of a subspace can go through the filter
 // together, and where the codebook gives no useful grid all its tokens go there at once.
 // What the data make of it, 32 heads, us, grids built / kept from an earlier append / the filter alone: encode of 9000 tokens,
-// normal 360 / 136 / 440, Laplace's distribution 390 / 158 / 441, 2 % of the coordinates times 20 395 / 165 / 446; of 32K 630 / 367
-// / 1590, 710 / 462 / 1596, 730 / 483 / 1610.  Centroids that repeat others are taken out: 16 values in all 1480 kept, 2496 by the
+// normal 358 / 135 / 430, Laplace's distribution 382 / 158 / 429, 2 % of the coordinates times 20 387 / 165 / 429; of 32K 593 / 369
+// / 1566, 680 / 462 / 1567, 704 / 485 / 1569.  Centroids that repeat others are taken out: 16 values in all 1430 kept, 2472 by the
 // filter (9000 tokens; 2850 when a repeated centroid made its tokens unsure), k-means of 64K samples rounded to quarters 18.5 ->
 // 8.1 ms.  A codebook without a useful grid costs the filter four wavefronts per SIMD instead of five: one dead axis in every
-// subspace 863 / 757 and 3000 / 2611.
+// subspace 867 / 750 and 3000 / 2577; with images kept such codebooks are known, and go to the filter's kernel (pq_grid_price_of).
 #pragma once
 
 #include <stddef.h>
