@@ -546,7 +546,9 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void pq_encode_few_kernel(const pq_
             }
             d[r] = __float_as_uint(dist);  // (positive floats order like their bits)
         }
-        const uint32_t least = few_wave_min(min(min(min(d[0], d[1]), d[2]), d[3]));
+        uint32_t least = few_wave_min(min(min(min(d[0], d[1]), d[2]), d[3]));
+        if constexpr (sizeof(T) == 2)  // (no distance of finite fp16 numbers comes near this: none is within 16 steps of it)
+            least = min(least, 0x7f000000u);
         uint64_t near[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -555,7 +557,7 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void pq_encode_few_kernel(const pq_
                            __builtin_popcountll(near[3]);
         int code = 4 * __builtin_ctzll(near[0] | near[1] | near[2] | near[3] | 1ull << 63) +
                    (near[1] != 0 ? 1 : near[2] != 0 ? 2 : near[3] != 0 ? 3 : 0);
-        if (n_near != 1 || least >= 0x7f800000u || (sizeof(T) == 4 && least < 0x0d800000u)) {  // wave-uniform, rare
+        if (n_near != 1 || (sizeof(T) == 4 && least - 0x0d800000u >= 0x7f800000u - 0x0d800000u)) {  // wave-uniform, rare
             double bd = __builtin_huge_val();
             int bc = 4 * lane;
 #pragma unroll
