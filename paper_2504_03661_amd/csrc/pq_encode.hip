@@ -793,7 +793,7 @@ hipError_t pq_launch_encode(pq_attn_ctx *ctx, const pq_encode_args &a, int32_t *
         const hipError_t e = keep_grids(ctx, filter_chunks, groups, s);
         if (e != hipSuccess)
             return e;
-        if (ctx->grid_phase.load(std::memory_order_relaxed) == GRIDS_KEPT)
+        if (ctx->grid_phase.load(std::memory_order_acquire) == GRIDS_KEPT)
             slices = pq_grid_slices(chunks, filter_chunks, groups, ctx->n_cu, true, grid_price(ctx, groups));
     }
     if (slices > 0) {
