@@ -235,3 +235,30 @@ def test_infinities_and_nans_in_long_appends(dtype):
         s.new = [torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape).copy_(t) for t in s.new]
         for got, ref in zip(_appended(s, n_new), want):
             np.testing.assert_array_equal(got, ref)
+
+
+def test_images_are_built_beside_a_recording():
+    """The append that allocates and builds them runs while another stream records a graph: neither minds the other."""
+    a, other, side, g = _LongAppends(9000), torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    a.register()
+    a.append()                                              # (pays for them, through grids of its own)
+    torch.cuda.synchronize()
+    first, y = a.codes.clone(), torch.zeros(1000, device="cuda")
+    a.codes.zero_()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()                                # (as the recording begins with)
+    before = torch.cuda.mem_get_info()[0]
+    with torch.cuda.graph(g, stream=side):
+        y += 1
+        with torch.cuda.stream(other):
+            a.append()
+        y += 1
+    assert _used(before) > 90 << 20
+    assert torch.equal(a.codes, first) and not y.any()
+    for n in range(1, 4):
+        a.codes.zero_()
+        g.replay()
+        a.append()                                          # with kept grids
+        torch.cuda.synchronize()
+        assert torch.equal(a.codes, first) and (y == 2 * n).all()
+    pq_attn_destroy(a.ctx)
